@@ -321,6 +321,32 @@ flp_status flp_lora_apply_gated(flp_pool* p, const flp_lora_batch* b, void* out,
 }
 
 namespace {
+// dense base products that run as one launch: projections which[0 .. n) of the call
+struct BaseGroup {
+  int n = 0;
+  int which[FLP_MAX_PROJ] = {0, 0, 0, 0};
+  FlpGemmPlan plan{};
+};
+
+// groups and plans of a call's dense base products; returns the bytes their slices take.  `room` bounds the slices; one
+// slice of every product is planned even where it does not fit.
+size_t plan_base(const flp_lora_batch* b, bool one_launch, size_t room, std::vector<BaseGroup>* groups) {
+  for (int q = 0; q < b->n_proj; ++q) {
+    if (!b->proj[q].w_base) continue;
+    if (groups->empty() || !one_launch) groups->push_back(BaseGroup{});
+    BaseGroup& g = groups->back();
+    g.which[g.n++] = q;
+  }
+  size_t total = 0;
+  for (BaseGroup& g : *groups) {
+    int N[FLP_MAX_PROJ];
+    for (int i = 0; i < g.n; ++i) N[i] = b->proj[g.which[i]].d_out;
+    g.plan = flp_gemm_plan(b->n_tokens, b->d_in, g.n, N, 0, room / groups->size());
+    for (int i = 0; i < g.n; ++i) total += ((size_t)g.plan.splits * b->n_tokens * N[i] * 4 + 255) & ~(size_t)255;
+  }
+  return total;
+}
+
 // gated_out != nullptr: two projections (gate, up) whose results are not stored; gated_out = silu(y0) * y1
 // fixed != nullptr: the intermediates go into the caller-provided buffer and nothing is allocated; a batch that
 // needs more than the buffer holds is refused before anything is enqueued
@@ -420,41 +446,44 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
   // accumulators before it rounds): no fp32 copy of the product, no second pass over y.
   // (Batches of 2048 tokens and more only: the epilogue walks the adapters present among a wave's 128 tokens, which
   // are one or two when tokens come in sequences and up to 128 in a large pure-decode batch.)
-  bool fused = mfma_ok && b->n_tokens >= 2048;
-  for (int q = 0; q < b->n_proj; ++q)
-    fused = fused && b->proj[q].w_base &&
-            flp_gemm_is_large(p->cfg.dtype, b->n_tokens, b->proj[q].d_out, b->d_in, b->ld_x);
+  bool fused = mfma_ok && b->n_tokens >= 2048 && b->d_in % 64 == 0;
+  int64_t fused_tiles = 0;                     // enough 256 x 128 tiles to occupy the chip without slices
+  for (int q = 0; q < b->n_proj; ++q) {
+    fused = fused && b->proj[q].w_base;
+    fused_tiles += (int64_t)((b->proj[q].d_out + 255) / 256) * ((b->n_tokens + 127) / 128);
+  }
+  fused = fused && fused_tiles >= 96;
   if (gated_out) {
-    const bool ok = fused && b->n_proj == 2 && b->proj[0].d_out == b->proj[1].d_out && b->proj[0].w_base_layout == 1 &&
-                    b->proj[1].w_base_layout == 1 && ld_gated >= b->proj[0].d_out && ld_gated % epl == 0 &&
-                    flp_gemm_gated_fits(p->cfg.dtype, b->n_tokens, b->proj[0].d_out, b->d_in, b->ld_x);
+    const bool ok = fused && b->n_proj == 2 && b->proj[0].d_out == b->proj[1].d_out && b->proj[0].d_out % 32 == 0 &&
+                    b->proj[0].w_base_layout == 1 && b->proj[1].w_base_layout == 1 && ld_gated >= b->proj[0].d_out &&
+                    ld_gated % epl == 0;
     if (!ok) return FLP_ENOTSUP;                // nothing launched: the caller takes the separate products
   }
   size_t wt_bytes = 0;                         // transposed copy of the widest dense base matrix
+  bool one_launch = true;                      // matrices stored [d_out, d_in] go in one launch, others one by one
   if (p->elem_bytes == 2)
     for (int q = 0; q < b->n_proj; ++q)
-      if (b->proj[q].w_base && b->proj[q].w_base_layout == 0)
+      if (b->proj[q].w_base && b->proj[q].w_base_layout == 0) {
         wt_bytes = std::max(wt_bytes, (size_t)b->d_in * b->proj[q].d_out * 2);
-  wt_bytes = (wt_bytes + 255) & ~(size_t)255;
-  size_t base_bytes[FLP_MAX_PROJ] = {0, 0, 0, 0}, base_total = 0;   // unrounded base terms (16-bit pools)
-  if (p->elem_bytes == 2 && !fused)
-    for (int q = 0; q < b->n_proj; ++q)
-      if (b->proj[q].w_base) {
-        base_bytes[q] = (T * b->proj[q].d_out * 4 + 255) & ~(size_t)255;
-        base_total += base_bytes[q];
+        one_launch = false;
       }
-  size_t splitk_bytes = 0;                     // slices of the dense product of a small batch
-  for (int q = 0; q < b->n_proj; ++q)
-    if (b->proj[q].w_base && p->elem_bytes == 2)
-      splitk_bytes = std::max(splitk_bytes, flp_gemm_splitk_bytes(b->n_tokens, b->proj[q].d_out));
-  splitk_bytes = (splitk_bytes + 255) & ~(size_t)255;
+  wt_bytes = (wt_bytes + 255) & ~(size_t)255;
   const size_t v_bytes = (v_elems * 4 + 255) & ~(size_t)255;
   const size_t seg_bytes = ((size_t)(4 * b->n_adapters + 5) * 4 + 255) & ~(size_t)255;
   const size_t perm_bytes = (T * 4 + 255) & ~(size_t)255;
   // token -> position in segment order, adapter -> first row of its tokens in the shrink output
   const size_t inv_bytes = fused ? perm_bytes + (((size_t)b->n_adapters * 4 + 255) & ~(size_t)255) : 0;
+  // dense products that are not fused with the expand step leave their unrounded result in the workspace, in slices
+  // of the contraction where the batch is small
+  std::vector<BaseGroup> groups;
+  size_t base_total = 0;
+  if (p->elem_bytes == 2 && !fused) {
+    const size_t rest = v_bytes + seg_bytes + perm_bytes + wt_bytes;
+    const size_t room = fixed ? (fixed->cap > rest ? fixed->cap - rest : 0) : (size_t)1 << 30;
+    base_total = plan_base(b, one_launch, room, &groups);
+  }
   void* ws = nullptr;
-  const size_t ws_bytes = v_bytes + seg_bytes + perm_bytes + wt_bytes + base_total + splitk_bytes + inv_bytes;
+  const size_t ws_bytes = v_bytes + seg_bytes + perm_bytes + wt_bytes + base_total + inv_bytes;
   if (fixed) {
     if (ws_bytes > fixed->cap) {
       flp_set_error("%s: the batch needs %zu bytes of intermediates, the fixed buffer holds %zu (fewer tokens, a lower "
@@ -489,7 +518,7 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
   a.group_start = a.tile_start + b->n_adapters + 1;
   a.perm = (int32_t*)(w + v_bytes + seg_bytes);
   if (fused) {
-    int32_t* inv_perm = (int32_t*)(w + v_bytes + seg_bytes + perm_bytes + wt_bytes + base_total + splitk_bytes);
+    int32_t* inv_perm = (int32_t*)(w + v_bytes + seg_bytes + perm_bytes + wt_bytes);
     uint8_t* wt = w + v_bytes + seg_bytes + perm_bytes;
     int32_t* vrow_base = (int32_t*)((uint8_t*)inv_perm + perm_bytes);
     FLP_TRY(flp_launch_lora_segment(a.T, a.token_adapter, a.n_adapters, a.n_seg, a.seg_adapter, a.seg_start, a.perm,
@@ -519,34 +548,66 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
       lp.vrow_base = vrow_base;
       return lp;
     };
-    if (gated_out) {
-      const FlpGemmLora lg = branch(0), lu = branch(1);
-      return flp_launch_gated_gemm(p->cfg.dtype, b->x, b->ld_x, b->proj[0].w_base, b->proj[1].w_base, gated_out, ld_gated,
-                                   b->n_tokens, b->proj[0].d_out, b->d_in, stream, &lg, &lu);
-    }
+    FlpGemmLora lp[FLP_MAX_PROJ];
+    FlpGemmOut out[FLP_MAX_PROJ] = {};
+    int N[FLP_MAX_PROJ];
     for (int q = 0; q < b->n_proj; ++q) {
-      const FlpGemmLora lp = branch(q);
-      FLP_TRY(flp_launch_base_gemm(p->cfg.dtype, b->x, b->ld_x, b->proj[q].w_base, b->proj[q].w_base_layout,
-                                   b->proj[q].y, b->proj[q].ld_y, b->n_tokens, b->proj[q].d_out, b->d_in, wt, nullptr,
-                                   nullptr, 0, stream, &lp));
+      lp[q] = branch(q);
+      N[q] = out[q].N = b->proj[q].d_out;
+      out[q].w = b->proj[q].w_base;
+      out[q].y = b->proj[q].y;
+      out[q].ld_y = b->proj[q].ld_y;
+    }
+    const unsigned allow = FLP_GEMM_NO_SPLIT | FLP_GEMM_LARGE_ONLY;
+    if (gated_out) {
+      out[0].w2 = out[1].w;
+      N[0] = out[0].N = 2 * b->proj[0].d_out;
+      out[0].y = gated_out;
+      out[0].ld_y = ld_gated;
+      const FlpGemmPlan plan = flp_gemm_plan(b->n_tokens, b->d_in, 1, N, allow, 0);
+      return flp_launch_gemm(p->cfg.dtype, b->x, b->ld_x, b->n_tokens, b->d_in, plan, 1, out, true, lp, stream);
+    }
+    const int step = one_launch ? b->n_proj : 1;
+    for (int q = 0; q < b->n_proj; q += step) {
+      if (b->proj[q].w_base_layout == 0) {
+        FLP_TRY(flp_launch_transpose16(out[q].w, wt, b->d_in, N[q], stream));
+        out[q].w = wt;
+      }
+      const FlpGemmPlan plan = flp_gemm_plan(b->n_tokens, b->d_in, step, N + q, allow, 0);
+      FLP_TRY(flp_launch_gemm(p->cfg.dtype, b->x, b->ld_x, b->n_tokens, b->d_in, plan, step, out + q, false, lp + q, stream));
     }
     return FLP_OK;
   }
   // base term first where the caller asked for it (x . W_base), then the adapters' deltas on top.
   // 16-bit pools also keep the product unrounded in the workspace so that base + delta is rounded
-  // once; tokens without an adapter keep the rounded value that the GEMM wrote into y.
-  {
+  // once; tokens without an adapter keep the rounded value that the product's kernels wrote into y.
+  if (p->elem_bytes == 4) {
+    for (int q = 0; q < b->n_proj; ++q)
+      if (b->proj[q].w_base)
+        FLP_TRY(flp_launch_gemm_f32((const float*)b->x, b->ld_x, (const float*)b->proj[q].w_base, b->proj[q].w_base_layout,
+                                    (float*)b->proj[q].y, b->proj[q].ld_y, b->n_tokens, b->proj[q].d_out, b->d_in, stream));
+  } else {
     uint8_t* wt = w + v_bytes + seg_bytes + perm_bytes;
     uint8_t* basep = wt + wt_bytes;
-    float* splitk = splitk_bytes ? (float*)(basep + base_total) : nullptr;
-    for (int q = 0; q < b->n_proj; ++q) {
-      if (!b->proj[q].w_base) continue;
-      float* y32 = p->elem_bytes == 2 ? (float*)basep : nullptr;
-      FLP_TRY(flp_launch_base_gemm(p->cfg.dtype, b->x, b->ld_x, b->proj[q].w_base, b->proj[q].w_base_layout,
-                                   b->proj[q].y, b->proj[q].ld_y, b->n_tokens, b->proj[q].d_out, b->d_in, wt, y32,
-                                   splitk, splitk_bytes, stream));
-      a.base32[q] = y32;
-      basep += base_bytes[q];
+    for (const BaseGroup& g : groups) {
+      FlpGemmOut out[FLP_MAX_PROJ] = {};
+      for (int i = 0; i < g.n; ++i) {
+        const flp_lora_proj& pr = b->proj[g.which[i]];
+        out[i].w = pr.w_base;
+        out[i].y = pr.y;
+        out[i].ld_y = pr.ld_y;
+        out[i].part = (float*)basep;
+        out[i].N = pr.d_out;
+        a.base32[g.which[i]] = (float*)basep;
+        basep += ((size_t)g.plan.splits * T * pr.d_out * 4 + 255) & ~(size_t)255;
+        if (pr.w_base_layout == 0) {
+          FLP_TRY(flp_launch_transpose16(pr.w_base, wt, b->d_in, pr.d_out, stream));
+          out[i].w = wt;
+        }
+      }
+      FLP_TRY(flp_launch_gemm(p->cfg.dtype, b->x, b->ld_x, b->n_tokens, b->d_in, g.plan, g.n, out, false, nullptr, stream));
+      if (g.plan.splits > 1)
+        FLP_TRY(flp_launch_gemm_reduce(p->cfg.dtype, b->n_tokens, g.n, out, g.plan.splits, false, true, stream));
     }
   }
   if (!mfma_ok) return flp_launch_lora_simple(p->cfg.dtype, a, stream);

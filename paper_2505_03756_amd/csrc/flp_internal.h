@@ -221,23 +221,51 @@ flp_status flp_launch_lora_segment(int32_t T, const int32_t* token_adapter, int3
                                    int32_t* inv_perm = nullptr, int32_t* vrow_base = nullptr);
 flp_status flp_launch_lora_mfma(int dtype, const FlpLoraArgs& a, const FlpLoraMfma& c, hipStream_t stream);
 flp_status flp_launch_lora_simple(int dtype, const FlpLoraArgs& a, hipStream_t stream);
-flp_status flp_launch_base_gemm(int dtype, const void* x, int64_t ld_x, const void* w, int w_layout, void* y,
-                                int64_t ld_y, int M, int N, int K, void* wt_scratch, float* y32, float* splitk_scratch,
-                                size_t splitk_bytes, hipStream_t stream, const FlpGemmLora* lora = nullptr);
-// true when flp_launch_base_gemm runs the large-batch kernel for this shape (the one that can take the LoRA branch
-// as an epilogue)
-bool flp_gemm_is_large(int dtype, int M, int N, int K, int64_t ld_x);
-// silu(x . Wg^T) * (x . Wu^T) in one pass (16-bit types, weights [N, K]); FLP_ENOTSUP, nothing launched, for shapes
-// that the large-batch kernel does not take
-flp_status flp_launch_gated_gemm(int dtype, const void* x, int64_t ld_x, const void* w_gate, const void* w_up,
-                                 void* out, int64_t ld_out, int M, int N, int K, hipStream_t stream,
-                                 const FlpGemmLora* lora_gate = nullptr, const FlpGemmLora* lora_up = nullptr);
-// true when flp_launch_gated_gemm takes this shape
-bool flp_gemm_gated_fits(int dtype, int M, int N, int K, int64_t ld_x);
+
+// ---- dense products (gemm.hip): up to FLP_MAX_PROJ matrices [N, K] over one input, 16-bit types
+enum { FLP_GEMM_64x32 = 0, FLP_GEMM_128x64, FLP_GEMM_128x128, FLP_GEMM_256x128, FLP_GEMM_256x256, FLP_GEMM_KINDS };
+struct FlpGemmPlan {
+  int kind;                    // tile, features x tokens
+  int splits;                  // slices of the contraction
+};
+struct FlpGemmOut {
+  const void* w;               // [N, K]
+  const void* w2;              // gated pair: the up matrix (w is the gate matrix), each [N / 2, K]
+  void* y;                     // rounded result (with several slices: written by flp_launch_gemm_reduce), or null
+  int64_t ld_y;
+  float* part;                 // unrounded slices [splits][M][N], or null (only with one slice)
+  int32_t N;
+};
+struct FlpGemmProj {           // the kernel's view of one FlpGemmOut
+  const uint16_t* w;
+  const uint16_t* w2;
+  uint16_t* y;
+  int64_t ld_y;
+  float* part;
+  int32_t N, tile0;            // tile0: first feature tile of this projection
+};
+struct FlpGemmArgs {
+  const uint16_t* x;
+  int64_t ld_x;
+  int32_t M, K, n_proj, f_tiles, m_tiles, splits;
+  int32_t gf, gm;              // (feature tile, slice) units x token tiles that run next to each other on one XCD
+  FlpGemmProj proj[FLP_MAX_PROJ];
+};
+enum { FLP_GEMM_NO_SPLIT = 1, FLP_GEMM_LARGE_ONLY = 2 };   // whole contractions only; only the tiles that take a LoRA epilogue
+// N: features of every projection (of a gated pair: both matrices' together)
+FlpGemmPlan flp_gemm_plan(int M, int K, int n_proj, const int* N, unsigned allow, size_t max_part_bytes);
+size_t flp_gemm_part_bytes(const FlpGemmPlan& plan, int M, int n_proj, const int* N);
+// lora: one per projection (gated: gate, up), or null
+flp_status flp_launch_gemm(int dtype, const void* x, int64_t ld_x, int M, int K, const FlpGemmPlan& plan, int n_proj,
+                           const FlpGemmOut* out, bool gated, const FlpGemmLora* lora, hipStream_t stream);
+// adds the slices; keep_sum: the unrounded sum stays in slice 0
+flp_status flp_launch_gemm_reduce(int dtype, int M, int n_proj, const FlpGemmOut* out, int splits, bool gated, bool keep_sum,
+                                  hipStream_t stream);
+flp_status flp_launch_transpose16(const void* w, void* wt, int K, int N, hipStream_t stream);   // [K, N] -> [N, K]
+flp_status flp_launch_gemm_f32(const float* x, int64_t ld_x, const float* w, int w_layout, float* y, int64_t ld_y, int M, int N,
+                               int K, hipStream_t stream);
 // flp_lora_apply_paged for exactly two projections with dense bases stored [d_out, d_in] and equal widths (gate and
 // up of an MLP), whose results are not stored: out = silu(y0) * y1 in one pass of the large-batch GEMM, each product
 // with its LoRA branch added before it is rounded.  FLP_ENOTSUP, nothing launched, when the batch is not one that
 // this path takes; the caller then runs flp_lora_apply_paged and the element-wise step.
 flp_status flp_lora_apply_gated(flp_pool* pool, const flp_lora_batch* batch, void* out, int64_t ld_out, void* hip_stream);
-// bytes of split-K scratch worth offering for an [M, N] product (0 for large batches, which are not split)
-inline size_t flp_gemm_splitk_bytes(int M, int N) { return M <= 1024 ? (size_t)8 * M * N * 4 : 0; }

@@ -4,18 +4,14 @@
 // projections of fll_layer_forward.
 //
 // 16-bit pools: both operands are read along the contraction (a W given as [d_in, d_out] is first transposed into
-// the pool's workspace).  Two tiled MFMA kernels, both computing the product transposed (A operand = rows of W^T,
-// B operand = token rows) with the rows of W^T fed in a permuted order, so that a lane ends up with 16 consecutive
-// output columns of one token and y is written in 32-byte pieces:
-//   gemm_nt_kernel      128 x 128 tile, 4 waves x (64 x 64), k tiles of 64 through LDS with the next tile prefetched
-//                       through registers; small batches, with the contraction split over grid z when tiles are few;
-//   gemm_nt256_kernel   256 x 256 tile, 4 waves x (128 x 128), operands streamed by direct global-to-LDS loads; large
-//                       batches.  Two epilogue variants: GATED (gate and up of an MLP in one pass, silu(g) * u stored)
-//                       and LORA (the expand step of the projection's LoRA branch added to the accumulators).
-// fp32 pools: a plain one-thread-per-output kernel (the fp32 workload is tiny).
-#include <atomic>
+// the pool's workspace), the projections that share an input go in one launch, and the contraction may be split into
+// slices whose fp32 partial products a second kernel (or the LoRA expand kernel) adds in slice order.
+// fp32 pools: a matrix-core kernel of its own (the fp32 workload is tiny and bound by latency).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <atomic>
+#include <cmath>
 #include <type_traits>
 
 #include "flp_internal.h"
@@ -23,7 +19,6 @@
 
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4g __attribute__((ext_vector_type(4)));
 typedef _Float16 h16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 b16x8 __attribute__((ext_vector_type(8)));
@@ -31,20 +26,18 @@ typedef __bf16 b16x8 __attribute__((ext_vector_type(8)));
 struct GF16 {
   typedef h16x8 vec;
   typedef _Float16 elem;
-  static __device__ __forceinline__ f32x16 mfma(vec a, vec b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+  typedef F16 S;
+  static __device__ __forceinline__ f32x4g mfma(vec a, vec b, f32x4g c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
   }
-  static __device__ __forceinline__ uint16_t out(float f) { return F16::from_float(f); }
-  static __device__ __forceinline__ float in(uint16_t b) { return F16::to_float(b); }
 };
 struct GBF16 {
   typedef b16x8 vec;
   typedef __bf16 elem;
-  static __device__ __forceinline__ f32x16 mfma(vec a, vec b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+  typedef BF16 S;
+  static __device__ __forceinline__ f32x4g mfma(vec a, vec b, f32x4g c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
-  static __device__ __forceinline__ uint16_t out(float f) { return BF16::from_float(f); }
-  static __device__ __forceinline__ float in(uint16_t b) { return BF16::to_float(b); }
 };
 
 // ---- W [K, N] -> Wt [N, K], 16-bit elements, 64 x 64 tiles through LDS
@@ -63,152 +56,45 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __rest
   }
 }
 
-constexpr int BM = 128, BN = 128, BK = 64;
-constexpr int kTile = 128 * BK * 2;        // bytes of one operand tile (16 KiB)
-
-// byte offset of 16-byte chunk c (0..7) of row r (0..127) inside an operand tile: two rows share
-// a 256-byte line and the 16 chunk slots of the line are XOR-swizzled with the line index, so the
-// 16 lanes that read one logical chunk of 16 consecutive rows hit 16 different bank groups
-__device__ __forceinline__ int tile_off(int r, int c) { return (r >> 1) * 256 + (((((r & 1) << 3) | c) ^ ((r >> 1) & 15)) << 4); }
-
-// The product is stored rounded into y and, when y32 is given, also unrounded as fp32 ([M, N]
-// dense): the LoRA expand kernel adds the adapter's delta to the unrounded value and rounds once;
-// rows of tokens without an adapter keep the rounded value.
-// With gridDim.z > 1 the contraction is split: slice z covers K / gridDim.z coefficients and writes its
-// unrounded partial product to part + z * M * N (dense fp32); gemm_splitk_reduce_kernel adds the slices in
-// order and rounds.  Small batches (decode) have too few 128 x 128 tiles to occupy the chip otherwise.
-template <typename G>
-__global__ __launch_bounds__(256, 2) void gemm_nt_kernel(const uint16_t* __restrict__ x, int64_t ld_x,
-                                                         const uint16_t* __restrict__ wt, uint16_t* __restrict__ y,
-                                                         int64_t ld_y, float* __restrict__ y32, int M, int N, int K,
-                                                         float* __restrict__ part) {
-  typedef typename G::vec vec;
-  __shared__ __attribute__((aligned(16))) uint8_t smem[2][2 * kTile];      // [buffer][Wt tile | x tile]
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lr = lane & 31, hf = lane >> 5;
-  const int n0 = blockIdx.x * BN, m0 = blockIdx.y * BM;
-  const int wn = (wave & 1) * 64, wm = (wave >> 1) * 64;                   // this wave's 64 x 64 corner
-
-  // staging: thread -> chunk (tid & 7) of rows (tid >> 3) + 32*i, i = 0..3, for both operands
-  const int sc = tid & 7, sr = tid >> 3;
-  u32x4 areg[4], breg[4];
-  auto load_tiles = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = sr + 32 * i;
-      const int n = n0 + r < N ? n0 + r : N - 1;                            // clamped rows are never stored
-      const int m = m0 + r < M ? m0 + r : M - 1;
-      areg[i] = *reinterpret_cast<const u32x4*>(wt + (int64_t)n * K + k0 + 8 * sc);
-      breg[i] = *reinterpret_cast<const u32x4*>(x + (int64_t)m * ld_x + k0 + 8 * sc);
-    }
-  };
-  auto store_tiles = [&](uint8_t* buf) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = sr + 32 * i;
-      *reinterpret_cast<u32x4*>(buf + tile_off(r, sc)) = areg[i];
-      *reinterpret_cast<u32x4*>(buf + kTile + tile_off(r, sc)) = breg[i];
-    }
-  };
-
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  // A-operand row a of a 32-row tile is output column 16*((a>>2)&1) + 4*(a>>3) + (a&3) of that tile
-  const int acol = (((lr >> 2) & 1) << 4) | ((lr >> 3) << 2) | (lr & 3);
-
-  const int nk = K / BK / (int)gridDim.z, kt0 = (int)blockIdx.z * nk;    // this slice's k tiles
-  if (gridDim.z > 1) {
-    y = nullptr;
-    y32 = part + (int64_t)blockIdx.z * M * N;
-  }
-  load_tiles(kt0 * BK);
-  store_tiles(smem[0]);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const uint8_t* buf = smem[kt & 1];
-    if (kt + 1 < nk) load_tiles((kt0 + kt + 1) * BK);
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      vec af[2], bf[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        af[i] = *reinterpret_cast<const vec*>(buf + tile_off(wn + 32 * i + acol, 2 * kk + hf));
-        bf[i] = *reinterpret_cast<const vec*>(buf + kTile + tile_off(wm + 32 * i + lr, 2 * kk + hf));
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = G::mfma(af[i], bf[j], acc[i][j]);
-    }
-    if (kt + 1 < nk) store_tiles(smem[(kt + 1) & 1]);
-    __syncthreads();
-  }
-
-  // lane (token lr of tile j, half hf) holds columns 16*hf .. 16*hf+15 of column tile i:
-  // register 4*q + r of the accumulator is column 16*hf + 4*q + r
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int m = m0 + wm + 32 * j + lr;
-    if (m >= M) continue;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int n = n0 + wn + 32 * i + 16 * hf;
-      if (y32) {                                     // 64 contiguous bytes per lane where the row allows it
-        float* yp32 = y32 + (int64_t)m * N + n;
-        if (n + 16 <= N && (N & 3) == 0) {
-#pragma unroll
-          for (int e4 = 0; e4 < 4; ++e4) {
-            f32x4g v4 = {acc[i][j][4 * e4], acc[i][j][4 * e4 + 1], acc[i][j][4 * e4 + 2], acc[i][j][4 * e4 + 3]};
-            reinterpret_cast<f32x4g*>(yp32)[e4] = v4;
-          }
-        } else {
-          for (int e = 0; e < 16; ++e)
-            if (n + e < N) yp32[e] = acc[i][j][e];
-        }
-      }
-      if (!y) continue;                              // a slice of a split contraction writes only its partial
-      uint16_t o[16];
-#pragma unroll
-      for (int e = 0; e < 16; ++e) o[e] = G::out(acc[i][j][e]);
-      uint16_t* yp = y + (int64_t)m * ld_y + n;
-      if (n + 16 <= N) {
-        u32x4 raw[2];
-        __builtin_memcpy(raw, o, 32);
-        reinterpret_cast<u32x4*>(yp)[0] = raw[0];
-        reinterpret_cast<u32x4*>(yp)[1] = raw[1];
-      } else {
-        for (int e = 0; e < 16; ++e)
-          if (n + e < N) yp[e] = o[e];
-      }
-    }
-  }
-}
-
-// ---- large batches: 256 x 256 output tile per workgroup, operands streamed by direct global-to-LDS loads
+// ------------------------------------------------------------------------------- the tiled kernel
+// One workgroup computes a tile of FT features x MT tokens of one projection and one slice of the contraction, as
+// the transposed product (A operand = rows of W, B operand = token rows) with mfma_f32_16x16x32.  Measured against
+// 32x32x16 in the same loop (M 16384, N = K = 4096): the chip holds 2.02 GHz instead of 1.70 at the same matrix-pipe
+// share (the 16 x 16 form moves less accumulator data per product) and the launch is 8 - 17 % shorter.
 //
-// Four waves, each a 128 x 128 corner (4 x 4 accumulators of mfma_f32_32x32x16: 256 accumulator registers,
-// one wave per SIMD), so that a k step of 16 costs 8 fragment reads for 16 MFMAs: LDS traffic per flop is
-// half that of a 64 x 64 corner, and the operand tiles are fetched from L2 half as often as with 128 x 128
-// workgroup tiles.  Operand tiles are 256 rows x 64 coefficients (32 KiB each, 64 KiB per stage, two stages):
-// a row's 64 coefficients are one whole 128-byte line, and a global_load_lds_dwordx4 instruction (no registers,
-// no LDS store instructions; inline assembly with its own s_waitcnt vmcnt) moves 8 whole lines.  Requests of
-// half a line (tiles of 32 coefficients in a ring of four) made every line cross from L2 twice and were 4-8 %
-// slower.  One barrier per stage, before its last k step: by then the wave has waited for its loads of the next
-// stage and has read the last fragments of this one, so after the barrier the next stage is complete for
-// everybody (its first fragments are read during the last step) and this stage's buffer is free for the stage
-// after next.  LDS layout: row r at r * 128, its 16-byte chunk c in slot c ^ gswz(r), which spreads the 16 lanes
-// that read one chunk of their (permuted) 16 rows over the 16 slots of a 256-byte bank window; the swizzle is
-// applied on the global side (a lane fetches the chunk that belongs at its fixed LDS slot).  Workgroups of one
-// XCD (ids congruent modulo 8) cover 4 x 8 blocks of tiles, so the 32 that run together fetch 12 operand panels
-// instead of 64.
-constexpr int GT = 256, GK = 64, kGOperand = GT * GK * 2, kGStage = 2 * kGOperand, kGStages = 2;   // 64 KiB per stage
-// s_waitcnt immediate (gfx9 encoding: vmcnt[3:0] + [15:14], expcnt[6:4], lgkmcnt[11:8]): vmcnt only
-constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+// Operands travel in k tiles of 64 coefficients, so that a row of a tile is one whole 128-byte line, from memory to
+// LDS with the direct loads of gfx950 (8 lines per instruction; inline assembly with its own s_waitcnt vmcnt) into a
+// ring of ST stages.  LDS position rho of a row inside a tile: chunk c (16 bytes) sits in slot c ^ ((rho >> 1) & 7) of
+// the row's 128 bytes; the 16 rows of an operand fragment are 16 neighbouring positions, so the 16 lanes that read one
+// chunk hit 16 different slots of a 256-byte window.  Which feature a position holds is free (the lane that loads
+// it fetches any row): positions 16 tau + m of a 64-feature group hold feature 4 m + tau, so that a lane's four
+// accumulators of one token are 16 consecutive features and results leave in 32-byte (fp32: 64-byte) pieces.
+//
+// Two loops:
+//   ring (ST >= 3)   every wave reads the fragments of the next k step while it multiplies the current one; one barrier
+//                    per stage, ahead of the stage's last k step; ST - 1 stages in flight.  Small batches live on loads
+//                    in flight, so their tiles are narrow in tokens and the ring is deep.
+//   ping-pong (PP)   256 x 256 tiles, two stages of 64 KiB, eight waves in two groups of four (one wave of each group
+//                    per SIMD) that take turns: while one group reads its fragments and requests the stage after next,
+//                    the other multiplies; they change places at every barrier.  (M 20000, N = K = 4096: 0.542 ms,
+//                    against 0.590 ms for the ring form of the same tile and 0.659 ms for the four-wave kernel with
+//                    128 x 128 corners that was here before.)
+//
+// GATED: the gated-SiLU pair of an MLP in one pass.  The features are those of both matrices interleaved in groups
+// of 64 (32 gate rows, the same 32 up rows: positions 16 tau + m hold feature 2 m + (tau & 1) of matrix tau >> 1), so a
+// lane holds gate and up of the same 8 features and stores silu(g) * u, both rounded to the element type first as
+// two separate products and an element-wise kernel would have stored and re-read them.
+//
+// LORA: the expand step of the projections' LoRA branches as an epilogue.  For every adapter among a wave's tokens
+// (tokens of a sequence are neighbours, so one or two) it adds B^T (64 features x ranks) times the tokens' scaled v,
+// 16 ranks per step: v enters as a 16-bit high part (k slots 0 .. 15) plus remainder (16 .. 31) against the same
+// coefficients, so it keeps its fp32 precision.  The look-ups are made before the loop and v is laid out in LDS once
+// per workgroup; chains of dependent loads per adapter, token tile and slice of v had cost a fifth of the launch.  The coefficients come from the adapter's pages eight bytes (four
+// features) per lane and rank and are turned into the four tiles' fragments in registers.  The sum is rounded once.
+constexpr int GK = 64;
+constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }   // s_waitcnt vmcnt(n) only
+constexpr int kWaitLgkm0 = 15 | (3 << 14) | (7 << 4);                                           // lgkmcnt(0) only
+constexpr int kWaitAll0 = 7 << 4;                                                               // vmcnt(0) and lgkmcnt(0)
 
 // M0 is named as clobbered so that no pass keeps a value of its own alive in it across the statement; the
 // compiler notes that it reserves the register, which is the point.
@@ -221,502 +107,749 @@ __device__ __forceinline__ void gload_lds16(const void* base, uint32_t voff, uin
 #pragma clang diagnostic pop
 typedef __attribute__((address_space(3))) uint8_t g_lds_u8;
 
-// swizzle of row r: the 16-byte chunk c of the row sits in slot c ^ gswz(r) of the row's 128 bytes
-__device__ __forceinline__ int gswz(int r) { return ((r >> 1) & 3) | (((r >> 4) & 1) << 2); }
-// byte offset of 16-byte chunk c (0..7) of row r (0..255) inside a 256 x 64 operand tile
-__device__ __forceinline__ int gtile_off(int r, int c) { return r * 128 + ((c ^ gswz(r)) << 4); }
+__device__ __forceinline__ int gswz(int rho) { return (rho >> 1) & 7; }
 
-//
-// GATED: the gated-SiLU pair of an MLP in one pass.  The 256 feature rows of a tile are 128 rows of the gate
-// matrix (wt) and the same 128 rows of the up matrix (wt2): the waves with wi = 0 multiply the gate rows, those
-// with wi = 1 the up rows of the same features and tokens.  After the loop the up waves hand their accumulators
-// over through LDS (lane to lane: both layouts are the same) and the gate waves store silu(g) * u, with g and u rounded to the element type first, as the two separate products and
-// the element-wise kernel would have stored and re-read them.  Neither product is written.
-//
-// LORA: the expand step of one projection's LoRA branch as an epilogue.  After the loop a wave holds the dense product
-// of its 128 tokens x 128 features; for every adapter among those tokens (tokens of a sequence are neighbours, so one
-// or two) it adds B^T (features x ranks, gathered from the adapter's pages in the A-operand layout of the same
-// permuted feature rows) times the tokens' scaled v (ranks x tokens, zero for tokens of other adapters; split into a
-// 16-bit high part and remainder, two MFMAs, so that v keeps its fp32 precision), 16 ranks per step, straight into
-// the accumulators.  The sum is rounded once; there is no fp32 copy of the product and no second pass over y.
-template <typename G, bool GATED, bool LORA>
-__global__ __launch_bounds__(256, 1) void gemm_nt256_kernel(const uint16_t* __restrict__ x, int64_t ld_x,
-                                                            const uint16_t* __restrict__ wt,
-                                                            const uint16_t* __restrict__ wt2, uint16_t* __restrict__ y,
-                                                            int64_t ld_y, float* __restrict__ y32, int M, int N, int K,
-                                                            int tiles_n, int tiles_m, int groups_n, FlpGemmLora lpa,
-                                                            FlpGemmLora lp2) {
-  constexpr int GTN = GATED ? GT / 2 : GT;              // output features per tile
-  typedef typename G::vec vec;
-  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, hf = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wi = wave & 1, wj = wave >> 1;
+struct GemmLoraArgs {
+  FlpGemmLora p[FLP_MAX_PROJ];     // per projection; gated: gate, up
+};
+struct NoLora {};
 
-  // workgroup -> tile: 32 consecutive workgroups of one XCD form a block of 4 feature tiles x 8 token tiles
-  const int xcd = blockIdx.x & 7, l = blockIdx.x >> 3;
-  const int gid = (l >> 5) * 8 + xcd, within = l & 31;
-  const int tn = (gid % groups_n) * 4 + (within & 3), tm = (gid / groups_n) * 8 + (within >> 2);
-  if (tn >= tiles_n || tm >= tiles_m) return;
-  const int n0 = tn * GTN, m0 = tm * GT;
-  const uint16_t* __restrict__ wsrc = GATED && wave >= 2 ? wt2 : wt;   // feature rows 128 .. 255 of a gated tile: the up matrix
+// What the LoRA epilogue needs to know about a tile's tokens, looked up while the first stages of the tile are on
+// their way: which adapter (slot of the current round) and row of v a token has, and the page rows of the slots'
+// coefficients.  Without it every adapter costs the epilogue five dependent trips to memory.  A tile with more than
+// kLoraSlots adapters takes them in rounds.
+constexpr int kLoraSlots = 8;
+struct GemmLoraLds {
+  uint64_t row[2][kLoraSlots][64];  // address of rank row rho of a slot's B; [1]: the up matrix of a gated pair
+  int32_t ad[256];                  // adapter of a token of the tile, -1: none
+  int32_t vrow[256];                // row of v of the token
+  int32_t index[256];               // position of the token's adapter in `list`, -1: none
+  int32_t list[256];                // the tile's adapters
+  int32_t n, rank[kLoraSlots];
+};
 
-  // ---- staging: wave w moves rows 64w .. 64w+63 of both tiles, 8 rows (8 whole 128-byte lines) per instruction;
-  //      lane l fills slot l % 8 of row l / 8 of the instruction's 1 KiB of LDS, i.e. fetches chunk slot ^ gswz(row)
-  uint32_t va[8], vb[8];
+// the tables of the adapters list[first .. first + kLoraSlots)
+template <bool GATED, int NTHR>
+__device__ __forceinline__ void lora_round(const FlpGemmLora* lp0, const FlpGemmLora* lp1, int N, int first, GemmLoraLds& t) {
+  const int rpb = (int)(lp0->block_elems / N);
+  const int n = t.n - first < kLoraSlots ? t.n - first : kLoraSlots;
+  for (int e = threadIdx.x; e < n * 64; e += NTHR) {
+    const int s = e >> 6, rho = e & 63, ad = t.list[first + s];
+    const int r = lp0->rank[ad] < lp0->max_rank ? lp0->rank[ad] : lp0->max_rank;
+    if (rho == 0) t.rank[s] = r;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int r = 64 * wave + 8 * q + (lane >> 3);
-    const int ch = (lane & 7) ^ gswz(r);
-    const int rf = GATED ? (r & (GTN - 1)) : r;
-    const int n = n0 + rf < N ? n0 + rf : N - 1;              // clamped rows are never stored
-    const int m = m0 + r < M ? m0 + r : M - 1;
-    va[q] = (uint32_t)(((int64_t)n * K + 8 * ch) * 2);
-    vb[q] = (uint32_t)(((int64_t)m * ld_x + 8 * ch) * 2);
-  }
-  const uint32_t lds_wave = (uint32_t)(uintptr_t)(g_lds_u8*)smem + 8192u * (uint32_t)wave;
-  const int nk = K / GK;
-  // one of the 16 direct loads of stage t: q = 0..7 the W^T tile, q = 8..15 the token tile
-  auto issue_load = [&](int t, int q) {
-    const int tk = t < nk ? t : nk - 1;                       // past the end: the last tile again, into a free stage
-    const uint32_t dst = lds_wave + (uint32_t)(t & 1) * kGStage;
-    if (q < 8)
-      gload_lds16(wsrc + (int64_t)tk * GK, va[q], dst + 1024 * q);
-    else
-      gload_lds16(x + (int64_t)tk * GK, vb[q - 8], dst + kGOperand + 1024 * (q - 8));
-  };
-
-  // ---- fragments: both operands take their 32 rows in the permuted order that gives a lane 16 consecutive output
-  //      columns (row a of a 32-row tile is column 16*((a>>2)&1) + 4*(a>>3) + (a&3)); for the token tile the
-  //      permutation only decides which token a lane ends up holding
-  const int acol = (((lr >> 2) & 1) << 4) | ((lr >> 3) << 2) | (lr & 3);
-  int offa[4], offb[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    offa[i] = gtile_off(128 * wi + 32 * i + acol, hf);
-    offb[i] = kGOperand + gtile_off(128 * wj + 32 * i + acol, hf);
-  }
-  // chunk 2*kk + hf of the row: bits 1, 2 of the slot, bits 5, 6 of the offset
-  auto frag = [&](int t, int kk, int off) {
-    return *reinterpret_cast<const vec*>(smem + (t & 1) * kGStage + (off ^ (kk << 5)));
-  };
-
-  f32x16 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  vec a0[4], b0[4], a1[4], b1[4];
-  // One k step of 16: four groups of {two direct loads or none, the two fragment reads that the step after this
-  // one needs, four MFMAs}, fenced so that they stay in this order (a burst of loads holds the wave's in-order
-  // instruction stream, and with it the matrix pipe, for as long as the memory pipeline takes to accept them;
-  // measured: two loads per group over two steps; all sixteen in one step costs 5 %, waiting a stage later for
-  // them changes nothing - the stream's rate, not its latency, is what the loop feels).
-  auto kstep = [&](vec(&ca)[4], vec(&cb)[4], vec(&na)[4], vec(&nb)[4], int t_next, int kk_next, int t_load, int q0) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      if (q0 >= 0) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) issue_load(t_load, q0 + 2 * g + u);
+    for (int g = 0; g < (GATED ? 2 : 1); ++g) {
+      const FlpGemmLora& lp = g ? *lp1 : *lp0;
+      if (r > 0) {
+        const int row = lp.b_row_base[ad] + (rho < r ? rho : 0);
+        const uint16_t* a = reinterpret_cast<const uint16_t*>(lp.pool) +
+                            (int64_t)lp.tables[lp.b_tab_off[ad] + row / rpb] * lp.block_elems + (int64_t)(row % rpb) * N;
+        t.row[g][s][rho] = (uint64_t)(uintptr_t)a;
       }
-      if (g < 2) {                                            // all token fragments first: the next step's first group needs them
-        nb[2 * g] = frag(t_next, kk_next, offb[2 * g]);
-        nb[2 * g + 1] = frag(t_next, kk_next, offb[2 * g + 1]);
-      } else {
-        na[2 * g - 4] = frag(t_next, kk_next, offa[2 * g - 4]);
-        na[2 * g - 3] = frag(t_next, kk_next, offa[2 * g - 3]);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[g][j] = G::mfma(ca[g], cb[j], acc[g][j]);
-      __builtin_amdgcn_sched_barrier(0);
     }
-  };
+  }
+}
 
-  // ---- prologue: stage 0 complete, the first half of stage 1 requested
-#pragma unroll
-  for (int q = 0; q < 16; ++q) issue_load(0, q);
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+template <bool GATED, int MT, int NTHR>
+__device__ __forceinline__ void lora_setup(const FlpGemmLora* lp0, const FlpGemmLora* lp1, int N, int m0, int M, GemmLoraLds& t) {
+  static_assert(MT <= NTHR && MT <= 256, "a thread looks up one token");
+  const int tid = threadIdx.x;
+  if (tid < MT) {
+    const int m = m0 + tid;
+    int ad = m < M ? lp0->token_adapter[m] : -1;
+    if (ad >= lp0->n_adapters) ad = -1;
+    t.ad[tid] = ad;
+    t.vrow[tid] = ad >= 0 ? lp0->vrow_base[ad] + lp0->inv_perm[m] : 0;
+    t.index[tid] = -1;
+  }
   __syncthreads();
+  if (tid < 64) {                                         // one wave lists the adapters
+    int mine[MT / 64], n = 0;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) issue_load(1, q);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    a0[i] = frag(0, 0, offa[i]);
-    b0[i] = frag(0, 0, offb[i]);
-  }
-  for (int kt = 0; kt < nk; ++kt) {
-    // Stage kt is multiplied in four k steps.  The second half of stage kt + 1 is requested during the first step;
-    // before the last step the wave waits for its loads of stage kt + 1, and after the barrier everybody's have
-    // landed and everybody has read the last fragments of stage kt: the last step reads the first fragments of
-    // stage kt + 1 and requests the first half of stage kt + 2 into the buffer that stage kt leaves.
-    kstep(a0, b0, a1, b1, kt, 1, kt + 1, 8);
-    kstep(a1, b1, a0, b0, kt, 2, 0, -1);
-    kstep(a0, b0, a1, b1, kt, 3, 0, -1);
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    __syncthreads();
-    kstep(a1, b1, a0, b0, kt + 1, 0, kt + 2, 0);
-  }
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));               // the look-ahead loads must land before the LDS is released
-
-  if constexpr (LORA) {
-    typedef typename G::elem elem;
-    // a gated tile's up waves add the up projection's branch (lp2), everybody else the projection's own (lpa)
-    const FlpGemmLora& lp = GATED && wi == 1 ? lp2 : lpa;
-    const int fbase = GATED ? n0 : n0 + 128 * wi;         // the wave's first feature
-    const uint16_t* __restrict__ pool = reinterpret_cast<const uint16_t*>(lp.pool);
-    const int rpb = (int)(lp.block_elems / N);
-    int adj[4], posj[4];                                  // adapter and segment-order position of the lane's four tokens
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + 128 * wj + 32 * j + acol;
-      int ad = m < M ? lp.token_adapter[m] : -1;
-      if (ad >= lp.n_adapters) ad = -1;
-      adj[j] = ad;
-      posj[j] = ad >= 0 ? lp.inv_perm[m] : 0;
-    }
+    for (int k = 0; k < MT / 64; ++k) mine[k] = t.ad[64 * k + tid];
     for (;;) {
       int cand = -1;
 #pragma unroll
-      for (int j = 3; j >= 0; --j) cand = adj[j] >= 0 ? adj[j] : cand;
+      for (int k = 0; k < MT / 64; ++k) cand = mine[k] >= 0 ? mine[k] : cand;
       const uint64_t todo = __ballot(cand >= 0);
       if (!todo) break;
-      const int ad = __builtin_amdgcn_readlane(cand, __ffsll((long long)todo) - 1);      // wave-uniform
-      const int r = lp.rank[ad] < lp.max_rank ? lp.rank[ad] : lp.max_rank;
-      if (r > 0) {
-        const float sc = lp.scale[ad];
-        const int64_t vrow0 = lp.vrow_base[ad];
-        const int32_t* __restrict__ tab = lp.tables + lp.b_tab_off[ad];
-        const int brow0 = lp.b_row_base[ad];
-        for (int nt = 0; 16 * nt < r; ++nt) {
-          // A operand: B[rho, feature] for the lane's 8 ranks and its feature row of each of the four feature tiles
-          const uint16_t* rowp[8];
+      const int ad = __builtin_amdgcn_readlane(cand, __ffsll((long long)todo) - 1);
 #pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const int rho = 16 * nt + 8 * hf + q;
-            const int row = brow0 + (rho < r ? rho : 0);
-            rowp[q] = pool + (int64_t)tab[row / rpb] * lp.block_elems + (int64_t)(row % rpb) * N;
-          }
-          vec af[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int f = fbase + 32 * i + acol;
-            const int fc = f < N ? f : N - 1;
-            uint16_t g8[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) g8[q] = rowp[q][fc];
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-              if (!(16 * nt + 8 * hf + q < r && f < N)) g8[q] = 0;
-            __builtin_memcpy(&af[i], g8, 16);
-          }
-          // B operand: the tokens' scaled v for those 8 ranks, zero for tokens of other adapters
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            float v8[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v8[q] = 0.f;
-            if (adj[j] == ad) {
-              for (int ks = 0; ks < lp.k_splits; ++ks) {
-                const float* vp = lp.v + (((int64_t)ks * lp.v_rows + vrow0 + posj[j]) * lp.n_proj + lp.p) * lp.rp +
-                                  16 * nt + 8 * hf;
-                const f32x4g x0 = *reinterpret_cast<const f32x4g*>(vp), x1 = *reinterpret_cast<const f32x4g*>(vp + 4);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                  v8[q] += x0[q];
-                  v8[4 + q] += x1[q];
-                }
-              }
-            }
-            vec bh, bl;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              const float vs = v8[q] * sc;
-              const elem h = (elem)vs;
-              bh[q] = h;
-              bl[q] = (elem)(vs - (float)h);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              acc[i][j] = G::mfma(af[i], bh, acc[i][j]);
-              acc[i][j] = G::mfma(af[i], bl, acc[i][j]);
-            }
-          }
+      for (int k = 0; k < MT / 64; ++k)
+        if (mine[k] == ad) {
+          t.index[64 * k + tid] = n;
+          mine[k] = -1;
         }
+      if (tid == 0) t.list[n] = ad;
+      ++n;
+    }
+    if (tid == 0) t.n = n;
+  }
+  __syncthreads();
+  lora_round<GATED, NTHR>(lp0, lp1, N, 0, t);
+}
+
+// The scaled v of the tile's tokens as B operands, in the LDS that the ring leaves: block (token tile, rank tile) of 1 KiB
+// holds the 64 lanes' fragments, ranks 8 kq .. 8 kq + 7 as a 16-bit high part (lanes 16 kq ..) and remainder
+// (lanes 32 + 16 kq ..).  Once per workgroup: its waves share the tokens, and the sums over the shrink step's slices
+// are all in flight together.
+template <typename G, int MT, int NTHR>
+__device__ __forceinline__ void lora_stage_v(const FlpGemmLora& lp, const GemmLoraLds& t, uint8_t* smem) {
+  typedef typename G::elem elem;
+  const int n_g8 = lp.rp / 8;                             // groups of 8 ranks: 2, 4 or 8
+  const int64_t step = (int64_t)lp.v_rows * lp.n_proj * lp.rp;
+#pragma unroll 2
+  for (int e = threadIdx.x; e < MT * n_g8; e += NTHR) {
+    const int tok = e / n_g8, g8 = e - tok * n_g8;
+    const int ad = t.ad[tok];
+    f32x4g x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
+    if (ad >= 0) {
+      const float* vp = lp.v + ((int64_t)t.vrow[tok] * lp.n_proj + lp.p) * lp.rp + 8 * g8;
+      for (int ks = 0; ks < lp.k_splits; ++ks, vp += step) {
+        x0 += *reinterpret_cast<const f32x4g*>(vp);
+        x1 += *reinterpret_cast<const f32x4g*>(vp + 4);
       }
+      const float sc = lp.scale[ad];
+      x0 *= sc;
+      x1 *= sc;
+    }
+    elem hi[8], lo[8];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) adj[j] = adj[j] == ad ? -1 : adj[j];
+    for (int q = 0; q < 8; ++q) {
+      const float v = q < 4 ? x0[q & 3] : x1[q & 3];
+      hi[q] = (elem)v;
+      lo[q] = (elem)(v - (float)hi[q]);
+    }
+    uint8_t* blk = smem + ((tok >> 4) * (n_g8 / 2) + (g8 >> 1)) * 1024 + ((tok & 15) + 16 * (g8 & 1)) * 16;
+    u32x4 raw;
+    __builtin_memcpy(&raw, hi, 16);
+    *reinterpret_cast<u32x4*>(blk) = raw;
+    __builtin_memcpy(&raw, lo, 16);
+    *reinterpret_cast<u32x4*>(blk + 512) = raw;
+  }
+}
+
+// adds one projection's LoRA branch of one slot to NTAU feature tiles (acc[TAU0 .. TAU0 + NTAU - 1][.]) of a wave; the
+// lane's tile row m of tile TAU0 + q is feature f0 + NTAU * m + q; v: the wave's first token tile's fragments
+template <typename G, int TAU0, int NTAU, int AT>
+__device__ __forceinline__ void add_lora(const uint64_t* rows, int r, int n_nt, const int32_t* index, int slot,
+                                         const uint8_t* v, int f0, int N, f32x4g (&acc)[4][AT]) {
+  typedef typename G::vec vec;
+  const int lane = threadIdx.x & 63, m16 = lane & 15, kg = lane >> 4, kq = kg & 1;
+  int fc = f0 + NTAU * m16;                               // N is a multiple of 8 and f0 of 32: a lane's features are all in or all out
+  const bool fvalid = fc < N;
+  fc = fvalid ? fc : 0;
+  // A operand: B[rho, feature] for the lane's 8 ranks and its NTAU neighbouring features, one rank tile ahead
+  uint32_t g[8][NTAU / 2];
+  auto fetch = [&](int nt) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const uint32_t* rp = reinterpret_cast<const uint32_t*>((uintptr_t)rows[16 * nt + 8 * kq + q] + 2 * fc);
+#pragma unroll
+      for (int h = 0; h < NTAU / 2; ++h) g[q][h] = rp[h];
+    }
+  };
+  fetch(0);
+  for (int nt = 0; 16 * nt < r; ++nt) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int h = 0; h < NTAU / 2; ++h) g[q][h] = 16 * nt + 8 * kq + q < r && fvalid ? g[q][h] : 0u;
+    vec af[NTAU];
+#pragma unroll
+    for (int t = 0; t < NTAU; ++t) {
+      u32x4 e;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)                         // ranks 2 q, 2 q + 1 of feature t: its half of the two words
+        e[q] = __builtin_amdgcn_perm(g[2 * q + 1][t / 2], g[2 * q][t / 2], t & 1 ? 0x07060302u : 0x05040100u);
+      __builtin_memcpy(&af[t], &e, 16);
+    }
+    if (16 * (nt + 1) < r) fetch(nt + 1);
+#pragma unroll
+    for (int j = 0; j < AT; ++j) {
+      u32x4 raw = *reinterpret_cast<const u32x4*>(v + (j * n_nt + nt) * 1024 + lane * 16);
+      const uint32_t keep = index[16 * j + m16] == slot ? 0xffffffffu : 0u;     // zero for tokens of other adapters
+      raw &= keep;
+      vec b;
+      __builtin_memcpy(&b, &raw, 16);
+#pragma unroll
+      for (int t = 0; t < NTAU; ++t) acc[TAU0 + t][j] = G::mfma(af[t], b, acc[TAU0 + t][j]);
+    }
+  }
+}
+
+// WF x WT waves of 64 features x 16 AT tokens each
+template <typename G, int WF, int WT, int AT, int ST, bool PP, bool GATED, bool LORA>
+__global__ __launch_bounds__(64 * WF * WT, (WF * WT + 3) / 4)
+    void gemm_kernel(FlpGemmArgs a, std::conditional_t<LORA, GemmLoraArgs, NoLora> la) {
+  typedef typename G::vec vec;
+  typedef typename G::S S;
+  constexpr int FT = 64 * WF, MT = 16 * WT * AT, NW = WF * WT;
+  constexpr int NF = FT / 8 / NW;                       // loads of W rows of a wave per stage (8 rows each)
+  constexpr int NPER = (FT + MT) / 8 / NW;              // all loads of a wave per stage
+  constexpr int kStage = (FT + MT) * 128;
+  static_assert(FT / 8 % NW == 0 && MT / 8 % NW == 0, "the waves share the loads of a stage evenly");
+  static_assert(!PP || (ST == 2 && WT == 2 && WF == 4), "ping-pong: two groups of four waves, two stages");
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  const int tid = threadIdx.x, lane = tid & 63, m16 = lane & 15, kg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wf = wave % WF, wt = wave / WF;
+
+  // workgroup -> (feature tile, slice, token tile): blocks of gf (feature tile, slice) units x gm token tiles run next
+  // to each other on one XCD (workgroups are placed on the 8 XCDs in turn), so that an operand tile crosses from memory
+  // into one L2 once
+  const int xcd = blockIdx.x & 7, l = blockIdx.x >> 3;
+  const int grp = (l / (a.gf * a.gm)) * 8 + xcd, within = l % (a.gf * a.gm);
+  const int n_units = a.f_tiles * a.splits, ug = (n_units + a.gf - 1) / a.gf;
+  const int u = (grp % ug) * a.gf + within % a.gf, tm = (grp / ug) * a.gm + within / a.gf;
+  if (u >= n_units || tm >= a.m_tiles) return;
+  const int z = u / a.f_tiles;
+  int ft = u - z * a.f_tiles;
+  int p = 0;
+  while (p + 1 < a.n_proj && ft >= a.proj[p + 1].tile0) ++p;
+  const FlpGemmProj& pr = a.proj[p];
+  ft -= pr.tile0;
+  const int N = pr.N;                                   // GATED: rows of both matrices together
+  const int n0 = ft * FT, m0 = tm * MT, K = a.K;
+  const int nk_all = K / GK;
+  const int kt0 = (int)((int64_t)nk_all * z / a.splits), nk = (int)((int64_t)nk_all * (z + 1) / a.splits) - kt0;
+
+  // ---- loads: instruction j of a stage covers LDS rows 8 j .. 8 j + 7 (W rows first, then tokens); wave w issues
+  //      j = w, w + NW, ...; offsets are relative to the tile's first row, so 32 bits always do.  Rows past the end
+  //      repeat the last one and are never stored.
+  uint32_t voff[NPER];
+#pragma unroll
+  for (int q = 0; q < NPER; ++q) {
+    const int rl = 8 * (wave + NW * q) + (lane >> 3);
+    if (q < NF) {
+      const int g64 = rl & ~63, tau = (rl >> 4) & 3, m = rl & 15;
+      int row;
+      if (GATED) {
+        row = (g64 >> 1) + 2 * m + (tau & 1);
+        row = n0 / 2 + row < N / 2 ? row : N / 2 - 1 - n0 / 2;
+      } else {
+        row = g64 + 4 * m + tau;
+        row = n0 + row < N ? row : N - 1 - n0;
+      }
+      voff[q] = (uint32_t)row * (uint32_t)(K * 2) + 16u * ((lane & 7) ^ gswz(rl));
+    } else {
+      const int r = rl - FT;
+      const int row = m0 + r < a.M ? r : a.M - 1 - m0;
+      voff[q] = (uint32_t)row * (uint32_t)(a.ld_x * 2) + 16u * ((lane & 7) ^ gswz(rl));
+    }
+  }
+  const uint32_t lds_wave = (uint32_t)(uintptr_t)(g_lds_u8*)smem + 1024u * (uint32_t)wave;
+  const uint16_t* const xk = a.x + (int64_t)m0 * a.ld_x + (int64_t)kt0 * GK;
+  const uint16_t* const wk = pr.w + (int64_t)(GATED ? n0 / 2 : n0) * K + (int64_t)kt0 * GK;
+  const uint16_t* const wk2 = GATED ? pr.w2 + (int64_t)(n0 / 2) * K + (int64_t)kt0 * GK : nullptr;
+  auto issue_load = [&](int t, int st, int q) {         // load q of k tile t into stage st
+    const uint32_t dst = lds_wave + (uint32_t)(st * kStage + 1024 * NW * q);
+    if (q < NF) {
+      const bool up = GATED && ((wave + NW * q) & 4);    // rows 32 .. 63 of a group of 64
+      gload_lds16((up ? wk2 : wk) + (int64_t)t * GK, voff[q], dst);
+    } else {
+      gload_lds16(xk + (int64_t)t * GK, voff[q], dst);
+    }
+  };
+
+  // ---- fragments: chunk 4 kk + kg of the row
+  const uint32_t offa = (uint32_t)((64 * wf + m16) * 128 + ((kg ^ gswz(m16)) << 4));             // + 2048 per tile
+  const uint32_t offb = (uint32_t)((FT + 16 * wt * AT + m16) * 128 + ((kg ^ gswz(m16)) << 4));
+  f32x4g acc[4][AT];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < AT; ++j) acc[i][j] = f32x4g{0.f, 0.f, 0.f, 0.f};
+  auto read_frags = [&](vec(&fa)[4], vec(&fb)[AT], int st, int kk) {
+    const uint8_t* base = smem + st * kStage;
+#pragma unroll
+    for (int j = 0; j < AT; ++j) fb[j] = *reinterpret_cast<const vec*>(base + ((offb ^ (kk << 6)) + 2048 * j));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fa[i] = *reinterpret_cast<const vec*>(base + ((offa ^ (kk << 6)) + 2048 * i));
+  };
+  auto products = [&](const vec(&fa)[4], const vec(&fb)[AT]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < AT; ++j) acc[i][j] = G::mfma(fa[i], fb[j], acc[i][j]);
+  };
+
+  const FlpGemmLora *lp0 = nullptr, *lp1 = nullptr;
+  __shared__ std::conditional_t<LORA, GemmLoraLds, NoLora> lds;
+  if constexpr (LORA) {
+    lp0 = &la.p[GATED ? 0 : p];
+    lp1 = &la.p[GATED ? 1 : p];
+  }
+  if constexpr (PP) {
+    vec fa[4], fb[AT];
+    auto bar = [&]() {
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_barrier" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int q = 0; q < NPER; ++q) issue_load(0, 0, q);
+    if (nk > 1) {
+#pragma unroll
+      for (int q = 0; q < NPER; ++q) issue_load(1, 1, q);
+    }
+    if constexpr (LORA) lora_setup<GATED, MT, 64 * NW>(lp0, lp1, GATED ? N / 2 : N, m0, a.M, lds);
+    if (nk > 1 && !LORA)
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(NPER));
+    else
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    __syncthreads();
+    // Intervals between barriers: group 0 reads k step s (two per stage) in interval 2 s and multiplies in 2 s + 1,
+    // group 1 one interval later.  The last reads of stage t end with interval 4 t + 3; its buffer is refilled from
+    // interval 4 t + 4 on, and what arrives there is first read in interval 4 t + 8: every wave waits for its own loads
+    // before the barrier that ends interval 4 t + 7 (group 0 after a product, group 1 after a read).  Every wave passes
+    // 4 nk + 1 barriers.
+    if (wt) bar();
+    for (int kt = 0; kt < nk; ++kt) {
+      const int st = kt & 1;
+      if (kt > 0 && kt + 1 < nk) {
+#pragma unroll
+        for (int q = 0; q < NPER; ++q) issue_load(kt + 1, st ^ 1, q);
+      }
+      read_frags(fa, fb, st, 0);
+      __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+      bar();
+      products(fa, fb);
+      bar();
+      read_frags(fa, fb, st, 1);
+      if (wt)
+        __builtin_amdgcn_s_waitcnt(kWaitAll0);
+      else
+        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+      bar();
+      products(fa, fb);
+      if (!wt) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+      bar();
+    }
+    if (!wt) bar();
+  } else {
+    // prologue: stages 0 .. ST - 2 requested, stage 0 complete
+    vec a0[4], b0[AT], a1[4], b1[AT];
+#pragma unroll
+    for (int t = 0; t < ST - 1; ++t)
+      if (t < nk) {
+#pragma unroll
+        for (int q = 0; q < NPER; ++q) issue_load(t, t, q);
+      }
+    if constexpr (LORA) lora_setup<GATED, MT, 64 * NW>(lp0, lp1, GATED ? N / 2 : N, m0, a.M, lds);
+    if (ST - 1 <= nk && !LORA)
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm((ST - 2) * NPER));
+    else
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));           // the set-up's own loads are the newest
+    __syncthreads();
+    read_frags(a0, b0, 0, 0);
+    int st = 0, st_load = ST - 1;                       // stage of k tile kt; stage that takes k tile kt + ST - 1
+    for (int kt = 0; kt < nk; ++kt) {
+      // the buffer of k tile kt - 1 is free: everybody read its last fragments before the previous barrier
+      const bool more = kt + ST - 1 < nk;
+      if (more) {
+#pragma unroll
+        for (int q = 0; q < NPER; ++q) issue_load(kt + ST - 1, st_load, q);
+      }
+      read_frags(a1, b1, st, 1);
+      products(a0, b0);
+      __builtin_amdgcn_sched_barrier(0);
+      st = st + 1 == ST ? 0 : st + 1;
+      st_load = st_load + 1 == ST ? 0 : st_load + 1;
+      // k tile kt + 1 has landed when at most ST - 2 later ones are outstanding
+      if (more)
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((ST - 2) * NPER));
+      else
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+      __syncthreads();
+      if (kt + 1 < nk) read_frags(a0, b0, st, 0);
+      products(a1, b1);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 
-  if constexpr (GATED) {
-    // The gate wave and the up wave of a token half split the gating between them: the gate wave hands over its
-    // feature tiles 2, 3 and finishes tiles 0, 1, the up wave the other way round (128 accumulator values per lane
-    // each way, [wave][value][lane] in the 128 KiB the stages leave), so all four waves share the element-wise work.
-    float* const xbase = reinterpret_cast<float*>(smem) + lane;
-    float* const xown = xbase + (wave * 128) * 64;
-    const float* const xother = xbase + ((wave ^ 1) * 128) * 64;
-    __syncthreads();                                       // everybody's loads have landed, nobody reads fragments any more
-    auto send = [&](auto i0) {                             // feature tiles i0, i0 + 1 of this wave
-      constexpr int I0 = decltype(i0)::value;
+  const int m_first = m0 + 16 * wt * AT;                // the wave's first token
+  if constexpr (LORA) {
+    const int32_t* const index = lds.index + 16 * wt * AT;
+    const int n_nt = lp0->rp / 16;
+    const int v_bytes = MT / 16 * n_nt * 1024;            // at most 64 KiB, twice for a gated pair: the ring holds it
+    __syncthreads();                                      // nobody reads the ring any more
+    lora_stage_v<G, MT, 64 * NW>(*lp0, lds, smem);
+    if constexpr (GATED) lora_stage_v<G, MT, 64 * NW>(*lp1, lds, smem + v_bytes);
+    __syncthreads();
+    const uint8_t* const v0 = smem + wt * AT * n_nt * 1024;
+    for (int first = 0; first < lds.n; first += kLoraSlots) {
+      if (first > 0) {
+        __syncthreads();                                // the previous round's tables are no longer read
+        lora_round<GATED, 64 * NW>(lp0, lp1, GATED ? N / 2 : N, first, lds);
+        __syncthreads();
+      }
+      for (int s = 0; s < kLoraSlots && first + s < lds.n; ++s) {
+        bool any = false;
 #pragma unroll
-      for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) xown[((ii * 4 + j) * 16 + e) * 64] = acc[I0 + ii][j][e];
-    };
-    auto finish = [&](auto i0, auto own_is_gate) {         // feature tiles i0, i0 + 1: own values and the partner's
-      constexpr int I0 = decltype(i0)::value;
-      constexpr bool OWN_GATE = decltype(own_is_gate)::value;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int m = m0 + 128 * wj + 32 * j + acol;
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii) {
-          const int n = n0 + 32 * (I0 + ii) + 16 * hf;
-          uint16_t o[16];
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const float own = G::in(G::out(acc[I0 + ii][j][e]));
-            const float oth = G::in(G::out(xother[((ii * 4 + j) * 16 + e) * 64]));
-            const float g = OWN_GATE ? own : oth, u = OWN_GATE ? oth : own;
-            o[e] = G::out(g / (1.0f + expf(-g)) * u);
-          }
-          if (m >= M || n >= N) continue;
-          uint16_t* yp = y + (int64_t)m * ld_y + n;
-          if (n + 16 <= N) {
-            u32x4 raw[2];
-            __builtin_memcpy(raw, o, 32);
-            reinterpret_cast<u32x4*>(yp)[0] = raw[0];
-            reinterpret_cast<u32x4*>(yp)[1] = raw[1];
-          } else {
-            for (int e = 0; e < 16; ++e)
-              if (n + e < N) yp[e] = o[e];
-          }
+        for (int j = 0; j < AT; ++j) any = any || index[16 * j + m16] == first + s;
+        const int r = lds.rank[s];
+        if (!__ballot(any) || r <= 0) continue;
+        if constexpr (GATED) {
+          add_lora<G, 0, 2, AT>(lds.row[0][s], r, n_nt, index, first + s, v0, n0 / 2 + 32 * wf, N / 2, acc);
+          add_lora<G, 2, 2, AT>(lds.row[1][s], r, n_nt, index, first + s, v0 + v_bytes, n0 / 2 + 32 * wf, N / 2, acc);
+        } else {
+          add_lora<G, 0, 4, AT>(lds.row[0][s], r, n_nt, index, first + s, v0, n0 + 64 * wf, N, acc);
         }
       }
-    };
-    using I0c = std::integral_constant<int, 0>;
-    using I2c = std::integral_constant<int, 2>;
-    if (wi == 0) send(I2c{}); else send(I0c{});
-    __syncthreads();
-    if (wi == 0) finish(I0c{}, std::true_type{}); else finish(I2c{}, std::false_type{});
-    return;
+    }
   }
 
-  // lane (token acol of tile j, half hf) holds columns 16*hf .. 16*hf+15 of feature tile i
+  // ---- lane (token m16 of tile j, group kg): tile row 4 kg + i of tile tau is feature 16 kg + 4 i + tau of the 64
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int m = m0 + 128 * wj + 32 * j + acol;
-    if (m >= M) continue;
+  for (int j = 0; j < AT; ++j) {
+    const int m = m_first + 16 * j + m16;
+    if (m >= a.M) continue;
+    if constexpr (GATED) {
+      if (pr.y) {
+        const int n = n0 / 2 + 32 * wf + 8 * kg;        // the MLP width is a multiple of 32: all 8 features are in
+        if (n >= N / 2) continue;
+        uint16_t o[8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int n = n0 + 128 * wi + 32 * i + 16 * hf;
+        for (int e = 0; e < 8; ++e) {
+          const float g = S::to_float(S::from_float(acc[e & 1][j][e >> 1]));
+          const float up = S::to_float(S::from_float(acc[2 + (e & 1)][j][e >> 1]));
+          o[e] = S::from_float(g / (1.0f + expf(-g)) * up);
+        }
+        u32x4 raw;
+        __builtin_memcpy(&raw, o, 16);
+        *reinterpret_cast<u32x4*>(pr.y + (int64_t)m * pr.ld_y + n) = raw;
+      } else {
+        // slices keep the two products apart: [gate | up] of width N / 2 each
+        const int n = n0 / 2 + 32 * wf + 8 * kg;
+        if (n >= N / 2) continue;
+        float* yp = pr.part + ((int64_t)z * a.M + m) * N + n;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+            *reinterpret_cast<f32x4g*>(yp + h * (N / 2) + 4 * q) =
+                f32x4g{acc[2 * h][j][2 * q], acc[2 * h + 1][j][2 * q], acc[2 * h][j][2 * q + 1], acc[2 * h + 1][j][2 * q + 1]};
+      }
+    } else {
+      const int n = n0 + 64 * wf + 16 * kg;
       if (n >= N) continue;
-      if (y32) {
-        float* yp32 = y32 + (int64_t)m * N + n;
+      float v[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[e] = acc[e & 3][j][e >> 2];
+      if (pr.part) {
+        float* yp = pr.part + ((int64_t)z * a.M + m) * N + n;
         if (n + 16 <= N && (N & 3) == 0) {
 #pragma unroll
-          for (int e4 = 0; e4 < 4; ++e4) {
-            f32x4g v4 = {acc[i][j][4 * e4], acc[i][j][4 * e4 + 1], acc[i][j][4 * e4 + 2], acc[i][j][4 * e4 + 3]};
-            reinterpret_cast<f32x4g*>(yp32)[e4] = v4;
-          }
+          for (int e = 0; e < 4; ++e)
+            reinterpret_cast<f32x4g*>(yp)[e] = f32x4g{v[4 * e], v[4 * e + 1], v[4 * e + 2], v[4 * e + 3]};
         } else {
+#pragma unroll
           for (int e = 0; e < 16; ++e)
-            if (n + e < N) yp32[e] = acc[i][j][e];
+            if (n + e < N) yp[e] = v[e];
         }
       }
-      uint16_t o[16];
+      if (pr.y) {
+        uint16_t o[16];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) o[e] = G::out(acc[i][j][e]);
-      uint16_t* yp = y + (int64_t)m * ld_y + n;
-      if (n + 16 <= N) {
-        u32x4 raw[2];
-        __builtin_memcpy(raw, o, 32);
-        reinterpret_cast<u32x4*>(yp)[0] = raw[0];
-        reinterpret_cast<u32x4*>(yp)[1] = raw[1];
-      } else {
-        for (int e = 0; e < 16; ++e)
-          if (n + e < N) yp[e] = o[e];
+        for (int e = 0; e < 16; ++e) o[e] = S::from_float(v[e]);
+        uint16_t* yp = pr.y + (int64_t)m * pr.ld_y + n;
+        if (n + 16 <= N) {
+          u32x4 raw[2];
+          __builtin_memcpy(raw, o, 32);
+          reinterpret_cast<u32x4*>(yp)[0] = raw[0];
+          reinterpret_cast<u32x4*>(yp)[1] = raw[1];
+        } else {
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            if (n + e < N) yp[e] = o[e];
+        }
       }
     }
   }
 }
 
-// y[m, n] = round(sum over the slices, in slice order); y32 (optional) gets the unrounded sum
-template <typename G>
-__global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(const float* __restrict__ part, int slices, int M, int N,
-                                                                 uint16_t* __restrict__ y, int64_t ld_y,
-                                                                 float* __restrict__ y32) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, total = (int64_t)M * N;
-  if (i >= total) return;
-  float sum = part[i];
-  for (int z = 1; z < slices; ++z) sum += part[(int64_t)z * total + i];
-  const int64_t m = i / N;
-  const int n = (int)(i - m * N);
-  y[m * ld_y + n] = G::out(sum);
-  if (y32) y32[i] = sum;
+// ---- sum of the slices, in slice order, four features per thread.  GATED: the slices hold [gate | up]; the result is
+//      silu(g) * u with both rounded first.  The unrounded sum goes back into slice 0 where keep_sum says so.
+template <typename G, bool GATED>
+__global__ __launch_bounds__(256) void gemm_reduce_kernel(FlpGemmArgs a, int keep_sum) {
+  typedef typename G::S S;
+  const FlpGemmProj& pr = a.proj[blockIdx.y];
+  const int n_out = GATED ? pr.N / 2 : pr.N, n4 = n_out / 4;
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (int64_t)a.M * n4) return;
+  const int m = (int)(i / n4), n = (int)(i - (int64_t)m * n4) * 4;
+  float* pp = pr.part + (int64_t)m * pr.N + n;
+  const int64_t step = (int64_t)a.M * pr.N;
+  f32x4g s = *reinterpret_cast<const f32x4g*>(pp), s2 = {0.f, 0.f, 0.f, 0.f};
+  if (GATED) s2 = *reinterpret_cast<const f32x4g*>(pp + n_out);
+  for (int z = 1; z < a.splits; ++z) {
+    s += *reinterpret_cast<const f32x4g*>(pp + z * step);
+    if (GATED) s2 += *reinterpret_cast<const f32x4g*>(pp + z * step + n_out);
+  }
+  uint16_t o[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (GATED) {
+      const float g = S::to_float(S::from_float(s[e])), up = S::to_float(S::from_float(s2[e]));
+      o[e] = S::from_float(g / (1.0f + expf(-g)) * up);
+    } else {
+      o[e] = S::from_float(s[e]);
+    }
+  }
+  uint2 raw;
+  __builtin_memcpy(&raw, o, 8);
+  *reinterpret_cast<uint2*>(pr.y + (int64_t)m * pr.ld_y + n) = raw;
+  if (keep_sum) *reinterpret_cast<f32x4g*>(pp) = s;
 }
 
+// ---- fp32: y = x . W^T, one 16 x 16 tile per workgroup with mfma_f32_16x16x4 (fp32 products and sums).  Bound by
+//      latency, not by rate: the four waves take every fourth piece of 16 coefficients, operands come straight from
+//      global memory (16 bytes per lane along the contraction; each of a piece's four instructions contracts one of
+//      the lane's four coefficients), and the waves' sums meet in LDS in wave order.  20 tokens x 256 x 256: 33 us
+//      with one thread per output.
+template <bool KMAJOR>                                    // W stored [N, K]; otherwise [K, N]
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ x, int64_t ld_x,
-                                                       const float* __restrict__ w, int64_t w_k_stride,
-                                                       int64_t w_n_stride, float* __restrict__ y, int64_t ld_y, int M,
-                                                       int N, int K) {
-  const int n = blockIdx.x * 256 + threadIdx.x, m = blockIdx.y;
-  if (n >= N) return;
-  float acc = 0.f;
-  for (int k = 0; k < K; ++k) acc = fmaf(x[(int64_t)m * ld_x + k], w[k * w_k_stride + n * w_n_stride], acc);
-  y[(int64_t)m * ld_y + n] = acc;
-}
-
-flp_status gemm256_attrs() {
-  const void* fns[8] = {(const void*)gemm_nt256_kernel<GF16, false, false>, (const void*)gemm_nt256_kernel<GBF16, false, false>,
-                        (const void*)gemm_nt256_kernel<GF16, true, false>, (const void*)gemm_nt256_kernel<GBF16, true, false>,
-                        (const void*)gemm_nt256_kernel<GF16, false, true>, (const void*)gemm_nt256_kernel<GBF16, false, true>,
-                        (const void*)gemm_nt256_kernel<GF16, true, true>, (const void*)gemm_nt256_kernel<GBF16, true, true>};
-  for (const void* f : fns)
-    FLP_TRY_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kGStages * kGStage));
-  return FLP_OK;
-}
-
-// the shapes the 256 x 256 kernel takes: 32-bit byte offsets inside the operands, whole 64-coefficient stages
-bool gemm256_fits(int64_t M, int64_t n_rows_w, int64_t K, int64_t ld_x) {
-  return M >= 1024 && M * ld_x * 2 < ((int64_t)1 << 32) && n_rows_w * K * 2 < ((int64_t)1 << 32) && ld_x % 8 == 0 &&
-         K % GK == 0 && K / GK >= kGStages;
+                                                       const float* __restrict__ w, float* __restrict__ y, int64_t ld_y,
+                                                       int M, int N, int K) {
+  __shared__ f32x4g red[4][64];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r16 = lane & 15, kg = lane >> 4;
+  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
+  const int n = n0 + r16 < N ? n0 + r16 : N - 1, m = m0 + r16 < M ? m0 + r16 : M - 1;     // clamped rows are never stored
+  const float* xr = x + (int64_t)m * ld_x;
+  f32x4g acc = {0.f, 0.f, 0.f, 0.f};
+  const bool vec4 = (K & 3) == 0 && (ld_x & 3) == 0;
+  for (int k0 = 16 * wave; k0 < K; k0 += 64) {
+    const int k = k0 + 4 * kg;
+    f32x4g xv = {0.f, 0.f, 0.f, 0.f}, wv = {0.f, 0.f, 0.f, 0.f};
+    if (vec4 && k < K) {
+      xv = *reinterpret_cast<const f32x4g*>(xr + k);
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (k + c < K) xv[c] = xr[k + c];
+    }
+    if (KMAJOR && vec4 && k < K) {
+      wv = *reinterpret_cast<const f32x4g*>(w + (int64_t)n * K + k);
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (k + c < K) wv[c] = KMAJOR ? w[(int64_t)n * K + k + c] : w[(int64_t)(k + c) * N + n];
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[c], wv[c], acc, 0, 0, 0);
+  }
+  red[wave][lane] = acc;
+  __syncthreads();
+  if (wave == 0) {
+    const f32x4g s = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {                         // row (token) 4 kg + i, column (feature) r16
+      const int mm = m0 + 4 * kg + i;
+      if (mm < M && n0 + r16 < N) y[(int64_t)mm * ld_y + n0 + r16] = s[i];
+    }
+  }
 }
 
 }  // namespace
 
-// out[M, N] = silu(x . Wg^T) * (x . Wu^T) with both matrices stored [N, K], 16-bit element types, in one pass of
-// the large-batch kernel (the two products are rounded to the element type before the gate is applied, as if
-// they had been stored).  Returns FLP_ENOTSUP without launching when the shape is one that the kernel does not
-// take (small batches, few tiles, offsets beyond 32 bits): the caller then runs the two products and the
-// element-wise step.
-flp_status flp_launch_gated_gemm(int dtype, const void* x, int64_t ld_x, const void* w_gate, const void* w_up,
-                                 void* out, int64_t ld_out, int M, int N, int K, hipStream_t stream,
-                                 const FlpGemmLora* lora_gate, const FlpGemmLora* lora_up) {
-  if (dtype != FLP_F16 && dtype != FLP_BF16) return FLP_ENOTSUP;
-  const int tiles_n = (N + GT / 2 - 1) / (GT / 2), tiles_m = (M + GT - 1) / GT;
-  if (M <= 0 || N < 128 || K <= 0 || !gemm256_fits(M, N, K, ld_x) || (int64_t)tiles_n * tiles_m < 96) return FLP_ENOTSUP;
-  if ((lora_gate != nullptr) != (lora_up != nullptr)) return FLP_ENOTSUP;
-  static std::atomic<bool> attr_set{false};   // pools on different threads share it
-  if (!attr_set.load(std::memory_order_acquire)) {
-    FLP_TRY(gemm256_attrs());
-    attr_set.store(true, std::memory_order_release);
+namespace {
+
+struct GemmCfg {
+  int ft, mt, waves, lds;
+  int per_cu;            // workgroups that fit a CU
+  float step_us;         // time of one k tile when every CU runs its workgroups (products and loads)
+  float fill_us;         // start-up and epilogue of a workgroup
+  float part;            // time of a round that is nearly empty, as a share of a full one
+};
+constexpr int stage_bytes(int ft, int mt) { return (ft + mt) * 128; }
+// kinds of tile, FLP_GEMM_*.  The times are what the planner adds up, fitted to 600 launches on MI355X (every kind and
+// number of slices over 1 .. 2000 tokens and the matrices of the 7B, 13B and 34B shapes): over those the plan it picks is
+// 1.2 % slower than the best one on average, 15 % at worst.
+const GemmCfg kCfg[FLP_GEMM_KINDS] = {
+    {64, 32, 2, 4 * stage_bytes(64, 32), 3, 0.488f, 4.44f, 0.53f},
+    {128, 64, 4, 3 * stage_bytes(128, 64), 2, 0.949f, 4.69f, 0.63f},
+    {128, 128, 4, 4 * stage_bytes(128, 128), 1, 0.609f, 4.66f, 1.0f},
+    {256, 128, 8, 3 * stage_bytes(256, 128), 1, 0.797f, 4.38f, 0.94f},
+    {256, 256, 8, 2 * stage_bytes(256, 256), 1, 1.442f, 8.53f, 0.70f},
+};
+
+template <typename G, bool GATED, bool LORA>
+const void* gemm_fn(int kind) {
+  if constexpr (LORA) {
+    return kind == FLP_GEMM_256x128 ? (const void*)gemm_kernel<G, 4, 2, 4, 3, false, GATED, true>
+                                    : (const void*)gemm_kernel<G, 4, 2, 8, 2, true, GATED, true>;
+  } else {
+    switch (kind) {
+      case FLP_GEMM_64x32: return (const void*)gemm_kernel<G, 1, 2, 1, 4, false, GATED, false>;
+      case FLP_GEMM_128x64: return (const void*)gemm_kernel<G, 2, 2, 2, 3, false, GATED, false>;
+      case FLP_GEMM_128x128: return (const void*)gemm_kernel<G, 2, 2, 4, 4, false, GATED, false>;
+      case FLP_GEMM_256x128: return (const void*)gemm_kernel<G, 4, 2, 4, 3, false, GATED, false>;
+      default: return (const void*)gemm_kernel<G, 4, 2, 8, 2, true, GATED, false>;
+    }
   }
-  const int groups_n = (tiles_n + 3) / 4, groups_m = (tiles_m + 7) / 8;
-  const int n_groups = (groups_n * groups_m + 7) / 8 * 8;
-  dim3 grid((unsigned)(n_groups * 32));
-  const uint16_t *xs = (const uint16_t*)x, *wg = (const uint16_t*)w_gate, *wu = (const uint16_t*)w_up;
-  float* no32 = nullptr;
-  const size_t lds = kGStages * kGStage;
-  if (lora_gate && dtype == FLP_F16)
-    hipLaunchKernelGGL((gemm_nt256_kernel<GF16, true, true>), grid, dim3(256), lds, stream, xs, ld_x, wg, wu, (uint16_t*)out,
-                       ld_out, no32, M, N, K, tiles_n, tiles_m, groups_n, *lora_gate, *lora_up);
-  else if (lora_gate)
-    hipLaunchKernelGGL((gemm_nt256_kernel<GBF16, true, true>), grid, dim3(256), lds, stream, xs, ld_x, wg, wu, (uint16_t*)out,
-                       ld_out, no32, M, N, K, tiles_n, tiles_m, groups_n, *lora_gate, *lora_up);
+}
+
+const void* gemm_entry(int dtype, int kind, bool gated, bool lora) {
+  const auto pick = [&](auto g) -> const void* {
+    using G = decltype(g);
+    return gated ? (lora ? gemm_fn<G, true, true>(kind) : gemm_fn<G, true, false>(kind))
+                 : (lora ? gemm_fn<G, false, true>(kind) : gemm_fn<G, false, false>(kind));
+  };
+  return dtype == FLP_F16 ? pick(GF16{}) : pick(GBF16{});
+}
+
+// the kernels that use more than 64 KiB of LDS have to say so once (pools on different threads share it)
+flp_status gemm_attrs() {
+  static std::atomic<bool> done{false};
+  if (done.load(std::memory_order_acquire)) return FLP_OK;
+  for (int dtype : {FLP_F16, FLP_BF16})
+    for (int kind = 0; kind < FLP_GEMM_KINDS; ++kind)
+      for (int gated = 0; gated < 2; ++gated)
+        for (int lora = 0; lora < 2; ++lora)
+          if (!lora || kind >= FLP_GEMM_256x128)
+            FLP_TRY_HIP(hipFuncSetAttribute(gemm_entry(dtype, kind, gated, lora), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                            kCfg[kind].lds));
+  done.store(true, std::memory_order_release);
+  return FLP_OK;
+}
+
+}  // namespace
+
+size_t flp_gemm_part_bytes(const FlpGemmPlan& plan, int M, int n_proj, const int* N) {
+  size_t n = 0;
+  for (int p = 0; p < n_proj; ++p) n += (size_t)N[p];
+  return (size_t)plan.splits * M * n * 4;
+}
+
+// The plan with the least estimated time: rounds of workgroups x (k tiles of a slice x time per k tile + start-up),
+// at least the time the matrices take from memory, plus the slices' way through memory and the kernel that adds them.
+FlpGemmPlan flp_gemm_plan(int M, int K, int n_proj, const int* N, unsigned allow, size_t max_part_bytes) {
+  FlpGemmPlan best{FLP_GEMM_128x128, 1};
+  double best_us = 1e30, n_all = 0;
+  bool split_ok = !(allow & FLP_GEMM_NO_SPLIT);
+  for (int p = 0; p < n_proj; ++p) {
+    n_all += N[p];
+    split_ok = split_ok && N[p] % 4 == 0;
+  }
+  const int nk = K / GK;
+  for (int kind = (allow & FLP_GEMM_LARGE_ONLY) ? FLP_GEMM_256x128 : 0; kind < FLP_GEMM_KINDS; ++kind) {
+    const GemmCfg& c = kCfg[kind];
+    int64_t f_tiles = 0;
+    for (int p = 0; p < n_proj; ++p) f_tiles += (N[p] + c.ft - 1) / c.ft;
+    const int64_t m_tiles = (M + c.mt - 1) / c.mt, tiles = f_tiles * m_tiles;
+    for (int s = 1; s <= 16; s = s < 4 ? s + 1 : s < 8 ? s + 2 : s + 4) {
+      if (s > 1 && (!split_ok || nk / s < 4 || (double)s * M * n_all * 4 > (double)max_part_bytes)) break;
+      const double wgs = (double)tiles * s, slots = 256.0 * c.per_cu;
+      const double full = std::floor(wgs / slots), rest = wgs - full * slots;
+      const double share = rest <= 0 ? 0 : c.per_cu == 1 ? c.part + (1 - c.part) * rest / 256
+                                                         : std::max((double)c.part, std::ceil(rest / 256) / c.per_cu);
+      double us = (full + share) * ((double)nk / s * c.step_us + c.fill_us);
+      us = std::max(us, n_all * K * 2 / 8.36e6 + 3.3);
+      if (s > 1) us += (double)s * M * n_all * 8 / 4.64e6 + 3.5;      // slices written and read, and the launch that adds them
+      if (us < best_us) {
+        best_us = us;
+        best = FlpGemmPlan{kind, s};
+      }
+    }
+  }
+  return best;
+}
+
+flp_status flp_launch_gemm(int dtype, const void* x, int64_t ld_x, int M, int K, const FlpGemmPlan& plan, int n_proj,
+                           const FlpGemmOut* out, bool gated, const FlpGemmLora* lora, hipStream_t stream) {
+  if (M <= 0 || K <= 0 || n_proj <= 0) return FLP_OK;
+  if (K % GK != 0) {
+    flp_set_error("dense product: d_in %d is not a multiple of %d", K, GK);
+    return FLP_ENOTSUP;
+  }
+  const GemmCfg& c = kCfg[plan.kind];
+  if (lora && (plan.kind < FLP_GEMM_256x128 || plan.splits != 1)) {
+    flp_set_error("dense product: the LoRA epilogue needs whole contractions on the large tiles");
+    return FLP_ENOTSUP;
+  }
+  FLP_TRY(gemm_attrs());
+  FlpGemmArgs a{};
+  a.x = (const uint16_t*)x;
+  a.ld_x = ld_x;
+  a.M = M;
+  a.K = K;
+  a.n_proj = n_proj;
+  a.splits = plan.splits;
+  a.m_tiles = (M + c.mt - 1) / c.mt;
+  for (int p = 0; p < n_proj; ++p) {
+    FlpGemmProj& pr = a.proj[p];
+    pr.w = (const uint16_t*)out[p].w;
+    pr.w2 = (const uint16_t*)out[p].w2;
+    pr.y = (uint16_t*)out[p].y;
+    pr.ld_y = out[p].ld_y;
+    pr.part = out[p].part;
+    pr.N = out[p].N;
+    pr.tile0 = a.f_tiles;
+    a.f_tiles += (pr.N + c.ft - 1) / c.ft;
+    if (plan.splits > 1) pr.y = nullptr;                 // gemm_reduce writes it
+  }
+  // with more than eight token tiles, 4 x 8 blocks: the workgroups that run together fetch 12 operand panels, not 33
+  a.gm = a.m_tiles > 8 ? 8 : a.m_tiles;
+  a.gf = a.m_tiles > 8 ? 4 : 1;
+  const int64_t ug = ((int64_t)a.f_tiles * a.splits + a.gf - 1) / a.gf, mg = (a.m_tiles + a.gm - 1) / a.gm;
+  const int64_t grid = (ug * mg + 7) / 8 * 8 * a.gf * a.gm;
+  if (grid > INT32_MAX) {
+    flp_set_error("dense product: %lld workgroups, too many for one launch", (long long)grid);
+    return FLP_ENOTSUP;
+  }
+  GemmLoraArgs la{};
+  if (lora)
+    for (int p = 0; p < (gated ? 2 : n_proj); ++p) la.p[p] = lora[p];
+  NoLora none;
+  void* args[2] = {&a, lora ? (void*)&la : (void*)&none};
+  FLP_TRY_HIP(hipLaunchKernel(gemm_entry(dtype, plan.kind, gated, lora != nullptr), dim3((unsigned)grid), dim3(64 * c.waves),
+                              args, (size_t)c.lds, stream));
+  return FLP_OK;
+}
+
+flp_status flp_launch_gemm_reduce(int dtype, int M, int n_proj, const FlpGemmOut* out, int splits, bool gated, bool keep_sum,
+                                  hipStream_t stream) {
+  FlpGemmArgs a{};
+  a.M = M;
+  a.n_proj = n_proj;
+  a.splits = splits;
+  int64_t most = 0;
+  for (int p = 0; p < n_proj; ++p) {
+    FlpGemmProj& pr = a.proj[p];
+    pr.y = (uint16_t*)out[p].y;
+    pr.ld_y = out[p].ld_y;
+    pr.part = out[p].part;
+    pr.N = out[p].N;
+    most = std::max(most, (int64_t)M * (gated ? pr.N / 2 : pr.N) / 4);
+  }
+  const dim3 grid((unsigned)((most + 255) / 256), (unsigned)n_proj);
+  if (dtype == FLP_F16 && gated)
+    hipLaunchKernelGGL((gemm_reduce_kernel<GF16, true>), grid, dim3(256), 0, stream, a, (int)keep_sum);
   else if (dtype == FLP_F16)
-    hipLaunchKernelGGL((gemm_nt256_kernel<GF16, true, false>), grid, dim3(256), lds, stream, xs, ld_x, wg, wu, (uint16_t*)out,
-                       ld_out, no32, M, N, K, tiles_n, tiles_m, groups_n, FlpGemmLora{}, FlpGemmLora{});
+    hipLaunchKernelGGL((gemm_reduce_kernel<GF16, false>), grid, dim3(256), 0, stream, a, (int)keep_sum);
+  else if (gated)
+    hipLaunchKernelGGL((gemm_reduce_kernel<GBF16, true>), grid, dim3(256), 0, stream, a, (int)keep_sum);
   else
-    hipLaunchKernelGGL((gemm_nt256_kernel<GBF16, true, false>), grid, dim3(256), lds, stream, xs, ld_x, wg, wu,
-                       (uint16_t*)out, ld_out, no32, M, N, K, tiles_n, tiles_m, groups_n, FlpGemmLora{}, FlpGemmLora{});
+    hipLaunchKernelGGL((gemm_reduce_kernel<GBF16, false>), grid, dim3(256), 0, stream, a, (int)keep_sum);
   FLP_TRY_HIP(hipGetLastError());
   return FLP_OK;
 }
 
-bool flp_gemm_gated_fits(int dtype, int M, int N, int K, int64_t ld_x) {
-  return (dtype == FLP_F16 || dtype == FLP_BF16) && M > 0 && N >= 128 && K > 0 && gemm256_fits(M, N, K, ld_x) &&
-         (int64_t)((N + GT / 2 - 1) / (GT / 2)) * ((M + GT - 1) / GT) >= 96;
-}
-
-bool flp_gemm_is_large(int dtype, int M, int N, int K, int64_t ld_x) {
-  return (dtype == FLP_F16 || dtype == FLP_BF16) && N >= 256 &&
-         (int64_t)((M + GT - 1) / GT) * ((N + GT - 1) / GT) >= 96 && gemm256_fits(M, N, K, ld_x);
-}
-
-// y[M, N] = x[M, K] . W with w stored [K, N] (w_layout 0) or [N, K] (w_layout 1).  `wt_scratch` (16-bit
-// types with layout 0 only) must hold N*K elements; `y32` (16-bit types, optional) receives the
-// unrounded product as dense fp32 [M, N].
-flp_status flp_launch_base_gemm(int dtype, const void* x, int64_t ld_x, const void* w, int w_layout, void* y,
-                                int64_t ld_y, int M, int N, int K, void* wt_scratch, float* y32, float* splitk_scratch,
-                                size_t splitk_bytes, hipStream_t stream, const FlpGemmLora* lora) {
-  if (M <= 0 || N <= 0 || K <= 0) return FLP_OK;
-  if (lora && !flp_gemm_is_large(dtype, M, N, K, ld_x)) {
-    flp_set_error("base GEMM: the LoRA epilogue needs the large-batch kernel (M=%d N=%d K=%d)", M, N, K);
-    return FLP_ENOTSUP;
-  }
-  if (dtype == FLP_F32) {
-    hipLaunchKernelGGL(gemm_f32_kernel, dim3((N + 255) / 256, M), dim3(256), 0, stream, (const float*)x, ld_x,
-                       (const float*)w, w_layout ? (int64_t)1 : (int64_t)N, w_layout ? (int64_t)K : (int64_t)1, (float*)y,
-                       ld_y, M, N, K);
-    FLP_TRY_HIP(hipGetLastError());
-    return FLP_OK;
-  }
-  if (K % BK != 0) {
-    flp_set_error("base GEMM: d_in %d is not a multiple of %d", K, BK);
-    return FLP_ENOTSUP;
-  }
-  if (w_layout == 0)
-    hipLaunchKernelGGL(transpose16_kernel, dim3((N + 63) / 64, (K + 63) / 64), dim3(256), 0, stream, (const uint16_t*)w,
-                       (uint16_t*)wt_scratch, K, N);
-  const uint16_t* xs = (const uint16_t*)x;
-  const uint16_t* ws = w_layout == 0 ? (const uint16_t*)wt_scratch : (const uint16_t*)w;
-  // 32-bit byte offsets inside the operands and enough 256 x 256 tiles to occupy the chip (measured: with 64
-  // tiles the 128 x 128 kernel is ahead, from 172 tiles on this one): the 256 x 256 kernel
-  if (flp_gemm_is_large(dtype, M, N, K, ld_x)) {
-    const int tiles_n = (N + GT - 1) / GT, tiles_m = (M + GT - 1) / GT;
-    const int groups_n = (tiles_n + 3) / 4, groups_m = (tiles_m + 7) / 8;
-    const int n_groups = (groups_n * groups_m + 7) / 8 * 8;
-    dim3 grid256((unsigned)(n_groups * 32));
-    static std::atomic<bool> attr_set{false};   // pools on different threads share it
-    if (!attr_set.load(std::memory_order_acquire)) {
-      FLP_TRY(gemm256_attrs());
-      attr_set.store(true, std::memory_order_release);
-    }
-    const uint16_t* none = nullptr;
-    if (lora && dtype == FLP_F16)
-      hipLaunchKernelGGL((gemm_nt256_kernel<GF16, false, true>), grid256, dim3(256), kGStages * kGStage, stream, xs, ld_x,
-                         ws, none, (uint16_t*)y, ld_y, y32, M, N, K, tiles_n, tiles_m, groups_n, *lora, FlpGemmLora{});
-    else if (lora)
-      hipLaunchKernelGGL((gemm_nt256_kernel<GBF16, false, true>), grid256, dim3(256), kGStages * kGStage, stream, xs, ld_x,
-                         ws, none, (uint16_t*)y, ld_y, y32, M, N, K, tiles_n, tiles_m, groups_n, *lora, FlpGemmLora{});
-    else if (dtype == FLP_F16)
-      hipLaunchKernelGGL((gemm_nt256_kernel<GF16, false, false>), grid256, dim3(256), kGStages * kGStage, stream, xs, ld_x,
-                         ws, none, (uint16_t*)y, ld_y, y32, M, N, K, tiles_n, tiles_m, groups_n, FlpGemmLora{}, FlpGemmLora{});
-    else
-      hipLaunchKernelGGL((gemm_nt256_kernel<GBF16, false, false>), grid256, dim3(256), kGStages * kGStage, stream, xs,
-                         ld_x, ws, none, (uint16_t*)y, ld_y, y32, M, N, K, tiles_n, tiles_m, groups_n, FlpGemmLora{}, FlpGemmLora{});
-    FLP_TRY_HIP(hipGetLastError());
-    return FLP_OK;
-  }
-  // few tiles (decode batches): split the contraction over up to 8 slices until about 256 workgroups run
-  const int tiles = ((N + BN - 1) / BN) * ((M + BM - 1) / BM);
-  int slices = 1;
-  while (slices < 8 && tiles * slices < 192 && (K / BK) % (slices * 2) == 0 && K / (slices * 2) >= 512 &&
-         splitk_scratch && (size_t)slices * 2 * M * N * 4 <= splitk_bytes)
-    slices *= 2;
-  dim3 grid((N + BN - 1) / BN, (M + BM - 1) / BM, slices);
-  if (dtype == FLP_F16)
-    hipLaunchKernelGGL(gemm_nt_kernel<GF16>, grid, dim3(256), 0, stream, xs, ld_x, ws, (uint16_t*)y, ld_y, y32, M, N, K,
-                       splitk_scratch);
-  else
-    hipLaunchKernelGGL(gemm_nt_kernel<GBF16>, grid, dim3(256), 0, stream, xs, ld_x, ws, (uint16_t*)y, ld_y, y32, M, N,
-                       K, splitk_scratch);
+flp_status flp_launch_transpose16(const void* w, void* wt, int K, int N, hipStream_t stream) {
+  hipLaunchKernelGGL(transpose16_kernel, dim3((N + 63) / 64, (K + 63) / 64), dim3(256), 0, stream, (const uint16_t*)w,
+                     (uint16_t*)wt, K, N);
   FLP_TRY_HIP(hipGetLastError());
-  if (slices > 1) {
-    const unsigned nb = (unsigned)(((int64_t)M * N + 255) / 256);
-    if (dtype == FLP_F16)
-      hipLaunchKernelGGL(gemm_splitk_reduce_kernel<GF16>, dim3(nb), dim3(256), 0, stream, splitk_scratch, slices, M, N,
-                         (uint16_t*)y, ld_y, y32);
-    else
-      hipLaunchKernelGGL(gemm_splitk_reduce_kernel<GBF16>, dim3(nb), dim3(256), 0, stream, splitk_scratch, slices, M, N,
-                         (uint16_t*)y, ld_y, y32);
-    FLP_TRY_HIP(hipGetLastError());
-  }
+  return FLP_OK;
+}
+
+flp_status flp_launch_gemm_f32(const float* x, int64_t ld_x, const float* w, int w_layout, float* y, int64_t ld_y, int M, int N,
+                               int K, hipStream_t stream) {
+  const dim3 grid((unsigned)((N + 15) / 16), (unsigned)((M + 15) / 16));
+  if (w_layout)
+    hipLaunchKernelGGL(gemm_f32_kernel<true>, grid, dim3(256), 0, stream, x, ld_x, w, y, ld_y, M, N, K);
+  else
+    hipLaunchKernelGGL(gemm_f32_kernel<false>, grid, dim3(256), 0, stream, x, ld_x, w, y, ld_y, M, N, K);
+  FLP_TRY_HIP(hipGetLastError());
   return FLP_OK;
 }

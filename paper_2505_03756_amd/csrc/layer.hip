@@ -272,6 +272,34 @@ Scratch layout(const flp_pool* p, const fll_layer_config* c, int64_t T) {
 bool cfg_ok(const flp_pool* p, const fll_layer_config* c) {
   return p && c && c->hidden > 0 && c->n_q_heads > 0 && c->mlp_dim > 0 && c->n_q_heads % p->cfg.n_kv_heads == 0;
 }
+
+// Dense products alone (gated: the gated-SiLU pair as one output).  Slices of a small batch's contraction live in the
+// pool's workspace (stream order keeps them apart from the LoRA intermediates of the calls before and after).
+flp_status dense_products(flp_pool* p, const void* x, int d_in, int T, int n, FlpGemmOut* out, const int* N, bool gated,
+                          hipStream_t stream) {
+  if (p->elem_bytes == 4) {
+    for (int i = 0; i < n; ++i)
+      FLP_TRY(flp_launch_gemm_f32((const float*)x, d_in, (const float*)out[i].w, 1, (float*)out[i].y, out[i].ld_y, T, N[i], d_in,
+                                  stream));
+    return FLP_OK;
+  }
+  const FlpGemmPlan plan = flp_gemm_plan(T, d_in, n, N, 0, (size_t)1 << 30);
+  if (plan.splits > 1) {
+    void* part = nullptr;
+    {
+      std::lock_guard<std::mutex> lk(p->mu);
+      FLP_TRY(flp_workspace(p, flp_gemm_part_bytes(plan, T, n, N), &part));
+    }
+    float* f = (float*)part;
+    for (int i = 0; i < n; ++i) {
+      out[i].part = f;
+      f += (size_t)plan.splits * T * N[i];
+    }
+  }
+  FLP_TRY(flp_launch_gemm(p->cfg.dtype, x, d_in, T, d_in, plan, n, out, gated, nullptr, stream));
+  if (plan.splits > 1) return flp_launch_gemm_reduce(p->cfg.dtype, T, n, out, plan.splits, gated, false, stream);
+  return FLP_OK;
+}
 }  // namespace
 
 extern "C" int64_t fll_layer_scratch_bytes(const flp_pool* pool, const fll_layer_config* cfg, int32_t n_tokens) {
@@ -319,7 +347,8 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
     lb.rank = b->rank;
     lb.scale = b->scale;
     lb.block_tables = b->lora_tables;
-    int n_lora = 0;
+    int n_lora = 0, n_dense = 0, dense_N[3];
+    FlpGemmOut dense[3] = {};
     for (int i = 0; i < n_proj; ++i) {
       const fll_lora_place& pl = b->lora[which[i]];
       const int n_set = (pl.a_tab_off != nullptr) + (pl.a_row_base != nullptr) + (pl.b_tab_off != nullptr) +
@@ -329,16 +358,11 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
           flp_set_error("fll_layer_forward: projection %d: d_in %d is not a multiple of 64", which[i], d_in);
           return FLP_ENOTSUP;
         }
-        // split-K slices of a small batch live in the pool's workspace (stream order keeps them apart from the
-        // LoRA intermediates of the calls before and after)
-        const size_t sk_bytes = p->elem_bytes == 2 ? flp_gemm_splitk_bytes(T, d_outs[i]) : 0;
-        void* sk = nullptr;
-        if (sk_bytes) {
-          std::lock_guard<std::mutex> lk(p->mu);
-          FLP_TRY(flp_workspace(p, sk_bytes, &sk));
-        }
-        FLP_TRY(flp_launch_base_gemm(dtype, x, d_in, ws[i], 1, ys[i], d_outs[i], T, d_outs[i], d_in, nullptr, nullptr,
-                                     (float*)sk, sk_bytes, (hipStream_t)hip_stream));
+        dense[n_dense].w = ws[i];
+        dense[n_dense].y = ys[i];
+        dense[n_dense].ld_y = d_outs[i];
+        dense[n_dense].N = dense_N[n_dense] = d_outs[i];
+        ++n_dense;
         continue;
       }
       if (n_set != 4) {
@@ -356,6 +380,7 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
       pr.b_tab_off = pl.b_tab_off;
       pr.b_row_base = pl.b_row_base;
     }
+    if (n_dense > 0) FLP_TRY(dense_products(p, x, d_in, T, n_dense, dense, dense_N, false, (hipStream_t)hip_stream));
     if (n_lora == 0) return FLP_OK;
     lb.n_proj = n_lora;
     if (gated_out) return flp_lora_apply_gated(p, &lb, gated_out, d_outs[0], hip_stream);
@@ -393,8 +418,8 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
   }
   FLP_TRY(fll_add_rmsnorm(dtype, h, proj, w->post_norm, n, T, H, eps, hip_stream));
   {
-    // without LoRA branches on gate and up, and for a batch that the large-batch GEMM takes, the two products
-    // and the gate are one kernel that writes only silu(g) * u; otherwise two products and the element-wise step
+    // without LoRA branches on gate and up the two products and the gate are one step that writes only silu(g) * u;
+    // with branches on both that holds for large batches; otherwise two products and the element-wise step
     const auto no_lora = [&](int i) {
       const fll_lora_place& pl = b->lora[i];
       return !pl.a_tab_off && !pl.a_row_base && !pl.b_tab_off && !pl.b_row_base;
@@ -407,8 +432,16 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
     void* const ys[2] = {gate, up};
     const void* const ws[2] = {w->w_gate, w->w_up};
     flp_status fused = FLP_ENOTSUP;
-    if (no_lora(4) && no_lora(5))
-      fused = flp_launch_gated_gemm(dtype, n, H, w->w_gate, w->w_up, gate, M, T, M, H, (hipStream_t)hip_stream);
+    if (no_lora(4) && no_lora(5) && p->elem_bytes == 2 && H % 64 == 0 && M % 32 == 0) {
+      const int N[1] = {2 * M};
+      FlpGemmOut o{};
+      o.w = w->w_gate;
+      o.w2 = w->w_up;
+      o.y = gate;
+      o.ld_y = M;
+      o.N = N[0];
+      fused = dense_products(p, n, H, T, 1, &o, N, true, (hipStream_t)hip_stream);
+    }
     else if (full_lora(4) && full_lora(5))          // both with a LoRA branch: the branches are added inside the same pass
       fused = project(n, H, 2, which, ys, d_outs, ws, gate);
     if (fused == FLP_ENOTSUP) {
