@@ -134,7 +134,8 @@ __global__ __launch_bounds__(256, 2) void kv_append_kernel(FlpAttnArgs a, const 
 // Per block of 16 positions: K rows are read 16 bytes per lane (LPK lanes cover one key),
 // scores are reduced inside each LPK-lane group, the online-softmax statistics are kept
 // wave-uniform, and each lane accumulates its D/64 channels from the transposed V rows.
-// HBM-bound for decode (one row per sequence and head); also the generic path for fp32.
+// The generic path: fp32 pools, head_dim 64, more than 16 query heads per kv head (single tokens of other 16-bit pools
+// with head_dim 128 go to the decode kernel, which reads K and V once for all heads of a group).
 template <typename S, int D>
 struct RowCfg {
   static constexpr int EPL = 16 / (int)sizeof(typename S::storage);   // elements per 16-byte load
@@ -246,7 +247,7 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(FlpAttnArgs a, const Flp
     }
     if (split) {
       // unnormalised piece: running maximum (in the exponent's units), sum of weights, channels
-      float* pp = a.partials + (((int64_t)u.part_row * a.n_h + h) * a.max_split + u.split) * (D + 2);
+      float* pp = a.partials + ((int64_t)(u.part_row + u.split) * a.n_h + h) * (D + 2);
       if (lane == 0) {
         pp[0] = m;
         pp[1] = l;
@@ -263,28 +264,45 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(FlpAttnArgs a, const Flp
 }
 
 // Merge of the split-KV pieces of one (token, head) row: out = sum_i acc_i 2^(m_i - M) / sum_i l_i 2^(m_i - M)
-// with M = max_i m_i, the pieces taken in piece order.  One wave per row, four heads per workgroup.
+// with M = max_i m_i, the pieces taken in piece order.  One wave per row, four heads per workgroup; bound by latency, so
+// lane i fetches piece i's maximum and sum, and the channels of eight pieces are requested together.
 template <typename S, int D>
 __global__ __launch_bounds__(256) void attn_merge_kernel(FlpAttnArgs a, const int32_t* __restrict__ merge_tok,
-                                                         const int32_t* __restrict__ merge_nsplit) {
+                                                         const int32_t* __restrict__ merge_first) {
   typedef typename S::storage ST;
   constexpr int CPL = D / 64;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int row = blockIdx.x, h = blockIdx.y * 4 + wave;
   if (h >= a.n_h) return;
-  const int t = merge_tok[row], ns = merge_nsplit[row];
-  const float* pp = a.partials + ((int64_t)row * a.n_h + h) * a.max_split * (D + 2);
-  float M = -INFINITY;
-  for (int i = 0; i < ns; ++i) M = fmaxf(M, pp[(int64_t)i * (D + 2)]);
-  float l = 0.f, acc[CPL];
+  const int t = merge_tok[row], first = merge_first[row], ns = merge_first[row + 1] - first;
+  const int64_t stride = (int64_t)a.n_h * (D + 2);
+  const float* pp = a.partials + (int64_t)first * stride + (int64_t)h * (D + 2);
+  const float* mine = pp + (lane < ns ? lane : 0) * stride;
+  const float mi = mine[0], li = mine[1];
+  float M = mi;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) M = fmaxf(M, __shfl_xor(M, off));
+  const float wi = lane < ns ? exp2f(mi - M) : 0.f;     // a piece without visible keys has m = -inf, l = 0: weight 0
+  float l = lane < ns ? li * wi : 0.f;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) l += __shfl_xor(l, off);
+  float acc[CPL];
 #pragma unroll
   for (int c = 0; c < CPL; ++c) acc[c] = 0.f;
-  for (int i = 0; i < ns; ++i) {
-    const float* q = pp + (int64_t)i * (D + 2);
-    const float w = exp2f(q[0] - M);                    // a piece without visible keys has m = -inf, l = 0: weight 0
-    l = fmaf(q[1], w, l);
+  for (int i0 = 0; i0 < ns; i0 += 8) {
+    float q[8][CPL];
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) acc[c] = fmaf(q[2 + lane + 64 * c], w, acc[c]);
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) q[i][c] = pp[(int64_t)(i0 + i < ns ? i0 + i : ns - 1) * stride + 2 + lane + 64 * c];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (i0 + i < ns) {
+        const float w = __shfl(wi, i0 + i);
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) acc[c] = fmaf(q[i][c], w, acc[c]);
+      }
+    }
   }
   const float inv = 1.f / l;
   ST* op = reinterpret_cast<ST*>(a.out) + ((int64_t)t * a.n_h + h) * D;
@@ -346,10 +364,10 @@ flp_status flp_launch_attn_rows(int dtype, int head_dim, const FlpAttnArgs& a, c
 }
 
 flp_status flp_launch_attn_merge(int dtype, int head_dim, const FlpAttnArgs& a, const int32_t* merge_tok_dev,
-                                 const int32_t* merge_nsplit_dev, int32_t n_rows, hipStream_t stream) {
+                                 const int32_t* merge_first_dev, int32_t n_rows, hipStream_t stream) {
   if (n_rows <= 0) return FLP_OK;
   dim3 grid((unsigned)n_rows, (unsigned)((a.n_h + 3) / 4));
-  FLP_DISPATCH(attn_merge_kernel, dtype, head_dim, grid, dim3(256), stream, a, merge_tok_dev, merge_nsplit_dev);
+  FLP_DISPATCH(attn_merge_kernel, dtype, head_dim, grid, dim3(256), stream, a, merge_tok_dev, merge_first_dev);
   FLP_TRY_HIP(hipGetLastError());
   return FLP_OK;
 }

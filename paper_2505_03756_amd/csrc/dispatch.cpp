@@ -150,10 +150,13 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   hipStream_t stream = (hipStream_t)hip_stream;
   if (with_append) FLP_TRY(append_locked(p, b, stream));
 
-  // Two kinds of work.  Sequences with at least 8 query rows per kv head (prefill, or decode
-  // under grouped-query attention) on a 16-bit pool with head_dim 128 go to the matrix-core
-  // kernel in tiles of 256 rows; everything else (fp32, head_dim 64, single-row decode) goes to
-  // the row-streaming kernel in runs of up to 4 tokens.  Both lists are ordered heaviest first.
+  // Three kinds of work.  On a 16-bit pool with head_dim 128, sequences with at least 8 query rows per kv head (prefill,
+  // or decode under grouped-query attention) go to the tiled matrix-core kernel in tiles of 256 rows, and the others
+  // (and all short ones of a small launch, below) token by token to the decode kernel.  A large grouped-query batch
+  // stays with the tiles as a whole: the single tokens' traffic overlaps with the other tiles' products (128 prefill
+  // and 384 decode sequences, 64 / 8 heads: 17.5 ms for the step against 17.8 ms with the single tokens in a launch of their
+  // own).  fp32, head_dim 64 and more than 16 query heads per kv head: the row-streaming kernel in runs of up to 4
+  // tokens.  All lists are ordered heaviest first.
   const bool mfma_ok = p->cfg.dtype != FLP_F32 && p->cfg.head_dim == 128;
   const int G = b->n_q_heads / p->cfg.n_kv_heads;
   const int n_kv = p->cfg.n_kv_heads;
@@ -165,12 +168,14 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   };
   std::stable_sort(seq_order.begin(), seq_order.end(), [&](int32_t x, int32_t y) { return seq_cost(x) > seq_cost(y); });
 
+  const bool decode_ok = mfma_ok && G <= kDecodeMaxGroup;
+
   std::vector<FlpAttnUnit> units;
   std::vector<int64_t> cost;
   constexpr int kTokPerUnit = 4;
   // A launch of a handful of matrix-core items (a few decode sequences under grouped-query attention) would leave
-  // most of the chip idle: such sequences go to the row-streaming kernel instead, where their long contexts are
-  // split over many waves (below).
+  // most of the chip idle: such sequences go to the decode kernel (more than 16 heads per kv head: the row kernel)
+  // instead, where their long contexts are split over many waves (below).
   int64_t mfma_items_est = 0;
   if (mfma_ok)
     for (int32_t i = 0; i < b->n_seqs; ++i) {
@@ -183,7 +188,7 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   // XCDs the tiles that re-read the same K/V run on the same XCD and share its L2.
   std::vector<FlpMfmaItem> queue[8];
   int next_q = 0;
-  std::vector<int32_t> row_seqs;                      // sequences of the row-streaming kernel, heaviest first
+  std::vector<int32_t> row_seqs;                      // sequences of the decode or the row kernel, heaviest first
   int64_t row_tokens = 0;
   for (int32_t i : seq_order) {
     const int32_t n = b->cu_new[i + 1] - b->cu_new[i];
@@ -201,32 +206,39 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
       row_tokens += n;
     }
   }
-  // Split-KV.  The row kernel runs one wave per (token, head); with few rows and long contexts (a handful of decode
-  // sequences at 16 k tokens) that is far fewer waves than the chip holds.  Below kSplitBelow waves every token
-  // becomes a unit of its own and its context is cut into pieces of at least kMinGroups groups of 16 positions, each
-  // piece a wave; a second kernel merges the pieces of a row in piece order.
-  constexpr int64_t kSplitBelow = 2048, kSplitTarget = 8192;
+  // Split-KV.  A wave of the decode kernel takes one (token, kv head), one of the row kernel one (token, head); with
+  // few tokens and long contexts (a handful of decode sequences at 16 k) that is far fewer waves than the chip holds,
+  // and with unequal contexts the longest one decides.  Contexts are cut into pieces, each piece a wave; a second kernel
+  // merges the pieces of a row in piece order.  Decode kernel: pieces of equal length, about kPieces of them (twice
+  // what the chip holds), at least kMinGroups groups of 16 positions.  Row kernel: below kSplitBelow waves.
+  constexpr int64_t kSplitBelow = 2048, kSplitTarget = 8192, kPieces = 4096;
   constexpr int kMinGroups = 16, kMaxSplit = 64;
   const int64_t row_waves = row_tokens * b->n_q_heads;
   const int want_split = row_waves > 0 && row_waves < kSplitBelow
                              ? (int)std::min<int64_t>(kMaxSplit, (kSplitTarget + row_waves - 1) / row_waves) : 1;
-  std::vector<int32_t> merge_tok, merge_nsplit;
-  int max_split = 1;
+  int64_t all_groups = 0;
+  if (decode_ok)
+    for (int32_t i : row_seqs) {
+      const int64_t n = b->cu_new[i + 1] - b->cu_new[i];
+      all_groups += n * (((int64_t)b->prefix_len[i] + n + 15) / 16);
+    }
+  const int64_t piece = std::max<int64_t>(kMinGroups, all_groups * n_kv / kPieces);
+  std::vector<int32_t> merge_tok, merge_first{0};
   for (int32_t i : row_seqs) {
     const int32_t n = b->cu_new[i + 1] - b->cu_new[i];
-    if (want_split > 1) {
+    if (decode_ok || want_split > 1) {
       for (int32_t j = 0; j < n; ++j) {
         const int32_t groups = (b->prefix_len[i] + j + 1 + 15) / 16;
-        const int ns = std::max(1, std::min(want_split, groups / kMinGroups));
+        const int ns = decode_ok ? (int)std::min<int64_t>(kMaxSplit, (groups + piece - 1) / piece)
+                                 : std::max(1, std::min(want_split, groups / kMinGroups));
         if (ns == 1) {
-          units.push_back(FlpAttnUnit{i, j, 1, 1, 0, 0, 0, 0});
+          units.push_back(FlpAttnUnit{i, j, 1, 1, 0, 0, groups, 0});
           cost.push_back(groups);
           continue;
         }
-        const int32_t row = (int32_t)merge_tok.size();
+        const int32_t row = merge_first.back();
         merge_tok.push_back(b->cu_new[i] + j);
-        merge_nsplit.push_back(ns);
-        max_split = std::max(max_split, ns);
+        merge_first.push_back(row + ns);
         for (int sidx = 0; sidx < ns; ++sidx) {
           const int32_t lo = (int32_t)((int64_t)groups * sidx / ns), hi = (int32_t)((int64_t)groups * (sidx + 1) / ns);
           units.push_back(FlpAttnUnit{i, j, 1, ns, sidx, lo, hi, row});
@@ -251,7 +263,7 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
 
   const size_t units_bytes = units.size() * sizeof(FlpAttnUnit), items_bytes = n_items * sizeof(FlpMfmaItem);
   const size_t n_merge = merge_tok.size();
-  std::vector<uint8_t> blob(units_bytes + items_bytes + 2 * n_merge * sizeof(int32_t));
+  std::vector<uint8_t> blob(units_bytes + items_bytes + (2 * n_merge + 1) * sizeof(int32_t));
   FlpAttnUnit* hu = (FlpAttnUnit*)blob.data();
   for (size_t k = 0; k < order.size(); ++k) hu[k] = units[order[k]];
   FlpMfmaItem* hi = (FlpMfmaItem*)(blob.data() + units_bytes);
@@ -260,23 +272,22 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   if (n_merge) {
     int32_t* hm = (int32_t*)(blob.data() + units_bytes + items_bytes);
     memcpy(hm, merge_tok.data(), n_merge * sizeof(int32_t));
-    memcpy(hm + n_merge, merge_nsplit.data(), n_merge * sizeof(int32_t));
+    memcpy(hm + n_merge, merge_first.data(), (n_merge + 1) * sizeof(int32_t));
   }
   void* partials = nullptr;
   if (n_merge)
-    FLP_TRY(flp_attn_workspace(p, n_merge * (size_t)b->n_q_heads * max_split * (p->cfg.head_dim + 2) * sizeof(float),
-                               &partials));
+    FLP_TRY(flp_attn_workspace(p, (size_t)merge_first.back() * b->n_q_heads * (p->cfg.head_dim + 2) * sizeof(float), &partials));
 
   StagedSeqs st;
   FLP_TRY(stage_seqs(p, b, blob.data(), blob.size(), stream, &st));
   FlpAttnArgs a = make_args(p, b, st);
   a.partials = (float*)partials;
-  a.max_split = max_split;
   const FlpAttnUnit* du = (const FlpAttnUnit*)st.units;
   const FlpMfmaItem* di = (const FlpMfmaItem*)((const uint8_t*)st.units + units_bytes);
   const int32_t* dm = (const int32_t*)((const uint8_t*)st.units + units_bytes + items_bytes);
   flp_status s0 = flp_launch_attn_mfma(p->cfg.dtype, a, di, (int32_t)n_items, stream);
-  flp_status s1 = flp_launch_attn_rows(p->cfg.dtype, p->cfg.head_dim, a, du, (int32_t)units.size(), stream);
+  flp_status s1 = decode_ok ? flp_launch_attn_decode(p->cfg.dtype, a, du, (int32_t)units.size(), stream)
+                            : flp_launch_attn_rows(p->cfg.dtype, p->cfg.head_dim, a, du, (int32_t)units.size(), stream);
   flp_status s3 = s1 == FLP_OK ? flp_launch_attn_merge(p->cfg.dtype, p->cfg.head_dim, a, dm, dm + n_merge,
                                                         (int32_t)n_merge, stream) : FLP_OK;
   flp_status s2 = flp_stage_release(st.slot, stream);

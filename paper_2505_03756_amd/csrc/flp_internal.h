@@ -115,8 +115,8 @@ struct FlpAppendUnit {   // the slots [s0, s1) of the 16-position group `blk_idx
 };
 struct FlpAttnUnit {     // new tokens [j0, j0+n_tok) of sequence `seq`
   int32_t seq, j0, n_tok;
-  // split-KV (few long sequences): with n_split > 1 the unit is ONE token and covers only the 16-position groups
-  // [g_lo, g_hi) of its context; its unnormalised result goes to row part_row of the partials buffer, piece `split`
+  // split-KV (long contexts): with n_split > 1 the unit is ONE token and covers only the 16-position groups
+  // [g_lo, g_hi) of its context; its unnormalised result is piece part_row + split of the partials buffer
   int32_t n_split, split, g_lo, g_hi, part_row;
 };
 
@@ -138,18 +138,23 @@ struct FlpAttnArgs {
   const int32_t* cu_new;       // device copies
   const int32_t* prefix_len;
   float scale_log2e;
-  float* partials;             // split-KV: [part_row][n_h][max_split][head_dim + 2] fp32 (running max, sum, channels)
-  int32_t max_split;
+  float* partials;             // split-KV: [piece][n_h][head_dim + 2] fp32 (running max, sum, channels)
 };
 
 flp_status flp_launch_kv_append(int dtype, int head_dim, const FlpAttnArgs& a, const FlpAppendUnit* units_dev,
                                 int32_t n_units, hipStream_t stream);
 flp_status flp_launch_attn_rows(int dtype, int head_dim, const FlpAttnArgs& a, const FlpAttnUnit* units_dev,
                                 int32_t n_units, hipStream_t stream);
-// split-KV: one merged row per (partials row, head): token t = merge_tok[row], n_split[row] pieces combined in
-// piece order (so the result does not depend on which piece finished first)
+// single new tokens on the matrix cores: 16-bit pools, head_dim 128, n_h / n_kv <= kDecodeMaxGroup; every unit is ONE token
+// with its groups [g_lo, g_hi) filled in
+constexpr int kDecodeMaxGroup = 16;
+flp_status flp_launch_attn_decode(int dtype, const FlpAttnArgs& a, const FlpAttnUnit* units_dev, int32_t n_units,
+                                  hipStream_t stream);
+// split-KV: one merged row per (row of the lists, head): token t = merge_tok[row], the merge_first[row + 1] -
+// merge_first[row] <= 64 pieces from merge_first[row] on combined in piece order (so the result does not depend on
+// which piece finished first)
 flp_status flp_launch_attn_merge(int dtype, int head_dim, const FlpAttnArgs& a, const int32_t* merge_tok_dev,
-                                 const int32_t* merge_nsplit_dev, int32_t n_rows, hipStream_t stream);
+                                 const int32_t* merge_first_dev, int32_t n_rows, hipStream_t stream);
 flp_status flp_attn_workspace(flp_pool* pool, size_t bytes, void** out);
 
 flp_status flp_launch_attn_mfma(int dtype, const FlpAttnArgs& a, const FlpMfmaItem* items_dev, int32_t n_items,

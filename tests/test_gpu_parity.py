@@ -1,6 +1,7 @@
 """GPU parity: the HIP path through the C ABI against the CPU oracle, element by element."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from helpers import TOL, GpuStep, build_pools, close, resident_pool, to_dev, to_np
@@ -530,3 +531,53 @@ def test_split_kv_for_few_long_sequences(dtype, heads, kv, d, seqs, prefix, new)
                                   step.acts["q"])
     ok, worst, nbad = close(wl.dequantize(out1, dtype).reshape(want.shape), want, *TOL[dtype])
     assert ok, "max err %g (%d bad)" % (worst, nbad)
+
+
+@pytest.mark.parametrize("dtype,bt,heads,kv,ctx", [
+    ("f16", 16, 8, 8, (1, 2, 15, 16, 17, 31, 32, 33)),          # one row per kv head; one, two and three tiles of positions
+    ("bf16", 16, 32, 2, (1, 33, 255, 256, 257, 511, 513)),      # 16 rows per kv head, around one piece and two
+    ("f16", 32, 15, 5, (16, 17, 32, 47, 48, 65, 300, 1100)),    # 3 rows per kv head, blocks of 32, kv heads not a multiple of 4
+    ("bf16", 32, 16, 2, (31, 64, 769, 1025, 2047)),
+    ("f16", 16, 34, 2, (5, 40, 700)),                           # 17 rows per kv head: past what one wave holds
+])
+def test_single_token_attention_at_the_edges_of_groups_tiles_and_pieces(dtype, bt, heads, kv, ctx):
+    """One new token per sequence, contexts around the edges of groups (16), tiles (32) and pieces (256 positions).
+    Slots past a context hold NaN, one visible V is infinite (its channel of that sequence alone becomes infinite)."""
+    d = 128
+    rng = np.random.default_rng(7 + heads + len(ctx))
+    n_blk = [(c + bt - 1) // bt for c in ctx]
+    n = sum(n_blk)
+    ids = rng.permutation(n).astype(np.int32)
+    tables = np.full((len(ctx), max(n_blk)), -1, np.int32)
+    at = 0
+    for i, k in enumerate(n_blk):
+        tables[i, :k] = ids[at:at + k]
+        at += k
+    cu, prefix = np.arange(len(ctx) + 1, dtype=np.int32), np.array(ctx, np.int32) - 1
+    tt = torch.float16 if dtype == "f16" else torch.bfloat16
+    K, V = (torch.from_numpy(rng.standard_normal((n, kv, bt, d)).astype(np.float32)).to(tt) for _ in range(2))
+    V = V.transpose(2, 3).contiguous()                          # [block, kv head, channel, slot]
+    for i, c in enumerate(ctx):
+        if c % bt:
+            K[tables[i, n_blk[i] - 1], :, c % bt:] = float("nan")
+            V[tables[i, n_blk[i] - 1], :, :, c % bt:] = float("nan")
+    V[tables[-1, 0], 0, 3, 2] = float("inf")
+    q = torch.from_numpy(rng.standard_normal((len(ctx), heads, d)).astype(np.float32)).to(tt)
+    dev = torch.cat([K.reshape(n, -1), V.reshape(n, -1)], 1).contiguous().cuda()
+    pool = flpool.Pool(dtype, kv, d, n, 0, block_tokens=bt, dev=dev)
+    out = torch.empty_like(q, device="cuda")
+    pool.paged_prefix_attention(q.cuda(), out, cu, prefix, torch.from_numpy(tables).cuda(), heads)
+    got = out.cpu().double()
+    G = heads // kv
+    for i, c in enumerate(ctx):
+        tab = torch.from_numpy(tables[i, :n_blk[i]].astype(np.int64))
+        k = K[tab].double().permute(1, 0, 2, 3).reshape(kv, -1, d)[:, :c].repeat_interleave(G, 0)
+        v = V[tab].double().permute(1, 0, 3, 2).reshape(kv, -1, d)[:, :c].repeat_interleave(G, 0)
+        w = torch.softmax(torch.einsum("hd,hcd->hc", q[i].double(), k) / d ** 0.5, 1)
+        want = torch.einsum("hc,hcd->hd", w, v)
+        inf = torch.isinf(want)
+        assert torch.equal(got[i][inf], want[inf]) and int(inf.sum()) == (G if i == len(ctx) - 1 else 0)
+        err = (got[i] - want)[~inf].abs()
+        # the result's own rounding (2^-11 or 2^-8 of it) plus 32-bit sums and weights of at most 2^-16 of sum w |v| off
+        bound = (2.0 ** -11 if dtype == "f16" else 2.0 ** -8) * want.abs() + 2.0 ** -15 * torch.einsum("hc,hcd->hd", w, v.abs())
+        assert bool((err <= bound[~inf] + 1e-7).all()), (c, float(err.max()))
