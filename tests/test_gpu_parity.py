@@ -581,3 +581,32 @@ def test_single_token_attention_at_the_edges_of_groups_tiles_and_pieces(dtype, b
         # the result's own rounding (2^-11 or 2^-8 of it) plus 32-bit sums and weights of at most 2^-16 of sum w |v| off
         bound = (2.0 ** -11 if dtype == "f16" else 2.0 ** -8) * want.abs() + 2.0 ** -15 * torch.einsum("hc,hcd->hd", w, v.abs())
         assert bool((err <= bound[~inf] + 1e-7).all()), (c, float(err.max()))
+
+
+@pytest.mark.parametrize("T", [1, 31, 33, 127, 129, 255, 257, 513, 1025, 2049])
+@pytest.mark.parametrize("dtype,d_in,widths", [
+    ("f16", 64, (64, 32, 40)),                 # one step of the contraction, widths that no tile divides
+    ("bf16", 1088, (264, 136, 72)),            # three outputs in one launch, remainders of every tile
+    ("f16", 4096, (4096, 1032)),               # enough contraction for slices at small batches, whole tiles at large ones
+])
+def test_dense_products_at_the_edges_of_their_tiles(dtype, d_in, widths, T):
+    """Tokens without an adapter keep the dense product, whatever tile and number of slices the batch size selects."""
+    tt = torch.float16 if dtype == "f16" else torch.bfloat16
+    g = torch.Generator().manual_seed(T + d_in)
+    x = torch.randn((T, d_in), generator=g).to(tt)
+    w = [(torch.randn((n, d_in), generator=g) / d_in ** 0.5).to(tt) for n in widths]
+    pool = flpool.Pool(dtype, 4, 128, 4, 0, dev=torch.zeros((4, 2 * 16 * 4 * 128), dtype=tt, device="cuda"))
+    zero = torch.zeros(1, dtype=torch.int32, device="cuda")
+    dx, dw = x.cuda(), [m.cuda() for m in w]
+    y = [torch.full((T, n), float("nan"), dtype=tt, device="cuda") for n in widths]
+    projs = [dict(y=yi, d_out=n, w_base=wi, w_base_layout=1, a_tab_off=zero, a_row_base=zero, b_tab_off=zero, b_row_base=zero)
+             for yi, n, wi in zip(y, widths, dw)]
+    none = torch.full((T,), -1, dtype=torch.int32, device="cuda")
+    rank, scale = torch.full((1,), 8, dtype=torch.int32, device="cuda"), torch.ones(1, device="cuda")
+    pool.lora_apply_paged(dx, none, rank, scale, zero, projs, n_tokens=T, d_in=d_in, n_adapters=1, max_rank=8)
+    half_ulp = 2.0 ** -11 if dtype == "f16" else 2.0 ** -8
+    for yi, wi in zip(y, dw):
+        want = dx.double() @ wi.double().T
+        # the result's rounding, and d_in additions in 32 bits
+        bound = half_ulp * want.abs() + d_in * 2.0 ** -24 * (dx.double().abs() @ wi.double().abs().T) + 1e-7
+        assert bool(((yi.double() - want).abs() <= bound).all())
