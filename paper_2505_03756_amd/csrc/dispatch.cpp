@@ -311,16 +311,22 @@ extern "C" flp_status flp_lora_segment(flp_pool* p, int32_t n_tokens, const int3
 }
 
 namespace {
-flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_stream, void* gated_out, int64_t ld_gated,
-                           const FlpFixedWorkspace* fixed = nullptr);
+flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_stream, size_t budget, void* gated_out,
+                           int64_t ld_gated, const FlpFixedWorkspace* fixed = nullptr);
 }
 
+// The call and its form in a fixed buffer plan the dense products for the same room, the fixed buffer's, so that they take
+// the same slices and return the same bits.
 extern "C" flp_status flp_lora_apply_paged(flp_pool* p, const flp_lora_batch* b, void* hip_stream) {
-  return lora_apply_impl(p, b, hip_stream, nullptr, 0);
+  return lora_apply_impl(p, b, hip_stream, kStaticScratchBytes, nullptr, 0);
 }
 
 flp_status flp_lora_apply_fixed(flp_pool* p, const flp_lora_batch* b, void* hip_stream, const FlpFixedWorkspace& ws) {
-  return lora_apply_impl(p, b, hip_stream, nullptr, 0, &ws);
+  return lora_apply_impl(p, b, hip_stream, ws.cap, nullptr, 0, &ws);
+}
+
+flp_status flp_lora_apply_layer(flp_pool* p, const flp_lora_batch* b, void* hip_stream) {
+  return lora_apply_impl(p, b, hip_stream, kLayerSliceBytes, nullptr, 0);
 }
 
 flp_status flp_lora_apply_gated(flp_pool* p, const flp_lora_batch* b, void* out, int64_t ld_out, void* hip_stream) {
@@ -328,7 +334,7 @@ flp_status flp_lora_apply_gated(flp_pool* p, const flp_lora_batch* b, void* out,
     flp_set_error("flp_lora_apply_gated: out is null or misaligned");
     return FLP_EINVAL;
   }
-  return lora_apply_impl(p, b, hip_stream, out, ld_out);
+  return lora_apply_impl(p, b, hip_stream, kLayerSliceBytes, out, ld_out);
 }
 
 namespace {
@@ -339,8 +345,9 @@ struct BaseGroup {
   FlpGemmPlan plan{};
 };
 
-// groups and plans of a call's dense base products; returns the bytes their slices take.  `room` bounds the slices; one
-// slice of every product is planned even where it does not fit.
+// groups and plans of a call's dense base products; returns the bytes their slices take, every product's rounded up to
+// 256.  More than one slice is taken only where all slices stay within `room`; one slice of every product is planned
+// even where that does not fit.
 size_t plan_base(const flp_lora_batch* b, bool one_launch, size_t room, std::vector<BaseGroup>* groups) {
   for (int q = 0; q < b->n_proj; ++q) {
     if (!b->proj[q].w_base) continue;
@@ -348,21 +355,27 @@ size_t plan_base(const flp_lora_batch* b, bool one_launch, size_t room, std::vec
     BaseGroup& g = groups->back();
     g.which[g.n++] = q;
   }
-  size_t total = 0;
-  for (BaseGroup& g : *groups) {
-    int N[FLP_MAX_PROJ];
-    for (int i = 0; i < g.n; ++i) N[i] = b->proj[g.which[i]].d_out;
-    g.plan = flp_gemm_plan(b->n_tokens, b->d_in, g.n, N, 0, room / groups->size());
-    for (int i = 0; i < g.n; ++i) total += ((size_t)g.plan.splits * b->n_tokens * N[i] * 4 + 255) & ~(size_t)255;
+  const size_t pad = 255 * (size_t)b->n_proj;
+  const size_t share = groups->empty() || room < pad ? 0 : (room - pad) / groups->size();
+  for (unsigned allow = 0;; allow = FLP_GEMM_NO_SPLIT) {
+    size_t total = 0;
+    for (BaseGroup& g : *groups) {
+      int N[FLP_MAX_PROJ];
+      for (int i = 0; i < g.n; ++i) N[i] = b->proj[g.which[i]].d_out;
+      g.plan = flp_gemm_plan(b->n_tokens, b->d_in, g.n, N, allow, share);
+      for (int i = 0; i < g.n; ++i) total += ((size_t)g.plan.splits * b->n_tokens * N[i] * 4 + 255) & ~(size_t)255;
+    }
+    if (total <= room || allow) return total;          // a product larger than its share: the others may not slice either
   }
-  return total;
 }
 
 // gated_out != nullptr: two projections (gate, up) whose results are not stored; gated_out = silu(y0) * y1
 // fixed != nullptr: the intermediates go into the caller-provided buffer and nothing is allocated; a batch that
 // needs more than the buffer holds is refused before anything is enqueued
-flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_stream, void* gated_out, int64_t ld_gated,
-                           const FlpFixedWorkspace* fixed) {
+// budget: bytes of intermediates that slices of dense products may bring the call to, whatever the buffer is (the sums'
+// order, and with it the result's last bits, depends on the number of slices)
+flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_stream, size_t budget, void* gated_out,
+                           int64_t ld_gated, const FlpFixedWorkspace* fixed) {
   if (!p || !b) {
     flp_set_error("flp_lora_apply_paged: null pool or batch");
     return FLP_EINVAL;
@@ -490,8 +503,7 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
   size_t base_total = 0;
   if (p->elem_bytes == 2 && !fused) {
     const size_t rest = v_bytes + seg_bytes + perm_bytes + wt_bytes;
-    const size_t room = fixed ? (fixed->cap > rest ? fixed->cap - rest : 0) : (size_t)1 << 30;
-    base_total = plan_base(b, one_launch, room, &groups);
+    base_total = plan_base(b, one_launch, budget > rest ? budget - rest : 0, &groups);
   }
   void* ws = nullptr;
   const size_t ws_bytes = v_bytes + seg_bytes + perm_bytes + wt_bytes + base_total + inv_bytes;

@@ -87,8 +87,12 @@ struct FlpFixedWorkspace {
   flp_status (*resolve)(flp_pool* pool, void** out);
   const char* who;
 };
+constexpr size_t kStaticScratchBytes = (size_t)64 << 20;   // what flp_lora_apply_paged_static has per GPU
+constexpr size_t kLayerSliceBytes = (size_t)1 << 30;       // what slices of a layer's dense products may take
 // flp_lora_apply_paged with its intermediates in `ws` (no allocation, no growth)
 flp_status flp_lora_apply_fixed(flp_pool* pool, const flp_lora_batch* batch, void* hip_stream, const FlpFixedWorkspace& ws);
+// flp_lora_apply_paged for the layer step, whose larger slice room only the pool's growing workspace has
+flp_status flp_lora_apply_layer(flp_pool* pool, const flp_lora_batch* batch, void* hip_stream);
 // set-up of the file-scope scratch array for the current device (looks its device address up once per device);
 // called when a pool is created, and again by the entry point that uses the array if that first attempt failed
 flp_status flp_static_scratch_setup(int device, void** out);
@@ -259,6 +263,9 @@ struct FlpGemmArgs {
 enum { FLP_GEMM_NO_SPLIT = 1, FLP_GEMM_LARGE_ONLY = 2 };   // whole contractions only; only the tiles that take a LoRA epilogue
 // N: features of every projection (of a gated pair: both matrices' together)
 FlpGemmPlan flp_gemm_plan(int M, int K, int n_proj, const int* N, unsigned allow, size_t max_part_bytes);
+// the same through the C ABI, for tests that state which tile and how many slices a shape gets; room < 0: a layer's
+extern "C" void flp_dense_plan(int32_t M, int32_t K, int32_t n_proj, const int32_t* N, int32_t large_only, int64_t room,
+                               int32_t* kind, int32_t* splits);
 size_t flp_gemm_part_bytes(const FlpGemmPlan& plan, int M, int n_proj, const int* N);
 // lora: one per projection (gated: gate, up), or null
 flp_status flp_launch_gemm(int dtype, const void* x, int64_t ld_x, int M, int K, const FlpGemmPlan& plan, int n_proj,
@@ -272,5 +279,5 @@ flp_status flp_launch_gemm_f32(const float* x, int64_t ld_x, const float* w, int
 // flp_lora_apply_paged for exactly two projections with dense bases stored [d_out, d_in] and equal widths (gate and
 // up of an MLP), whose results are not stored: out = silu(y0) * y1 in one pass of the large-batch GEMM, each product
 // with its LoRA branch added before it is rounded.  FLP_ENOTSUP, nothing launched, when the batch is not one that
-// this path takes; the caller then runs flp_lora_apply_paged and the element-wise step.
+// this path takes; the caller then runs flp_lora_apply_layer and the element-wise step.
 flp_status flp_lora_apply_gated(flp_pool* pool, const flp_lora_batch* batch, void* out, int64_t ld_out, void* hip_stream);

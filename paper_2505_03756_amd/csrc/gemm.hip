@@ -756,6 +756,14 @@ FlpGemmPlan flp_gemm_plan(int M, int K, int n_proj, const int* N, unsigned allow
   return best;
 }
 
+extern "C" void flp_dense_plan(int32_t M, int32_t K, int32_t n_proj, const int32_t* N, int32_t large_only, int64_t room,
+                               int32_t* kind, int32_t* splits) {
+  const FlpGemmPlan p = flp_gemm_plan(M, K, n_proj, N, large_only ? FLP_GEMM_NO_SPLIT | FLP_GEMM_LARGE_ONLY : 0,
+                                      room < 0 ? kLayerSliceBytes : (size_t)room);
+  *kind = p.kind;
+  *splits = p.splits;
+}
+
 flp_status flp_launch_gemm(int dtype, const void* x, int64_t ld_x, int M, int K, const FlpGemmPlan& plan, int n_proj,
                            const FlpGemmOut* out, bool gated, const FlpGemmLora* lora, hipStream_t stream) {
   if (M <= 0 || K <= 0 || n_proj <= 0) return FLP_OK;

@@ -283,7 +283,7 @@ flp_status dense_products(flp_pool* p, const void* x, int d_in, int T, int n, Fl
                                   stream));
     return FLP_OK;
   }
-  const FlpGemmPlan plan = flp_gemm_plan(T, d_in, n, N, 0, (size_t)1 << 30);
+  const FlpGemmPlan plan = flp_gemm_plan(T, d_in, n, N, 0, kLayerSliceBytes);
   if (plan.splits > 1) {
     void* part = nullptr;
     {
@@ -384,7 +384,7 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
     if (n_lora == 0) return FLP_OK;
     lb.n_proj = n_lora;
     if (gated_out) return flp_lora_apply_gated(p, &lb, gated_out, d_outs[0], hip_stream);
-    return flp_lora_apply_paged(p, &lb, hip_stream);
+    return flp_lora_apply_layer(p, &lb, hip_stream);
   };
 
   FLP_TRY(fll_rmsnorm(dtype, h, w->in_norm, n, T, H, eps, hip_stream));

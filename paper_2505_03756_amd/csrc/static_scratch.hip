@@ -8,15 +8,10 @@
 
 #include "flp_internal.h"
 
-namespace {
-
-constexpr size_t kScratchBytes = (size_t)64 << 20;   // 64 MiB per GPU, held until the process ends
-
-}  // namespace
-
-// Every GPU that loads the library holds its own copy of this array at its own address.  In host code the name is
-// only a handle for hipGetSymbolAddress; kernels and copies get the looked-up device pointer.
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+// Every GPU that loads the library holds its own copy of this array (64 MiB, until the process ends) at its own
+// address.  In host code the name is only a handle for hipGetSymbolAddress; kernels and copies get the looked-up
+// device pointer.
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
 
@@ -62,9 +57,9 @@ flp_status flp_static_scratch_setup(int device, void** out) {
   return FLP_OK;
 }
 
-extern "C" int64_t flp_static_scratch_bytes(void) { return (int64_t)kScratchBytes; }
+extern "C" int64_t flp_static_scratch_bytes(void) { return (int64_t)kStaticScratchBytes; }
 
 extern "C" flp_status flp_lora_apply_paged_static(flp_pool* pool, const flp_lora_batch* batch, void* hip_stream) {
-  const FlpFixedWorkspace ws{kScratchBytes, resolve_for_pool, "flp_lora_apply_paged_static"};
+  const FlpFixedWorkspace ws{kStaticScratchBytes, resolve_for_pool, "flp_lora_apply_paged_static"};
   return flp_lora_apply_fixed(pool, batch, hip_stream, ws);
 }

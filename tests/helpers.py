@@ -18,6 +18,22 @@ def close(got, ref, rtol, atol):
 TOL = {"f32": (1e-4, 1e-5), "f16": (2e-3, 1e-2), "bf16": (2e-3, 1e-2)}
 
 
+GEMM_TILES = ("64x32", "128x64", "128x128", "256x128", "256x256")      # features x tokens
+
+
+def dense_plan(n_tokens, d_in, widths, large_only=False, room=-1):
+    """(tile, slices) that the library takes for dense products of these widths over one input (of a gated pair: both
+    matrices' width together); room: bytes that slices may take, -1: what a layer gives them."""
+    import ctypes as C
+
+    from paper_2505_03756_amd import flpool
+    f = flpool.load().flp_dense_plan
+    f.restype, f.argtypes = None, [C.c_int32] * 3 + [C.c_void_p, C.c_int32, C.c_int64, C.c_void_p, C.c_void_p]
+    n, kind, slices = (C.c_int32 * len(widths))(*widths), C.c_int32(), C.c_int32()
+    f(n_tokens, d_in, len(widths), n, large_only, room, C.byref(kind), C.byref(slices))
+    return GEMM_TILES[kind.value], slices.value
+
+
 # ------------------------------------------------------------------ stratified samples of a large batch
 def attention_rows_sample(step, rng, per_cell=1, cells_per_seq=None, seqs=None):
     """Token indices for the attention check, chosen over the structure the matrix-core kernel works in: a

@@ -86,3 +86,44 @@ def test_static_entry_point_refuses_what_does_not_fit():
     torch.cuda.synchronize()
     assert bool((y == 7).all())
     pool.close()
+
+
+SLICED = [   # tokens, d_in, widths, max_rank, and how many slices a layer's larger room would give
+    (1747, 13824, (5120,), 8, 3),          # one slice in 64 MiB
+    (257, 22016, (8192,), 8, 8),           # fewer than eight
+    (313, 16384, (13400, 13384), 16, 3),   # two slices fill the array to the last byte before every product is rounded up
+    (33, 4096, (4096, 4096, 4096), 16, 4),
+    (499, 4096, (4096, 4096, 4096), 16, 1),
+]
+
+
+@pytest.mark.parametrize("T,d_in,widths,max_rank,layer_slices", SLICED)
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_static_entry_point_sums_dense_products_in_the_same_order(dtype, T, d_in, widths, max_rank, layer_slices):
+    """Dense bases outside the fused path: both entry points cut the contraction into the same slices, so the results
+    agree bit for bit also where the fixed array holds fewer slices than the pool's workspace would."""
+    import torch
+    from helpers import dense_plan
+    assert dense_plan(T, d_in, widths)[1] == layer_slices
+    tt = torch.float16 if dtype == "f16" else torch.bfloat16
+    pool = flpool.Pool(dtype, 8, 128, 2, 0, block_tokens=16)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.randn((T, d_in), generator=g, device="cuda").to(tt)
+    w = [(torch.randn((n, d_in), generator=g, device="cuda") / d_in ** 0.5).to(tt) for n in widths]
+    z = torch.zeros(1, dtype=torch.int32, device="cuda")
+    none = torch.full((T,), -1, dtype=torch.int32, device="cuda")
+    got = []
+    for static in (False, True):
+        y = [torch.full((T, n), float("nan"), dtype=tt, device="cuda") for n in widths]
+        projs = [dict(y=yi, d_out=n, w_base=wi, w_base_layout=1, a_tab_off=z, a_row_base=z, b_tab_off=z, b_row_base=z)
+                 for yi, n, wi in zip(y, widths, w)]
+        pool.lora_apply_paged(x, none, z, torch.ones(1, device="cuda"), z, projs, n_tokens=T, d_in=d_in, n_adapters=1,
+                              max_rank=max_rank, static=static)
+        got.append(y)
+    torch.cuda.synchronize()
+    for a, b, wi in zip(got[0], got[1], w):
+        assert torch.equal(a, b), "static and allocating entry points differ"
+        want = x.float() @ wi.float().T
+        # one rounding of a result of standard deviation 1, and two fp32 sums in different orders
+        assert float((b.float() - want).abs().max()) < (2.0 ** -8 if dtype == "f16" else 2.0 ** -5)
+    pool.close()
