@@ -8,19 +8,25 @@
 // twice) and no wave waits for another one: the 16 loads (16 KiB) of the next 32 positions are in flight while the
 // present ones are multiplied, 8 such waves per CU.
 //
-// Both products are computed transposed with 16x16x32 instructions.  S^T = K Q^T: a lane holds one query row
-// (column l % 16) and, with the keys fed in the order key(m) = 8 (m / 4) + 4 t + m % 4 for row m of instruction t, the
-// 8 consecutive positions 8 (l / 16) ... + 7: P^T is then already in B-operand layout, and the A operand of
-// O^T = V^T P^T is one 16-byte run of the transposed V of a pool block.  The rows past G repeat the last one.
+// S^T = K Q^T is computed transposed with 16x16x32 instructions: a lane holds one query row (column l % 16) and, with the
+// keys fed in the order key(m) = 8 (m / 4) + 4 t + m % 4 for row m of instruction t, the 8 consecutive positions
+// 8 (l / 16) ... + 7, which are also the positions of its 16-byte run of the transposed V of a pool block.
 //
-// The weights keep 32-bit accuracy: each is fed as a 16-bit value and the 16-bit remainder in a second instruction
-// (the matrix cores are idle otherwise).  Weights are taken relative to 2^-10 of the running maximum's weight, so that
-// the remainder of an fp16 weight stays a normal number down to weights of 2^-24 of the largest.
-//
-// Against the row-streaming kernel (a wave per query head, K/V widened and multiplied on the vector units, no loads
-// ahead), whole steps on MI355X: 6 sequences of 8-16 k positions, 64 / 8 heads (K/V re-read for each of 8 heads there):
-// 234 -> 136 us; 256 sequences of 512-4096 positions, 32 / 32 heads, 9.8 GB of K/V: 1941 -> 1868 us; layer with 200
-// decode tokens, 32 / 32 heads: 1092 -> 1047 us.
+// O^T = V^T P^T takes 32-bit instructions: weights and sums are fp32 and V is widened, so an element of V contributes
+// exactly what an fp32 multiply-add gives (infinities and the largest bf16 values included).  A 16-bit instruction
+// would need the weights in pieces: value and remainder keep 16 bits of them in bf16, fewer still of small ones in
+// fp16, where the value of a weight below 2^-25 is zero.  Element e of the runs goes into instruction e, with weight e of
+// every lane:
+//   up to 4 heads per kv head   4x4x1: sixteen blocks, each four channels of one position times four rows; column
+//                               l % 16 holds row l % 4.  The quarters of the wave sum different positions and are
+//                               added at the end.  A quarter of the matrix time of the other form.
+//   up to 16                    16x16x4: 16 channels times 16 rows over the wave's four positions; the rows past the last
+//                               head repeat it.
+// Measured, whole steps on MI355X: 256 sequences of 512-4096 positions, 32 / 32 heads, 9.8 GB of K/V: 1872 us (16x16x4
+// there: 1903; 16-bit value and remainder: 1864; a wave per query head on the vector units, nothing loaded ahead: 1941);
+// layer with 200 decode tokens, 32 / 32 heads: 1046 us (1064, 1045, 1092); 6 sequences of 8-16 k positions, 64 / 8 heads:
+// 143 us (16-bit: 137; wave per query head, K/V re-read for each of 8 heads: 234).  There two sets of 4x4x1 accumulators
+// (q in LDS, 256 registers) took 143 us as well, two waves of four rows each 145.
 #include <hip/hip_runtime.h>
 
 #include "flp_internal.h"
@@ -30,7 +36,6 @@ namespace {
 
 constexpr int D = 128;
 constexpr int BT = 16;
-constexpr float kShift = 10.f;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h16x8 __attribute__((ext_vector_type(8)));
@@ -38,20 +43,22 @@ typedef __bf16 b16x8 __attribute__((ext_vector_type(8)));
 
 struct DF16 {
   typedef h16x8 vec;
-  typedef _Float16 el;
   typedef F16 S;
-  static constexpr uint32_t kExp = 0x7c007c00u, kOne = 0x04000400u;      // exponent fields of two values, their lowest bits
   static __device__ __forceinline__ f32x4 mfma(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ float widen(uint32_t two, int odd) {      // one of the two values of a word
+    return F16::to_float((uint16_t)(odd ? two >> 16 : two));
   }
 };
 struct DBF16 {
   typedef b16x8 vec;
-  typedef __bf16 el;
   typedef BF16 S;
-  static constexpr uint32_t kExp = 0x7f807f80u, kOne = 0x00800080u;
   static __device__ __forceinline__ f32x4 mfma(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ float widen(uint32_t two, int odd) {
+    return __uint_as_float(odd ? two & 0xffff0000u : two << 16);
   }
 };
 
@@ -66,10 +73,10 @@ struct Tile {                    // K and V of 32 positions
   u32x4 k[2][4], v[8];
 };
 
-template <typename M>
+// ROWS: 4 or 16, the next one from the query heads per kv head on
+template <typename M, int ROWS>
 __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, const FlpAttnUnit* __restrict__ units) {
   typedef typename M::vec vec;
-  typedef typename M::el el;
   const FlpAttnUnit u = units[blockIdx.x];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int g = blockIdx.y * 4 + wave;
@@ -85,7 +92,8 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
   const uint16_t* __restrict__ pool = reinterpret_cast<const uint16_t*>(a.pool);
   const float c = a.scale_log2e;
 
-  const int h = g * G + (lr < G ? lr : G - 1);         // this lane's query head
+  const int row = lr & (ROWS - 1);
+  const int h = g * G + (row < G ? row : G - 1);       // this lane's query head
   const int64_t rowoff = ((int64_t)t * a.n_h + h) * D;
   vec qf[4];
 #pragma unroll
@@ -116,7 +124,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
   f32x4 O[8];
 #pragma unroll
   for (int ct = 0; ct < 8; ++ct) O[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f;                        // m: running maximum - kShift; l: this lane's share of the sum
+  float m = -INFINITY, l = 0.f;                        // m: running maximum; l: this lane's share of the sum
 
   auto multiply = [&](Tile& T, int tile) {
     f32x4 s[2];
@@ -146,7 +154,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
 #pragma unroll
     for (int e = 1; e < 8; ++e) mx = fmaxf(mx, p[e]);
     mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32)) - kShift;
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
     if (__builtin_amdgcn_ballot_w64(mx > m)) {         // some row's maximum grew
       const float mn = fmaxf(m, mx);
       const float alpha = exp2f(m - mn);               // 0 on the first tile (m = -inf)
@@ -157,34 +165,17 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
 #pragma unroll
         for (int i = 0; i < 4; ++i) O[ct][i] *= alpha;
     }
-    vec hi, lo;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float w = exp2f(p[e] - m);
       l += w;
-      hi[e] = (el)w;
-      lo[e] = (el)(w - (float)hi[e]);
+#pragma unroll
+      for (int ct = 0; ct < 8; ++ct) {
+        const float v = M::widen(T.v[ct][e >> 1], e & 1);
+        O[ct] = ROWS == 16 ? __builtin_amdgcn_mfma_f32_16x16x4f32(v, w, O[ct], 0, 0, 0)
+                           : __builtin_amdgcn_mfma_f32_4x4x1f32(v, w, O[ct], 0, 0, 0);
+      }
     }
-    // An infinite V belongs in the sum once: 0 (or a negative remainder) times it would make the result NaN, so the
-    // remainders see it as zero.  An all-ones exponent plus its lowest bit carries into the sign position.
-    uint32_t carry = 0;
-#pragma unroll
-    for (int ct = 0; ct < 8; ++ct) {
-      O[ct] = M::mfma(as_vec<vec>(T.v[ct]), hi, O[ct]);
-#pragma unroll
-      for (int w = 0; w < 4; ++w) carry |= (T.v[ct][w] & M::kExp) + M::kOne;
-    }
-    if (__builtin_amdgcn_ballot_w64((carry & 0x80008000u) != 0)) {
-#pragma unroll
-      for (int ct = 0; ct < 8; ++ct)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const uint32_t over = ((T.v[ct][w] & M::kExp) + M::kOne) & 0x80008000u;
-          T.v[ct][w] &= ~((over >> 15) * 0xffffu);
-        }
-    }
-#pragma unroll
-    for (int ct = 0; ct < 8; ++ct) O[ct] = M::mfma(as_vec<vec>(T.v[ct]), lo, O[ct]);
   };
 
   // Block ids are requested one tile ahead of the loads that use them, and before the loads of the tile in between, so
@@ -213,29 +204,53 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
 
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
-  if (lr >= G) return;
-  // lane (row lr, quarter lh) holds channels 16 ct + 4 lh + (0..3)
-  if (u.n_split > 1) {
-    float* pp = a.partials + ((int64_t)(u.part_row + u.split) * a.n_h + h) * (D + 2);
-    if (lh == 0) *reinterpret_cast<float2*>(pp) = make_float2(m, l);
+  auto store = [&](const f32x4* o, int n, int c0) {    // n runs of 4 channels of the lane's row, 16 apart, from c0 on
+    if (row >= G) return;
+    if (u.n_split > 1) {
+      float* pp = a.partials + ((int64_t)(u.part_row + u.split) * a.n_h + h) * (D + 2);
+      if (c0 == 0) *reinterpret_cast<float2*>(pp) = make_float2(m, l);
 #pragma unroll
-    for (int ct = 0; ct < 8; ++ct) {
-      float2* o = reinterpret_cast<float2*>(pp + 2 + 16 * ct + 4 * lh);
-      o[0] = make_float2(O[ct][0], O[ct][1]);
-      o[1] = make_float2(O[ct][2], O[ct][3]);
+      for (int k = 0; k < n; ++k) {
+        float2* w = reinterpret_cast<float2*>(pp + 2 + c0 + 16 * k);
+        w[0] = make_float2(o[k][0], o[k][1]);
+        w[1] = make_float2(o[k][2], o[k][3]);
+      }
+      return;
     }
-    return;
-  }
-  const float inv = 1.f / l;
-  uint16_t* op = reinterpret_cast<uint16_t*>(a.out) + rowoff;
+    const float inv = 1.f / l;
+    uint16_t* op = reinterpret_cast<uint16_t*>(a.out) + rowoff + c0;
 #pragma unroll
-  for (int ct = 0; ct < 8; ++ct) {
-    uint16_t o4[4];
+    for (int k = 0; k < n; ++k) {
+      uint16_t o4[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o4[i] = M::S::from_float(O[ct][i] * inv);
-    uint2 w;
-    __builtin_memcpy(&w, o4, 8);
-    *reinterpret_cast<uint2*>(op + 16 * ct + 4 * lh) = w;
+      for (int i = 0; i < 4; ++i) o4[i] = M::S::from_float(o[k][i] * inv);
+      uint2 w;
+      __builtin_memcpy(&w, o4, 8);
+      *reinterpret_cast<uint2*>(op + 16 * k) = w;
+    }
+  };
+  if constexpr (ROWS == 16) {
+    // lane (row lr, quarter lh) holds channels 16 ct + 4 lh + (0..3)
+    store(O, 8, 4 * lh);
+  } else {
+    // it holds its quarter's share of the sum over positions for channels 16 ct + 4 (lr / 4) + (0..3) of row lr % 4; the
+    // quarters exchange halves twice, and quarter lh is left with channel tiles 2 lh and 2 lh + 1
+    f32x4 half[4], own[2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float lo = O[k][i], hi = O[4 + k][i];
+        half[k][i] = (lh & 2 ? hi : lo) + __shfl_xor(lh & 2 ? lo : hi, 32);
+      }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float lo = half[k][i], hi = half[2 + k][i];
+        own[k][i] = (lh & 1 ? hi : lo) + __shfl_xor(lh & 1 ? lo : hi, 16);
+      }
+    store(own, 2, 32 * lh + 4 * (lr >> 2));
   }
 }
 
@@ -244,15 +259,23 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
 flp_status flp_launch_attn_decode(int dtype, const FlpAttnArgs& a, const FlpAttnUnit* units_dev, int32_t n_units,
                                   hipStream_t stream) {
   if (n_units <= 0) return FLP_OK;
-  const dim3 grid((unsigned)n_units, (unsigned)((a.n_kv + 3) / 4));
-  if (dtype == FLP_F16)
-    hipLaunchKernelGGL((attn_decode_kernel<DF16>), grid, dim3(256), 0, stream, a, units_dev);
-  else if (dtype == FLP_BF16)
-    hipLaunchKernelGGL((attn_decode_kernel<DBF16>), grid, dim3(256), 0, stream, a, units_dev);
-  else {
+  if (dtype != FLP_F16 && dtype != FLP_BF16) {
     flp_set_error("attention (decode path): dtype %d not supported", dtype);
     return FLP_ENOTSUP;
   }
+  const dim3 grid((unsigned)n_units, (unsigned)((a.n_kv + 3) / 4));
+  const int G = a.n_h / a.n_kv;
+  const auto launch = [&](auto m) {
+    typedef decltype(m) M;
+    if (G <= 4)
+      hipLaunchKernelGGL((attn_decode_kernel<M, 4>), grid, dim3(256), 0, stream, a, units_dev);
+    else
+      hipLaunchKernelGGL((attn_decode_kernel<M, 16>), grid, dim3(256), 0, stream, a, units_dev);
+  };
+  if (dtype == FLP_F16)
+    launch(DF16{});
+  else
+    launch(DBF16{});
   FLP_TRY_HIP(hipGetLastError());
   return FLP_OK;
 }

@@ -538,6 +538,8 @@ def test_split_kv_for_few_long_sequences(dtype, heads, kv, d, seqs, prefix, new)
     ("bf16", 16, 32, 2, (1, 33, 255, 256, 257, 511, 513)),      # 16 rows per kv head, around one piece and two
     ("f16", 32, 15, 5, (16, 17, 32, 47, 48, 65, 300, 1100)),    # 3 rows per kv head, blocks of 32, kv heads not a multiple of 4
     ("bf16", 32, 16, 2, (31, 64, 769, 1025, 2047)),
+    ("bf16", 16, 8, 2, (7, 300, 513)),                          # 4 and 5 rows per kv head: both sides of the narrow form
+    ("f16", 32, 20, 4, (33, 600)),
     ("f16", 16, 34, 2, (5, 40, 700)),                           # 17 rows per kv head: past what one wave holds
 ])
 def test_single_token_attention_at_the_edges_of_groups_tiles_and_pieces(dtype, bt, heads, kv, ctx):
@@ -578,9 +580,86 @@ def test_single_token_attention_at_the_edges_of_groups_tiles_and_pieces(dtype, b
         inf = torch.isinf(want)
         assert torch.equal(got[i][inf], want[inf]) and int(inf.sum()) == (G if i == len(ctx) - 1 else 0)
         err = (got[i] - want)[~inf].abs()
-        # the result's own rounding (2^-11 or 2^-8 of it) plus 32-bit sums and weights of at most 2^-16 of sum w |v| off
+        # the result's own rounding (2^-11 or 2^-8 of it) plus the errors of 32-bit weights and sums over up to 2^11 positions
         bound = (2.0 ** -11 if dtype == "f16" else 2.0 ** -8) * want.abs() + 2.0 ** -15 * torch.einsum("hc,hcd->hd", w, v.abs())
         assert bool((err <= bound[~inf] + 1e-7).all()), (c, float(err.max()))
+
+
+def _single_tokens(dtype, ctx, q, K, V):
+    """Attention of one new token per sequence of `ctx` positions: q [seqs, heads, d], K and V [seqs, heads, ctx, d] in
+    the pool's type.  Returns the result and, in fp64, the weights' sum with V and with |V|."""
+    n, heads, d = q.shape
+    bt = 16
+    nb = (ctx + bt - 1) // bt
+    pad = torch.zeros((n, heads, nb * bt - ctx, d), dtype=K.dtype)
+    kb, vb = (torch.cat([t, pad], 2).reshape(n, heads, nb, bt, d).permute(0, 2, 1, 3, 4) for t in (K, V))
+    dev = torch.cat([kb.reshape(n * nb, -1), vb.transpose(3, 4).reshape(n * nb, -1)], 1).contiguous().cuda()
+    pool = flpool.Pool(dtype, heads, d, n * nb, 0, block_tokens=bt, dev=dev)
+    out = torch.empty_like(q, device="cuda")
+    tables = torch.arange(n * nb, dtype=torch.int32).reshape(n, nb).cuda()
+    pool.paged_prefix_attention(q.cuda(), out, np.arange(n + 1, dtype=np.int32), np.full(n, ctx - 1, np.int32), tables, heads)
+    got = out.cpu().double()
+    pool.close()
+    w = torch.softmax((K.double() * q.double()[:, :, None]).sum(3) / d ** 0.5, 2)[..., None]
+    return got, (w * V.double()).sum(2), (w * V.double().abs()).sum(2)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("drop", [0.3, 12.0, 24.0])
+def test_single_token_weights_keep_32_bits(dtype, drop):
+    """Four positions of weights 1 : 2^-drop : almost the same : 0 where the second and third have opposite V: the sum
+    shows their difference, and with it every bit of the weights, above the rounding of the result."""
+    tt = torch.float16 if dtype == "f16" else torch.bfloat16
+    n, heads, d = 16, 32, 128
+    g = torch.Generator().manual_seed(int(drop) + 3)
+    q = (0.5 + torch.rand((n, heads, d), generator=g)).to(tt)
+    K = torch.zeros((n, heads, 4, d), dtype=tt)
+    ch = [5, 40, 77, 126]                                   # one channel in every 32: exact products, three additions
+    K[:, :, 1, ch] = (-drop * np.log(2) * d ** 0.5 / 4 / q[:, :, ch].float()).to(tt)
+    K[:, :, 2] = K[:, :, 1]
+    K[:, :, 2, 5] = (K[:, :, 1, 5].view(torch.int16) + 1).view(tt)
+    K[:, :, 3, ch] = (-200 * np.log(2) * d ** 0.5 / 4 / q[:, :, ch].float()).to(tt)
+    V = torch.zeros((n, heads, 4, d), dtype=tt)
+    big = (40000.0 if drop > 1 else 1.0) * (1 + torch.rand((n, heads, d), generator=g) / 2)
+    V[:, :, 1], V[:, :, 2] = big.to(tt), -big.to(tt)
+    got, want, size = _single_tokens(dtype, 4, q, K, V)
+    # a weight: its exponent (a few roundings of a number of about drop) and its own two roundings; the sum: two additions
+    rel = (4 + 8 * drop) * 2.0 ** -24
+    bound = (2.0 ** -11 if dtype == "f16" else 2.0 ** -8) * want.abs() + rel * size + (2.0 ** -25 if dtype == "f16" else 0)
+    worst = float(((got - want).abs() / bound).max())
+    assert worst <= 1, worst
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("ctx", [20, 700])
+def test_single_tokens_see_an_infinite_v_at_any_weight(dtype, ctx):
+    """An infinite V makes its channel infinite as long as its weight is not zero in 32 bits, however small it is; the
+    other channels and heads keep finite results."""
+    tt = torch.float16 if dtype == "f16" else torch.bfloat16
+    heads, d = 8, 128
+    drops = [0.0, 20.0, 30.0, 40.0, 60.0, 100.0]            # the weight of position 7 in powers of two below the largest
+    g = torch.Generator().manual_seed(5)
+    q = torch.ones((len(drops), heads, d), dtype=tt)
+    K = torch.zeros((len(drops), heads, ctx, d), dtype=tt)
+    V = torch.randn((len(drops), heads, ctx, d), generator=g).to(tt)
+    for i, drop in enumerate(drops):
+        K[i, :, 7] = -drop * np.log(2) * d ** 0.5 / d
+        V[i, 3, 7, 11], V[i, 5, 7, 100] = float("inf"), -float("inf")
+    got, want, size = _single_tokens(dtype, ctx, q, K, V)
+    assert torch.equal(torch.isinf(want), torch.isinf(got)) and int(torch.isinf(got).sum()) == 2 * len(drops)
+    assert torch.equal(got[torch.isinf(got)], want[torch.isinf(want)])
+    fin = ~torch.isinf(want)
+    assert float(((got - want).abs() / (size + 1e-3))[fin].max()) < (2.0 ** -10 if dtype == "f16" else 2.0 ** -7)
+
+
+def test_single_tokens_of_large_bfloat16_values_stay_finite():
+    """V of up to 2^120: the weighted sum of 64 of them is below the largest 32-bit number, so the result is finite."""
+    g = torch.Generator().manual_seed(6)
+    q = torch.randn((3, 8, 128), generator=g).to(torch.bfloat16)
+    K = torch.randn((3, 8, 64, 128), generator=g).to(torch.bfloat16)
+    V = (torch.randn((3, 8, 64, 128), generator=g) * 2.0 ** 118).to(torch.bfloat16)
+    got, want, size = _single_tokens("bf16", 64, q, K, V)
+    assert bool(torch.isfinite(got).all()) and bool(((got - want).abs() <= 2.0 ** -7 * size).all())
 
 
 @pytest.mark.parametrize("T", [1, 31, 33, 127, 129, 255, 257, 513, 1025, 2049])
