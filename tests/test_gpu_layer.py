@@ -213,6 +213,47 @@ def test_layer_forward_matches_composed_oracle(name):
         assert np.abs(a[m] - b[m]).max() <= 4 * ULP[cfg.dtype] * max(1.0, np.abs(b[m]).max())
 
 
+def test_an_adapter_s_infinities_stay_with_its_tokens_in_the_gated_pair():
+    """Infinities and NaN in one adapter's B of gate and up: the rows of sequences with other adapters come out as before, bit
+    for bit (the branches of both are added inside the gated pass; sequences meet inside its tiles)."""
+    import torch
+    cfg = LAYER_CASES["f16_all_lora_inside_gemm"]()
+    step = wl.make_step(cfg)
+    T = step.n_tokens
+    dev0 = resident_pool(step)
+    bad = int(step.seq_adapter[len(step.seq_adapter) // 2])
+    poisoned = dev0.copy()
+    for p in ("gate", "up"):
+        pr = step.proj[p]
+        rpb = cfg.block_elems // pr.d_out
+        for row in range(int(pr.b_row_base[bad]), int(pr.b_row_base[bad]) + int(step.rank[bad])):
+            at = row % rpb * pr.d_out
+            poisoned[step.lora_tables[pr.b_tab_off[bad] + row // rpb], at:at + pr.d_out] = wl.quantize(
+                np.array([np.inf, np.nan], np.float32), cfg.dtype)[row % 2]
+    W = make_weights(cfg, np.random.default_rng(7))
+    h0_st, _ = lo.round_store(np.random.default_rng(8).normal(0, 1, (T, cfg.hidden)), cfg.dtype)
+    pos = np.concatenate([step.prefix_len[i] + np.arange(step.cu_new[i + 1] - step.cu_new[i])
+                          for i in range(cfg.n_seqs)]).astype(np.int32)
+    Wd = {k: to_dev(v) for k, v in W.items()}
+    out = []
+    for img in (dev0, poisoned):
+        g = GpuStep(step, img, np.zeros((1, cfg.block_elems), dev0.dtype))
+        layer = fllayer.Layer(g.pool, cfg.hidden, cfg.n_q_heads, cfg.mlp_dim, Wd)
+        batch = fllayer.Batch(step.cu_new, step.prefix_len, to_dev(pos), g.kv_tables, g.token_adapter, g.rank, g.scale,
+                              g.lora_tables, g.proj, n_adapters=len(step.rank), max_rank=int(step.rank.max()),
+                              max_blocks_per_seq=step.kv_tables.shape[1])
+        nbytes = layer.scratch_bytes(T)
+        scratch = torch.zeros(nbytes + 256, dtype=torch.uint8, device="cuda")
+        h = to_dev(h0_st)
+        layer.forward(batch, h, (scratch.data_ptr() + 255) & ~255, nbytes)
+        torch.cuda.synchronize()
+        out.append(lo.load(to_np(h, h0_st.dtype), cfg.dtype))
+    others = step.token_adapter != bad
+    assert others.any() and np.isfinite(out[0]).all()
+    assert np.array_equal(out[1][others], out[0][others])
+    assert not np.isfinite(out[1][~others]).all(1).any()
+
+
 def test_two_layer_stack_with_per_layer_pools():
     """Two layers, each with its own pool (the same block ids and tables in both) and its own weights: the second
     layer's input is the first one's residual stream; each layer appends its K/V to its own pool."""

@@ -662,6 +662,74 @@ def test_single_tokens_of_large_bfloat16_values_stay_finite():
     assert bool(torch.isfinite(got).all()) and bool(((got - want).abs() <= 2.0 ** -7 * size).all())
 
 
+def _lora_call(dtype, T, d_in, widths, adapters, ranks, seed, poison=None):
+    """x, dense bases and LoRA pages of adapters with `ranks`, tokens drawn from `adapters` (-1: none); `poison`: an adapter
+    whose B holds infinities and NaN.  Returns the call's results and its reference in fp64."""
+    tt = torch.float16 if dtype == "f16" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rnd = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(tt)
+    n_ad, E = len(ranks), 2 * 16 * 8 * 128
+    pages, tab, place = [], [], []
+    for w in widths:
+        pl = {k: np.zeros(n_ad, np.int32) for k in ("a_tab_off", "a_row_base", "b_tab_off", "b_row_base")}
+        mats = []
+        for a, r in enumerate(ranks):
+            A, B = rnd((r, d_in), d_in ** -0.5), rnd((r, w), 0.3)
+            if a == poison:
+                B[0, ::3], B[r - 1, 1::3] = float("inf"), float("nan")
+            for key, m in (("a", A), ("b", B)):
+                rpb = E // m.shape[1]
+                pl[key + "_tab_off"][a] = len(tab)
+                for lo in range(0, r, rpb):
+                    blk = torch.full((E,), float("nan"), dtype=tt, device="cuda")
+                    part = m[lo:lo + rpb].reshape(-1)
+                    blk[:part.numel()] = part
+                    tab.append(len(pages))
+                    pages.append(blk)
+            mats.append((A, B))
+        place.append((pl, mats))
+    pool = flpool.Pool(dtype, 8, 128, len(pages), 0, block_tokens=16, dev=torch.stack(pages).contiguous())
+    x, w = rnd((T, d_in), 1.0), [rnd((n, d_in), d_in ** -0.5) for n in widths]
+    ta = torch.from_numpy(np.random.default_rng(seed).choice(np.asarray(adapters, np.int32), T)).cuda()
+    rank = torch.tensor(ranks, dtype=torch.int32, device="cuda")
+    scale = torch.linspace(0.5, 1.5, n_ad, device="cuda")
+    y = [torch.full((T, n), float("nan"), dtype=tt, device="cuda") for n in widths]
+    up = lambda pl: {k: torch.from_numpy(v).cuda() for k, v in pl.items()}
+    projs = [dict(y=yi, d_out=n, w_base=wi, w_base_layout=1, **up(pl)) for yi, n, wi, (pl, _) in zip(y, widths, w, place)]
+    pool.lora_apply_paged(x, ta, rank, scale, torch.tensor(tab, dtype=torch.int32, device="cuda"), projs, n_tokens=T, d_in=d_in,
+                          n_adapters=n_ad, max_rank=max(ranks))
+    want, size = [], []
+    for wi, (_, mats) in zip(w, place):
+        r, m = x.double() @ wi.double().T, x.double().abs() @ wi.double().abs().T
+        for a, (A, B) in enumerate(mats):
+            sel = ta == a
+            v = float(scale[a]) * x[sel].double() @ A.double().T
+            r[sel] += v @ B.double()
+            m[sel] += v.abs() @ B.double().abs()
+        want.append(r)
+        size.append(m)
+    torch.cuda.synchronize()
+    pool.close()
+    return ta, y, want, size
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("T,widths", [(2100, (1024, 1024, 1024)),       # three outputs, 68 tiles of 256 x 128 each
+                                      (2049, (2048,)), (4100, (4096,)),  # one output: few tiles and many
+                                      (1500, (512,))])                   # outside the fused path
+def test_an_adapter_s_infinities_stay_with_its_tokens(dtype, T, widths):
+    """Adapters mixed token by token, one of them with infinities and NaN in its B: every other token's result is what
+    it is without that adapter."""
+    ta, y, want, size = _lora_call(dtype, T, 512, widths, [-1, 0, 1, 2, 3], [16, 8, 64, 40], T, poison=1)
+    ok = ta != 1
+    for yi, wi, si in zip(y, want, size):
+        assert bool(torch.isfinite(yi[ok]).all())
+        assert not bool(torch.isfinite(yi[~ok]).all(1).any())
+        # the result's rounding; v as value and remainder (2^-16 of it in bf16); 32-bit sums of 512 and 64 terms
+        bound = (2.0 ** -11 if dtype == "f16" else 2.0 ** -8) * wi[ok].abs() + 2.0 ** -15 * si[ok] + 1e-7
+        assert bool(((yi[ok].double() - wi[ok]).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("T", [1, 31, 33, 127, 129, 255, 257, 513, 1025, 2049])
 @pytest.mark.parametrize("dtype,d_in,widths", [
     ("f16", 64, (64, 32, 40)),                 # one step of the contraction, widths that no tile divides
