@@ -320,6 +320,12 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
   }
   const int32_t T = b->n_tokens;
   if (T == 0) return FLP_OK;
+  // the direct global-to-LDS loads of the 16-bit products drop the low bits of a misaligned address without an error
+  for (const void* m : {w->wq, w->wk, w->wv, w->wo, w->w_gate, w->w_up, w->w_down})
+    if (p->elem_bytes == 2 && ((uintptr_t)m & 15)) {
+      flp_set_error("fll_layer_forward: a weight matrix is not 16-byte aligned");
+      return FLP_EINVAL;
+    }
   const Scratch s = layout(p, c, T);
   if (((uintptr_t)scratch & 255) || scratch_bytes < (int64_t)s.total) {
     flp_set_error("fll_layer_forward: scratch misaligned or smaller than %lld bytes", (long long)s.total);

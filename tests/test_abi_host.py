@@ -65,6 +65,25 @@ def test_layer_header_symbols_and_structs():
     assert lib.fll_rmsnorm(1, buf.ctypes.data, buf.ctypes.data, buf.ctypes.data, 0, 64, C.c_float(1e-5), None) == flpool.FLP_OK
 
 
+def test_layer_refuses_misaligned_weight_matrices():
+    """16-bit weight matrices have to be 16-byte aligned, also where no LoRA branch is on the projection: refused before
+    anything is enqueued (with aligned ones the call gets as far as the scratch size, which is zero here)."""
+    from paper_2505_03756_amd import fllayer
+    base = np.zeros(4096, np.uint8)
+    at = (base.ctypes.data + 255) & ~255
+    region = np.zeros(2 * 2 * 16 * 2 * 64 * 2 + 256, np.uint8)
+    pool = flpool.Pool("f16", 2, 64, 2, 0, dev=(region.ctypes.data + 255) & ~255)
+    batch = fllayer.Batch(np.array([0, 1], np.int32), np.zeros(1, np.int32), at, at, at, at, at, at, {}, 0, 8, 1)
+    names = ("q", "k", "v", "o", "gate", "up", "down")
+    for bad in (None,) + names:
+        w = {n: at + (8 if n == bad else 0) for n in names + ("in_norm", "post_norm")}
+        layer = fllayer.Layer(pool, 128, 2, 256, w)
+        with pytest.raises(flpool.FlpError) as e:
+            layer.forward(batch, at, at, 0, stream=0)
+        assert e.value.code == flpool.FLP_EINVAL and ("weight matrix" if bad else "scratch") in str(e.value)
+    pool.close()
+
+
 def test_struct_sizes_match_header_layout():
     # natural alignment of the C structs in include/flpool.h
     assert C.sizeof(flpool.PoolConfig) == 48
