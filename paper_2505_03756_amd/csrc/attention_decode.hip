@@ -12,22 +12,29 @@
 // keys fed in the order key(m) = 8 (m / 4) + 4 t + m % 4 for row m of instruction t, the 8 consecutive positions
 // 8 (l / 16) ... + 7, which are also the positions of its 16-byte run of the transposed V of a pool block.
 //
-// O^T = V^T P^T takes 32-bit instructions: weights and sums are fp32 and V is widened, so an element of V contributes
-// exactly what an fp32 multiply-add gives (infinities and the largest bf16 values included).  A 16-bit instruction
-// would need the weights in pieces: value and remainder keep 16 bits of them in bf16, fewer still of small ones in
-// fp16, where the value of a weight below 2^-25 is zero.  Element e of the runs goes into instruction e, with weight e of
-// every lane:
-//   up to 4 heads per kv head   4x4x1: sixteen blocks, each four channels of one position times four rows; column
-//                               l % 16 holds row l % 4.  The quarters of the wave sum different positions and are
-//                               added at the end.  A quarter of the matrix time of the other form.
-//   up to 16                    16x16x4: 16 channels times 16 rows over the wave's four positions; the rows past the last
-//                               head repeat it.
-// Measured, whole steps on MI355X: 256 sequences of 512-4096 positions, 32 / 32 heads, 9.8 GB of K/V: 1872 us (16x16x4
-// there: 1903; 16-bit value and remainder: 1864; a wave per query head on the vector units, nothing loaded ahead: 1941);
-// layer with 200 decode tokens, 32 / 32 heads: 1046 us (1064, 1045, 1092); 6 sequences of 8-16 k positions, 64 / 8 heads:
-// 143 us (16-bit: 137; wave per query head, K/V re-read for each of 8 heads: 234).  There two sets of 4x4x1 accumulators
-// (q in LDS, 256 registers) took 143 us as well, two waves of four rows each 145.
+// O^T = V^T P^T takes fp32 weights and sums:
+//   bf16   three 16x16x32 instructions per weight: a weight is exactly the sum of three bf16 pieces (value, remainder,
+//          remainder of that; 8 bits each) and a product of two bf16 numbers is exact in fp32.  Taken times 2^16, a
+//          weight keeps its last piece a normal number down to 2^-126 of the largest one.  What the pieces cannot
+//          express is an infinite or overflowing product (0 x inf, inf - inf): a wave whose sums are not all finite
+//          walks its piece of the context again with the 32-bit instructions below, so infinities and NaN in V
+//          come out as an fp32 multiply-add makes them.
+//   fp16   has no exponents for such pieces (the value of a weight below 2^-25 is zero).  V is widened and element e of the
+//          16-byte runs goes into 32-bit instruction e with weight e of every lane.  Up to 4 heads per kv head 4x4x1:
+//          sixteen blocks, each four channels of one position times four rows; column l % 16 holds row l % 4, and the
+//          quarters of the wave sum different positions and are added at the end.  Up to 16 heads 16x16x4: 16 channels
+//          times 16 rows over four positions, twice the matrix time (0.9 us per 32 positions of a wave).
+// The rows past the last head repeat it.
+//
+// Measured, whole steps on MI355X.  Before this kernel (a wave per query head on the vector units, fp32, nothing loaded
+// ahead), then with bf16 weights as value and remainder only (16 bits of them), 16x16x4, 4x4x1, three pieces:
+//   256 sequences of 512-4096 positions, 32 / 32 heads, 9.8 GB of K/V    1941   1865   1903   1872   1867 us
+//   6 sequences of 8-16 k positions, 64 / 8 heads                         234    137    143     -     138 us
+//   layer with 200 decode tokens, 32 / 32 heads                          1092   1047   1064   1046   1049 us
+// 4x4x1 in two sets of accumulators for 8 heads (q in LDS, 256 registers) took 143 us as well, two waves of four rows 145.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "flp_internal.h"
 #include "flp_types.h"
@@ -36,6 +43,8 @@ namespace {
 
 constexpr int D = 128;
 constexpr int BT = 16;
+constexpr int kChains = 4;                             // independent sums that hide a matrix instruction's latency
+constexpr float kScale = 65536.f;                      // of weights in pieces
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h16x8 __attribute__((ext_vector_type(8)));
@@ -43,7 +52,9 @@ typedef __bf16 b16x8 __attribute__((ext_vector_type(8)));
 
 struct DF16 {
   typedef h16x8 vec;
+  typedef _Float16 el;
   typedef F16 S;
+  static constexpr bool kPieces = false;               // weights in 16-bit pieces
   static __device__ __forceinline__ f32x4 mfma(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
   }
@@ -53,7 +64,9 @@ struct DF16 {
 };
 struct DBF16 {
   typedef b16x8 vec;
+  typedef __bf16 el;
   typedef BF16 S;
+  static constexpr bool kPieces = true;
   static __device__ __forceinline__ f32x4 mfma(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
@@ -73,7 +86,7 @@ struct Tile {                    // K and V of 32 positions
   u32x4 k[2][4], v[8];
 };
 
-// ROWS: 4 or 16, the next one from the query heads per kv head on
+// ROWS: how many rows a wave has, at least the query heads per kv head: 16, or 4 for the fp16 form with 4x4x1
 template <typename M, int ROWS>
 __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, const FlpAttnUnit* __restrict__ units) {
   typedef typename M::vec vec;
@@ -122,11 +135,10 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
   };
 
   f32x4 O[8];
-#pragma unroll
-  for (int ct = 0; ct < 8; ++ct) O[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f;                        // m: running maximum; l: this lane's share of the sum
+  float m, l;                                          // m: running maximum; l: this lane's share of the sum
 
-  auto multiply = [&](Tile& T, int tile) {
+  auto multiply = [&](Tile& T, int tile, auto pieces) {
+    constexpr bool PIECES = decltype(pieces)::value;
     f32x4 s[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -165,16 +177,47 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
 #pragma unroll
         for (int i = 0; i < 4; ++i) O[ct][i] *= alpha;
     }
+    // a tile's sums are taken by themselves, its small terms first, and then added: one rounding of the running sum per tile
+    float w[8], lw = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float w = exp2f(p[e] - m);
-      l += w;
+      w[e] = exp2f(p[e] - m) * (PIECES ? kScale : 1.f);
+      lw += w[e];
+    }
+    l += lw;
+    vec piece[3];                                      // PIECES: the weights are their sum
+    if constexpr (PIECES)
 #pragma unroll
-      for (int ct = 0; ct < 8; ++ct) {
-        const float v = M::widen(T.v[ct][e >> 1], e & 1);
-        O[ct] = ROWS == 16 ? __builtin_amdgcn_mfma_f32_16x16x4f32(v, w, O[ct], 0, 0, 0)
-                           : __builtin_amdgcn_mfma_f32_4x4x1f32(v, w, O[ct], 0, 0, 0);
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          piece[i][e] = (typename M::el)w[e];
+          w[e] -= (float)piece[i][e];
+        }
+#pragma unroll
+    for (int ct0 = 0; ct0 < 8; ct0 += kChains) {
+      f32x4 sum[kChains];
+#pragma unroll
+      for (int k = 0; k < kChains; ++k) sum[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (PIECES) {
+#pragma unroll
+        for (int i = 2; i >= 0; --i)
+#pragma unroll
+          for (int k = 0; k < kChains; ++k) sum[k] = M::mfma(as_vec<vec>(T.v[ct0 + k]), piece[i], sum[k]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+          for (int k = 0; k < kChains; ++k) {
+            const float v = M::widen(T.v[ct0 + k][e >> 1], e & 1);
+            sum[k] = ROWS == 16 ? __builtin_amdgcn_mfma_f32_16x16x4f32(v, w[e], sum[k], 0, 0, 0)
+                                : __builtin_amdgcn_mfma_f32_4x4x1f32(v, w[e], sum[k], 0, 0, 0);
+          }
       }
+#pragma unroll
+      for (int k = 0; k < kChains; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) O[ct0 + k][i] += sum[k][i];
     }
   };
 
@@ -182,24 +225,43 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
   // that waiting for them leaves those in flight.
   const int n_tiles = (g_hi - g_lo + 1) >> 1;
   auto id = [&](int tile, int sel) { return table[group(tile, sel) >> hsh]; };
-  int32_t idk = id(0, ksel), idv = id(0, vsel);
-  int32_t idk1 = id(1, ksel), idv1 = id(1, vsel);
-  Tile T0, T1;
-  load(T0, 0, idk, idv);
-  for (int tile = 0; tile < n_tiles; tile += 2) {
-    idk = id(tile + 2, ksel);
-    idv = id(tile + 2, vsel);
-    load(T1, tile + 1, idk1, idv1);                    // past the end: the last group again (in cache), not used
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(T0, tile);
-    __builtin_amdgcn_sched_barrier(0);
-    if (tile + 1 >= n_tiles) break;
-    idk1 = id(tile + 3, ksel);
-    idv1 = id(tile + 3, vsel);
-    load(T0, tile + 2, idk, idv);
-    __builtin_amdgcn_sched_barrier(0);
-    multiply(T1, tile + 1);
-    __builtin_amdgcn_sched_barrier(0);
+  auto walk = [&](auto pieces) {
+#pragma unroll
+    for (int ct = 0; ct < 8; ++ct) O[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m = -INFINITY;
+    l = 0.f;
+    int32_t idk = id(0, ksel), idv = id(0, vsel);
+    int32_t idk1 = id(1, ksel), idv1 = id(1, vsel);
+    Tile T0, T1;
+    load(T0, 0, idk, idv);
+    for (int tile = 0; tile < n_tiles; tile += 2) {
+      idk = id(tile + 2, ksel);
+      idv = id(tile + 2, vsel);
+      load(T1, tile + 1, idk1, idv1);                  // past the end: the last group again (in cache), not used
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(T0, tile, pieces);
+      __builtin_amdgcn_sched_barrier(0);
+      if (tile + 1 >= n_tiles) break;
+      idk1 = id(tile + 3, ksel);
+      idv1 = id(tile + 3, vsel);
+      load(T0, tile + 2, idk, idv);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(T1, tile + 1, pieces);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  walk(std::bool_constant<M::kPieces>{});
+  if constexpr (M::kPieces) {                          // an infinite V never leaves a finite sum: even 0 x inf is NaN
+    bool finite = true;
+    l *= 1.f / kScale;
+#pragma unroll
+    for (int ct = 0; ct < 8; ++ct)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        finite = finite && fabsf(O[ct][i]) < INFINITY;
+        O[ct][i] *= 1.f / kScale;
+      }
+    if (__builtin_amdgcn_ballot_w64(!finite)) walk(std::false_type{});
   }
 
   l += __shfl_xor(l, 16);
@@ -267,10 +329,12 @@ flp_status flp_launch_attn_decode(int dtype, const FlpAttnArgs& a, const FlpAttn
   const int G = a.n_h / a.n_kv;
   const auto launch = [&](auto m) {
     typedef decltype(m) M;
-    if (G <= 4)
-      hipLaunchKernelGGL((attn_decode_kernel<M, 4>), grid, dim3(256), 0, stream, a, units_dev);
-    else
-      hipLaunchKernelGGL((attn_decode_kernel<M, 16>), grid, dim3(256), 0, stream, a, units_dev);
+    if constexpr (!M::kPieces)
+      if (G <= 4) {
+        hipLaunchKernelGGL((attn_decode_kernel<M, 4>), grid, dim3(256), 0, stream, a, units_dev);
+        return;
+      }
+    hipLaunchKernelGGL((attn_decode_kernel<M, 16>), grid, dim3(256), 0, stream, a, units_dev);
   };
   if (dtype == FLP_F16)
     launch(DF16{});
