@@ -155,6 +155,10 @@ LAYER_CASES = {
     "f16_all_lora_inside_gemm": lambda: layer_cfg("f16", hidden=2048, n_q_heads=16, n_kv_heads=16, n_seqs=24,
                                                   prefix_range=(0, 200), new_range=(125, 150), mlp_dim=3136,
                                                   n_dev_blocks=3500, ranks=(8, 16, 32), seed=51),
+    # sequences of 11-14 tokens with 40 adapters: more adapters in a tile than the epilogue's tables hold at a time
+    "f16_many_adapters_inside_gemm": lambda: layer_cfg("f16", hidden=2048, n_q_heads=16, n_kv_heads=16, n_seqs=200,
+                                                       prefix_range=(0, 40), new_range=(11, 14), mlp_dim=3136,
+                                                       n_dev_blocks=3500, n_adapters=40, ranks=(8, 16, 32), seed=52),
     "bf16_fused_gate_up": lambda: layer_cfg("bf16", projections=("q", "k", "v", "o"), n_seqs=10, prefix_range=(0, 300),
                                             new_range=(110, 160), mlp_dim=3136, n_dev_blocks=2500, seed=48),
 }
@@ -211,6 +215,64 @@ def test_layer_forward_matches_composed_oracle(name):
         m = np.isfinite(a) & np.isfinite(b)
         assert (np.isfinite(a) == np.isfinite(b)).all()
         assert np.abs(a[m] - b[m]).max() <= 4 * ULP[cfg.dtype] * max(1.0, np.abs(b[m]).max())
+
+
+@pytest.mark.parametrize("T,H,M,plan", [
+    (1, 2048, 64, ("64x32", 8)), (64, 4096, 3136, ("64x32", 2)), (255, 1024, 3136, ("128x64", 1)), (65, 4096, 2112, ("128x128", 6)),
+    (33, 4096, 3136, ("256x128", 8)), (33, 4096, 11008, ("256x128", 2)), (128, 4096, 11008, ("256x128", 2)),
+    (257, 1024, 11008, ("256x256", 1)), (129, 8192, 11008, ("256x256", 2)),
+])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_gated_pair_without_lora(dtype, T, H, M, plan):
+    """gate, up and silu(g) * u as one step, on every tile with and without slices: g and u are rounded, then their product.
+    The layer shows it: no attention output (wo = 0), a down matrix that selects features, and a small residual stream."""
+    import torch
+    from helpers import dense_plan
+    from paper_2505_03756_amd import flpool
+    assert dense_plan(T, H, (2 * M,)) == plan
+    tt = torch.float16 if dtype == "f16" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(T + M)
+    rnd = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(tt)
+    d, n_blk = 128, (T + 15) // 16
+    pool = flpool.Pool(dtype, 1, d, n_blk, 0, block_tokens=16)
+    n = min(H, M)
+    sel = torch.randperm(M, generator=g, device="cuda")[:n]
+    W = {p: rnd((d, H), H ** -0.5) for p in "qkv"}
+    W.update(o=torch.zeros((H, d), dtype=tt, device="cuda"), gate=rnd((M, H), H ** -0.5), up=rnd((M, H), H ** -0.5),
+             down=torch.zeros((H, M), dtype=tt, device="cuda"), in_norm=rnd((H,), 0.1) + 1, post_norm=rnd((H,), 0.1) + 1)
+    W["down"][torch.arange(n, device="cuda"), sel] = 1
+    h0 = rnd((T, H), 2.0 ** -10)
+    n2 = torch.empty_like(h0)
+    fllayer.rmsnorm(dtype, h0, W["post_norm"], n2, T, H, eps=1e-20)
+    layer = fllayer.Layer(pool, H, 1, M, W, rms_eps=1e-20)
+    i32 = lambda a: torch.tensor(a, dtype=torch.int32, device="cuda")
+    batch = fllayer.Batch([0, T], [0], torch.arange(T, dtype=torch.int32, device="cuda"), i32([list(range(n_blk))]),
+                          i32([-1] * T), i32([8]), torch.ones(1, device="cuda"), i32([0]), {}, 1, 8, n_blk)
+    nbytes = layer.scratch_bytes(T)
+    scratch = torch.zeros(nbytes + 256, dtype=torch.uint8, device="cuda")
+    h = h0.clone()
+    layer.forward(batch, h, (scratch.data_ptr() + 255) & ~255, nbytes)
+    torch.cuda.synchronize()
+    gate, up = ((n2.double() @ W[p].double().T).to(tt).double() for p in ("gate", "up"))
+    silu = gate * torch.sigmoid(gate)
+    act = (silu * up).to(tt)
+    want = h0.clone()
+    want[:, :n] = (h0[:, :n].float() + act[:, sel].float()).to(tt)
+    got, want = h.double(), want.double()
+    # 32-bit sums near a rounding boundary may round g, u, the product or the result to the neighbour: few do.  Where g or u is
+    # near zero the sums' own error shows instead of a spacing: about 128 additions of numbers up to 2 or so, 2^-24 each and
+    # random, 2^-21 together, five times that over 10^6 entries (|silu'| <= 1.1).
+    ulp, e32 = ULP[dtype], 2.0 ** -19
+    off = torch.zeros_like(got)
+    dg, du = ulp * gate.abs() + e32, ulp * up.abs() + e32
+    off[:, :n] = (1.1 * up.abs() * dg + silu.abs() * du + ulp * act.double().abs())[:, sel] + ulp * want[:, :n].abs() + 2.0 ** -23
+    diff = (got - want).abs()
+    assert bool((diff <= 1.01 * off).all())
+    share = float((diff[:, :n] > 0).double().mean())
+    raw = [n2.double() @ W[p].double().T for p in ("gate", "up")]              # without the rounding of g and u
+    other = (h0[:, :n].float() + (raw[0] * torch.sigmoid(raw[0]) * raw[1]).to(tt)[:, sel].float()).to(tt).double()
+    assert share < 0.02 < 0.1 < float((other != want[:, :n]).double().mean())
+    pool.close()
 
 
 def test_an_adapter_s_infinities_stay_with_its_tokens_in_the_gated_pair():

@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import oracle
-from helpers import TOL, GpuStep, build_pools, close, resident_pool, to_dev, to_np
+from helpers import TOL, GpuStep, build_pools, close, dense_plan, resident_pool, to_dev, to_np
 from paper_2505_03756_amd import flpool
 from paper_2505_03756_amd import workload as wl
 
@@ -664,7 +664,8 @@ def test_single_tokens_of_large_bfloat16_values_stay_finite():
 
 def _lora_call(dtype, T, d_in, widths, adapters, ranks, seed, poison=None):
     """x, dense bases and LoRA pages of adapters with `ranks`, tokens drawn from `adapters` (-1: none); `poison`: an adapter
-    whose B holds infinities and NaN.  Returns the call's results and its reference in fp64."""
+    whose B holds infinities and NaN.  Returns the tokens' adapters, the results, their reference in fp64 and the bound of
+    an entry: its rounding, 32-bit sums of the dense product, v as value and remainder (2^-16 of it in bf16)."""
     tt = torch.float16 if dtype == "f16" else torch.bfloat16
     g = torch.Generator(device="cuda").manual_seed(seed)
     rnd = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(tt)
@@ -698,19 +699,19 @@ def _lora_call(dtype, T, d_in, widths, adapters, ranks, seed, poison=None):
     projs = [dict(y=yi, d_out=n, w_base=wi, w_base_layout=1, **up(pl)) for yi, n, wi, (pl, _) in zip(y, widths, w, place)]
     pool.lora_apply_paged(x, ta, rank, scale, torch.tensor(tab, dtype=torch.int32, device="cuda"), projs, n_tokens=T, d_in=d_in,
                           n_adapters=n_ad, max_rank=max(ranks))
-    want, size = [], []
+    want, bound = [], []
     for wi, (_, mats) in zip(w, place):
-        r, m = x.double() @ wi.double().T, x.double().abs() @ wi.double().abs().T
+        r, m = x.double() @ wi.double().T, 2.0 ** -19 * x.double().abs() @ wi.double().abs().T
         for a, (A, B) in enumerate(mats):
             sel = ta == a
             v = float(scale[a]) * x[sel].double() @ A.double().T
             r[sel] += v @ B.double()
-            m[sel] += v.abs() @ B.double().abs()
+            m[sel] += 2.0 ** -15 * v.abs() @ B.double().abs()
         want.append(r)
-        size.append(m)
+        bound.append((2.0 ** -11 if dtype == "f16" else 2.0 ** -8) * r.abs() + m + 1e-7)
     torch.cuda.synchronize()
     pool.close()
-    return ta, y, want, size
+    return ta, y, want, bound
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
@@ -720,24 +721,53 @@ def _lora_call(dtype, T, d_in, widths, adapters, ranks, seed, poison=None):
 def test_an_adapter_s_infinities_stay_with_its_tokens(dtype, T, widths):
     """Adapters mixed token by token, one of them with infinities and NaN in its B: every other token's result is what
     it is without that adapter."""
-    ta, y, want, size = _lora_call(dtype, T, 512, widths, [-1, 0, 1, 2, 3], [16, 8, 64, 40], T, poison=1)
+    ta, y, want, bound = _lora_call(dtype, T, 512, widths, [-1, 0, 1, 2, 3], [16, 8, 64, 40], T, poison=1)
     ok = ta != 1
-    for yi, wi, si in zip(y, want, size):
+    for yi, wi, bi in zip(y, want, bound):
         assert bool(torch.isfinite(yi[ok]).all())
         assert not bool(torch.isfinite(yi[~ok]).all(1).any())
-        # the result's rounding; v as value and remainder (2^-16 of it in bf16); 32-bit sums of 512 and 64 terms
-        bound = (2.0 ** -11 if dtype == "f16" else 2.0 ** -8) * wi[ok].abs() + 2.0 ** -15 * si[ok] + 1e-7
-        assert bool(((yi[ok].double() - wi[ok]).abs() <= bound).all())
+        assert bool(((yi[ok].double() - wi[ok]).abs() <= bi[ok]).all())
+
+
+@pytest.mark.parametrize("T,d_in,widths,plan", [
+    (1, 1024, (264, 72, 72), ("64x32", 1)), (1, 2048, (72,), ("64x32", 8)), (7, 2048, (264, 72, 72), ("64x32", 8)),
+    (129, 1024, (2056, 4104, 4104), ("128x64", 1)), (33, 4096, (2056, 4104, 4104), ("128x64", 3)), (33, 11008, (2056,), ("128x64", 12)),
+    (129, 1024, (4104, 4104, 4104), ("128x128", 1)), (300, 8192, (264, 72, 72), ("128x128", 16)),
+    (257, 1024, (4104, 4104, 4104), ("256x128", 1)), (33, 8192, (2056, 264, 264), ("256x128", 16)), (33, 8192, (4104,), ("256x128", 12)),
+    (641, 1024, (2056, 4104, 4104), ("256x256", 1)), (129, 8192, (2056, 4104, 4104), ("256x256", 4)), (1000, 8192, (4104,), ("256x256", 3)),
+])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_dense_products_with_adapters_on_every_tile_whole_and_in_slices(dtype, T, d_in, widths, plan):
+    """Each tile with the whole contraction and with slices, with one output and three, remainders in tokens and features;
+    a third of the tokens has no adapter and keeps the rounded product, the others add their branch to the unrounded one."""
+    assert dense_plan(T, d_in, widths, room=60 << 20) == plan
+    ta, y, want, bound = _lora_call(dtype, T, d_in, widths, [-1, 0, 2], [8, 16, 64], T)
+    for yi, wi, bi in zip(y, want, bound):
+        assert bool(((yi.double() - wi).abs() <= bi).all())
+
+
+@pytest.mark.parametrize("T,widths,plan", [(2050, (1088, 320), ("256x128", 1)), (2177, (4032,), ("256x256", 1)),
+                                           (4100, (1088, 1088, 320), ("256x256", 1))])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_branches_inside_the_product_with_many_adapters_and_remainders(dtype, T, widths, plan):
+    """Thirteen adapters mixed token by token: a tile's adapters take two rounds of the epilogue's tables, in the last, partly
+    filled tile as well (of 2, 129 and 4 tokens); widths that are no multiple of the tile."""
+    assert dense_plan(T, 512, widths, large_only=True) == plan
+    ranks = [8, 16, 64, 40, 1, 33, 24, 8, 16, 64, 32, 48, 8]
+    ta, y, want, bound = _lora_call(dtype, T, 512, widths, list(range(-1, 13)), ranks, T)
+    for yi, wi, bi in zip(y, want, bound):
+        assert bool(((yi.double() - wi).abs() <= bi).all())
 
 
 @pytest.mark.parametrize("T", [1, 31, 33, 127, 129, 255, 257, 513, 1025, 2049])
 @pytest.mark.parametrize("dtype,d_in,widths", [
     ("f16", 64, (64, 32, 40)),                 # one step of the contraction, widths that no tile divides
-    ("bf16", 1088, (264, 136, 72)),            # three outputs in one launch, remainders of every tile
+    ("bf16", 1088, (264, 136, 72)),            # three outputs in one launch, remainders in the last tiles
     ("f16", 4096, (4096, 1032)),               # enough contraction for slices at small batches, whole tiles at large ones
 ])
 def test_dense_products_at_the_edges_of_their_tiles(dtype, d_in, widths, T):
-    """Tokens without an adapter keep the dense product, whatever tile and number of slices the batch size selects."""
+    """Tokens without an adapter keep the dense product, over batch sizes around every tile's (the first two sets of widths
+    stay with the smallest tile at all of them, the third has slices at small batches and large tiles at large ones)."""
     tt = torch.float16 if dtype == "f16" else torch.bfloat16
     g = torch.Generator().manual_seed(T + d_in)
     x = torch.randn((T, d_in), generator=g).to(tt)
