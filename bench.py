@@ -19,7 +19,8 @@ A serialised pass (everything on one stream, HIP events between the stages) give
 durations of one batch; the roofline figure of the dominant on-chip kernel comes from HIP events
 around that kernel inside the timed region.
 
-Prints ONE JSON line.
+Prints ONE JSON line of a few kilobytes: the headline's figures and one short entry per further workload.  --record FILE
+writes the whole record there (per-step series, every stage's roofline figures, the sub-records with all their fields).
 """
 import argparse
 import hashlib
@@ -92,6 +93,8 @@ def parse():
                     "stage of one batch of the workload in a loop for SECONDS while rocm-smi samples the shader "
                     "clock, on the pool as drawn and then on a zeroed pool, and print the two rates and clocks")
     ap.add_argument("--seed", type=int, default=None)
+    ap.add_argument("--record", default=None, metavar="FILE", help="write the whole record to FILE (the printed line "
+                    "holds a summary)")
     return ap.parse_args()
 
 
@@ -520,7 +523,9 @@ def run_workload(name, args, headline):
     n_h, n_kv, d = cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim
     st_last = recs[-1]["st"]
     mfma_path = cfg.dtype != "f32" and d == 128 and int(st_last.new_len.max()) * (n_h // n_kv) >= 8
-    kname, ksrc = ("attn_mfma_kernel", "attention_mfma.hip") if mfma_path else ("attn_rows_kernel", "attention.hip")
+    decode_path = cfg.dtype != "f32" and d == 128 and n_h // n_kv <= 16
+    kname, ksrc = (("attn_mfma_kernel", "attention_mfma.hip") if mfma_path else ("attn_decode_kernel", "attention_decode.hip")
+                   if decode_path else ("attn_rows_kernel", "attention.hip"))
     gbps, tflops = a_bytes / (a_ms * 1e6), a_flops / (a_ms * 1e9)
     t_hbm, t_mfma = a_bytes / (HBM_PEAK_GBS * 1e9), a_flops / (MFMA_PEAK_TFLOPS * 1e12)
     traffic = measured_traffic(cfg.name, kname, ksrc) if not b.over and args.swap_frac is None else None
@@ -677,7 +682,25 @@ def main():
             out["sub_records"][name] = rec
     if not args.no_cpu_baseline:
         out["host_logic"] = host_logic()
-    print(json.dumps(out))
+    if args.record:
+        with open(args.record, "w") as f:
+            json.dump(out, f)
+    print(json.dumps(summary(out)))
+
+
+def summary(rec):
+    """What the printed line holds of a run's record.  Its readers keep the last few kilobytes of the output, so the
+    per-step series, the stages' figures and the sub-records' details stay out of it."""
+    keep = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+            "vs_baseline", "dtype", "data", "config", "roofline", "cpu_baseline")
+    out = {k: rec[k] for k in keep if k in rec}
+    out["config"] = {k: v for k, v in rec["config"].items() if k != "trace"}
+    out["config"]["trace"] = {k: v for k, v in rec["config"].get("trace", {}).items() if not k.endswith("_per_step")}
+    if rec.get("sub_records"):
+        out["sub_records"] = {n: {"value": r["value"], "ms_per_step": r["ms_per_step"],
+                                  "roofline": {k: r["roofline"][k] for k in ("bound", "kernel", "frac", "avg_launch_ms")}}
+                              for n, r in rec["sub_records"].items()}
+    return out
 
 
 # ----------------------------------------------------------------------------------------------- side figures
