@@ -276,7 +276,8 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   }
   void* partials = nullptr;
   if (n_merge)
-    FLP_TRY(flp_attn_workspace(p, (size_t)merge_first.back() * b->n_q_heads * (p->cfg.head_dim + 2) * sizeof(float), &partials));
+    FLP_TRY(flp_attn_workspace(p, (size_t)merge_first.back() * b->n_q_heads * (p->cfg.head_dim + 2) * sizeof(float), stream,
+                               &partials));
 
   StagedSeqs st;
   FLP_TRY(stage_seqs(p, b, blob.data(), blob.size(), stream, &st));
@@ -291,6 +292,10 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   flp_status s3 = s1 == FLP_OK ? flp_launch_attn_merge(p->cfg.dtype, p->cfg.head_dim, a, dm, dm + n_merge,
                                                         (int32_t)n_merge, stream) : FLP_OK;
   flp_status s2 = flp_stage_release(st.slot, stream);
+  if (n_merge && s2 == FLP_OK) {
+    p->attn_slot = st.slot;
+    p->attn_stream = stream;
+  }
   return s0 != FLP_OK ? s0 : (s1 != FLP_OK ? s1 : (s3 != FLP_OK ? s3 : s2));
 }
 

@@ -65,6 +65,8 @@ struct flp_pool {
   size_t work_cap = 0;
   void* attn_work = nullptr;      // device workspace of the attention call (split-KV partial results)
   size_t attn_work_cap = 0;
+  FlpStageSlot* attn_slot = nullptr;   // its event follows the last call that used attn_work, which ran on attn_stream
+  hipStream_t attn_stream = nullptr;
   std::vector<void*> retired;     // outgrown workspace buffers, freed with the pool
   mutable std::mutex mu;          // guards the free lists, the staging slots and the workspace
 };
@@ -159,7 +161,9 @@ flp_status flp_launch_attn_decode(int dtype, const FlpAttnArgs& a, const FlpAttn
 // which piece finished first)
 flp_status flp_launch_attn_merge(int dtype, int head_dim, const FlpAttnArgs& a, const int32_t* merge_tok_dev,
                                  const int32_t* merge_first_dev, int32_t n_rows, hipStream_t stream);
-flp_status flp_attn_workspace(flp_pool* pool, size_t bytes, void** out);
+// the workspace of an attention call that splits, for work on `stream`: a call on another stream waits for the one before it
+// (the caller owes no ordering to calls whose sequences are different ones, and cannot see which of them split)
+flp_status flp_attn_workspace(flp_pool* pool, size_t bytes, hipStream_t stream, void** out);
 
 flp_status flp_launch_attn_mfma(int dtype, const FlpAttnArgs& a, const FlpMfmaItem* items_dev, int32_t n_items,
                                 hipStream_t stream);

@@ -216,6 +216,7 @@ flp_status flp_stage_acquire(flp_pool* p, size_t bytes, FlpStageSlot** out) {
     }
     s.in_flight = false;
   }
+  if (p->attn_slot == &s) p->attn_slot = nullptr;        // that call's work is done
   if (s.cap < bytes) {
     // freeing device or pinned memory waits for the whole device, so a slot starts large
     // enough (1 MiB) that ordinary id lists and work lists never make it grow
@@ -265,8 +266,10 @@ flp_status flp_workspace(flp_pool* p, size_t bytes, void** out) {
   return FLP_OK;
 }
 
-flp_status flp_attn_workspace(flp_pool* p, size_t bytes, void** out) {
+flp_status flp_attn_workspace(flp_pool* p, size_t bytes, hipStream_t stream, void** out) {
   FLP_TRY(grow(p, &p->attn_work, &p->attn_work_cap, bytes));
+  if (p->attn_slot && (stream != p->attn_stream || stream == hipStreamPerThread))
+    FLP_TRY_HIP(hipStreamWaitEvent(stream, p->attn_slot->ev, 0));
   *out = p->attn_work;
   return FLP_OK;
 }

@@ -662,6 +662,33 @@ def test_single_tokens_of_large_bfloat16_values_stay_finite():
     assert bool(torch.isfinite(got).all()) and bool(((got - want).abs() <= 2.0 ** -7 * size).all())
 
 
+@pytest.mark.parametrize("dtype,heads,kv", [("bf16", 32, 32), ("f16", 32, 8)])
+def test_split_attention_of_two_streams_over_one_pool(dtype, heads, kv):
+    """Two batches of single tokens over one pool, each on a stream of its own with nothing between them: the pieces of their
+    contexts (both split) do not meet."""
+    d, bt, n, ctx = 128, 16, 80, 1500
+    tt = torch.float16 if dtype == "f16" else torch.bfloat16
+    nb = (ctx + bt - 1) // bt
+    g = torch.Generator(device="cuda").manual_seed(9)
+    dev = torch.empty((2 * n * nb, 2 * bt * kv * d), dtype=tt, device="cuda").normal_(generator=g)
+    pool = flpool.Pool(dtype, kv, d, 2 * n * nb, 0, block_tokens=bt, dev=dev)
+    tables = torch.arange(2 * n * nb, dtype=torch.int32, device="cuda").reshape(2, n, nb)
+    q = torch.randn((2, n, heads, d), generator=g, device="cuda").to(tt)
+    cu, prefix = np.arange(n + 1, dtype=np.int32), np.full(n, ctx - 1, np.int32)
+    run = lambda i, out, stream: pool.paged_prefix_attention(q[i], out, cu, prefix, tables[i], heads, stream=stream)
+    want, got = torch.empty_like(q), torch.empty((6,) + q.shape, dtype=tt, device="cuda")
+    for i in range(2):
+        run(i, want[i], torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for k in range(6):
+        for i in range(2):
+            run(i, got[k, i], streams[i])
+    torch.cuda.synchronize()
+    assert bool((got == want).all())
+    pool.close()
+
+
 def _lora_call(dtype, T, d_in, widths, adapters, ranks, seed, poison=None):
     """x, dense bases and LoRA pages of adapters with `ranks`, tokens drawn from `adapters` (-1: none); `poison`: an adapter
     whose B holds infinities and NaN.  Returns the tokens' adapters, the results, their reference in fp64 and the bound of
