@@ -92,7 +92,8 @@ typedef struct {
 } fll_layer_batch;
 
 /* Bytes of device scratch that fll_layer_forward needs for n_tokens tokens (activations between the
- * steps; the LoRA intermediates live in the pool's own workspace). */
+ * steps; the LoRA intermediates, and the slices of dense products of up to 1024 tokens, live in the
+ * pool's own workspace: calls that use it are ordered with respect to each other like LoRA calls). */
 int64_t fll_layer_scratch_bytes(const flp_pool* pool, const fll_layer_config* cfg, int32_t n_tokens);
 
 /* One decoder layer over the batch, on the pool that holds this layer's KV blocks and LoRA pages:

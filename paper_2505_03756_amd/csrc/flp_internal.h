@@ -67,6 +67,10 @@ struct flp_pool {
   size_t attn_work_cap = 0;
   FlpStageSlot* attn_slot = nullptr;   // its event follows the last call that used attn_work, which ran on attn_stream
   hipStream_t attn_stream = nullptr;
+  void* dense_work = nullptr;          // slices of a layer's dense products without LoRA on more than 1024 tokens
+  size_t dense_work_cap = 0;
+  hipEvent_t dense_ev = nullptr;       // follows the last use of dense_work, which was on dense_stream
+  hipStream_t dense_stream = nullptr;
   std::vector<void*> retired;     // outgrown workspace buffers, freed with the pool
   mutable std::mutex mu;          // guards the free lists, the staging slots and the workspace
 };
@@ -78,6 +82,9 @@ flp_status flp_stage_acquire(flp_pool* pool, size_t bytes, FlpStageSlot** slot);
 flp_status flp_stage_upload(FlpStageSlot* slot, size_t bytes, hipStream_t stream);
 flp_status flp_stage_release(FlpStageSlot* slot, hipStream_t stream);
 flp_status flp_workspace(flp_pool* pool, size_t bytes, void** out);
+// a workspace for slices of dense products that is handed from call to call, also between streams (with the pool's lock held)
+flp_status flp_dense_workspace_acquire(flp_pool* pool, size_t bytes, hipStream_t stream, void** out);
+flp_status flp_dense_workspace_release(flp_pool* pool, hipStream_t stream);
 // the host-side checks of flp_pool_swap_in (src_tier 1) / flp_pool_swap_out (src_tier 0) without enqueuing anything
 flp_status flp_swap_check(flp_pool* pool, int32_t n, const int32_t* src_ids, const int32_t* dst_ids, int src_tier,
                           const char* who);

@@ -274,7 +274,11 @@ bool cfg_ok(const flp_pool* p, const fll_layer_config* c) {
 }
 
 // Dense products alone (gated: the gated-SiLU pair as one output).  Slices of a small batch's contraction live in the
-// pool's workspace (stream order keeps them apart from the LoRA intermediates of the calls before and after).
+// pool's workspace (stream order keeps them apart from the LoRA intermediates of the calls before and after).  Larger
+// batches without LoRA needed no workspace before they were sliced, so calls on several streams owe each other no order:
+// their slices have a workspace of their own that one call hands to the next, for an event per product (products of
+// 100 us and more; the small ones would notice it).
+constexpr int kSharedWorkTokens = 1024;
 flp_status dense_products(flp_pool* p, const void* x, int d_in, int T, int n, FlpGemmOut* out, const int* N, bool gated,
                           hipStream_t stream) {
   if (p->elem_bytes == 4) {
@@ -284,21 +288,28 @@ flp_status dense_products(flp_pool* p, const void* x, int d_in, int T, int n, Fl
     return FLP_OK;
   }
   const FlpGemmPlan plan = flp_gemm_plan(T, d_in, n, N, 0, kLayerSliceBytes);
+  const bool own = plan.splits > 1 && T > kSharedWorkTokens;
+  std::unique_lock<std::mutex> lk(p->mu, std::defer_lock);
   if (plan.splits > 1) {
     void* part = nullptr;
-    {
-      std::lock_guard<std::mutex> lk(p->mu);
+    lk.lock();
+    if (own)
+      FLP_TRY(flp_dense_workspace_acquire(p, flp_gemm_part_bytes(plan, T, n, N), stream, &part));
+    else
       FLP_TRY(flp_workspace(p, flp_gemm_part_bytes(plan, T, n, N), &part));
-    }
     float* f = (float*)part;
     for (int i = 0; i < n; ++i) {
       out[i].part = f;
       f += (size_t)plan.splits * T * N[i];
     }
   }
-  FLP_TRY(flp_launch_gemm(p->cfg.dtype, x, d_in, T, d_in, plan, n, out, gated, nullptr, stream));
-  if (plan.splits > 1) return flp_launch_gemm_reduce(p->cfg.dtype, T, n, out, plan.splits, gated, false, stream);
-  return FLP_OK;
+  flp_status s = flp_launch_gemm(p->cfg.dtype, x, d_in, T, d_in, plan, n, out, gated, nullptr, stream);
+  if (s == FLP_OK && plan.splits > 1) s = flp_launch_gemm_reduce(p->cfg.dtype, T, n, out, plan.splits, gated, false, stream);
+  if (own) {
+    const flp_status r = flp_dense_workspace_release(p, stream);
+    return s != FLP_OK ? s : r;
+  }
+  return s;
 }
 }  // namespace
 

@@ -135,6 +135,8 @@ extern "C" flp_status flp_pool_destroy(flp_pool* p) {
   }
   if (p->work) (void)hipFree(p->work);
   if (p->attn_work) (void)hipFree(p->attn_work);
+  if (p->dense_work) (void)hipFree(p->dense_work);
+  if (p->dense_ev) (void)hipEventDestroy(p->dense_ev);
   for (void* old : p->retired) (void)hipFree(old);
   if (p->own_dev && p->dev_base) (void)hipFree(p->dev_base);
   if (p->own_host && p->host_base) (void)hipHostFree(p->host_base);
@@ -271,6 +273,22 @@ flp_status flp_attn_workspace(flp_pool* p, size_t bytes, hipStream_t stream, voi
   if (p->attn_slot && (stream != p->attn_stream || stream == hipStreamPerThread))
     FLP_TRY_HIP(hipStreamWaitEvent(stream, p->attn_slot->ev, 0));
   *out = p->attn_work;
+  return FLP_OK;
+}
+
+flp_status flp_dense_workspace_acquire(flp_pool* p, size_t bytes, hipStream_t stream, void** out) {
+  FLP_TRY(grow(p, &p->dense_work, &p->dense_work_cap, bytes));
+  if (!p->dense_ev)
+    FLP_TRY_HIP(hipEventCreateWithFlags(&p->dense_ev, hipEventDisableTiming));
+  else if (stream != p->dense_stream || stream == hipStreamPerThread)
+    FLP_TRY_HIP(hipStreamWaitEvent(stream, p->dense_ev, 0));
+  *out = p->dense_work;
+  return FLP_OK;
+}
+
+flp_status flp_dense_workspace_release(flp_pool* p, hipStream_t stream) {
+  p->dense_stream = stream;
+  FLP_TRY_HIP(hipEventRecord(p->dense_ev, stream));
   return FLP_OK;
 }
 

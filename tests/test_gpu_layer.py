@@ -275,6 +275,43 @@ def test_gated_pair_without_lora(dtype, T, H, M, plan):
     pool.close()
 
 
+def test_layers_without_lora_on_two_streams_of_one_pool():
+    """Two batches of 1100 tokens through a layer without LoRA, each on a stream of its own with nothing between them: their
+    sliced products (q, k, v and down) do not meet in the pool's workspace."""
+    import torch
+    from helpers import dense_plan
+    from paper_2505_03756_amd import flpool
+    T, H, M, d = 1100, 4096, 11008, 128
+    assert dense_plan(T, M, (H,))[1] > 1
+    tt, n_blk = torch.bfloat16, (T + 15) // 16
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(tt)
+    dims = {"q": (d, H), "k": (d, H), "v": (d, H), "o": (H, d), "gate": (M, H), "up": (M, H), "down": (H, M)}
+    W = {p: rnd(s, s[1] ** -0.5) for p, s in dims.items()}
+    W.update(in_norm=rnd((H,), 0.1) + 1, post_norm=rnd((H,), 0.1) + 1)
+    pool = flpool.Pool("bf16", 1, d, 2 * n_blk, 0, block_tokens=16)
+    layer = fllayer.Layer(pool, H, 1, M, W)
+    i32 = lambda a: torch.tensor(a, dtype=torch.int32, device="cuda")
+    batch = [fllayer.Batch([0, T], [0], torch.arange(T, dtype=torch.int32, device="cuda"),
+                           i32([list(range(i * n_blk, (i + 1) * n_blk))]), i32([-1] * T), i32([8]),
+                           torch.ones(1, device="cuda"), i32([0]), {}, 1, 8, n_blk) for i in range(2)]
+    nbytes = layer.scratch_bytes(T)
+    scratch = [torch.zeros(nbytes + 256, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    at = [(s.data_ptr() + 255) & ~255 for s in scratch]
+    h0 = rnd((2, T, H), 1.0)
+    want, got = h0.clone(), h0.repeat(4, 1, 1, 1)
+    for i in range(2):
+        layer.forward(batch[i], want[i], at[i], nbytes)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for k in range(4):
+        for i in range(2):
+            layer.forward(batch[i], got[k, i], at[i], nbytes, stream=streams[i])
+    torch.cuda.synchronize()
+    assert bool((got == want).all()) and not bool((want == h0).all())
+    pool.close()
+
+
 def test_an_adapter_s_infinities_stay_with_its_tokens_in_the_gated_pair():
     """Infinities and NaN in one adapter's B of gate and up: the rows of sequences with other adapters come out as before, bit
     for bit (the branches of both are added inside the gated pass; sequences meet inside its tiles)."""
