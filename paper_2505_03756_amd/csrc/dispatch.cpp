@@ -475,7 +475,7 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
   // accumulators before it rounds): no fp32 copy of the product, no second pass over y.
   // (Batches of 2048 tokens and more only: the epilogue walks the adapters present among a wave's 128 tokens, which
   // are one or two when tokens come in sequences and up to 128 in a large pure-decode batch.)
-  bool fused = mfma_ok && b->n_tokens >= 2048 && b->d_in % 64 == 0;
+  bool fused = mfma_ok && b->n_tokens >= 2048 && b->d_in % 64 == 0 && flp_gemm_offsets_fit(FLP_GEMM_256x256, b->n_tokens, b->ld_x);
   int64_t fused_tiles = 0;                     // enough 256 x 128 tiles to occupy the chip without slices
   for (int q = 0; q < b->n_proj; ++q) {
     fused = fused && b->proj[q].w_base;

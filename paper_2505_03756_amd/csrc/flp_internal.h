@@ -277,6 +277,8 @@ FlpGemmPlan flp_gemm_plan(int M, int K, int n_proj, const int* N, unsigned allow
 // the same through the C ABI, for tests that state which tile and how many slices a shape gets; room < 0: a layer's
 extern "C" void flp_dense_plan(int32_t M, int32_t K, int32_t n_proj, const int32_t* N, int32_t large_only, int64_t room,
                                int32_t* kind, int32_t* splits);
+// rows of x this far apart can be addressed inside a tile of this kind
+bool flp_gemm_offsets_fit(int kind, int M, int64_t ld_x);
 size_t flp_gemm_part_bytes(const FlpGemmPlan& plan, int M, int n_proj, const int* N);
 // lora: one per projection (gated: gate, up), or null
 flp_status flp_launch_gemm(int dtype, const void* x, int64_t ld_x, int M, int K, const FlpGemmPlan& plan, int n_proj,

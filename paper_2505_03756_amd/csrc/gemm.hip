@@ -766,6 +766,10 @@ FlpGemmPlan flp_gemm_plan(int M, int K, int n_proj, const int* N, unsigned allow
   return best;
 }
 
+bool flp_gemm_offsets_fit(int kind, int M, int64_t ld_x) {
+  return ld_x <= (int64_t)UINT32_MAX / 2 / std::min(kCfg[kind].mt, M);
+}
+
 extern "C" void flp_dense_plan(int32_t M, int32_t K, int32_t n_proj, const int32_t* N, int32_t large_only, int64_t room,
                                int32_t* kind, int32_t* splits) {
   const FlpGemmPlan p = flp_gemm_plan(M, K, n_proj, N, large_only ? FLP_GEMM_NO_SPLIT | FLP_GEMM_LARGE_ONLY : 0,
@@ -781,7 +785,14 @@ flp_status flp_launch_gemm(int dtype, const void* x, int64_t ld_x, int M, int K,
     flp_set_error("dense product: d_in %d is not a multiple of %d", K, GK);
     return FLP_ENOTSUP;
   }
-  const GemmCfg& c = kCfg[plan.kind];
+  // a tile's token rows are addressed with 32-bit byte offsets from its first one: rows too far apart for that take the
+  // narrowest tile (32 tokens that span 4 GiB are refused)
+  const int kind = !lora && !flp_gemm_offsets_fit(plan.kind, M, ld_x) ? FLP_GEMM_64x32 : plan.kind;
+  if (!flp_gemm_offsets_fit(kind, M, ld_x)) {
+    flp_set_error("dense product: rows of the input are %lld elements apart", (long long)ld_x);
+    return FLP_ENOTSUP;
+  }
+  const GemmCfg& c = kCfg[kind];
   if (lora && (plan.kind < FLP_GEMM_256x128 || plan.splits != 1)) {
     flp_set_error("dense product: the LoRA epilogue needs whole contractions on the large tiles");
     return FLP_ENOTSUP;
@@ -821,7 +832,7 @@ flp_status flp_launch_gemm(int dtype, const void* x, int64_t ld_x, int M, int K,
     for (int p = 0; p < (gated ? 2 : n_proj); ++p) la.p[p] = lora[p];
   NoLora none;
   void* args[2] = {&a, lora ? (void*)&la : (void*)&none};
-  FLP_TRY_HIP(hipLaunchKernel(gemm_entry(dtype, plan.kind, gated, lora != nullptr), dim3((unsigned)grid), dim3(64 * c.waves),
+  FLP_TRY_HIP(hipLaunchKernel(gemm_entry(dtype, kind, gated, lora != nullptr), dim3((unsigned)grid), dim3(64 * c.waves),
                               args, (size_t)c.lds, stream));
   return FLP_OK;
 }

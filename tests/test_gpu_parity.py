@@ -773,6 +773,34 @@ def test_dense_products_with_adapters_on_every_tile_whole_and_in_slices(dtype, T
         assert bool(((yi.double() - wi).abs() <= bi).all())
 
 
+@pytest.mark.parametrize("T,d_in,widths,ld_x,plan", [
+    (641, 1024, (2056, 4104, 4104), (1 << 23) + 64, ("256x256", 1)),        # 256 rows span a little more than 4 GiB
+    (300, 8192, (264, 72, 72), (1 << 24) + 64, ("128x128", 16)),            # 128 rows do
+    (2100, 512, (1024, 1024, 1024), (1 << 23) + 64, ("256x128", 1)),        # as many tokens as the fused path takes
+])
+def test_dense_products_of_rows_far_apart(T, d_in, widths, ld_x, plan):
+    """Token rows of x so far apart that a tile's rows do not all lie within 32-bit byte offsets of its first one."""
+    assert dense_plan(T, d_in, widths, large_only=T >= 2048, room=60 << 20) == plan
+    g = torch.Generator(device="cuda").manual_seed(T)
+    store = torch.empty(((T - 1) * ld_x + d_in,), dtype=torch.float16, device="cuda")
+    x = store.as_strided((T, d_in), (ld_x, 1))
+    x.copy_(torch.randn((T, d_in), generator=g, device="cuda"))
+    w = [(torch.randn((n, d_in), generator=g, device="cuda") / d_in ** 0.5).half() for n in widths]
+    pool = flpool.Pool("f16", 8, 128, 2, 0, block_tokens=16)
+    z = torch.zeros(1, dtype=torch.int32, device="cuda")
+    y = [torch.full((T, n), float("nan"), dtype=torch.float16, device="cuda") for n in widths]
+    projs = [dict(y=yi, d_out=n, w_base=wi, w_base_layout=1, a_tab_off=z, a_row_base=z, b_tab_off=z, b_row_base=z)
+             for yi, n, wi in zip(y, widths, w)]
+    none = torch.full((T,), -1, dtype=torch.int32, device="cuda")
+    pool.lora_apply_paged(store, none, z, torch.ones(1, device="cuda"), z, projs, n_tokens=T, d_in=d_in, n_adapters=1,
+                          max_rank=8, ld_x=ld_x)
+    for yi, wi in zip(y, w):
+        want = x.double() @ wi.double().T
+        bound = 2.0 ** -11 * want.abs() + 2.0 ** -19 * (x.double().abs() @ wi.double().abs().T) + 1e-7
+        assert bool(((yi.double() - want).abs() <= bound).all())
+    pool.close()
+
+
 @pytest.mark.parametrize("T,widths,plan", [(2050, (1088, 320), ("256x128", 1)), (2177, (4032,), ("256x256", 1)),
                                            (4100, (1088, 1088, 320), ("256x256", 1))])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
