@@ -13,13 +13,13 @@ LIB = os.path.join(HERE, "libflpool.so")
 SOURCES = ["pool.cpp", "dispatch.cpp", "cache_manager.cpp", "sched.cpp", "swap.hip", "attention.hip", "attention_mfma.hip", "attention_decode.hip", "lora.hip", "lora_mfma.hip", "gemm.hip", "layer.hip", "static_scratch.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function", "-Wno-pass-failed",
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function",
          "-Rpass-analysis=kernel-resource-usage", "-fno-caret-diagnostics"]
-# Private (scratch) memory a kernel may use, bytes per lane.  A few dozen spilled registers in an epilogue are fine
-# (the large-batch GEMM holds 256 accumulators and spills up to 36 registers after its loop); an accumulator array
-# that the compiler could not keep in registers (a loop it did not unroll, an index it could not resolve) is a
-# kilobyte and makes the kernel many times slower without failing any test, so the build stops.
-MAX_SCRATCH_BYTES = 256
+# Private (scratch) memory a kernel may use, bytes per lane.  No kernel uses any; a few registers spilled outside a loop
+# would do no harm, but accumulators that leave the registers (a loop that was not unrolled, an index that could not be
+# resolved, 52 registers spilled around the LoRA epilogue's branches: that product took four times as long) fail no test,
+# so the build stops.
+MAX_SCRATCH_BYTES = 64
 RESOURCES = {}      # kernel name -> dict(vgprs, agprs, scratch, occupancy), filled by build()
 
 
