@@ -152,11 +152,19 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
 
   // Three kinds of work.  On a 16-bit pool with head_dim 128, sequences with at least 8 query rows per kv head (prefill,
   // or decode under grouped-query attention) go to the tiled matrix-core kernel in tiles of 256 rows, and the others
-  // (and all short ones of a small launch, below) token by token to the decode kernel.  A large grouped-query batch
-  // stays with the tiles as a whole: the single tokens' traffic overlaps with the other tiles' products (128 prefill
-  // and 384 decode sequences, 64 / 8 heads: 17.5 ms for the step against 17.8 ms with the single tokens in a launch of their
-  // own).  fp32, head_dim 64 and more than 16 query heads per kv head: the row-streaming kernel in runs of up to 4
-  // tokens.  All lists are ordered heaviest first.
+  // (and all short ones of a small launch, below) token by token to the decode kernel.  fp32, head_dim 64 and more than 16
+  // query heads per kv head: the row-streaming kernel in runs of up to 4 tokens.  All lists are ordered heaviest first.
+  //
+  // Single tokens of a grouped-query batch, tiles against decode kernel (64 / 8 heads, bf16, us per call):
+  //                     6 seqs   15    16    24    32    64   128   300     contexts
+  //   tiles               232   262   261   263   280   423   796  1846     1 - 16 k
+  //   decode kernel        65   136   153   207   264   461   863  1969
+  //   tiles               268   269   270   279   379   726  1415  3366     16 k each
+  //   decode kernel       109   227   242   342   431   795  1491  3441
+  // With many sequences a tile's one pass over K and V for all heads of a group is ahead, also where the batch has nothing
+  // but single tokens (and with 128 prefill sequences beside 384 decoding ones: 17.5 ms for the step against 17.8); with
+  // few the tiles leave the chip idle.  The line, 128 items (16 sequences here), is right for equal contexts; where they
+  // differ, the longest one decides what unsplit tiles take and the decode kernel would stay ahead up to 32 sequences.
   const bool mfma_ok = p->cfg.dtype != FLP_F32 && p->cfg.head_dim == 128;
   const int G = b->n_q_heads / p->cfg.n_kv_heads;
   const int n_kv = p->cfg.n_kv_heads;
@@ -173,9 +181,9 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   std::vector<FlpAttnUnit> units;
   std::vector<int64_t> cost;
   constexpr int kTokPerUnit = 4;
-  // A launch of a handful of matrix-core items (a few decode sequences under grouped-query attention) would leave
-  // most of the chip idle: such sequences go to the decode kernel (more than 16 heads per kv head: the row kernel)
-  // instead, where their long contexts are split over many waves (below).
+  // A launch of fewer than 128 matrix-core items (a few decode sequences under grouped-query attention) goes to the
+  // decode kernel (more than 16 heads per kv head: the row kernel) instead, where long contexts are split over many waves
+  // (below).
   int64_t mfma_items_est = 0;
   if (mfma_ok)
     for (int32_t i = 0; i < b->n_seqs; ++i) {
@@ -209,8 +217,9 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   // Split-KV.  A wave of the decode kernel takes one (token, kv head), one of the row kernel one (token, head); with
   // few tokens and long contexts (a handful of decode sequences at 16 k) that is far fewer waves than the chip holds,
   // and with unequal contexts the longest one decides.  Contexts are cut into pieces, each piece a wave; a second kernel
-  // merges the pieces of a row in piece order.  Decode kernel: pieces of equal length, about kPieces of them (twice
-  // what the chip holds), at least kMinGroups groups of 16 positions.  Row kernel: below kSplitBelow waves.
+  // merges the pieces of a row in piece order.  Decode kernel: a row's pieces are of equal length, at most `piece` groups of
+  // 16 positions each (so more than half of that), which makes about kPieces of them (twice what the chip holds) or,
+  // for small launches, pieces of 8 to 16 groups.  Row kernel: below kSplitBelow waves, pieces of kMinGroups and more.
   constexpr int64_t kSplitBelow = 2048, kSplitTarget = 8192, kPieces = 4096;
   constexpr int kMinGroups = 16, kMaxSplit = 64;
   const int64_t row_waves = row_tokens * b->n_q_heads;
@@ -470,11 +479,11 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
     const int rp = 16 * nt;
     v_elems = (size_t)ks * c.v_rows * b->n_proj * rp;
   }
-  // Dense base on every projection, and every product large enough for the large-batch GEMM: the expand step runs
-  // as that kernel's epilogue (segment, shrink, then one GEMM per projection that adds the LoRA branch to its
-  // accumulators before it rounds): no fp32 copy of the product, no second pass over y.
-  // (Batches of 2048 tokens and more only: the epilogue walks the adapters present among a wave's 128 tokens, which
-  // are one or two when tokens come in sequences and up to 128 in a large pure-decode batch.)
+  // Dense base on every projection, and products that together have enough of the large tiles: the expand step runs as
+  // their epilogue (segment, shrink, then one launch for the projections, or one each where W is stored [d_in, d_out],
+  // that adds the LoRA branch to its accumulators before it rounds): no fp32 copy of the product, no second pass over y.
+  // (Batches of 2048 tokens and more only: the epilogue walks the adapters present among a wave's 64 or 128 tokens,
+  // which are one or two when tokens come in sequences and as many as tokens in a large pure-decode batch.)
   bool fused = mfma_ok && b->n_tokens >= 2048 && b->d_in % 64 == 0 && flp_gemm_offsets_fit(FLP_GEMM_256x256, b->n_tokens, b->ld_x);
   int64_t fused_tiles = 0;                     // enough 256 x 128 tiles to occupy the chip without slices
   for (int q = 0; q < b->n_proj; ++q) {

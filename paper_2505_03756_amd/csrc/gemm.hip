@@ -5,7 +5,7 @@
 //
 // 16-bit pools: both operands are read along the contraction (a W given as [d_in, d_out] is first transposed into
 // the pool's workspace), the projections that share an input go in one launch, and the contraction may be split into
-// slices whose fp32 partial products a second kernel (or the LoRA expand kernel) adds in slice order.
+// slices whose fp32 partial products a second kernel adds in slice order.
 // fp32 pools: a matrix-core kernel of its own (the fp32 workload is tiny and bound by latency).
 #include <hip/hip_runtime.h>
 
@@ -58,9 +58,9 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __rest
 
 // ------------------------------------------------------------------------------- the tiled kernel
 // One workgroup computes a tile of FT features x MT tokens of one projection and one slice of the contraction, as
-// the transposed product (A operand = rows of W, B operand = token rows) with mfma_f32_16x16x32.  Measured against
-// 32x32x16 in the same loop (M 16384, N = K = 4096): the chip holds 2.02 GHz instead of 1.70 at the same matrix-pipe
-// share (the 16 x 16 form moves less accumulator data per product) and the launch is 8 - 17 % shorter.
+// the transposed product (A operand = rows of W, B operand = token rows) with mfma_f32_16x16x32.  Large products are
+// bound by the power the chip may draw: M 16384, N = K = 4096 takes 402 us at 2.05 GHz (1.37 PFLOP/s); a four-wave kernel
+// with 128 x 128 corners on 32x32x16 instructions took 429 us at 1.85 GHz.
 //
 // Operands travel in k tiles of 64 coefficients, so that a row of a tile is one whole 128-byte line, from memory to
 // LDS with the direct loads of gfx950 (8 lines per instruction; inline assembly with its own s_waitcnt vmcnt) into a
@@ -76,9 +76,8 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __rest
 //                    in flight, so their tiles are narrow in tokens and the ring is deep.
 //   ping-pong (PP)   256 x 256 tiles, two stages of 64 KiB, eight waves in two groups of four (one wave of each group
 //                    per SIMD) that take turns: while one group reads its fragments and requests the stage after next,
-//                    the other multiplies; they change places at every barrier.  (M 20000, N = K = 4096: 0.542 ms,
-//                    against 0.590 ms for the ring form of the same tile and 0.659 ms for the four-wave kernel with
-//                    128 x 128 corners that was here before.)
+//                    the other multiplies; they change places at every barrier.  (M 20000, N = K = 4096: 525 us, with
+//                    256 x 128 tiles in the ring form 574 us.)
 //
 // GATED: the gated-SiLU pair of an MLP in one pass.  The features are those of both matrices interleaved in groups
 // of 64 (32 gate rows, the same 32 up rows: positions 16 tau + m hold feature 2 m + (tau & 1) of matrix tau >> 1), so a
@@ -673,9 +672,10 @@ struct GemmCfg {
   float part;            // time of a round that is nearly empty, as a share of a full one
 };
 constexpr int stage_bytes(int ft, int mt) { return (ft + mt) * 128; }
-// kinds of tile, FLP_GEMM_*.  The times are what the planner adds up, fitted to 600 launches on MI355X (every kind and
-// number of slices over 1 .. 2000 tokens and the matrices of the 7B, 13B and 34B shapes): over those the plan it picks is
-// 1.2 % slower than the best one on average, 15 % at worst.
+// kinds of tile, FLP_GEMM_*.  The times are what the planner adds up, fitted to launches on MI355X.  Against all kinds and
+// numbers of slices at 96 shapes (1 .. 2000 tokens, the matrices of the 7B, 13B and 34B shapes; 3720 timings with operands
+// from memory) the plan it picks is 2.4 % slower than the best one on average and 23 % at worst (34B gate and up at 33 tokens;
+// one shape in six is more than 5 % off).
 const GemmCfg kCfg[FLP_GEMM_KINDS] = {
     {64, 32, 2, 4 * stage_bytes(64, 32), 3, 0.488f, 4.44f, 0.53f},
     {128, 64, 4, 3 * stage_bytes(128, 64), 2, 0.949f, 4.69f, 0.63f},
