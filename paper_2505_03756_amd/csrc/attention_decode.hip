@@ -12,26 +12,22 @@
 // keys fed in the order key(m) = 8 (m / 4) + 4 t + m % 4 for row m of instruction t, the 8 consecutive positions
 // 8 (l / 16) ... + 7, which are also the positions of its 16-byte run of the transposed V of a pool block.
 //
-// O^T = V^T P^T takes fp32 weights and sums:
-//   bf16   three 16x16x32 instructions per weight: a weight is exactly the sum of three bf16 pieces (value, remainder,
-//          remainder of that; 8 bits each) and a product of two bf16 numbers is exact in fp32.  Taken times 2^16, a
-//          weight keeps its last piece a normal number down to 2^-126 of the largest one.  What the pieces cannot
-//          express is an infinite or overflowing product (0 x inf, inf - inf): a wave whose sums are not all finite
-//          walks its piece of the context again with the 32-bit instructions below, so infinities and NaN in V
-//          come out as an fp32 multiply-add makes them.
-//   fp16   has no exponents for such pieces (the value of a weight below 2^-25 is zero).  V is widened and element e of the
-//          16-byte runs goes into 32-bit instruction e with weight e of every lane.  Up to 4 heads per kv head 4x4x1:
-//          sixteen blocks, each four channels of one position times four rows; column l % 16 holds row l % 4, and the
-//          quarters of the wave sum different positions and are added at the end.  Up to 16 heads 16x16x4: 16 channels
-//          times 16 rows over four positions, twice the matrix time (0.9 us per 32 positions of a wave).
-// The rows past the last head repeat it.
+// O^T = V^T P^T takes fp32 weights and sums with three 16x16x32 instructions per weight: its value in the pool's type,
+// the remainder, and the remainder of that; a product of two 16-bit numbers is exact in fp32.
+//   bf16   8 bits each, so a weight is exactly the sum of its pieces.  Taken times 2^16 it keeps the last one a normal
+//          number down to 2^-126 of the largest weight.
+//   fp16   11 bits each; weights are taken times 2^15 and every remainder times 2^11, and the tile's sums are scaled back from
+//          piece to piece.  Exact down to 2^-38 of the largest weight; below, at most 2^-62 of the largest is lost, which
+//          times 65504 and a million positions is still less than half the smallest fp16 number.
+// What the pieces cannot express is an infinite or overflowing product (0 x inf, inf - inf): a wave whose sums are not all
+// finite walks its piece of the context again with 16x16x4 fp32 instructions on the widened V, so infinities and NaN
+// in V come out as an fp32 multiply-add makes them.  The rows past the last head repeat it.
 //
 // Measured, whole steps on MI355X.  Before this kernel (a wave per query head on the vector units, fp32, nothing loaded
-// ahead), then with bf16 weights as value and remainder only (16 bits of them), 16x16x4, 4x4x1, three pieces:
-//   256 sequences of 512-4096 positions, 32 / 32 heads, 9.8 GB of K/V    1941   1865   1903   1872   1867 us
-//   6 sequences of 8-16 k positions, 64 / 8 heads                         234    137    143     -     138 us
-//   layer with 200 decode tokens, 32 / 32 heads                          1092   1047   1064   1046   1049 us
-// 4x4x1 in two sets of accumulators for 8 heads (q in LDS, 256 registers) took 143 us as well, two waves of four rows 145.
+// ahead), then with weights as value and remainder only (16 bits of them in bf16), 16x16x4 throughout, three pieces:
+//   256 sequences of 512-4096 positions, 32 / 32 heads, bf16, 9.8 GB of K/V    1941   1865   1903   1867 us
+//   6 sequences of 8-16 k positions, 64 / 8 heads, bf16                         234    137    143    137 us
+//   layer with 200 decode tokens, 32 / 32 heads, bf16                          1092   1047   1064   1046 us
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -44,7 +40,6 @@ namespace {
 constexpr int D = 128;
 constexpr int BT = 16;
 constexpr int kChains = 4;                             // independent sums that hide a matrix instruction's latency
-constexpr float kScale = 65536.f;                      // of weights in pieces
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h16x8 __attribute__((ext_vector_type(8)));
@@ -54,7 +49,7 @@ struct DF16 {
   typedef h16x8 vec;
   typedef _Float16 el;
   typedef F16 S;
-  static constexpr bool kPieces = false;               // weights in 16-bit pieces
+  static constexpr float kScale = 32768.f, kStep = 2048.f;      // of the weights, and from one of their pieces to the next
   static __device__ __forceinline__ f32x4 mfma(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
   }
@@ -66,7 +61,7 @@ struct DBF16 {
   typedef b16x8 vec;
   typedef __bf16 el;
   typedef BF16 S;
-  static constexpr bool kPieces = true;
+  static constexpr float kScale = 65536.f, kStep = 1.f;
   static __device__ __forceinline__ f32x4 mfma(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
@@ -86,8 +81,7 @@ struct Tile {                    // K and V of 32 positions
   u32x4 k[2][4], v[8];
 };
 
-// ROWS: how many rows a wave has, at least the query heads per kv head: 16, or 4 for the fp16 form with 4x4x1
-template <typename M, int ROWS>
+template <typename M>
 __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, const FlpAttnUnit* __restrict__ units) {
   typedef typename M::vec vec;
   const FlpAttnUnit u = units[blockIdx.x];
@@ -105,8 +99,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
   const uint16_t* __restrict__ pool = reinterpret_cast<const uint16_t*>(a.pool);
   const float c = a.scale_log2e;
 
-  const int row = lr & (ROWS - 1);
-  const int h = g * G + (row < G ? row : G - 1);       // this lane's query head
+  const int h = g * G + (lr < G ? lr : G - 1);         // this lane's query head
   const int64_t rowoff = ((int64_t)t * a.n_h + h) * D;
   vec qf[4];
 #pragma unroll
@@ -181,18 +174,18 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
     float w[8], lw = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      w[e] = exp2f(p[e] - m) * (PIECES ? kScale : 1.f);
+      w[e] = exp2f(p[e] - m) * (PIECES ? M::kScale : 1.f);
       lw += w[e];
     }
     l += lw;
-    vec piece[3];                                      // PIECES: the weights are their sum
+    vec piece[3];                                      // the weights are piece[0] + (piece[1] + piece[2] / kStep) / kStep
     if constexpr (PIECES)
 #pragma unroll
       for (int e = 0; e < 8; ++e)
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
           piece[i][e] = (typename M::el)w[e];
-          w[e] -= (float)piece[i][e];
+          w[e] = (w[e] - (float)piece[i][e]) * M::kStep;
         }
 #pragma unroll
     for (int ct0 = 0; ct0 < 8; ct0 += kChains) {
@@ -203,15 +196,19 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
 #pragma unroll
         for (int i = 2; i >= 0; --i)
 #pragma unroll
-          for (int k = 0; k < kChains; ++k) sum[k] = M::mfma(as_vec<vec>(T.v[ct0 + k]), piece[i], sum[k]);
+          for (int k = 0; k < kChains; ++k) {
+            sum[k] = M::mfma(as_vec<vec>(T.v[ct0 + k]), piece[i], sum[k]);
+            if (i > 0 && M::kStep != 1.f)
+#pragma unroll
+              for (int j = 0; j < 4; ++j) sum[k][j] *= 1.f / M::kStep;
+          }
       } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e)
 #pragma unroll
           for (int k = 0; k < kChains; ++k) {
             const float v = M::widen(T.v[ct0 + k][e >> 1], e & 1);
-            sum[k] = ROWS == 16 ? __builtin_amdgcn_mfma_f32_16x16x4f32(v, w[e], sum[k], 0, 0, 0)
-                                : __builtin_amdgcn_mfma_f32_4x4x1f32(v, w[e], sum[k], 0, 0, 0);
+            sum[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, w[e], sum[k], 0, 0, 0);
           }
       }
 #pragma unroll
@@ -250,69 +247,43 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  walk(std::bool_constant<M::kPieces>{});
-  if constexpr (M::kPieces) {                          // an infinite V never leaves a finite sum: even 0 x inf is NaN
-    bool finite = true;
-    l *= 1.f / kScale;
+  walk(std::true_type{});
+  bool finite = true;                                  // an infinite V never leaves a finite sum: even 0 x inf is NaN
+  l *= 1.f / M::kScale;
 #pragma unroll
-    for (int ct = 0; ct < 8; ++ct)
+  for (int ct = 0; ct < 8; ++ct)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        finite = finite && fabsf(O[ct][i]) < INFINITY;
-        O[ct][i] *= 1.f / kScale;
-      }
-    if (__builtin_amdgcn_ballot_w64(!finite)) walk(std::false_type{});
-  }
+    for (int i = 0; i < 4; ++i) {
+      finite = finite && fabsf(O[ct][i]) < INFINITY;
+      O[ct][i] *= 1.f / M::kScale;
+    }
+  if (__builtin_amdgcn_ballot_w64(!finite)) walk(std::false_type{});
 
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
-  auto store = [&](const f32x4* o, int n, int c0) {    // n runs of 4 channels of the lane's row, 16 apart, from c0 on
-    if (row >= G) return;
-    if (u.n_split > 1) {
-      float* pp = a.partials + ((int64_t)(u.part_row + u.split) * a.n_h + h) * (D + 2);
-      if (c0 == 0) *reinterpret_cast<float2*>(pp) = make_float2(m, l);
+  if (lr >= G) return;
+  // lane (row lr, quarter lh) holds channels 16 ct + 4 lh + (0..3)
+  if (u.n_split > 1) {
+    float* pp = a.partials + ((int64_t)(u.part_row + u.split) * a.n_h + h) * (D + 2);
+    if (lh == 0) *reinterpret_cast<float2*>(pp) = make_float2(m, l);
 #pragma unroll
-      for (int k = 0; k < n; ++k) {
-        float2* w = reinterpret_cast<float2*>(pp + 2 + c0 + 16 * k);
-        w[0] = make_float2(o[k][0], o[k][1]);
-        w[1] = make_float2(o[k][2], o[k][3]);
-      }
-      return;
+    for (int ct = 0; ct < 8; ++ct) {
+      float2* o = reinterpret_cast<float2*>(pp + 2 + 16 * ct + 4 * lh);
+      o[0] = make_float2(O[ct][0], O[ct][1]);
+      o[1] = make_float2(O[ct][2], O[ct][3]);
     }
-    const float inv = 1.f / l;
-    uint16_t* op = reinterpret_cast<uint16_t*>(a.out) + rowoff + c0;
+    return;
+  }
+  const float inv = 1.f / l;
+  uint16_t* op = reinterpret_cast<uint16_t*>(a.out) + rowoff;
 #pragma unroll
-    for (int k = 0; k < n; ++k) {
-      uint16_t o4[4];
+  for (int ct = 0; ct < 8; ++ct) {
+    uint16_t o4[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) o4[i] = M::S::from_float(o[k][i] * inv);
-      uint2 w;
-      __builtin_memcpy(&w, o4, 8);
-      *reinterpret_cast<uint2*>(op + 16 * k) = w;
-    }
-  };
-  if constexpr (ROWS == 16) {
-    // lane (row lr, quarter lh) holds channels 16 ct + 4 lh + (0..3)
-    store(O, 8, 4 * lh);
-  } else {
-    // it holds its quarter's share of the sum over positions for channels 16 ct + 4 (lr / 4) + (0..3) of row lr % 4; the
-    // quarters exchange halves twice, and quarter lh is left with channel tiles 2 lh and 2 lh + 1
-    f32x4 half[4], own[2];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float lo = O[k][i], hi = O[4 + k][i];
-        half[k][i] = (lh & 2 ? hi : lo) + __shfl_xor(lh & 2 ? lo : hi, 32);
-      }
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float lo = half[k][i], hi = half[2 + k][i];
-        own[k][i] = (lh & 1 ? hi : lo) + __shfl_xor(lh & 1 ? lo : hi, 16);
-      }
-    store(own, 2, 32 * lh + 4 * (lr >> 2));
+    for (int i = 0; i < 4; ++i) o4[i] = M::S::from_float(O[ct][i] * inv);
+    uint2 w;
+    __builtin_memcpy(&w, o4, 8);
+    *reinterpret_cast<uint2*>(op + 16 * ct + 4 * lh) = w;
   }
 }
 
@@ -321,25 +292,15 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
 flp_status flp_launch_attn_decode(int dtype, const FlpAttnArgs& a, const FlpAttnUnit* units_dev, int32_t n_units,
                                   hipStream_t stream) {
   if (n_units <= 0) return FLP_OK;
-  if (dtype != FLP_F16 && dtype != FLP_BF16) {
+  const dim3 grid((unsigned)n_units, (unsigned)((a.n_kv + 3) / 4));
+  if (dtype == FLP_F16)
+    hipLaunchKernelGGL((attn_decode_kernel<DF16>), grid, dim3(256), 0, stream, a, units_dev);
+  else if (dtype == FLP_BF16)
+    hipLaunchKernelGGL((attn_decode_kernel<DBF16>), grid, dim3(256), 0, stream, a, units_dev);
+  else {
     flp_set_error("attention (decode path): dtype %d not supported", dtype);
     return FLP_ENOTSUP;
   }
-  const dim3 grid((unsigned)n_units, (unsigned)((a.n_kv + 3) / 4));
-  const int G = a.n_h / a.n_kv;
-  const auto launch = [&](auto m) {
-    typedef decltype(m) M;
-    if constexpr (!M::kPieces)
-      if (G <= 4) {
-        hipLaunchKernelGGL((attn_decode_kernel<M, 4>), grid, dim3(256), 0, stream, a, units_dev);
-        return;
-      }
-    hipLaunchKernelGGL((attn_decode_kernel<M, 16>), grid, dim3(256), 0, stream, a, units_dev);
-  };
-  if (dtype == FLP_F16)
-    launch(DF16{});
-  else
-    launch(DBF16{});
   FLP_TRY_HIP(hipGetLastError());
   return FLP_OK;
 }

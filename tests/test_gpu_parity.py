@@ -538,7 +538,7 @@ def test_split_kv_for_few_long_sequences(dtype, heads, kv, d, seqs, prefix, new)
     ("bf16", 16, 32, 2, (1, 33, 255, 256, 257, 511, 513)),      # 16 rows per kv head, around one piece and two
     ("f16", 32, 15, 5, (16, 17, 32, 47, 48, 65, 300, 1100)),    # 3 rows per kv head, blocks of 32, kv heads not a multiple of 4
     ("bf16", 32, 16, 2, (31, 64, 769, 1025, 2047)),
-    ("bf16", 16, 8, 2, (7, 300, 513)),                          # 4 and 5 rows per kv head: both sides of the narrow form
+    ("bf16", 16, 8, 2, (7, 300, 513)),                          # 4 and 5 rows per kv head
     ("f16", 32, 20, 4, (33, 600)),
     ("f16", 16, 34, 2, (5, 40, 700)),                           # 17 rows per kv head: past what one wave holds
 ])
