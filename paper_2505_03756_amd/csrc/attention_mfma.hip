@@ -10,14 +10,20 @@
 // sit in the same tile and K/V are read once for all of them.  It walks the context in
 // tiles of 64 positions (4 pool blocks).
 //
-// The products are computed transposed, S^T = K Q^T and O^T = V^T P^T, with
-// mfma_f32_32x32x16: the accumulator layout then gives every lane ONE query row (column
-// l%32) and 16 keys of a 32-key sub-tile, so the softmax statistics are per-lane scalars
-// and P^T is already in B-operand layout for the second product.  The A operand of that
-// product needs, per lane, 8 consecutive positions of one channel: exactly what the
-// transposed V layout of the pool block provides as one 16-byte run.  The order in which
-// keys are fed to the first product is permuted (bits 2 and 3 of the key index swapped)
-// so that the 8 keys a lane ends up holding are consecutive positions.
+// The products are computed transposed, S^T = K Q^T and O^T = V^T P^T, with mfma_f32_16x16x32: a lane holds one query
+// row (column l % 16) of each of the wave's two row tiles, and with the keys of a 32-key group fed in the order
+// key(m) = 8 (m / 4) + 4 t + m % 4 for row m of key tile t it holds the weights of 8 consecutive positions, which is the
+// B-operand layout of the second product and also its 16-byte run of the transposed V of a pool block.  The row maximum
+// is only exchanged between lanes when it has to be raised.
+//
+// Long launches are bound by the power the chip may draw, so what counts is energy per tile: with 32x32x16 instructions,
+// which read and write twice the accumulator registers per product, the same loop held a lower clock (64 sequences of
+// 4096 + 512 positions, 64 / 8 heads, bf16: 4.49 ms, now 4.17; with all operands zero, where power does not limit, 3.62
+// against 3.77 ms).  A software pipeline inside a wave (the scores of tile t + 1 between the exponentials of tile t, 244
+// registers) was 3-8 % slower.  Batches of prefill, or prefill and decode, attention alone:
+//   64 sequences, prefixes to 2 k, 128-512 new tokens, 32 / 32 heads, fp16       756 -> 716 us
+//   128 sequences, prefixes to 4 k, 40 / 40 heads, fp16                          2984 -> 2836 us
+//   512 sequences, contexts to 16 k, a quarter prefill, 64 / 8 heads, bf16       15.33 -> 14.61 ms
 //
 // K/V tiles travel from the pool to LDS with the direct global-to-LDS loads of gfx950
 // (16 bytes per lane, landing at LDS base + 16 * lane): no registers and no LDS stores are
@@ -25,8 +31,9 @@
 // multiplied.  The XOR swizzle of the LDS layout is applied on the global side: a lane
 // fetches the 16-byte chunk that belongs at its fixed LDS slot.  A wave issues one
 // instruction about every 4.5 cycles whatever its kind, and LDS reads take a few hundred
-// cycles under load, so the loops below keep the instruction count per tile low and read the
-// operand fragments two steps ahead of the products that use them.
+// cycles under load, so operand fragments are read two steps ahead of the products that use them, the next tile is
+// requested from between the products of the scores, and the exponentials are spread between those of the second product
+// (2.5 % of the batches above).
 #include <hip/hip_runtime.h>
 
 #include "flp_internal.h"
@@ -39,9 +46,9 @@ constexpr int BT = 16;
 constexpr int BN = 64;                 // keys per tile
 constexpr int kTile = BN * D * 2;      // bytes of one K (or V) tile: 16 KiB
 constexpr int kStage = 2 * kTile;      // K tile followed by V tile
-constexpr int kStages = 3;         // tiles in the LDS ring: one being multiplied, kStages - 1 in flight
+constexpr int kStages = 3;             // tiles in the LDS ring: one being multiplied, kStages - 1 in flight
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 b16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h16x2 __attribute__((ext_vector_type(2)));
@@ -49,10 +56,10 @@ typedef __bf16 b16x2 __attribute__((ext_vector_type(2)));
 
 struct MF16 {
   typedef h16x8 vec;
-  static __device__ __forceinline__ f32x16 mfma(vec a, vec b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+  static __device__ __forceinline__ f32x4 mfma(vec a, vec b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
   }
-  // 8 weights -> 16 bit; returns their sum as seen after rounding
+  // 8 weights -> 16 bit; adds their sum as seen after rounding
   static __device__ __forceinline__ vec pack(const float* p, float& sum) {
     vec v;
 #pragma unroll
@@ -66,8 +73,8 @@ struct MF16 {
 };
 struct MBF16 {
   typedef b16x8 vec;
-  static __device__ __forceinline__ f32x16 mfma(vec a, vec b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+  static __device__ __forceinline__ f32x4 mfma(vec a, vec b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
   static __device__ __forceinline__ vec pack(const float* p, float& sum) {
     vec v;
@@ -88,10 +95,8 @@ __device__ __forceinline__ V as_vec(u32x4 r) {
   return v;
 }
 
-// m (row of the first product's A operand) -> position inside the 32-key sub-tile
-__device__ __forceinline__ int key_of_row(int m) { return (m & 0x13) | ((m & 4) << 1) | ((m & 8) >> 1); }
-// XOR term of the K row swizzle (= row of the A operand & 15) and of the V^T run swizzle
-__device__ __forceinline__ int k_swz(int key) { return ((key & 4) << 1) | ((key & 8) >> 1) | (key & 3); }
+// XOR term of the K row swizzle: the key's row of its A operand
+__device__ __forceinline__ int k_swz(int key32) { return ((key32 >> 3) << 2) | (key32 & 3); }
 __device__ __forceinline__ int v_swz(int d) { return ((d >> 2) & 1) ^ ((d >> 3) & 1); }
 
 // s_waitcnt immediates (gfx9 encoding: vmcnt[3:0] + [15:14], expcnt[6:4], lgkmcnt[11:8]), other counters untouched
@@ -113,7 +118,6 @@ __device__ __forceinline__ void load_to_lds16(const void* base, uint32_t voff, u
 }
 #pragma clang diagnostic pop
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 template <typename M>
 __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(FlpAttnArgs a, const FlpMfmaItem* __restrict__ items) {
@@ -123,21 +127,21 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(FlpAttnArgs a, const 
 
   const FlpMfmaItem it = items[blockIdx.x];
   if (it.n_rows <= 0) return;
-  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, hf = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lh = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = a.n_h / a.n_kv, g = it.g;
   const int P = a.prefix_len[it.seq];
   const int t0 = a.cu_new[it.seq];
   const int N = a.cu_new[it.seq + 1] - t0;
   const int L = P + N;
-  const int bt = a.bt, hpb = bt / BT;                 // a block holds one or two groups of 16 positions
+  const int bt = a.bt, hsh = bt / BT - 1;             // a block holds 1 << hsh groups of 16 positions
   const int ngrp_valid = (L + BT - 1) / BT;           // groups of 16 positions that hold keys of this sequence
   const int nblk_valid = (L + bt - 1) / bt;
   const int32_t* __restrict__ table = a.tables + (int64_t)it.seq * a.max_blocks;
   const uint16_t* __restrict__ pool = reinterpret_cast<const uint16_t*>(a.pool);
   const float c = a.scale_log2e;
 
-  // ---- this wave's 32 query rows
+  // ---- this wave's 32 query rows: rows wrow0 + 16 j + lr, j = 0, 1, of a lane
   const int row_end = it.r0 + it.n_rows;             // one past the tile's last valid row
   const int wrow0 = it.r0 + wave * 32;
   const bool wave_active = wrow0 < row_end;
@@ -146,27 +150,29 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(FlpAttnArgs a, const 
   const int n_tiles = (P + (row_end - 1) / G) / BN + 1;
   const int kt_last = wave_active ? (P + wrow_last / G) / BN : -1;   // last tile this wave has keys in
 
-  const int row = wrow0 + lr;
-  const bool rvalid = row < row_end;
-  const int rc = rvalid ? row : row_end - 1;
-  const int prow = P + rc / G;                        // position of this lane's row
-  const int64_t rowoff = ((int64_t)(t0 + rc / G) * a.n_h + (g * G + rc % G)) * D;
-  vec qf[8];
-  {
-    const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + rowoff + 8 * hf;
+  int prow[2];                                        // positions of this lane's rows
+  int64_t rowoff[2];
+  vec qf[2][4];
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) qf[kk] = as_vec<vec>(*reinterpret_cast<const u32x4*>(qp + 16 * kk));
+  for (int j = 0; j < 2; ++j) {
+    const int row = wrow0 + 16 * j + lr;
+    const int rc = row < row_end ? row : row_end - 1;
+    prow[j] = P + rc / G;
+    rowoff[j] = ((int64_t)(t0 + rc / G) * a.n_h + (g * G + rc % G)) * D;
+    const uint16_t* qp = reinterpret_cast<const uint16_t*>(a.q) + rowoff[j] + 8 * lh;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) qf[j][kk] = as_vec<vec>(*reinterpret_cast<const u32x4*>(qp + 32 * kk));
   }
 
-  f32x16 O[4];
-  float mrow = -INFINITY, lsum = 0.f;
+  f32x4 O[8][2];
+  float mrow[2] = {-INFINITY, -INFINITY}, lsum[2] = {0.f, 0.f};
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
+  for (int ct = 0; ct < 8; ++ct)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) O[dt][i] = 0.f;
+    for (int j = 0; j < 2; ++j) O[ct][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // ---- staging: wave w moves pool block w/2 of every tile, quarters 2(w%2) and 2(w%2)+1 of its K rows
-  //      and of its V^T runs (1 KiB per instruction).  LDS chunk ci (16 bytes) of a block's K part
+  // ---- staging: wave w moves group w/2 of every tile, quarters 2(w%2) and 2(w%2)+1 of its K rows
+  //      and of its V^T runs (1 KiB per instruction).  LDS chunk ci (16 bytes) of a group's K part
   //      holds key ci/16, logical chunk (ci%16) ^ swizzle(key); chunk ci of its V part holds channel
   //      ci/2, positions 8*((ci%2) ^ swizzle(channel)) .. +7.
   const int sblk = wave >> 1;
@@ -175,7 +181,7 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(FlpAttnArgs a, const 
   for (int j = 0; j < 2; ++j) {
     const int ci = (2 * (wave & 1) + j) * 64 + lane;
     const int key = ci >> 4;
-    kg[j] = (uint32_t)(2 * (key * D + 8 * ((ci & 15) ^ k_swz(key))));
+    kg[j] = (uint32_t)(2 * (key * D + 8 * ((ci & 15) ^ k_swz(16 * (sblk & 1) + key))));
     const int vd = ci >> 1;
     vg[j] = (uint32_t)(2 * (vd * bt + 8 * ((ci & 1) ^ v_swz(vd))));     // channel vd's run of 16 slots inside its bt-slot row
   }
@@ -186,15 +192,14 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(FlpAttnArgs a, const 
   for (int i = tid; i < nblk_valid; i += 512) tab_lds[i] = table[i];
   __builtin_amdgcn_s_waitcnt(kWaitVm0);                // the query fragments are in: from here on only tile loads are in flight
   __syncthreads();
-  // this wave's 16-position group of tile t (clamped: always valid), as block id * 2 + group inside the block
-  auto block_id = [&](int t) {
-    int gi = 4 * t + sblk;
-    gi = gi < ngrp_valid ? gi : ngrp_valid - 1;
-    return __builtin_amdgcn_readfirstlane(tab_lds[gi / hpb] * 2 + gi % hpb);
+  // this wave's 16-position group of tile t (clamped: always valid) and its block's id
+  auto group = [&](int t) {
+    const int gi = 4 * t + sblk;
+    return gi < ngrp_valid ? gi : ngrp_valid - 1;
   };
   auto issue_tile = [&](int t, int32_t id) {         // 4 direct loads: tile t -> stage t % kStages
-    const int half = id & 1;
-    const uint16_t* blk = pool + (int64_t)(id >> 1) * a.block_elems;
+    const int half = group(t) & hsh;
+    const uint16_t* blk = pool + (int64_t)__builtin_amdgcn_readfirstlane(id) * a.block_elems;
     const uint32_t dst = lds_wave + (t % kStages) * kStage;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -202,167 +207,191 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(FlpAttnArgs a, const 
       load_to_lds16(blk + v_region + BT * half, vg[j], dst + kTile + j * 1024);
     }
   };
-
 #pragma unroll
-  for (int t = 0; t < kStages - 1; ++t) issue_tile(t, block_id(t));
-  int32_t id_next = block_id(kStages - 1);
+  for (int t = 0; t < kStages - 1; ++t) issue_tile(t, tab_lds[group(t) >> hsh]);
+  int32_t id_next = tab_lds[group(kStages - 1) >> hsh];      // of the tile that is requested next
 
-  const int krow = key_of_row(lr);                    // this lane's key inside a 32-key sub-tile
-  const int a_swz = lr & 15;
-  int voff[4];                                        // V^T fragment of channel tile dt (block b adds b * 4096)
+  // ---- operand fragments.  Row m of key tile 2 b + t is key 32 b + 8 (m / 4) + 4 t + m % 4, so that a lane ends up with
+  //      the weights of 8 consecutive positions, which are also its 16-byte run of V^T
+  const uint32_t kbase = (uint32_t)((8 * (lr >> 2) + (lr & 3)) * 256 + ((lh ^ lr) << 4));
+  const uint32_t vbase = (uint32_t)(kTile + (lh >> 1) * 4096 + lr * 32 + (((lh & 1) ^ v_swz(lr)) << 4));
+  f32x4 S[4][2];
+  vec Pw[2][2];
+  auto load_k = [&](vec(&kf)[2], const uint8_t* buf, int q) {      // step q: key tiles of group q / 4, channels 32 (q % 4) ..
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt) {
-    const int d = 32 * dt + lr;
-    voff[dt] = kTile + ((2 * d + (hf ^ v_swz(d))) << 4);
-  }
-
-  for (int kt = 0; kt < n_tiles; ++kt) {
-    // tile kt has landed (this wave's part: all but the 4 loads of tile kt + 1 are complete), and after
-    // the barrier so has everybody's; everybody is also done with tile kt - 1, whose stage is refilled next
-    __builtin_amdgcn_s_waitcnt(kWaitTile);
-    __syncthreads();
-    uint8_t* buf = smem + (kt % kStages) * kStage;
-    if (BN * kt + BN > L) {
-      // slots at or past the sequence's length hold arbitrary bits: zero them so that a zero weight
-      // times such a value cannot turn into NaN (only the last tile of a sequence gets here)
+    for (int i = 0; i < 2; ++i)
+      kf[i] = *reinterpret_cast<const vec*>(buf + (kbase ^ (uint32_t)((q & 3) << 6)) + (q >> 2) * 8192 + i * 1024);
+  };
+  auto load_v = [&](vec(&vf)[2], const uint8_t* buf, int q) {      // step q: keys 32 (q / 4) .., channel tiles 2 (q % 4) ..
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      vf[i] = *reinterpret_cast<const vec*>(buf + vbase + (q >> 2) * 8192 + (2 * (q & 3) + i) * 512);
+  };
+  auto score = [&](const vec(&kf)[2], int q) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        S[2 * (q >> 2) + i][j] = M::mfma(kf[i], qf[j][q & 3], q & 3 ? S[2 * (q >> 2) + i][j] : f32x4{0.f, 0.f, 0.f, 0.f});
+  };
+  auto mask = [&](int t) {                             // causal mask on the tiles that reach past the first row's position
+    if (BN * t + BN - 1 > wave_min_pos) {
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
-        const int ci = tid + 512 * j;
-        const int u = ci >> 8, vd = (ci & 255) >> 1, vh = (ci & 1) ^ v_swz(vd);
-        const int pos0 = BN * kt + BT * u + 8 * vh;
-        if (pos0 + 8 > L) {
-          u32x4* slot = reinterpret_cast<u32x4*>(buf + kTile + ci * 16);
-          u32x4 v = *slot;
-          uint16_t e[8];
-          __builtin_memcpy(e, &v, 16);
+        const int thr = prow[j] - (BN * t + 8 * lh);
 #pragma unroll
-          for (int s = 0; s < 8; ++s)
-            if (pos0 + s >= L) e[s] = 0;
-          __builtin_memcpy(&v, e, 16);
-          *slot = v;
-        }
+        for (int k4 = 0; k4 < 4; ++k4)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) S[k4][j][i] = 32 * (k4 >> 1) + 4 * (k4 & 1) + i <= thr ? S[k4][j][i] : -INFINITY;
       }
-      __syncthreads();
     }
-    issue_tile(kt + kStages - 1, id_next);
-    id_next = block_id(kt + kStages);
+  };
+  // The running maximum is only raised when some row of the wave has outgrown it by more
+  // than 2^8: until then the weights are taken relative to the old maximum (they stay below
+  // 256, exact in fp32 and well inside the 16-bit range), which spares the rescaling of the
+  // 64 accumulator registers and the exchange between lanes on almost every tile.
+  auto raise = [&]() {
+    float tm[2];                                       // over the lane's keys
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      tm[j] = S[0][j][0];
+#pragma unroll
+      for (int k4 = 0; k4 < 4; ++k4)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tm[j] = fmaxf(tm[j], S[k4][j][i]);
+    }
+    if (__builtin_amdgcn_ballot_w64((tm[0] - mrow[0]) * c > 8.f || (tm[1] - mrow[1]) * c > 8.f)) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        tm[j] = fmaxf(tm[j], __shfl_xor(tm[j], 16));
+        tm[j] = fmaxf(tm[j], __shfl_xor(tm[j], 32));
+        const float m_new = fmaxf(mrow[j], tm[j]);
+        const float alpha = __builtin_amdgcn_exp2f((mrow[j] - m_new) * c);
+        mrow[j] = m_new;
+        lsum[j] *= alpha;
+#pragma unroll
+        for (int ct = 0; ct < 8; ++ct)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) O[ct][j][i] *= alpha;
+      }
+    }
+  };
+  auto weights = [&](int j, int b, float mc) {
+    float p[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(fmaf(S[2 * b + (e >> 2)][j][e & 3], c, -mc));
+    // the row sum is taken over the rounded weights, the ones the second product uses
+    Pw[j][b] = M::pack(p, lsum[j]);
+  };
 
-    if (kt <= kt_last) {
-      // ---- S^T = K Q^T for the tile's two 32-key sub-tiles; K fragments are read two steps ahead
-      f32x16 S[2];
+  auto request = [&](int kt) {                         // the tile that takes the stage of tile kt - 1
+    issue_tile(kt + kStages - 1, id_next);
+    id_next = tab_lds[group(kt + kStages) >> hsh];
+  };
+  auto step = [&](int kt) {
+    const uint8_t* buf = smem + (kt % kStages) * kStage;
+    vec kf[3][2];
+    load_k(kf[0], buf, 0);
+    load_k(kf[1], buf, 1);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) S[0][i] = S[1][i] = 0.f;
-      const uint8_t* krowp = buf + krow * 256;
-      vec kf[3][2];
-      auto load_k = [&](int kk) {
-        const int coff = ((2 * kk + hf) ^ a_swz) << 4;
-        kf[kk % 3][0] = as_vec<vec>(*reinterpret_cast<const u32x4*>(krowp + coff));
-        kf[kk % 3][1] = as_vec<vec>(*reinterpret_cast<const u32x4*>(krowp + 32 * 256 + coff));
-      };
-      load_k(0);
-      load_k(1);
+    for (int q = 0; q < 8; ++q) {
+      if (q < 6) load_k(kf[(q + 2) % 3], buf, q + 2);
+      score(kf[q % 3], q);
+      if (q == 3) request(kt);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    vec vf[3][2];                                      // on their way while the weights are computed
+    load_v(vf[0], buf, 0);
+    load_v(vf[1], buf, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    mask(kt);
+    raise();
+    const float mc[2] = {mrow[0] * c, mrow[1] * c};
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        if (kk + 2 < 8) load_k(kk + 2);
-        S[0] = M::mfma(kf[kk % 3][0], qf[kk], S[0]);
-        S[1] = M::mfma(kf[kk % 3][1], qf[kk], S[1]);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+    for (int q = 0; q < 4; ++q) weights(q & 1, q >> 1, mc[q & 1]);
 #pragma unroll
-      for (int kk = 0; kk < 6; ++kk) {
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      // ---- first V^T fragments: on their way while the weights are computed
-      vec vf[3][2];
-      auto load_v = [&](int s) {                       // step s: block s/2, channel tiles 2(s%2), 2(s%2)+1
-        const int b = s >> 1, d0 = 2 * (s & 1);
-        vf[s % 3][0] = as_vec<vec>(*reinterpret_cast<const u32x4*>(buf + b * 4096 + voff[d0]));
-        vf[s % 3][1] = as_vec<vec>(*reinterpret_cast<const u32x4*>(buf + b * 4096 + voff[d0 + 1]));
-      };
-      load_v(0);
-      load_v(1);
-      __builtin_amdgcn_sched_barrier(0);
-      // ---- causal mask on the tiles that reach past the first row's position
-      if (BN * kt + BN - 1 > wave_min_pos) {
+    for (int q = 0; q < 8; ++q) {
+      if (q < 6) load_v(vf[(q + 2) % 3], buf, q + 2);
 #pragma unroll
-        for (int st = 0; st < 2; ++st) {
-          const int thr = prow - (BN * kt + 32 * st + 8 * hf);
+      for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int off = 16 * (i / 8) + 4 * ((i / 4) % 2) + (i % 4);
-            S[st][i] = off <= thr ? S[st][i] : -INFINITY;
-          }
-        }
-      }
-      // ---- online softmax, one row per lane (both lane halves hold the same row)
-      float tmax = S[0][0];
+        for (int j = 0; j < 2; ++j)
+          O[2 * (q & 3) + i][j] = M::mfma(vf[q % 3][i], Pw[j][q >> 2], O[2 * (q & 3) + i][j]);
+    }
+    // the first weights, then three of the others' instructions between two products
+    __builtin_amdgcn_sched_group_barrier(0x002, 40, 0);
 #pragma unroll
-      for (int st = 0; st < 2; ++st)
+    for (int q = 0; q < 8; ++q) {
+      if (q < 6) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, S[st][i]);
-      {
-        // exchange between the lane halves: after the swap one register holds the lower half's value
-        // in both halves, the other the upper half's
-        const u32x2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(tmax), __float_as_uint(tmax), false, false);
-        tmax = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-      }
-      // The running maximum is only raised when some row of the wave has outgrown it by more
-      // than 2^8: until then the weights are taken relative to the old maximum (they stay below
-      // 256, exact in fp32 and well inside the 16-bit range), which spares the rescaling of the
-      // 64 accumulator registers on almost every tile.
-      if (__builtin_amdgcn_ballot_w64((tmax - mrow) * c > 8.f)) {
-        const float m_new = fmaxf(mrow, tmax);
-        const float alpha = __builtin_amdgcn_exp2f((mrow - m_new) * c);
-        mrow = m_new;
-        lsum *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) O[dt][i] *= alpha;
-      }
-      const float mc = mrow * c;
-      vec pb[2][2];
-#pragma unroll
-      for (int st = 0; st < 2; ++st) {
-        float p[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(S[st][i], c, -mc));
-        // the row sum is taken over the rounded weights, the ones the second product uses
-        pb[st][0] = M::pack(p, lsum);
-        pb[st][1] = M::pack(p + 8, lsum);
-      }
-      // ---- O^T += V^T P^T, one pool block (16 keys) per instruction, V^T fragments two steps ahead
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        if (s + 2 < 8) load_v(s + 2);
-        const int b = s >> 1, d0 = 2 * (s & 1);
-        O[d0] = M::mfma(vf[s % 3][0], pb[b >> 1][b & 1], O[d0]);
-        O[d0 + 1] = M::mfma(vf[s % 3][1], pb[b >> 1][b & 1], O[d0 + 1]);
+      for (int i = 0; i < 4; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
       }
     }
+  };
+  // slots at or past the sequence's length hold arbitrary bits: zero them so that a zero weight
+  // times such a value cannot turn into NaN (only the last tile of a sequence needs it)
+  auto clear_past_end = [&](int kt) {
+    if (BN * kt + BN <= L) return;
+    uint8_t* buf = smem + (kt % kStages) * kStage;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int ci = tid + 512 * j;
+      const int u = ci >> 8, vd = (ci & 255) >> 1, vh = (ci & 1) ^ v_swz(vd);
+      const int pos0 = BN * kt + BT * u + 8 * vh;
+      if (pos0 + 8 > L) {
+        u32x4* slot = reinterpret_cast<u32x4*>(buf + kTile + ci * 16);
+        u32x4 v = *slot;
+        uint16_t e[8];
+        __builtin_memcpy(e, &v, 16);
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+          if (pos0 + s >= L) e[s] = 0;
+        __builtin_memcpy(&v, e, 16);
+        *slot = v;
+      }
+    }
+    __syncthreads();
+  };
+
+  // tile kt has landed (this wave's part: all but the 4 loads of tile kt + 1 are complete), and after
+  // the barrier so has everybody's; everybody is also done with tile kt - 1, whose stage is refilled next
+  auto enter = [&](int kt) {
+    __builtin_amdgcn_s_waitcnt(kWaitTile);
+    __syncthreads();
+    clear_past_end(kt);
+  };
+  int kt = 0;
+  for (; kt <= kt_last; ++kt) {
+    enter(kt);
+    step(kt);
+  }
+  for (; kt < n_tiles; ++kt) {                         // tiles that only the other waves have keys in
+    enter(kt);
+    request(kt);
   }
   __builtin_amdgcn_s_waitcnt(kWaitVm0);                // the look-ahead loads past the last tile must land before the LDS is released
 
-  // ---- normalise and store: lane (row, half) holds channels 32dt + 8q + 4hf + (0..3)
+  // ---- normalise and store: lane (row lr of tile j, quarter lh) holds channels 16 ct + 4 lh + (0..3)
   if (wave_active) {
-    const u32x2 sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum), __float_as_uint(lsum), false, false);
-    const float inv = 1.f / (__uint_as_float(sw[0]) + __uint_as_float(sw[1]));
-    if (rvalid) {
-      uint16_t* op = reinterpret_cast<uint16_t*>(a.out) + rowoff;
 #pragma unroll
-      for (int dt = 0; dt < 4; ++dt)
+    for (int j = 0; j < 2; ++j) {
+      float l = lsum[j];
+      l += __shfl_xor(l, 16);
+      l += __shfl_xor(l, 32);
+      const float inv = 1.f / l;
+      if (wrow0 + 16 * j + lr >= row_end) continue;
+      uint16_t* op = reinterpret_cast<uint16_t*>(a.out) + rowoff[j] + 4 * lh;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          uint16_t o4[4];
+      for (int ct = 0; ct < 8; ++ct) {
+        uint16_t o4[4];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) o4[r] = M::out(O[dt][4 * q + r] * inv);
-          uint2 w;
-          __builtin_memcpy(&w, o4, 8);
-          *reinterpret_cast<uint2*>(op + 32 * dt + 8 * q + 4 * hf) = w;
-        }
+        for (int i = 0; i < 4; ++i) o4[i] = M::out(O[ct][j][i] * inv);
+        uint2 w;
+        __builtin_memcpy(&w, o4, 8);
+        *reinterpret_cast<uint2*>(op + 16 * ct) = w;
+      }
     }
   }
 }

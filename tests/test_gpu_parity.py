@@ -585,6 +585,56 @@ def test_single_token_attention_at_the_edges_of_groups_tiles_and_pieces(dtype, b
         assert bool((err <= bound[~inf] + 1e-7).all()), (c, float(err.max()))
 
 
+@pytest.mark.parametrize("dtype,bt,heads,kv,seqs", [
+    # (prefix, new): one key tile and its neighbours, one row tile of a wave (16 rows) and of a workgroup (256) and theirs
+    ("f16", 16, 2, 2, ((0, 8), (0, 15), (0, 17), (0, 63), (0, 64), (0, 65), (1, 31), (47, 33), (63, 256), (64, 257))),
+    ("bf16", 16, 16, 2, ((0, 5), (59, 5), (60, 5), (120, 9), (511, 32), (500, 33))),           # 8 rows per token
+    ("bf16", 32, 3, 3, ((0, 33), (31, 95), (32, 96), (129, 130), (190, 300))),
+    ("f16", 32, 10, 2, ((0, 7), (700, 26), (13, 52))),                                         # 5 rows per token
+])
+def test_tiled_attention_at_the_edges_of_tiles(dtype, bt, heads, kv, seqs):
+    """New tokens over prefixes around the edges of key tiles (64 positions), the row tiles of a wave and of a workgroup.
+    Slots past a sequence's end hold NaN."""
+    d, G = 128, heads // kv
+    rng = np.random.default_rng(17 + heads + bt)
+    n_blk = [(p + n + bt - 1) // bt for p, n in seqs]
+    ids = rng.permutation(sum(n_blk)).astype(np.int32)
+    tables = np.full((len(seqs), max(n_blk)), -1, np.int32)
+    at = 0
+    for i, k in enumerate(n_blk):
+        tables[i, :k] = ids[at:at + k]
+        at += k
+    cu = np.concatenate([[0], np.cumsum([n for _, n in seqs])]).astype(np.int32)
+    prefix = np.array([p for p, _ in seqs], np.int32)
+    tt = torch.float16 if dtype == "f16" else torch.bfloat16
+    K, V = (torch.from_numpy(rng.standard_normal((at, kv, bt, d)).astype(np.float32)).to(tt) for _ in range(2))
+    V = V.transpose(2, 3).contiguous()                          # [block, kv head, channel, slot]
+    for i, (p, n) in enumerate(seqs):
+        if (p + n) % bt:
+            K[tables[i, n_blk[i] - 1], :, (p + n) % bt:] = float("nan")
+            V[tables[i, n_blk[i] - 1], :, :, (p + n) % bt:] = float("nan")
+    q = torch.from_numpy(rng.standard_normal((int(cu[-1]), heads, d)).astype(np.float32)).to(tt)
+    dev = torch.cat([K.reshape(at, -1), V.reshape(at, -1)], 1).contiguous().cuda()
+    pool = flpool.Pool(dtype, kv, d, at, 0, block_tokens=bt, dev=dev)
+    out = torch.empty_like(q, device="cuda")
+    pool.paged_prefix_attention(q.cuda(), out, cu, prefix, torch.from_numpy(tables).cuda(), heads)
+    got = out.cpu().double()
+    u = 2.0 ** -11 if dtype == "f16" else 2.0 ** -8
+    for i, (p, n) in enumerate(seqs):
+        tab = torch.from_numpy(tables[i, :n_blk[i]].astype(np.int64))
+        k = K[tab].double().permute(1, 0, 2, 3).reshape(kv, -1, d)[:, :p + n].repeat_interleave(G, 0)
+        v = V[tab].double().permute(1, 0, 3, 2).reshape(kv, -1, d)[:, :p + n].repeat_interleave(G, 0)
+        s = torch.matmul(q[cu[i]:cu[i + 1]].double().transpose(0, 1), k.transpose(1, 2)) / d ** 0.5      # [head, row, key]
+        s = s.masked_fill(torch.arange(p + n)[None, None] > p + torch.arange(n)[None, :, None], float("-inf"))
+        w = torch.softmax(s, 2)
+        want, size = torch.matmul(w, v).transpose(0, 1), torch.matmul(w, v.abs()).transpose(0, 1)
+        # the result's rounding, that of the 16-bit weights and of their sum, and fp16 weights below the normal range (their
+        # sum is at least 1, so each is off by at most 2^-25 of it), plus 32-bit sums
+        bound = u * want.abs() + (2 * u + 2.0 ** -15) * size + 2.0 ** -25 * v.abs().sum(1)[None]
+        err = (got[cu[i]:cu[i + 1]] - want).abs()
+        assert bool((err <= bound).all()), (p, n, float((err / bound).max()))
+
+
 def _single_tokens(dtype, ctx, q, K, V):
     """Attention of one new token per sequence of `ctx` positions: q [seqs, heads, d], K and V [seqs, heads, ctx, d] in
     the pool's type.  Returns the result and, in fp64, the weights' sum with V and with |V|."""
