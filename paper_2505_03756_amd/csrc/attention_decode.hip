@@ -90,8 +90,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
   if (g >= a.n_kv) return;                             // waves share nothing: no barrier below
   const int lr = lane & 15, lh = lane >> 4;
   const int G = a.n_h / a.n_kv;
-  const int t = a.cu_new[u.seq] + u.j0;
-  const int ctx = a.prefix_len[u.seq] + u.j0 + 1;      // positions 0 .. ctx - 1 are visible
+  const int t = u.t, ctx = u.ctx;                      // positions 0 .. ctx - 1 are visible
   const int g_lo = u.g_lo, g_hi = u.g_hi;              // this piece: groups [g_lo, g_hi) of 16 positions
   const int lim = BT * g_hi < ctx ? BT * g_hi : ctx;
   const int bt = a.bt, hsh = bt / BT - 1;              // a block holds 1 << hsh groups
@@ -263,8 +262,8 @@ __global__ __launch_bounds__(256, 2) void attn_decode_kernel(FlpAttnArgs a, cons
   l += __shfl_xor(l, 32);
   if (lr >= G) return;
   // lane (row lr, quarter lh) holds channels 16 ct + 4 lh + (0..3)
-  if (u.n_split > 1) {
-    float* pp = a.partials + ((int64_t)(u.part_row + u.split) * a.n_h + h) * (D + 2);
+  if (u.part >= 0) {
+    float* pp = a.partials + ((int64_t)u.part * a.n_h + h) * (D + 2);
     if (lh == 0) *reinterpret_cast<float2*>(pp) = make_float2(m, l);
 #pragma unroll
     for (int ct = 0; ct < 8; ++ct) {

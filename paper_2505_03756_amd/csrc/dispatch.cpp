@@ -62,33 +62,7 @@ flp_status check_attn_batch(const flp_pool* p, const flp_attn_batch* b, bool nee
   return FLP_OK;
 }
 
-// device copies of cu_new / prefix_len plus a unit list, in one staging slot
-struct StagedSeqs {
-  FlpStageSlot* slot = nullptr;
-  const int32_t* cu_new = nullptr;
-  const int32_t* prefix_len = nullptr;
-  const void* units = nullptr;
-};
-
-flp_status stage_seqs(flp_pool* p, const flp_attn_batch* b, const void* units, size_t unit_bytes, hipStream_t stream,
-                      StagedSeqs* out) {
-  const size_t S = (size_t)b->n_seqs;
-  const size_t off_pl = (S + 1) * 4, off_units = ((off_pl + S * 4 + 31) / 32) * 32;
-  const size_t bytes = off_units + unit_bytes;
-  FLP_TRY(flp_stage_acquire(p, bytes, &out->slot));
-  uint8_t* h = (uint8_t*)out->slot->host;
-  memcpy(h, b->cu_new, (S + 1) * 4);
-  memcpy(h + off_pl, b->prefix_len, S * 4);
-  if (unit_bytes) memcpy(h + off_units, units, unit_bytes);
-  FLP_TRY(flp_stage_upload(out->slot, bytes, stream));
-  const uint8_t* d = (const uint8_t*)out->slot->dev;
-  out->cu_new = (const int32_t*)d;
-  out->prefix_len = (const int32_t*)(d + off_pl);
-  out->units = d + off_units;
-  return FLP_OK;
-}
-
-FlpAttnArgs make_args(const flp_pool* p, const flp_attn_batch* b, const StagedSeqs& st) {
+FlpAttnArgs make_args(const flp_pool* p, const flp_attn_batch* b) {
   FlpAttnArgs a{};
   a.pool = p->dev_base;
   a.block_elems = p->block_elems;
@@ -101,14 +75,13 @@ FlpAttnArgs make_args(const flp_pool* p, const flp_attn_batch* b, const StagedSe
   a.out = b->out;
   a.k_new = b->k_new;
   a.v_new = b->v_new;
-  a.cu_new = st.cu_new;
-  a.prefix_len = st.prefix_len;
   float sc = b->sm_scale > 0.f ? b->sm_scale : 1.0f / std::sqrt((float)p->cfg.head_dim);
   a.scale_log2e = sc * 1.4426950408889634f;
   return a;
 }
 
-flp_status append_locked(flp_pool* p, const flp_attn_batch* b, hipStream_t stream) {
+// the append step of a batch, a unit per 16-position group that gets new slots
+std::vector<FlpAppendUnit> append_units(const flp_attn_batch* b) {
   const int bt = 16;                                 // the kernel's unit is a group of 16 positions, whatever the block size
   std::vector<FlpAppendUnit> units;
   for (int32_t i = 0; i < b->n_seqs; ++i) {
@@ -125,14 +98,7 @@ flp_status append_locked(flp_pool* p, const flp_attn_batch* b, hipStream_t strea
       pos += u.s1 - u.s0;
     }
   }
-  if (units.empty()) return FLP_OK;
-  StagedSeqs st;
-  FLP_TRY(stage_seqs(p, b, units.data(), units.size() * sizeof(FlpAppendUnit), stream, &st));
-  FlpAttnArgs a = make_args(p, b, st);
-  flp_status s1 = flp_launch_kv_append(p->cfg.dtype, p->cfg.head_dim, a, (const FlpAppendUnit*)st.units,
-                                       (int32_t)units.size(), stream);
-  flp_status s2 = flp_stage_release(st.slot, stream);
-  return s1 != FLP_OK ? s1 : s2;
+  return units;
 }
 
 }  // namespace
@@ -140,7 +106,15 @@ flp_status append_locked(flp_pool* p, const flp_attn_batch* b, hipStream_t strea
 extern "C" flp_status flp_kv_append(flp_pool* p, const flp_attn_batch* b, void* hip_stream) {
   FLP_TRY(check_attn_batch(p, b, false, true, "flp_kv_append"));
   std::lock_guard<std::mutex> lk(p->mu);
-  return append_locked(p, b, (hipStream_t)hip_stream);
+  const std::vector<FlpAppendUnit> units = append_units(b);
+  if (units.empty()) return FLP_OK;
+  FlpStageSlot* slot = nullptr;
+  FLP_TRY(flp_stage_acquire(p, units.size() * sizeof(FlpAppendUnit), &slot));
+  memcpy(slot->host, units.data(), units.size() * sizeof(FlpAppendUnit));
+  flp_status s1 = flp_launch_kv_append(p->cfg.dtype, p->cfg.head_dim, make_args(p, b), (const FlpAppendUnit*)slot->host,
+                                       (int32_t)units.size(), nullptr, nullptr, 0, (hipStream_t)hip_stream);
+  flp_status s2 = flp_stage_release(slot, (hipStream_t)hip_stream);
+  return s1 != FLP_OK ? s1 : s2;
 }
 
 extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_batch* b, void* hip_stream) {
@@ -148,7 +122,6 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   FLP_TRY(check_attn_batch(p, b, true, with_append, "flp_paged_prefix_attention"));
   std::lock_guard<std::mutex> lk(p->mu);
   hipStream_t stream = (hipStream_t)hip_stream;
-  if (with_append) FLP_TRY(append_locked(p, b, stream));
 
   // Three kinds of work.  On a 16-bit pool with head_dim 128, sequences with at least 8 query rows per kv head (prefill,
   // or decode under grouped-query attention) go to the tiled matrix-core kernel in tiles of 256 rows, and the others
@@ -241,7 +214,7 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
         const int ns = decode_ok ? (int)std::min<int64_t>(kMaxSplit, (groups + piece - 1) / piece)
                                  : std::max(1, std::min(want_split, groups / kMinGroups));
         if (ns == 1) {
-          units.push_back(FlpAttnUnit{i, j, 1, 1, 0, 0, groups, 0});
+          units.push_back(FlpAttnUnit{i, b->cu_new[i] + j, 1, b->prefix_len[i] + j + 1, 0, groups, -1, 0});
           cost.push_back(groups);
           continue;
         }
@@ -250,13 +223,13 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
         merge_first.push_back(row + ns);
         for (int sidx = 0; sidx < ns; ++sidx) {
           const int32_t lo = (int32_t)((int64_t)groups * sidx / ns), hi = (int32_t)((int64_t)groups * (sidx + 1) / ns);
-          units.push_back(FlpAttnUnit{i, j, 1, ns, sidx, lo, hi, row});
+          units.push_back(FlpAttnUnit{i, b->cu_new[i] + j, 1, b->prefix_len[i] + j + 1, lo, hi, row + sidx, 0});
           cost.push_back(hi - lo);
         }
       }
     } else {
       for (int32_t j0 = 0; j0 < n; j0 += kTokPerUnit) {
-        FlpAttnUnit u{i, j0, std::min(kTokPerUnit, n - j0), 1, 0, 0, 0, 0};
+        FlpAttnUnit u{i, b->cu_new[i] + j0, std::min(kTokPerUnit, n - j0), b->prefix_len[i] + j0 + 1, 0, 0, -1, 0};
         units.push_back(u);
         cost.push_back((int64_t)u.n_tok * (b->prefix_len[i] + j0 + u.n_tok));
       }
@@ -270,42 +243,56 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   const size_t n_items = qmax * 8;
   if (units.empty() && n_items == 0) return FLP_OK;
 
-  const size_t units_bytes = units.size() * sizeof(FlpAttnUnit), items_bytes = n_items * sizeof(FlpMfmaItem);
-  const size_t n_merge = merge_tok.size();
-  std::vector<uint8_t> blob(units_bytes + items_bytes + (2 * n_merge + 1) * sizeof(int32_t));
-  FlpAttnUnit* hu = (FlpAttnUnit*)blob.data();
-  for (size_t k = 0; k < order.size(); ++k) hu[k] = units[order[k]];
-  FlpMfmaItem* hi = (FlpMfmaItem*)(blob.data() + units_bytes);
-  for (size_t s = 0; s < qmax; ++s)
-    for (int x = 0; x < 8; ++x) hi[8 * s + x] = s < queue[x].size() ? queue[x][s] : FlpMfmaItem{0, 0, 0, 0};
-  if (n_merge) {
-    int32_t* hm = (int32_t*)(blob.data() + units_bytes + items_bytes);
-    memcpy(hm, merge_tok.data(), n_merge * sizeof(int32_t));
-    memcpy(hm + n_merge, merge_first.data(), (n_merge + 1) * sizeof(int32_t));
-  }
   void* partials = nullptr;
+  const size_t n_merge = merge_tok.size();
   if (n_merge)
     FLP_TRY(flp_attn_workspace(p, (size_t)merge_first.back() * b->n_q_heads * (p->cfg.head_dim + 2) * sizeof(float), stream,
                                &partials));
-
-  StagedSeqs st;
-  FLP_TRY(stage_seqs(p, b, blob.data(), blob.size(), stream, &st));
-  FlpAttnArgs a = make_args(p, b, st);
+  // one staging slot: the append step's units, read from pinned memory, then what is copied to the device beside the append
+  // step: the lists of the attention launches and, for the tiled kernel, the sequences' lengths
+  const std::vector<FlpAppendUnit> append = with_append ? append_units(b) : std::vector<FlpAppendUnit>{};
+  const size_t S = (size_t)b->n_seqs;
+  const auto up = [](size_t n) { return (n + 31) & ~(size_t)31; };
+  const size_t off_units = up(append.size() * sizeof(FlpAppendUnit)), off_items = off_units + units.size() * sizeof(FlpAttnUnit);
+  const size_t off_merge = off_items + n_items * sizeof(FlpMfmaItem), off_cu = off_merge + (2 * n_merge + 1) * sizeof(int32_t);
+  const size_t off_pl = off_cu + (S + 1) * sizeof(int32_t), bytes = n_items ? off_pl + S * sizeof(int32_t) : off_cu;
+  FlpStageSlot* slot = nullptr;
+  FLP_TRY(flp_stage_acquire(p, up(bytes), &slot));
+  uint8_t* const h = (uint8_t*)slot->host;
+  const uint8_t* const d = (const uint8_t*)slot->dev;
+  if (!append.empty()) memcpy(h, append.data(), append.size() * sizeof(FlpAppendUnit));
+  FlpAttnUnit* hu = (FlpAttnUnit*)(h + off_units);
+  for (size_t k = 0; k < order.size(); ++k) hu[k] = units[order[k]];
+  FlpMfmaItem* hi = (FlpMfmaItem*)(h + off_items);
+  for (size_t s = 0; s < qmax; ++s)
+    for (int x = 0; x < 8; ++x) hi[8 * s + x] = s < queue[x].size() ? queue[x][s] : FlpMfmaItem{0, 0, 0, 0};
+  if (n_merge) memcpy(h + off_merge, merge_tok.data(), n_merge * sizeof(int32_t));
+  memcpy(h + off_merge + n_merge * sizeof(int32_t), merge_first.data(), (n_merge + 1) * sizeof(int32_t));
+  if (n_items) {
+    memcpy(h + off_cu, b->cu_new, (S + 1) * sizeof(int32_t));
+    memcpy(h + off_pl, b->prefix_len, S * sizeof(int32_t));
+  }
+  FlpAttnArgs a = make_args(p, b);
   a.partials = (float*)partials;
-  const FlpAttnUnit* du = (const FlpAttnUnit*)st.units;
-  const FlpMfmaItem* di = (const FlpMfmaItem*)((const uint8_t*)st.units + units_bytes);
-  const int32_t* dm = (const int32_t*)((const uint8_t*)st.units + units_bytes + items_bytes);
-  flp_status s0 = flp_launch_attn_mfma(p->cfg.dtype, a, di, (int32_t)n_items, stream);
-  flp_status s1 = decode_ok ? flp_launch_attn_decode(p->cfg.dtype, a, du, (int32_t)units.size(), stream)
-                            : flp_launch_attn_rows(p->cfg.dtype, p->cfg.head_dim, a, du, (int32_t)units.size(), stream);
-  flp_status s3 = s1 == FLP_OK ? flp_launch_attn_merge(p->cfg.dtype, p->cfg.head_dim, a, dm, dm + n_merge,
-                                                        (int32_t)n_merge, stream) : FLP_OK;
-  flp_status s2 = flp_stage_release(st.slot, stream);
-  if (n_merge && s2 == FLP_OK) {
-    p->attn_slot = st.slot;
+  a.cu_new = (const int32_t*)(d + off_cu);
+  a.prefix_len = (const int32_t*)(d + off_pl);
+  const FlpAttnUnit* du = (const FlpAttnUnit*)(d + off_units);
+  const FlpMfmaItem* di = (const FlpMfmaItem*)(d + off_items);
+  const int32_t* dm = (const int32_t*)(d + off_merge);
+  flp_status st = flp_launch_kv_append(p->cfg.dtype, p->cfg.head_dim, a, (const FlpAppendUnit*)h, (int32_t)append.size(),
+                                       h + off_units, (uint8_t*)slot->dev + off_units, bytes - off_units, stream);
+  if (st == FLP_OK) st = flp_launch_attn_mfma(p->cfg.dtype, a, di, (int32_t)n_items, stream);
+  if (st == FLP_OK)
+    st = decode_ok ? flp_launch_attn_decode(p->cfg.dtype, a, du, (int32_t)units.size(), stream)
+                   : flp_launch_attn_rows(p->cfg.dtype, p->cfg.head_dim, a, du, (int32_t)units.size(), stream);
+  if (st == FLP_OK)
+    st = flp_launch_attn_merge(p->cfg.dtype, p->cfg.head_dim, a, dm, dm + n_merge, (int32_t)n_merge, stream);
+  const flp_status released = flp_stage_release(slot, stream);
+  if (n_merge && released == FLP_OK) {
+    p->attn_slot = slot;
     p->attn_stream = stream;
   }
-  return s0 != FLP_OK ? s0 : (s1 != FLP_OK ? s1 : (s3 != FLP_OK ? s3 : s2));
+  return st != FLP_OK ? st : released;
 }
 
 // ------------------------------------------------------------------------------- LoRA

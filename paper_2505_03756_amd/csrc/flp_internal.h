@@ -126,11 +126,11 @@ flp_status flp_launch_stage_copy(const void* src_pinned, void* dst_dev, size_t b
 struct FlpAppendUnit {   // the slots [s0, s1) of the 16-position group `blk_idx` of sequence `seq`
   int32_t seq, blk_idx, s0, s1, t_first, pad0, pad1, pad2;
 };
-struct FlpAttnUnit {     // new tokens [j0, j0+n_tok) of sequence `seq`
-  int32_t seq, j0, n_tok;
-  // split-KV (long contexts): with n_split > 1 the unit is ONE token and covers only the 16-position groups
-  // [g_lo, g_hi) of its context; its unnormalised result is piece part_row + split of the partials buffer
-  int32_t n_split, split, g_lo, g_hi, part_row;
+struct FlpAttnUnit {     // new tokens t .. t + n_tok - 1 of sequence `seq`; positions 0 .. ctx - 1 are visible to the first one
+  int32_t seq, t, n_tok, ctx;
+  // part >= 0 (split-KV, long contexts): the unit is ONE token and its unnormalised result is piece `part` of the
+  // partials buffer.  The unit covers the 16-position groups [g_lo, g_hi) of the context (row kernel: only where it is split)
+  int32_t g_lo, g_hi, part, pad;
 };
 
 struct FlpMfmaItem {     // query rows [r0, r0+n_rows) of (sequence, kv head g); n_rows == 0: padding
@@ -154,8 +154,10 @@ struct FlpAttnArgs {
   float* partials;             // split-KV: [piece][n_h][head_dim + 2] fp32 (running max, sum, channels)
 };
 
-flp_status flp_launch_kv_append(int dtype, int head_dim, const FlpAttnArgs& a, const FlpAppendUnit* units_dev,
-                                int32_t n_units, hipStream_t stream);
+// The append units are read where they were staged, in pinned host memory; beside them the launch copies copy_bytes (a
+// multiple of 16) of the attention call's lists from pinned memory to their device mirror.
+flp_status flp_launch_kv_append(int dtype, int head_dim, const FlpAttnArgs& a, const FlpAppendUnit* units_host,
+                                int32_t n_units, const void* copy_src, void* copy_dst, size_t copy_bytes, hipStream_t stream);
 flp_status flp_launch_attn_rows(int dtype, int head_dim, const FlpAttnArgs& a, const FlpAttnUnit* units_dev,
                                 int32_t n_units, hipStream_t stream);
 // single new tokens on the matrix cores: 16-bit pools, head_dim 128, n_h / n_kv <= kDecodeMaxGroup; every unit is ONE token

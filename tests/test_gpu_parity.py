@@ -93,6 +93,43 @@ def test_kv_append_bit_exact(case):
     assert np.array_equal(g.dev_image().view(np.uint8), ref.view(np.uint8))
 
 
+@pytest.mark.parametrize("dtype,bt,kv,d", [("f16", 16, 2, 128), ("bf16", 32, 17, 128), ("f32", 16, 4, 64), ("f16", 32, 3, 64),
+                                           ("f32", 32, 9, 128)])
+def test_append_of_units_of_every_length(dtype, bt, kv, d):
+    """1 .. 17 new tokens at every offset of a group of 16 positions: units of every length, short ones whose slots are
+    written one by one and longer ones whose runs are merged, in rows of less and more than one workgroup's width.  Bit for
+    bit, the slots around them included; once as the append call and once in front of the attention step."""
+    rng = np.random.default_rng(3)
+    st = np.float32 if dtype == "f32" else np.uint16
+    seqs = [(p, n) for p in range(0, 18) for n in (1, 2, 3, 4, 5, 15, 16, 17)]
+    nb = [(p + n + bt - 1) // bt for p, n in seqs]
+    tables = np.full((len(seqs), max(nb)), -1, np.int32)
+    ids = rng.permutation(sum(nb)).astype(np.int32)
+    at = 0
+    for i, k in enumerate(nb):
+        tables[i, :k] = ids[at:at + k]
+        at += k
+    cu = np.concatenate([[0], np.cumsum([n for _, n in seqs])]).astype(np.int32)
+    prefix = np.array([p for p, _ in seqs], np.int32)
+    rand = lambda shape: rng.standard_normal(shape).astype(np.float32) if dtype == "f32" else \
+        rng.integers(0, 0x3c00, shape).astype(np.uint16)                           # finite in either 16-bit type
+    pool0, k, v, q = rand((at, 2 * bt * kv * d)), rand((int(cu[-1]), kv * d)), rand((int(cu[-1]), kv * d)), rand((int(cu[-1]), kv * d))
+    want = pool0.copy()
+    oracle.kv_append(want, dtype, bt, kv, d, cu, prefix, tables, k, v)
+    up = lambda a: torch.from_numpy(a if dtype == "f32" else a.view(np.int16)).cuda()
+    for attend in (False, True):
+        dev = up(pool0.copy())
+        pool = flpool.Pool(dtype, kv, d, at, 0, block_tokens=bt, dev=dev)
+        if attend:
+            pool.paged_prefix_attention(up(q), torch.empty_like(up(q)), cu, prefix, torch.from_numpy(tables).cuda(),
+                                        kv, k_new=up(k), v_new=up(v))
+        else:
+            pool.kv_append(up(k), up(v), cu, prefix, torch.from_numpy(tables).cuda())
+        torch.cuda.synchronize()
+        assert np.array_equal(dev.cpu().numpy().view(st).view(np.uint8), want.view(np.uint8)), attend
+        pool.close()
+
+
 def test_attention_matches_oracle(case):
     step, cfg = case, case.cfg
     dev0 = resident_pool(step)       # fresh blocks hold NaN patterns until the append fills their slots
