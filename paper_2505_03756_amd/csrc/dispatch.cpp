@@ -424,11 +424,9 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
   hipStream_t stream = (hipStream_t)hip_stream;
   const size_t T = (size_t)b->n_tokens;
 
-  // Matrix-core path for 16-bit pools when every width is a multiple of the tile widths (32 in, 64 out) and
-  // the batch is large enough for token tiles to fill (prefill); otherwise the vector-ALU
-  // kernels: fp32 pools, odd widths, and small decode batches, where a segment is a handful of
-  // tokens and the per-token kernels (measured on 256 tokens over 92 adapters: 0.11 ms against
-  // 0.20 ms for q/k/v) win because they need fewer dependent round trips per wave.
+  // Matrix-core path with tokens sorted by adapter for 16-bit pools when every width is a multiple of the tile widths (32
+  // in, 64 out) and the batch is large enough for token tiles to fill (prefill); smaller batches on the matrix cores as
+  // well, but without the sort (below); fp32 pools and odd widths on the vector-ALU kernels.
   bool mfma_ok = p->cfg.dtype != FLP_F32 && b->d_in % 32 == 0 && b->n_tokens >= 1024;
   int max_dout = 0;
   for (int q = 0; q < b->n_proj; ++q) {
@@ -493,21 +491,40 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
         one_launch = false;
       }
   wt_bytes = (wt_bytes + 255) & ~(size_t)255;
-  const size_t v_bytes = (v_elems * 4 + 255) & ~(size_t)255;
+  size_t v_bytes = (v_elems * 4 + 255) & ~(size_t)255;
   const size_t seg_bytes = ((size_t)(4 * b->n_adapters + 5) * 4 + 255) & ~(size_t)255;
   const size_t perm_bytes = (T * 4 + 255) & ~(size_t)255;
   // token -> position in segment order, adapter -> first row of its tokens in the shrink output
   const size_t inv_bytes = fused ? perm_bytes + (((size_t)b->n_adapters * 4 + 255) & ~(size_t)255) : 0;
+  // Batches of up to 1024 tokens: slices of d_in until some thousand waves are in flight.  Their intermediates are larger than
+  // the vector kernels' (slices of v, ranks in sixteens, a record per token): a batch that only fits the call's buffer without
+  // them takes those kernels, so that what a fixed buffer accepts does not depend on it.
+  FlpLoraSmall small{};
+  size_t group_bytes = 0;
+  if (!mfma_ok && p->elem_bytes == 2 && b->n_tokens <= kLoraSmallTokens && b->d_in % 64 == 0) {
+    small.n_tiles = b->max_rank <= 16 ? 1 : b->max_rank <= 32 ? 2 : 4;
+    small.k_splits = b->n_tokens <= 16 ? 16 : b->n_tokens <= 64 ? 8 : b->n_tokens <= 256 ? 4 : 2;
+    while (small.k_splits > 1 && b->d_in / 64 / small.k_splits < 4) small.k_splits /= 2;
+    const size_t v_small = ((size_t)small.k_splits * T * b->n_proj * 16 * small.n_tiles * 4 + 255) & ~(size_t)255;
+    const size_t g_small = (T * sizeof(FlpLoraGroup) + 255) & ~(size_t)255;
+    size_t total = v_small + g_small + seg_bytes + perm_bytes + wt_bytes;
+    for (int q = 0; q < b->n_proj; ++q)
+      if (b->proj[q].w_base) total += (T * b->proj[q].d_out * 4 + 255) & ~(size_t)255;
+    if (total <= budget) {
+      v_bytes = v_small;
+      group_bytes = g_small;
+    }
+  }
   // dense products that are not fused with the expand step leave their unrounded result in the workspace, in slices
   // of the contraction where the batch is small
   std::vector<BaseGroup> groups;
   size_t base_total = 0;
   if (p->elem_bytes == 2 && !fused) {
-    const size_t rest = v_bytes + seg_bytes + perm_bytes + wt_bytes;
+    const size_t rest = v_bytes + group_bytes + seg_bytes + perm_bytes + wt_bytes;
     base_total = plan_base(b, one_launch, budget > rest ? budget - rest : 0, &groups);
   }
   void* ws = nullptr;
-  const size_t ws_bytes = v_bytes + seg_bytes + perm_bytes + wt_bytes + base_total + inv_bytes;
+  const size_t ws_bytes = v_bytes + seg_bytes + perm_bytes + wt_bytes + base_total + inv_bytes + group_bytes;
   if (fixed) {
     if (ws_bytes > fixed->cap) {
       flp_set_error("%s: the batch needs %zu bytes of intermediates, the fixed buffer holds %zu (fewer tokens, a lower "
@@ -633,6 +650,10 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
       if (g.plan.splits > 1)
         FLP_TRY(flp_launch_gemm_reduce(p->cfg.dtype, b->n_tokens, g.n, out, g.plan.splits, false, true, stream));
     }
+  }
+  if (group_bytes) {
+    small.groups = (FlpLoraGroup*)(w + v_bytes + seg_bytes + perm_bytes + wt_bytes + base_total);
+    return flp_launch_lora_small(p->cfg.dtype, a, small, stream);
   }
   if (!mfma_ok) return flp_launch_lora_simple(p->cfg.dtype, a, stream);
   FLP_TRY(flp_launch_lora_segment(a.T, a.token_adapter, a.n_adapters, a.n_seg, a.seg_adapter, a.seg_start, a.perm,

@@ -217,6 +217,21 @@ struct FlpLoraMfma {
   int32_t shrink_only;         // 1: stop after the shrink step (the expand step runs inside the dense product)
 };
 
+// Batches of up to kLoraSmallTokens tokens (lora_small.hip): v is [k_splits][T][n_proj][16 n_tiles] by token, and the shrink step
+// leaves a record per token: how many tokens of its adapter it works for (0: none), which, and what the adapter is.
+constexpr int kLoraSmallTokens = 1024;
+struct FlpLoraGroup {
+  int32_t n, r;
+  float scale;
+  int32_t pad;
+  int32_t tok[16];
+  int32_t tab[FLP_MAX_PROJ], row[FLP_MAX_PROJ];      // where the projections' B lies: offset into the tables, first page row
+};
+struct FlpLoraSmall {
+  int32_t k_splits, n_tiles;   // slices of d_in; tiles of 16 ranks
+  FlpLoraGroup* groups;        // [T]
+};
+
 // What the large-batch dense product needs to add one projection's LoRA branch to its accumulators before it
 // rounds (the expand step as an epilogue: y = round(x . W + s (x A^T) B), no fp32 copy of the product, no second
 // pass over y).  v is the shrink step's output, rows in segment order: token t of adapter a sits in row
@@ -243,6 +258,7 @@ flp_status flp_launch_lora_segment(int32_t T, const int32_t* token_adapter, int3
                                    int32_t* inv_perm = nullptr, int32_t* vrow_base = nullptr);
 flp_status flp_launch_lora_mfma(int dtype, const FlpLoraArgs& a, const FlpLoraMfma& c, hipStream_t stream);
 flp_status flp_launch_lora_simple(int dtype, const FlpLoraArgs& a, hipStream_t stream);
+flp_status flp_launch_lora_small(int dtype, const FlpLoraArgs& a, const FlpLoraSmall& c, hipStream_t stream);   // d_in % 64 == 0
 
 // ---- dense products (gemm.hip): up to FLP_MAX_PROJ matrices [N, K] over one input, 16-bit types
 enum { FLP_GEMM_64x32 = 0, FLP_GEMM_128x64, FLP_GEMM_128x128, FLP_GEMM_256x128, FLP_GEMM_256x256, FLP_GEMM_KINDS };

@@ -1,0 +1,417 @@
+// Batched heterogeneous LoRA of up to kLoraSmallTokens tokens, 16-bit pools (paper Eq. 1 / Eq. 2 in row-vector form,
+// y = base + s (x A^T) B; section 2.1: tokens of different adapters share one batch; section 4.3: adapters live in pool
+// blocks as rank rows).
+//
+// In a decode batch a few tokens share each adapter and the adapters' pages are the traffic; in a single prompt all tokens
+// share one.  Either way the tokens of an adapter are taken in token order, sixteen at a time, as the sixteen columns of a
+// matrix instruction, so that a page is read once for all of them.  Who belongs together is found by every wave itself from
+// the batch's adapter ids (ballots over all of them): that costs a microsecond, a launch that sorts them costs eight.  Bound
+// by latency: a workgroup is one wave, which meets no barrier, has its loads in flight together and gives its place back at
+// once where it has nothing to do (with four waves to a workgroup the idle ones held theirs: 30 % longer at 256 tokens).
+//
+//   shrink  one wave per (sixteen tokens, projection, slice of d_in): v^T = A x^T with mfma_f32_16x16x32.  The slices'
+//           sums stay apart, the expand step adds them in order.
+//   expand  one wave per (sixteen tokens, projection, 128 columns): y^T += s B^T v^T with fp32 instructions, so that v
+//           keeps its 32 bits.  16x16x4: column 8 m + tau of the chunk is row m of tile tau (a lane reads 8 neighbouring
+//           columns of a page row and ends up with 32 neighbouring columns of one token), rank 4 k + i of a rank tile is slot k
+//           of step i.  Groups of up to four tokens take 4x4x1 instructions, a quarter of the time in the matrix pipe.
+//
+// Measured on MI355X, bf16, the q,k,v call / the o call in us, with the per-token vector kernels and with these:
+//   32 / 32 heads   256 tokens, 92 adapters of ranks 8-64     79.6 / 36.0   48.5 / 26.2
+//                   8 tokens, 8 adapters of rank 16           13.2 / 12.8   12.8 / 11.4
+//                   499 tokens of one adapter of rank 16      59.3 / 29.1   30.5 / 19.3
+//   40 / 40 heads   914 tokens of 40 sequences, rank 32        163 / 65.6   59.8 / 34.0
+//   64 / 8 heads    800 tokens of 2 sequences, rank 64         513 / 251     189 / 93.8
+//                   200 tokens, rank 64                        108 / 57.1    116 / 48.1
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "flp_internal.h"
+#include "flp_types.h"
+
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 b16x8 __attribute__((ext_vector_type(8)));
+
+struct SF16 {
+  typedef h16x8 vec;
+  typedef F16 S;
+  static __device__ __forceinline__ f32x4 mfma(vec a, vec b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+  }
+};
+struct SBF16 {
+  typedef b16x8 vec;
+  typedef BF16 S;
+  static __device__ __forceinline__ f32x4 mfma(vec a, vec b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+  }
+};
+
+// For token t of adapter ad (>= 0): the batch's tokens with the same adapter, in token order, are taken sixteen at a time and
+// the first of each sixteen works for all of them.  Returns how many tokens t works for (0: t is not a first); lane l gets
+// the index of token l % 16 of them in `tok` (t past the last one).  Wave-uniform; T <= kLoraSmallTokens.
+__device__ __forceinline__ int sixteen(const int32_t* __restrict__ token_adapter, int T, int t, int ad, int* tok) {
+  const int lane = threadIdx.x;
+  constexpr int W = kLoraSmallTokens / 64;
+  int ids[W];
+#pragma unroll
+  for (int w = 0; w < W; ++w) ids[w] = 64 * w + lane < T ? token_adapter[64 * w + lane] : -1;
+  uint64_t mask[W];
+  int before = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    mask[w] = __ballot(ids[w] == ad);
+    if (64 * w <= t) before += __popcll(t >= 64 * w + 63 ? mask[w] : mask[w] & ((1ull << (t & 63)) - 1));
+  }
+  if (t % 64 == 63) before -= 1;                       // the word's whole popcount holds t itself
+  *tok = t;
+  if (before % 16) return 0;
+  int n = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    uint64_t m = 64 * w + 63 < t ? 0 : 64 * w <= t ? mask[w] & ~((1ull << (t & 63)) - 1) : mask[w];
+    while (m && n < 16) {
+      const int i = 64 * w + __ffsll((long long)m) - 1;
+      if ((lane & 15) == n) *tok = i;
+      m &= m - 1;
+      ++n;
+    }
+  }
+  return n;
+}
+
+// M0 is named as clobbered so that no pass keeps a value of its own alive in it across the statement; the
+// compiler notes that it reserves the register, which is the point.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void sload_lds16(uint64_t addr, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(addr), "s"(lds) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+typedef __attribute__((address_space(3))) uint8_t s_lds_u8;
+
+template <typename T>
+__device__ __forceinline__ T load_global(uint64_t addr) {
+  return *reinterpret_cast<const __attribute__((address_space(1))) T*>(addr);
+}
+
+// lane rho's address (of a page row), as seen by the lane that asks for rank `from`
+__device__ __forceinline__ uint64_t address_of(const uint16_t* mine, int from) {
+  const uint64_t ad = (uint64_t)(uintptr_t)mine;
+  return (uint64_t)(uint32_t)__shfl((int)(uint32_t)ad, from) | (uint64_t)(uint32_t)__shfl((int)(ad >> 32), from) << 32;
+}
+
+// v of one group for NB tiles of 16 ranks over the chunks [c0, c1) of 64 coefficients.  The rows of x and of A travel as whole
+// 128-byte lines (8 rows per instruction) into a ring in LDS that belongs to this wave alone, so its own waits are all
+// the order it needs.  Piece j (16 bytes) of row r sits in slot j ^ ((r >> 1) & 7).  (Straight from global memory in operand
+// layout, 64 bytes of 16 rows per instruction, rows that are a multiple of 8 KiB apart met in one cache set.)
+template <typename L, int NB, int kLds>
+__device__ __forceinline__ void shrink_group(uint8_t* smem, const uint16_t* xrow, const uint16_t* arow, int tok, int64_t ld_x, int r,
+                                             int c0, int c1, int rotate, f32x4 (&v)[NB]) {
+  typedef typename L::vec vec;
+  constexpr int NPER = 2 * (1 + NB), kStage = 1024 * NPER, ST = kLds / kStage;
+  static_assert(ST >= 3, "two chunks in flight behind the one that is multiplied");
+  const int lane = threadIdx.x, m16 = lane & 15, kg = lane >> 4;
+  uint64_t addr[NPER];
+#pragma unroll
+  for (int i = 0; i < NPER; ++i) {
+    const int row = 8 * (i & 1) + (lane >> 3), piece = (lane & 7) ^ ((row >> 1) & 7);
+    if (i < 2) {
+      addr[i] = (uint64_t)(uintptr_t)(xrow + (int64_t)__shfl(tok, row) * ld_x + 8 * piece);
+    } else {
+      const int rho = 16 * (i / 2 - 1) + row;            // ranks past the adapter's read its first row, their v is zeroed
+      addr[i] = address_of(arow, rho < r ? rho : 0) + 16 * piece;
+    }
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(s_lds_u8*)smem;
+  const int n = c1 - c0;
+  // rows are often a power of two bytes apart: waves start at different chunks and wrap around, so that they do not all ask
+  // the same memory channels at the same time
+  const int start = rotate % n;
+  auto issue = [&](int c, int st) {                    // past the end: the last chunk again, into a free stage
+    int cc = (c < n ? c : n - 1) + start;
+    cc = c0 + (cc < n ? cc : cc - n);
+#pragma unroll
+    for (int i = 0; i < NPER; ++i) sload_lds16(addr[i] + (uint64_t)cc * 128, lds0 + (uint32_t)(st * kStage + 1024 * i));
+  };
+  f32x4 acc[NB][2];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) v[i] = acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");      // only chunk loads are in flight below
+#pragma unroll
+  for (int c = 0; c < ST - 1; ++c) issue(c, c);
+  const int off = m16 * 128 + ((kg ^ (m16 >> 1)) << 4);  // k step 0; step 1 is slot + 4: offset ^ 64
+  int st = 0, st_load = ST - 1;
+  for (int c = 0; c < n; ++c) {
+    // chunk c has landed, and the reads of chunk c - 1, whose stage is filled next, are done
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((ST - 2) * NPER) : "memory");
+    issue(c + ST - 1, st_load);
+    const uint8_t* buf = smem + st * kStage;
+#pragma unroll
+    for (int k2 = 0; k2 < 2; ++k2) {
+      const vec xf = *reinterpret_cast<const vec*>(buf + (off ^ (k2 << 6)));
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        acc[i][k2] = L::mfma(*reinterpret_cast<const vec*>(buf + 2048 * (1 + i) + (off ^ (k2 << 6))), xf, acc[i][k2]);
+    }
+    st = st + 1 == ST ? 0 : st + 1;
+    st_load = st_load + 1 == ST ? 0 : st_load + 1;
+    if ((c & 7) == 7 || c + 1 == n) {                  // sums of eight chunks, then of those: shorter chains of roundings
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        v[i] += acc[i][0] + acc[i][1];
+        acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the look-ahead loads must land before the LDS is released
+}
+
+// NT: tiles of 16 ranks the launch allows for
+template <typename L, int NT>
+__global__ __launch_bounds__(64) void lora_small_shrink_kernel(FlpLoraArgs a, FlpLoraSmall c) {
+  constexpr int kLds = NT == 4 ? 30 * 1024 : 24 * 1024;
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[kLds];
+  const int lane = threadIdx.x, m16 = lane & 15, kg = lane >> 4;
+  const int t = blockIdx.x;
+  const int ks = blockIdx.y % c.k_splits, p = blockIdx.y / c.k_splits;
+  FlpLoraGroup* rec = c.groups + t;
+  const bool writes = blockIdx.y == 0;                 // one of the token's waves leaves the record for the expand step
+  const int ad = __builtin_amdgcn_readfirstlane(a.token_adapter[t]);
+  int r = 0, tok = t, n = 0;
+  if (ad >= 0 && ad < a.n_adapters) {
+    r = __builtin_amdgcn_readfirstlane(a.rank[ad]);
+    r = r < a.max_rank ? r : a.max_rank;
+    n = sixteen(a.token_adapter, a.T, t, ad, &tok);
+    if (r <= 0) n = 0;
+  }
+  if (writes) {
+    if (lane < 16) rec->tok[lane] = tok;
+    if (lane == 0) {
+      rec->n = n;
+      rec->r = r;
+      rec->scale = n ? a.scale[ad] : 0.f;
+    }
+    if (n && lane < a.n_proj) {
+      rec->tab[lane] = a.proj[lane].b_tab_off[ad];
+      rec->row[lane] = a.proj[lane].b_row_base[ad];
+    }
+  }
+  if (n == 0) return;
+  const flp_lora_proj& pr = a.proj[p];
+  const int rpb = (int)(a.block_elems / a.d_in);
+  const int row = pr.a_row_base[ad] + (lane < r ? lane : 0);       // lane rho looks up the page row of rank rho
+  const uint16_t* const arow = reinterpret_cast<const uint16_t*>(a.pool) +
+                               (int64_t)a.tables[pr.a_tab_off[ad] + row / rpb] * a.block_elems + (int64_t)(row % rpb) * a.d_in;
+  const uint16_t* const x = reinterpret_cast<const uint16_t*>(a.x);
+  const int chunks = a.d_in / 64, c0 = chunks * ks / c.k_splits, c1 = chunks * (ks + 1) / c.k_splits;
+  // lane (token m16, ranks 4 kg .. 4 kg + 3 of a tile)
+  float* const vp = a.v + (((int64_t)ks * a.T + tok) * a.n_proj + p) * (16 * NT) + 4 * kg;
+  auto run = [&](auto tiles) {
+    constexpr int NB = decltype(tiles)::value;
+    f32x4 v[NB];
+    shrink_group<L, NB, kLds>(smem, x, arow, tok, a.ld_x, r, c0, c1, t + t / 16 + p, v);
+#pragma unroll
+    for (int nt = 0; nt < NB; ++nt) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[nt][i] = 16 * nt + 4 * kg + i < r ? v[nt][i] : 0.f;
+      if (m16 < n) *reinterpret_cast<f32x4*>(vp + 16 * nt) = v[nt];
+    }
+  };
+  if (NT == 1 || r <= 16)
+    run(std::integral_constant<int, 1>{});
+  else if (NT == 2 || r <= 32)
+    run(std::integral_constant<int, NT < 2 ? 1 : 2>{});
+  else
+    run(std::integral_constant<int, NT>{});
+}
+
+// Adds s * delta to 8 NP columns of a token, the unrounded base or y itself.
+template <typename S, int NP, typename F>
+__device__ __forceinline__ void add_to_y(uint16_t* yp, const float* bp, const u32x4 (&yraw)[NP], int left, float sc, F delta) {
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    if (8 * i >= left) break;
+    uint16_t y8[8];
+    if (bp) {
+      const f32x4 lo = *reinterpret_cast<const f32x4*>(bp + 8 * i), hi = *reinterpret_cast<const f32x4*>(bp + 8 * i + 4);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) y8[q] = S::from_float(fmaf(sc, delta(i, q), q < 4 ? lo[q & 3] : hi[q & 3]));
+    } else {
+      __builtin_memcpy(y8, &yraw[i], 16);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) y8[q] = S::from_float(fmaf(sc, delta(i, q), S::to_float(y8[q])));
+    }
+    u32x4 raw;
+    __builtin_memcpy(&raw, y8, 16);
+    *reinterpret_cast<u32x4*>(yp + 8 * i) = raw;
+  }
+}
+
+// the slices' sums in order, B of them requested together
+template <int B>
+__device__ __forceinline__ f32x4 sum_slices(const float* vp, int64_t slice, int n) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  for (int k = 0; k < n; k += B) {
+    f32x4 q[B];
+#pragma unroll
+    for (int i = 0; i < B; ++i) q[i] = *reinterpret_cast<const f32x4*>(vp + (k + i < n ? k + i : n - 1) * slice);
+#pragma unroll
+    for (int i = 0; i < B; ++i)
+      if (k + i < n) v += q[i];
+  }
+  return v;
+}
+
+// NT: tiles of 16 ranks the launch allows for
+template <typename L, int NT>
+__global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, FlpLoraSmall c) {
+  typedef typename L::S S;
+  __shared__ f32x4 v_lds[64 * NT / 4];                 // [token (of 4)][four ranks]
+  const int lane = threadIdx.x, m16 = lane & 15, kg = lane >> 4;
+  const int t = blockIdx.y, p = blockIdx.z;            // columns vary fastest: rows are often a power of two bytes apart
+  const flp_lora_proj& pr = a.proj[p];
+  const int col0 = blockIdx.x * 128;
+  if (col0 >= pr.d_out) return;
+  const FlpLoraGroup* __restrict__ rec = c.groups + t;
+  const int n = __builtin_amdgcn_readfirstlane(rec->n);
+  if (n == 0) return;
+  const int r = __builtin_amdgcn_readfirstlane(rec->r);
+  const int rpb = (int)(a.block_elems / pr.d_out);
+  constexpr int RP = 16 * NT;
+  // lane rho looks up the page row of rank rho
+  const int row = rec->row[p] + (lane < r ? lane : 0);
+  const uint16_t* const mine = reinterpret_cast<const uint16_t*>(a.pool) +
+                               (int64_t)a.tables[rec->tab[p] + row / rpb] * a.block_elems + (int64_t)(row % rpb) * pr.d_out;
+  const float sc = rec->scale;
+  const int64_t slice = (int64_t)a.T * a.n_proj * RP;
+  const auto v_of = [&](int tok) { return a.v + ((int64_t)tok * a.n_proj + p) * RP; };
+
+  if (n <= 4) {
+    // up to four tokens: 4x4x1 instructions, 64 columns x 4 tokens of one rank each; row l of tile q is column 2 l + q of
+    // the chunk, and a lane ends up with 8 neighbouring columns of token l % 4
+    const int tok = rec->tok[lane & 3];
+    const int f0 = col0 + 8 * (lane >> 2), fb = col0 + 2 * lane < pr.d_out ? col0 + 2 * lane : 0;
+    uint16_t* const yp = reinterpret_cast<uint16_t*>(pr.y) + (int64_t)tok * pr.ld_y + f0;
+    const float* const bp = a.base32[p] ? a.base32[p] + (int64_t)tok * pr.d_out + f0 : nullptr;
+    u32x4 yraw[1] = {u32x4{0u, 0u, 0u, 0u}};
+    if (!bp && f0 < pr.d_out) yraw[0] = *reinterpret_cast<const u32x4*>(yp);
+    if (lane < RP) {
+      const float* vp = v_of(rec->tok[lane / (RP / 4)]) + 4 * (lane % (RP / 4));
+      f32x4 v = {0.f, 0.f, 0.f, 0.f};
+      if (4 * (lane % (RP / 4)) < ((r + 15) & ~15)) v = sum_slices<8>(vp, slice, c.k_splits);
+      v_lds[lane] = v;
+    }
+    __syncthreads();                                   // one wave: order only
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    uint32_t b[NT][16];                                // all ranks' coefficients in flight together
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+      if (16 * nt < r) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const uint64_t ad = (uint64_t)(uintptr_t)mine;
+          const uint64_t base = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)ad, 16 * nt + e) |
+                                (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(ad >> 32), 16 * nt + e) << 32;
+          b[nt][e] = load_global<uint32_t>(base + 2 * fb);
+        }
+      }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      if (16 * nt >= r) break;
+#pragma unroll
+      for (int e4 = 0; e4 < 4; ++e4) {
+        const f32x4 v = v_lds[(lane & 3) * (RP / 4) + 4 * nt + e4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int e = 4 * e4 + i;
+          const uint32_t w = 16 * nt + e < r ? b[nt][e] : 0u;
+          acc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(S::to_float((uint16_t)w), v[i], acc[0], 0, 0, 0);
+          acc[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(S::to_float((uint16_t)(w >> 16)), v[i], acc[1], 0, 0, 0);
+        }
+      }
+    }
+    if ((lane & 3) < n) add_to_y<S, 1>(yp, bp, yraw, pr.d_out - f0, sc, [&](int, int q) { return acc[q & 1][q >> 1]; });
+    return;
+  }
+
+  const int tok = rec->tok[m16];
+  const float* const vp = v_of(tok) + 4 * kg;
+  f32x4 v[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    v[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (16 * nt < r) v[nt] = sum_slices<4>(vp + 16 * nt, slice, c.k_splits);
+  }
+  const int fb = col0 + 8 * m16 < pr.d_out ? col0 + 8 * m16 : 0;    // widths are multiples of 8: a lane's columns are all in or all out
+  const int f0 = col0 + 32 * kg;
+  uint16_t* const yp = reinterpret_cast<uint16_t*>(pr.y) + (int64_t)tok * pr.ld_y + f0;
+  const float* const bp = a.base32[p] ? a.base32[p] + (int64_t)tok * pr.d_out + f0 : nullptr;
+  u32x4 yraw[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) yraw[i] = !bp && f0 + 8 * i < pr.d_out ? *reinterpret_cast<const u32x4*>(yp + 8 * i) : u32x4{0u, 0u, 0u, 0u};
+  f32x4 acc[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 b[NT][4];                                    // ranks 16 nt + 4 kg + i of the lane's 8 columns
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt)
+    if (16 * nt < r) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        b[nt][i] = load_global<u32x4>(address_of(mine, 16 * nt + 4 * kg + i) + 2 * fb);
+    }
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    if (16 * nt >= r) break;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool live = 16 * nt + 4 * kg + i < r;
+      uint16_t e[8];
+      __builtin_memcpy(e, &b[nt][i], 16);
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(live ? S::to_float(e[q]) : 0.f, v[nt][i], acc[q], 0, 0, 0);
+    }
+  }
+  // lane (token m16, kg): element i of tile q is column 32 kg + 8 i + q of the chunk
+  if (m16 < n) add_to_y<S, 4>(yp, bp, yraw, pr.d_out - f0, sc, [&](int i, int q) { return acc[q][i]; });
+}
+
+template <typename L, int NT>
+void launch(const FlpLoraArgs& a, const FlpLoraSmall& c, hipStream_t stream) {
+  int max_dout = 0;
+  for (int p = 0; p < a.n_proj; ++p) max_dout = a.proj[p].d_out > max_dout ? a.proj[p].d_out : max_dout;
+  const dim3 gs((unsigned)a.T, (unsigned)(a.n_proj * c.k_splits));
+  const dim3 ge((unsigned)((max_dout + 127) / 128), (unsigned)a.T, (unsigned)a.n_proj);
+  hipLaunchKernelGGL((lora_small_shrink_kernel<L, NT>), gs, dim3(64), 0, stream, a, c);
+  hipLaunchKernelGGL((lora_small_expand_kernel<L, NT>), ge, dim3(64), 0, stream, a, c);
+}
+template <typename L>
+void launch(const FlpLoraArgs& a, const FlpLoraSmall& c, hipStream_t stream) {
+  if (c.n_tiles == 1)
+    launch<L, 1>(a, c, stream);
+  else if (c.n_tiles == 2)
+    launch<L, 2>(a, c, stream);
+  else
+    launch<L, 4>(a, c, stream);
+}
+
+}  // namespace
+
+flp_status flp_launch_lora_small(int dtype, const FlpLoraArgs& a, const FlpLoraSmall& c, hipStream_t stream) {
+  if (dtype == FLP_F32 || a.T > kLoraSmallTokens || a.d_in % 64) {
+    flp_set_error("LoRA (small batches): dtype %d, %d tokens or d_in %d not supported", dtype, a.T, a.d_in);
+    return FLP_ENOTSUP;
+  }
+  if (dtype == FLP_F16)
+    launch<SF16>(a, c, stream);
+  else
+    launch<SBF16>(a, c, stream);
+  FLP_TRY_HIP(hipGetLastError());
+  return FLP_OK;
+}

@@ -888,6 +888,60 @@ def test_dense_products_of_rows_far_apart(T, d_in, widths, ld_x, plan):
     pool.close()
 
 
+@pytest.mark.parametrize("dtype,T,d_in,widths,counts,ranks", [
+    ("bf16", 96, 64, (8, 136), (1, 4, 5, 16, 17, 33), (16, 1, 15, 8, 16, 7)),           # one chunk of d_in, ragged columns
+    ("f16", 96, 704, (128, 264, 8), (1, 4, 5, 16, 17, 33), (17, 32, 1, 31, 16, 32)),    # two tiles of ranks, 16 or fewer among them
+    ("bf16", 1024, 4096, (136,), (1, 3, 64, 500, 19, 437), (33, 64, 48, 1, 16, 49)),    # four tiles, the largest batch
+    ("f16", 3, 8192, (1032,), (3,), (64,)),                                             # sixteen slices of d_in
+])
+def test_lora_of_small_batches_in_groups_of_every_size(dtype, T, d_in, widths, counts, ranks):
+    """Adapters with 1 to 500 tokens, mixed over the batch (a group takes up to sixteen of one adapter, up to four go to
+    another form of the product), ranks at the edges of a rank tile, columns at those of a chunk; the rest of the tokens has no
+    adapter.  v keeps 32 bits: a large base-free delta is compared to within its rounding and 32-bit sums."""
+    tt = torch.float16 if dtype == "f16" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(T + d_in)
+    rnd = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(tt)
+    n_ad, E = len(ranks), 2 * 16 * 8 * 128
+    ta = np.full(T, -1, np.int32)
+    ta[np.random.default_rng(T).permutation(T)[:sum(counts)]] = np.repeat(np.arange(n_ad), counts)
+    pages, tab = [], []
+
+    def put(m):
+        off, rpb = len(tab), E // m.shape[1]
+        for lo in range(0, len(m), rpb):
+            blk = torch.full((E,), float("nan"), dtype=tt, device="cuda")
+            part = m[lo:lo + rpb].reshape(-1)
+            blk[:part.numel()] = part
+            tab.append(len(pages))
+            pages.append(blk)
+        return off
+
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    mats = [[(rnd((r, d_in), d_in ** -0.5), rnd((r, w), 1.0)) for r in ranks] for w in widths]
+    projs = [dict(d_out=w, a_tab_off=i32([put(a) for a, _ in m]), b_tab_off=i32([put(b) for _, b in m]), a_row_base=i32([0] * n_ad),
+                  b_row_base=i32([0] * n_ad)) for w, m in zip(widths, mats)]
+    x, scale = rnd((T, d_in), 1.0), torch.linspace(0.5, 1.5, n_ad, device="cuda")
+    y0 = [rnd((T, w), 2.0 ** -6) for w in widths]
+    pool = flpool.Pool(dtype, 8, 128, len(pages), 0, block_tokens=16, dev=torch.stack(pages).contiguous())
+    y = [t.clone() for t in y0]
+    pool.lora_apply_paged(x, torch.from_numpy(ta).cuda(), i32(ranks), scale, i32(tab), [dict(p, y=t) for p, t in zip(projs, y)],
+                          n_tokens=T, d_in=d_in, n_adapters=n_ad, max_rank=max(ranks))
+    for yi, y0i, m in zip(y, y0, mats):
+        want, size = y0i.double(), y0i.double().abs()
+        for a, (A, B) in enumerate(m):
+            sel = torch.from_numpy(ta == a).cuda()
+            v = float(scale[a]) * x[sel].double() @ A.double().T
+            vs = float(scale[a]) * x[sel].double().abs() @ A.double().abs().T
+            want[sel] += v @ B.double()
+            size[sel] += vs @ B.double().abs()
+        none = torch.from_numpy(ta < 0).cuda()
+        assert torch.equal(yi[none], y0i[none])
+        # the rounding of the result, and chains of at most 64 additions in 32 bits of terms that add up to `size`
+        bound = (2.0 ** -11 if dtype == "f16" else 2.0 ** -8) * want.abs() + 64 * 2.0 ** -24 * size + 1e-7
+        assert bool(((yi.double() - want).abs() <= bound).all())
+    pool.close()
+
+
 @pytest.mark.parametrize("T,widths,plan", [(2050, (1088, 320), ("256x128", 1)), (2177, (4032,), ("256x256", 1)),
                                            (4100, (1088, 1088, 320), ("256x256", 1))])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
