@@ -41,11 +41,69 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-// One wave per token row, four rows per workgroup.  Pass 1 accumulates the sum of squares (and, with
+// One workgroup per token row, for rows of up to 256 NV vectors of 16 bytes: all loads of the row (and of the delta and the
+// gains) are in flight together and the row stays in registers between the sum of squares and the scaling, so the call is
+// one trip to memory.  With a delta the rounded residual is stored and the sum is taken over it.  A batch of a few rows is
+// bound by that trip, a large one by the bytes.  The layer's three calls, with a wave per row in two passes, with this:
+//   8 rows of 4096, bf16          6.7 10.5 5.7    4.7 3.7 4.6 us
+//   9876 rows of 5120, fp16      45.8 83.8 55.8   30.8 61.1 46.4 us (6.6 TB/s in the second)
+template <typename S, int NV>
+__global__ __launch_bounds__(256) void rmsnorm_kernel(const typename S::storage* x_in, typename S::storage* resid,
+                                                      const typename S::storage* __restrict__ delta,
+                                                      const typename S::storage* __restrict__ w,
+                                                      typename S::storage* y, int H, float eps) {
+  typedef typename S::storage ST;
+  constexpr int N = Vec<S>::N;
+  __shared__ float part[4];
+  const int64_t row = (int64_t)blockIdx.x * H;
+  const int c0 = threadIdx.x * N;
+  const ST* xr = (delta ? resid : x_in) + row;
+  Vec<S> a[NV], d[NV], g[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = c0 + i * 256 * N;
+    if (c >= H) break;
+    a[i] = ldv<S>(xr + c);
+    if (delta) d[i] = ldv<S>(delta + row + c);
+    if (y) g[i] = ldv<S>(w + c);
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = c0 + i * 256 * N;
+    if (c >= H) break;
+    if (delta) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) a[i].e[j] = S::from_float(S::to_float(a[i].e[j]) + S::to_float(d[i].e[j]));
+      stv<S>(resid + row + c, a[i]);
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const float f = S::to_float(a[i].e[j]);
+      ss = fmaf(f, f, ss);
+    }
+  }
+  if (!y) return;
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  const float inv = 1.0f / sqrtf(((part[0] + part[1]) + (part[2] + part[3])) / (float)H + eps);
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int c = c0 + i * 256 * N;
+    if (c >= H) break;
+    Vec<S> o;
+#pragma unroll
+    for (int j = 0; j < N; ++j) o.e[j] = S::from_float(S::to_float(a[i].e[j]) * inv * S::to_float(g[i].e[j]));
+    stv<S>(y + row + c, o);
+  }
+}
+
+// Longer rows: one wave per token row, four rows per workgroup.  Pass 1 accumulates the sum of squares (and, with
 // a delta, stores the rounded residual it is taken over); pass 2 re-reads the row (each lane the bytes
 // it touched in pass 1: L1/L2 hits) and writes the normalised row.
 template <typename S>
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const typename S::storage* x_in, typename S::storage* resid,
+__global__ __launch_bounds__(256) void rmsnorm_long_kernel(const typename S::storage* x_in, typename S::storage* resid,
                                                       const typename S::storage* __restrict__ delta,
                                                       const typename S::storage* __restrict__ w,
                                                       typename S::storage* y, int T, int H, float eps) {
@@ -169,9 +227,19 @@ flp_status norm_common(int32_t dtype, const void* x, void* resid, const void* de
   }
   if (T == 0) return FLP_OK;
   hipStream_t st = (hipStream_t)hip_stream;
-  FLL_BY_DTYPE(dtype, hipLaunchKernelGGL(rmsnorm_kernel<S_>, dim3((T + 3) / 4), dim3(256), 0, st,
-                                         (const S_::storage*)x, (S_::storage*)resid, (const S_::storage*)delta,
-                                         (const S_::storage*)w, (S_::storage*)y, T, H, eps));
+  const int64_t vecs = (int64_t)H * elem_bytes(dtype) / 16;         // 16-byte vectors per row
+  if (vecs <= 512)
+    FLL_BY_DTYPE(dtype, hipLaunchKernelGGL((rmsnorm_kernel<S_, 2>), dim3(T), dim3(256), 0, st, (const S_::storage*)x,
+                                           (S_::storage*)resid, (const S_::storage*)delta, (const S_::storage*)w,
+                                           (S_::storage*)y, H, eps));
+  else if (vecs <= 1024)
+    FLL_BY_DTYPE(dtype, hipLaunchKernelGGL((rmsnorm_kernel<S_, 4>), dim3(T), dim3(256), 0, st, (const S_::storage*)x,
+                                           (S_::storage*)resid, (const S_::storage*)delta, (const S_::storage*)w,
+                                           (S_::storage*)y, H, eps));
+  else
+    FLL_BY_DTYPE(dtype, hipLaunchKernelGGL(rmsnorm_long_kernel<S_>, dim3((T + 3) / 4), dim3(256), 0, st,
+                                           (const S_::storage*)x, (S_::storage*)resid, (const S_::storage*)delta,
+                                           (const S_::storage*)w, (S_::storage*)y, T, H, eps));
   FLP_TRY_HIP(hipGetLastError());
   return FLP_OK;
 }
