@@ -647,8 +647,10 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
         }
       }
       FLP_TRY(flp_launch_gemm(p->cfg.dtype, b->x, b->ld_x, b->n_tokens, b->d_in, g.plan, g.n, out, false, nullptr, stream));
-      if (g.plan.splits > 1)
-        FLP_TRY(flp_launch_gemm_reduce(p->cfg.dtype, b->n_tokens, g.n, out, g.plan.splits, false, true, stream));
+      // the small batches' expand step adds the slices itself
+      if (g.plan.splits > 1 && !group_bytes)
+        FLP_TRY(flp_launch_gemm_reduce(p->cfg.dtype, b->n_tokens, g.n, out, g.plan.splits, false, FLP_REDUCE_KEEP, stream));
+      for (int i = 0; i < g.n; ++i) a.base_slices[g.which[i]] = group_bytes ? g.plan.splits : 1;
     }
   }
   if (group_bytes) {

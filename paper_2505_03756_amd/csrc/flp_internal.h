@@ -193,6 +193,7 @@ struct FlpLoraArgs {
   // unrounded base term x.W_base [T, d_out] of a projection whose w_base was given (16-bit pools), else null:
   // the expand kernels then take the base from here instead of y and round base + delta once
   const float* base32[FLP_MAX_PROJ];
+  int32_t base_slices[FLP_MAX_PROJ];   // slices of it, T * d_out apart (more than one: lora_small.hip only)
   // workspace
   float* v;                    // [T, n_proj, max_rank] fp32
   int32_t* n_seg;
@@ -301,8 +302,9 @@ size_t flp_gemm_part_bytes(const FlpGemmPlan& plan, int M, int n_proj, const int
 // lora: one per projection (gated: gate, up), or null
 flp_status flp_launch_gemm(int dtype, const void* x, int64_t ld_x, int M, int K, const FlpGemmPlan& plan, int n_proj,
                            const FlpGemmOut* out, bool gated, const FlpGemmLora* lora, hipStream_t stream);
-// adds the slices; keep_sum: the unrounded sum stays in slice 0
-flp_status flp_launch_gemm_reduce(int dtype, int M, int n_proj, const FlpGemmOut* out, int splits, bool gated, bool keep_sum,
+// adds the slices; KEEP: the unrounded sum stays in slice 0; ADD: the rounded sum is added to what `y` holds (not gated)
+enum { FLP_REDUCE_PLAIN = 0, FLP_REDUCE_KEEP, FLP_REDUCE_ADD };
+flp_status flp_launch_gemm_reduce(int dtype, int M, int n_proj, const FlpGemmOut* out, int splits, bool gated, int mode,
                                   hipStream_t stream);
 flp_status flp_launch_transpose16(const void* w, void* wt, int K, int N, hipStream_t stream);   // [K, N] -> [N, K]
 flp_status flp_launch_gemm_f32(const float* x, int64_t ld_x, const float* w, int w_layout, float* y, int64_t ld_y, int M, int N,

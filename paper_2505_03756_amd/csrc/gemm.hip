@@ -579,9 +579,10 @@ __global__ __launch_bounds__(64 * WF * WT, (WF * WT + 3) / 4)
 }
 
 // ---- sum of the slices, in slice order, four features per thread.  GATED: the slices hold [gate | up]; the result is
-//      silu(g) * u with both rounded first.  The unrounded sum goes back into slice 0 where keep_sum says so.
+//      silu(g) * u with both rounded first.  RED_KEEP: the unrounded sum goes back into slice 0.  RED_ADD: y is a residual
+//      stream that the rounded sum is added to.
 template <typename G, bool GATED>
-__global__ __launch_bounds__(256) void gemm_reduce_kernel(FlpGemmArgs a, int keep_sum) {
+__global__ __launch_bounds__(256) void gemm_reduce_kernel(FlpGemmArgs a, int mode) {
   typedef typename G::S S;
   const FlpGemmProj& pr = a.proj[blockIdx.y];
   const int n_out = GATED ? pr.N / 2 : pr.N, n4 = n_out / 4;
@@ -597,19 +598,25 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(FlpGemmArgs a, int kee
     if (GATED) s2 += *reinterpret_cast<const f32x4g*>(pp + z * step + n_out);
   }
   uint16_t o[4];
+  uint2 raw;
+  uint2* const yp = reinterpret_cast<uint2*>(pr.y + (int64_t)m * pr.ld_y + n);
+  if (mode == FLP_REDUCE_ADD) {
+    raw = *yp;
+    __builtin_memcpy(o, &raw, 8);
+  }
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     if (GATED) {
       const float g = S::to_float(S::from_float(s[e])), up = S::to_float(S::from_float(s2[e]));
       o[e] = S::from_float(g / (1.0f + expf(-g)) * up);
     } else {
-      o[e] = S::from_float(s[e]);
+      const uint16_t sum = S::from_float(s[e]);
+      o[e] = mode == FLP_REDUCE_ADD ? S::from_float(S::to_float(o[e]) + S::to_float(sum)) : sum;
     }
   }
-  uint2 raw;
   __builtin_memcpy(&raw, o, 8);
-  *reinterpret_cast<uint2*>(pr.y + (int64_t)m * pr.ld_y + n) = raw;
-  if (keep_sum) *reinterpret_cast<f32x4g*>(pp) = s;
+  *yp = raw;
+  if (mode == FLP_REDUCE_KEEP) *reinterpret_cast<f32x4g*>(pp) = s;
 }
 
 // ---- fp32: y = x . W^T, one 16 x 16 tile per workgroup with mfma_f32_16x16x4 (fp32 products and sums).  Bound by
@@ -837,7 +844,7 @@ flp_status flp_launch_gemm(int dtype, const void* x, int64_t ld_x, int M, int K,
   return FLP_OK;
 }
 
-flp_status flp_launch_gemm_reduce(int dtype, int M, int n_proj, const FlpGemmOut* out, int splits, bool gated, bool keep_sum,
+flp_status flp_launch_gemm_reduce(int dtype, int M, int n_proj, const FlpGemmOut* out, int splits, bool gated, int mode,
                                   hipStream_t stream) {
   FlpGemmArgs a{};
   a.M = M;
@@ -854,13 +861,13 @@ flp_status flp_launch_gemm_reduce(int dtype, int M, int n_proj, const FlpGemmOut
   }
   const dim3 grid((unsigned)((most + 255) / 256), (unsigned)n_proj);
   if (dtype == FLP_F16 && gated)
-    hipLaunchKernelGGL((gemm_reduce_kernel<GF16, true>), grid, dim3(256), 0, stream, a, (int)keep_sum);
+    hipLaunchKernelGGL((gemm_reduce_kernel<GF16, true>), grid, dim3(256), 0, stream, a, mode);
   else if (dtype == FLP_F16)
-    hipLaunchKernelGGL((gemm_reduce_kernel<GF16, false>), grid, dim3(256), 0, stream, a, (int)keep_sum);
+    hipLaunchKernelGGL((gemm_reduce_kernel<GF16, false>), grid, dim3(256), 0, stream, a, mode);
   else if (gated)
-    hipLaunchKernelGGL((gemm_reduce_kernel<GBF16, true>), grid, dim3(256), 0, stream, a, (int)keep_sum);
+    hipLaunchKernelGGL((gemm_reduce_kernel<GBF16, true>), grid, dim3(256), 0, stream, a, mode);
   else
-    hipLaunchKernelGGL((gemm_reduce_kernel<GBF16, false>), grid, dim3(256), 0, stream, a, (int)keep_sum);
+    hipLaunchKernelGGL((gemm_reduce_kernel<GBF16, false>), grid, dim3(256), 0, stream, a, mode);
   FLP_TRY_HIP(hipGetLastError());
   return FLP_OK;
 }

@@ -347,8 +347,10 @@ bool cfg_ok(const flp_pool* p, const fll_layer_config* c) {
 // their slices have a workspace of their own that one call hands to the next, for an event per product (products of
 // 100 us and more; the small ones would notice it).
 constexpr int kSharedWorkTokens = 1024;
+// `resid`, one product: where its slices are added by a kernel, that kernel adds the rounded result to the residual stream
+// instead of writing out->y, and *added says so.
 flp_status dense_products(flp_pool* p, const void* x, int d_in, int T, int n, FlpGemmOut* out, const int* N, bool gated,
-                          hipStream_t stream) {
+                          hipStream_t stream, void* resid = nullptr, bool* added = nullptr) {
   if (p->elem_bytes == 4) {
     for (int i = 0; i < n; ++i)
       FLP_TRY(flp_launch_gemm_f32((const float*)x, d_in, (const float*)out[i].w, 1, (float*)out[i].y, out[i].ld_y, T, N[i], d_in,
@@ -372,7 +374,13 @@ flp_status dense_products(flp_pool* p, const void* x, int d_in, int T, int n, Fl
     }
   }
   flp_status s = flp_launch_gemm(p->cfg.dtype, x, d_in, T, d_in, plan, n, out, gated, nullptr, stream);
-  if (s == FLP_OK && plan.splits > 1) s = flp_launch_gemm_reduce(p->cfg.dtype, T, n, out, plan.splits, gated, false, stream);
+  if (s == FLP_OK && plan.splits > 1) {
+    if (resid) {
+      out->y = resid;
+      *added = true;
+    }
+    s = flp_launch_gemm_reduce(p->cfg.dtype, T, n, out, plan.splits, gated, resid ? FLP_REDUCE_ADD : FLP_REDUCE_PLAIN, stream);
+  }
   if (own) {
     const flp_status r = flp_dense_workspace_release(p, stream);
     return s != FLP_OK ? s : r;
@@ -419,7 +427,7 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
 
   // base GEMM + LoRA branch of up to three projections that share their input
   auto project = [&](const void* x, int d_in, int n_proj, const int* which, void* const* ys, const int* d_outs,
-                     const void* const* ws, void* gated_out = nullptr) -> flp_status {
+                     const void* const* ws, void* gated_out = nullptr, bool* added = nullptr) -> flp_status {
     flp_lora_batch lb{};
     lb.n_tokens = T;
     lb.d_in = d_in;
@@ -465,7 +473,9 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
       pr.b_tab_off = pl.b_tab_off;
       pr.b_row_base = pl.b_row_base;
     }
-    if (n_dense > 0) FLP_TRY(dense_products(p, x, d_in, T, n_dense, dense, dense_N, false, (hipStream_t)hip_stream));
+    if (n_dense > 0)
+      FLP_TRY(dense_products(p, x, d_in, T, n_dense, dense, dense_N, false, (hipStream_t)hip_stream,
+                             added && n_proj == 1 ? h : nullptr, added));
     if (n_lora == 0) return FLP_OK;
     lb.n_proj = n_lora;
     if (gated_out) return flp_lora_apply_gated(p, &lb, gated_out, d_outs[0], hip_stream);
@@ -540,7 +550,9 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
     const int which[1] = {6}, d_outs[1] = {H};
     void* const ys[1] = {proj};
     const void* const ws[1] = {w->w_down};
-    FLP_TRY(project(gate, M, 1, which, ys, d_outs, ws));
+    bool added = false;
+    FLP_TRY(project(gate, M, 1, which, ys, d_outs, ws, nullptr, &added));
+    if (added) return FLP_OK;
   }
   return fll_add_rmsnorm(dtype, h, proj, nullptr, nullptr, T, H, eps, hip_stream);
 }

@@ -189,13 +189,15 @@ __global__ __launch_bounds__(64) void lora_small_shrink_kernel(FlpLoraArgs a, Fl
     n = sixteen(a.token_adapter, a.T, t, ad, &tok);
     if (r <= 0) n = 0;
   }
+  const bool lone = n == 0 && (r <= 0 || ad < 0 || ad >= a.n_adapters);     // no branch: only slices of its base to be added
   if (writes) {
     if (lane < 16) rec->tok[lane] = tok;
     if (lane == 0) {
-      rec->n = n;
-      rec->r = r;
+      rec->n = lone ? 1 : n;
+      rec->r = lone ? 0 : r;
       rec->scale = n ? a.scale[ad] : 0.f;
     }
+    if (lone && lane == 0) rec->tok[0] = t;
     if (n && lane < a.n_proj) {
       rec->tab[lane] = a.proj[lane].b_tab_off[ad];
       rec->row[lane] = a.proj[lane].b_row_base[ad];
@@ -230,15 +232,31 @@ __global__ __launch_bounds__(64) void lora_small_shrink_kernel(FlpLoraArgs a, Fl
     run(std::integral_constant<int, NT>{});
 }
 
-// Adds s * delta to 8 NP columns of a token, the unrounded base or y itself.
+// the slices' sums in order, B of them requested together
+template <int B>
+__device__ __forceinline__ f32x4 sum_slices(const float* vp, int64_t slice, int n) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  for (int k = 0; k < n; k += B) {
+    f32x4 q[B];
+#pragma unroll
+    for (int i = 0; i < B; ++i) q[i] = *reinterpret_cast<const f32x4*>(vp + (k + i < n ? k + i : n - 1) * slice);
+#pragma unroll
+    for (int i = 0; i < B; ++i)
+      if (k + i < n) v = k + i ? v + q[i] : q[i];
+  }
+  return v;
+}
+
+// Adds s * delta to 8 NP columns of a token: to the unrounded base, in `slices` slices, or to y itself.
 template <typename S, int NP, typename F>
-__device__ __forceinline__ void add_to_y(uint16_t* yp, const float* bp, const u32x4 (&yraw)[NP], int left, float sc, F delta) {
+__device__ __forceinline__ void add_to_y(uint16_t* yp, const float* bp, int64_t slice, int slices, const u32x4 (&yraw)[NP], int left,
+                                         float sc, F delta) {
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
     if (8 * i >= left) break;
     uint16_t y8[8];
     if (bp) {
-      const f32x4 lo = *reinterpret_cast<const f32x4*>(bp + 8 * i), hi = *reinterpret_cast<const f32x4*>(bp + 8 * i + 4);
+      const f32x4 lo = sum_slices<4>(bp + 8 * i, slice, slices), hi = sum_slices<4>(bp + 8 * i + 4, slice, slices);
 #pragma unroll
       for (int q = 0; q < 8; ++q) y8[q] = S::from_float(fmaf(sc, delta(i, q), q < 4 ? lo[q & 3] : hi[q & 3]));
     } else {
@@ -250,21 +268,6 @@ __device__ __forceinline__ void add_to_y(uint16_t* yp, const float* bp, const u3
     __builtin_memcpy(&raw, y8, 16);
     *reinterpret_cast<u32x4*>(yp + 8 * i) = raw;
   }
-}
-
-// the slices' sums in order, B of them requested together
-template <int B>
-__device__ __forceinline__ f32x4 sum_slices(const float* vp, int64_t slice, int n) {
-  f32x4 v = {0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < n; k += B) {
-    f32x4 q[B];
-#pragma unroll
-    for (int i = 0; i < B; ++i) q[i] = *reinterpret_cast<const f32x4*>(vp + (k + i < n ? k + i : n - 1) * slice);
-#pragma unroll
-    for (int i = 0; i < B; ++i)
-      if (k + i < n) v += q[i];
-  }
-  return v;
 }
 
 // NT: tiles of 16 ranks the launch allows for
@@ -281,6 +284,15 @@ __global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, Fl
   const int n = __builtin_amdgcn_readfirstlane(rec->n);
   if (n == 0) return;
   const int r = __builtin_amdgcn_readfirstlane(rec->r);
+  const int64_t base_slice = (int64_t)a.T * pr.d_out;
+  if (r == 0) {                                        // a token without a branch: its product has only to be added up
+    const int f0 = col0 + 8 * lane;
+    if (a.base_slices[p] <= 1 || lane >= 16 || f0 >= pr.d_out) return;
+    const u32x4 none[1] = {u32x4{0u, 0u, 0u, 0u}};
+    add_to_y<S, 1>(reinterpret_cast<uint16_t*>(pr.y) + (int64_t)t * pr.ld_y + f0, a.base32[p] + (int64_t)t * pr.d_out + f0, base_slice,
+                   a.base_slices[p], none, pr.d_out - f0, 0.f, [](int, int) { return 0.f; });
+    return;
+  }
   const int rpb = (int)(a.block_elems / pr.d_out);
   constexpr int RP = 16 * NT;
   // lane rho looks up the page row of rank rho
@@ -335,7 +347,7 @@ __global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, Fl
         }
       }
     }
-    if ((lane & 3) < n) add_to_y<S, 1>(yp, bp, yraw, pr.d_out - f0, sc, [&](int, int q) { return acc[q & 1][q >> 1]; });
+    if ((lane & 3) < n) add_to_y<S, 1>(yp, bp, base_slice, a.base_slices[p], yraw, pr.d_out - f0, sc, [&](int, int q) { return acc[q & 1][q >> 1]; });
     return;
   }
 
@@ -379,7 +391,7 @@ __global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, Fl
     }
   }
   // lane (token m16, kg): element i of tile q is column 32 kg + 8 i + q of the chunk
-  if (m16 < n) add_to_y<S, 4>(yp, bp, yraw, pr.d_out - f0, sc, [&](int i, int q) { return acc[q][i]; });
+  if (m16 < n) add_to_y<S, 4>(yp, bp, base_slice, a.base_slices[p], yraw, pr.d_out - f0, sc, [&](int i, int q) { return acc[q][i]; });
 }
 
 template <typename L, int NT>
