@@ -398,6 +398,25 @@ def test_segmentation_bit_exact():
         assert np.array_equal(d_perm.cpu().numpy()[:seg_start[n]], perm)
 
 
+@pytest.mark.parametrize("T,n_ad", [(1023, 7), (1024, 1), (1025, 40), (2049, 3), (16384, 2048), (16385, 17), (33000, 500)])
+def test_segmentation_by_several_workgroups(T, n_ad):
+    """Batches of one workgroup's range and around it, the most workgroups, and ranges of several steps; runs of equal ids as
+    sequences make them, over the edges of the ranges, mixed ids, and ids that name no adapter."""
+    rng = np.random.default_rng(T)
+    ta = np.repeat(rng.integers(-1, n_ad, size=T), rng.integers(1, 400, size=T))[:T].astype(np.int32)
+    ta[T // 3:T // 2] = rng.integers(-1, n_ad + 1, size=T // 2 - T // 3)
+    seg_adapter, seg_start, perm = oracle.segment(np.where(ta < n_ad, ta, -1).astype(np.int32), n_ad)
+    pool = flpool.Pool("f16", 1, 64, 2, 0)
+    d_nseg, d_sa, d_ss, d_perm = (torch.full((n,), -7, dtype=torch.int32, device="cuda") for n in (1, n_ad, n_ad + 1, T))
+    pool.lora_segment(to_dev(ta), T, n_ad, d_nseg, d_sa, d_ss, d_perm)
+    n = int(d_nseg.item())
+    assert n == len(seg_adapter)
+    assert np.array_equal(d_sa.cpu().numpy()[:n], seg_adapter) and bool((d_sa[n:] == -7).all())
+    assert np.array_equal(d_ss.cpu().numpy()[:n + 1], seg_start)
+    assert np.array_equal(d_perm.cpu().numpy()[:seg_start[n]], perm[:seg_start[n]]) and bool((d_perm[seg_start[n]:] == -7).all())
+    pool.close()
+
+
 def test_degenerate_batches():
     import torch
     cfg = small_cfg("f16", n_seqs=5, prefix_range=(64, 64), new_range=(16, 16), seed=90)
