@@ -691,6 +691,12 @@ def test_tiled_attention_at_the_edges_of_tiles(dtype, bt, heads, kv, seqs):
         assert bool((err <= bound).all()), (p, n, float((err / bound).max()))
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_merge_of_up_to_64_pieces(dtype):
+    """8, 9, 16, 17, 32, 33 and 64 pieces of 256 positions: the edges of what the merge requests together."""
+    test_single_token_attention_at_the_edges_of_groups_tiles_and_pieces(dtype, 16, 2, 2, (2048, 2049, 4096, 4097, 8192, 8193, 16384))
+
+
 def _single_tokens(dtype, ctx, q, K, V):
     """Attention of one new token per sequence of `ctx` positions: q [seqs, heads, d], K and V [seqs, heads, ctx, d] in
     the pool's type.  Returns the result and, in fp64, the weights' sum with V and with |V|."""
