@@ -16,6 +16,12 @@
 //           columns of a page row and ends up with 32 neighbouring columns of one token), rank 4 k + i of a rank tile is slot k
 //           of step i.  Groups of up to four tokens take 4x4x1 instructions, a quarter of the time in the matrix pipe.
 //
+// Both steps add in short chains: four chunks of d_in at a time, then those sums; a rank tile at a time (4x4x1: half a tile), then
+// the tiles.  Error of the branch against 64 bits (fp16, widths 4096 to 8192, 2-norm over 2-norm, 8 to 1000 tokens):
+//   rank 64    1.6e-7 with the vector kernels, 2.1e-7 with one chain over the ranks and eight chunks at a time, 1.5e-7 with these
+//   rank 16    1.8e-7 to 2.1e-7, 5 % more, 2 % less
+// (256 tokens of rank 64, q,k,v: shrink 42.8 -> 43.3, expand 22.6 -> 23.2 us.)
+//
 // Measured on MI355X, bf16, the q,k,v call / the o call in us, with the per-token vector kernels and with these:
 //   32 / 32 heads   256 tokens, 92 adapters of ranks 8-64     79.6 / 36.0   48.5 / 26.2
 //                   8 tokens, 8 adapters of rank 16           13.2 / 12.8   12.8 / 11.4
@@ -160,7 +166,7 @@ __device__ __forceinline__ void shrink_group(uint8_t* smem, const uint16_t* xrow
     }
     st = st + 1 == ST ? 0 : st + 1;
     st_load = st_load + 1 == ST ? 0 : st_load + 1;
-    if ((c & 7) == 7 || c + 1 == n) {                  // sums of eight chunks, then of those: shorter chains of roundings
+    if ((c & 3) == 3 || c + 1 == n) {                  // sums of four chunks, then of those: shorter chains of roundings
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         v[i] += acc[i][0] + acc[i][1];
@@ -335,17 +341,23 @@ __global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, Fl
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       if (16 * nt >= r) break;
+      f32x4 part[2][2];                                // ranks 8 h .. 8 h + 7 of the tile
+#pragma unroll
+      for (int h = 0; h < 2; ++h) part[h][0] = part[h][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int e4 = 0; e4 < 4; ++e4) {
         const f32x4 v = v_lds[(lane & 3) * (RP / 4) + 4 * nt + e4];
+        f32x4(&to)[2] = part[e4 >> 1];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int e = 4 * e4 + i;
           const uint32_t w = 16 * nt + e < r ? b[nt][e] : 0u;
-          acc[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(S::to_float((uint16_t)w), v[i], acc[0], 0, 0, 0);
-          acc[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(S::to_float((uint16_t)(w >> 16)), v[i], acc[1], 0, 0, 0);
+          to[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(S::to_float((uint16_t)w), v[i], to[0], 0, 0, 0);
+          to[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(S::to_float((uint16_t)(w >> 16)), v[i], to[1], 0, 0, 0);
         }
       }
+      acc[0] += part[0][0] + part[1][0];
+      acc[1] += part[0][1] + part[1][1];
     }
     if ((lane & 3) < n) add_to_y<S, 1>(yp, bp, base_slice, a.base_slices[p], yraw, pr.d_out - f0, sc, [&](int, int q) { return acc[q & 1][q >> 1]; });
     return;
@@ -367,8 +379,6 @@ __global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, Fl
 #pragma unroll
   for (int i = 0; i < 4; ++i) yraw[i] = !bp && f0 + 8 * i < pr.d_out ? *reinterpret_cast<const u32x4*>(yp + 8 * i) : u32x4{0u, 0u, 0u, 0u};
   f32x4 acc[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
   u32x4 b[NT][4];                                    // ranks 16 nt + 4 kg + i of the lane's 8 columns
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
@@ -380,6 +390,9 @@ __global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, Fl
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     if (16 * nt >= r) break;
+    f32x4 part[8];                                     // of this rank tile: chains of 16 roundings
+#pragma unroll
+    for (int q = 0; q < 8; ++q) part[q] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const bool live = 16 * nt + 4 * kg + i < r;
@@ -387,8 +400,10 @@ __global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, Fl
       __builtin_memcpy(e, &b[nt][i], 16);
 #pragma unroll
       for (int q = 0; q < 8; ++q)
-        acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(live ? S::to_float(e[q]) : 0.f, v[nt][i], acc[q], 0, 0, 0);
+        part[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(live ? S::to_float(e[q]) : 0.f, v[nt][i], part[q], 0, 0, 0);
     }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc[q] = nt ? acc[q] + part[q] : part[q];
   }
   // lane (token m16, kg): element i of tile q is column 32 kg + 8 i + q of the chunk
   if (m16 < n) add_to_y<S, 4>(yp, bp, base_slice, a.base_slices[p], yraw, pr.d_out - f0, sc, [&](int i, int q) { return acc[q][i]; });

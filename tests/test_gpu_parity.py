@@ -967,6 +967,41 @@ def test_lora_of_small_batches_in_groups_of_every_size(dtype, T, d_in, widths, c
     pool.close()
 
 
+@pytest.mark.parametrize("tokens_each", [3, 16])
+@pytest.mark.parametrize("T,d_in,rank", [(96, 4096, 64), (240, 8192, 64), (240, 5120, 40), (960, 4096, 64)])
+def test_lora_of_small_batches_sums_in_short_chains(T, d_in, rank, tokens_each):
+    """The branch's own error, below the 16-bit rounding of y: a first call over y = 0 leaves y1 = round(s delta), a second one over
+    -y1 leaves s delta - y1, which 16 bits hold to 2^-23 of delta.  64 products of equal size added one after the other in 32
+    bits are off by 1.9e-7 of the sum (each addition rounds a partial sum of k of them, sqrt(k) in size, by 2^-24 / sqrt(3):
+    sqrt(1/2 64) 3.4e-8); in tiles of 16 that are then added it is 1.1e-7.  With the shrink step's sums and the rounding of the
+    second result (0.3e-7 to 0.9e-7 each) the whole is 1.5e-7, and was 2.1e-7 with one chain."""
+    n_ad, d_out, E = T // tokens_each, 2048, 2 * 16 * 8 * 128
+    g = torch.Generator(device="cuda").manual_seed(T + d_in + rank)
+    rnd = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).half()
+    A, B, x = rnd((rank, d_in), d_in ** -0.5), rnd((rank, d_out), rank ** -0.5), rnd((T, d_in), 1.0)
+    rows_a, rows_b = E // d_in, E // d_out               # page rows per block; every adapter has the same pages
+    pages = [torch.zeros(E, dtype=torch.float16, device="cuda") for _ in range(-(-rank // rows_a) - (-rank // rows_b))]
+    for m, rpb, first in ((A, rows_a, 0), (B, rows_b, -(-rank // rows_a))):
+        for k, lo in enumerate(range(0, rank, rpb)):
+            part = m[lo:lo + rpb].reshape(-1)
+            pages[first + k][:part.numel()] = part
+    pool = flpool.Pool("f16", 8, 128, len(pages), 0, block_tokens=16, dev=torch.stack(pages).contiguous())
+    i32 = lambda v: torch.as_tensor(v, dtype=torch.int32, device="cuda")
+    z, y = i32(np.zeros(n_ad)), torch.zeros((T, d_out), dtype=torch.float16, device="cuda")
+    proj = dict(y=y, d_out=d_out, a_tab_off=z, a_row_base=z, b_tab_off=z + -(-rank // rows_a), b_row_base=z)
+    ta = i32(np.random.default_rng(T).permutation(np.repeat(np.arange(n_ad), tokens_each)))
+    call = lambda: pool.lora_apply_paged(x, ta, z + rank, torch.ones(n_ad, device="cuda"), i32(np.arange(len(pages))), [proj],
+                                         n_tokens=T, d_in=d_in, n_adapters=n_ad, max_rank=rank)
+    call()
+    y.neg_()
+    first = y.double()
+    call()
+    delta = (x.double() @ A.double().T) @ B.double()
+    err = float((y.double() - (first + delta)).norm() / delta.norm())
+    assert err < 1.8e-7, err
+    pool.close()
+
+
 @pytest.mark.parametrize("T,widths,plan", [(2050, (1088, 320), ("256x128", 1)), (2177, (4032,), ("256x256", 1)),
                                            (4100, (1088, 1088, 320), ("256x256", 1))])
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
