@@ -496,14 +496,17 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
   const size_t perm_bytes = (T * 4 + 255) & ~(size_t)255;
   // token -> position in segment order, adapter -> first row of its tokens in the shrink output
   const size_t inv_bytes = fused ? perm_bytes + (((size_t)b->n_adapters * 4 + 255) & ~(size_t)255) : 0;
-  // Batches of up to 1024 tokens: slices of d_in until some thousand waves are in flight.  Their intermediates are larger than
-  // the vector kernels' (slices of v, ranks in sixteens, a record per token): a batch that only fits the call's buffer without
-  // them takes those kernels, so that what a fixed buffer accepts does not depend on it.
+  // Batches of up to 1024 tokens: slices of d_in until some thousand waves are in flight.  Two slices, four (us): 300 tokens, o of
+  // ranks 8-64, 64 heads 74.0, 63.3; 300 tokens, q,k,v of rank 16, 32 heads 49.1, 50.8; 499 tokens of one adapter of rank 16, o, 40
+  // heads 30.4, 28.4, q,k,v, 32 heads 38.1, 40.3.  The intermediates are larger than the vector kernels' (slices of v, ranks in
+  // sixteens, a record per token): a batch that only fits the call's buffer without them takes those kernels, so that what a
+  // fixed buffer accepts does not depend on it.
   FlpLoraSmall small{};
   size_t group_bytes = 0;
   if (!mfma_ok && p->elem_bytes == 2 && b->n_tokens <= kLoraSmallTokens && b->d_in % 64 == 0) {
     small.n_tiles = b->max_rank <= 16 ? 1 : b->max_rank <= 32 ? 2 : 4;
-    small.k_splits = b->n_tokens <= 16 ? 16 : b->n_tokens <= 64 ? 8 : b->n_tokens <= 256 ? 4 : 2;
+    small.k_splits = b->n_tokens <= 16 ? 16 : b->n_tokens <= 64 ? 8
+                     : b->n_tokens <= 256 || b->n_tokens * b->n_proj <= 768 ? 4 : 2;
     while (small.k_splits > 1 && b->d_in / 64 / small.k_splits < 4) small.k_splits /= 2;
     const size_t v_small = ((size_t)small.k_splits * T * b->n_proj * 16 * small.n_tiles * 4 + 255) & ~(size_t)255;
     const size_t g_small = (T * sizeof(FlpLoraGroup) + 255) & ~(size_t)255;

@@ -9,8 +9,8 @@
 // by latency: a workgroup is one wave, which meets no barrier, has its loads in flight together and gives its place back at
 // once where it has nothing to do (with four waves to a workgroup the idle ones held theirs: 30 % longer at 256 tokens).
 //
-//   shrink  one wave per (sixteen tokens, projection, slice of d_in): v^T = A x^T with mfma_f32_16x16x32.  The slices'
-//           sums stay apart, the expand step adds them in order.
+//   shrink  one wave per (sixteen tokens, projection, slice of d_in, 32 ranks): v^T = A x^T with mfma_f32_16x16x32.  The
+//           slices' sums stay apart, the expand step adds them in order.
 //   expand  one wave per (sixteen tokens, projection, 128 columns): y^T += s B^T v^T with fp32 instructions, so that v
 //           keeps its 32 bits.  16x16x4: column 8 m + tau of the chunk is row m of tile tau (a lane reads 8 neighbouring
 //           columns of a page row and ends up with 32 neighbouring columns of one token), rank 4 k + i of a rank tile is slot k
@@ -19,16 +19,31 @@
 // Both steps add in short chains: four chunks of d_in at a time, then those sums; a rank tile at a time (4x4x1: half a tile), then
 // the tiles.  Error of the branch against 64 bits (fp16, widths 4096 to 8192, 2-norm over 2-norm, 8 to 1000 tokens):
 //   rank 64    1.6e-7 with the vector kernels, 2.1e-7 with one chain over the ranks and eight chunks at a time, 1.5e-7 with these
-//   rank 16    1.8e-7 to 2.1e-7, 5 % more, 2 % less
-// (256 tokens of rank 64, q,k,v: shrink 42.8 -> 43.3, expand 22.6 -> 23.2 us.)
+//   rank 16    1.8e-7 to 2.1e-7, 5 % more, 1 % less (2 % more where 4096 coefficients are in two slices; two running sums per
+//              slice mend that for 1 to 7 % of the time)
 //
-// Measured on MI355X, bf16, the q,k,v call / the o call in us, with the per-token vector kernels and with these:
-//   32 / 32 heads   256 tokens, 92 adapters of ranks 8-64     79.6 / 36.0   48.5 / 26.2
-//                   8 tokens, 8 adapters of rank 16           13.2 / 12.8   12.8 / 11.4
-//                   499 tokens of one adapter of rank 16      59.3 / 29.1   30.5 / 19.3
-//   40 / 40 heads   914 tokens of 40 sequences, rank 32        163 / 65.6   59.8 / 34.0
-//   64 / 8 heads    800 tokens of 2 sequences, rank 64         513 / 251     189 / 93.8
-//                   200 tokens, rank 64                        108 / 57.1    116 / 48.1
+// What keeps a batch of many adapters of high rank fast is how much of their pages is in flight: 64 ranks of one token are two
+// waves with a 20 KiB ring each (one with 30 KiB was 10 % slower, both together 15 to 20 % behind the vector kernels); groups of
+// up to eight tokens fetch eight rows of x instead of sixteen, which leaves room for a fourth stage.  Above 512 tokens the waves
+// with nothing to do are so many that one wave takes all 64 ranks (500 + 500 tokens, rank 64: 109 against 113 us).  The expand
+// step's grid holds the column chunks that there are, projection by projection (64 x 8 heads: three times the chunks of q had
+// two thirds of the waves leave at once: 85 -> 67 us).
+//
+// Measured on MI355X with the adapters' pages out of the caches, us: the per-token vector kernels / these
+//                                                             q,k,v           o
+//   32 / 32 heads    256 tokens, 92 adapters of ranks 8-64    93.6 / 73.5     43.9 / 40.2
+//   bf16             200 tokens, 100 adapters of ranks 8-64   75.7 / 71.5     41.4 / 35.9
+//                    8 tokens of rank 16                      19.7 / 17.5     18.3 / 15.2
+//                    499 tokens of one adapter of rank 16     64.1 / 37.8     33.8 / 26.5
+//                    64 tokens, 500 adapters of rank 64       84.2 / 88.2     40.0 / 40.5
+//   40 / 40 heads    1000 tokens of 2 sequences, rank 32       416 / 102       157 / 49.4
+//   64 / 8 heads     1000 tokens of 2 sequences, rank 64       652 / 142       321 / 81.5
+//   bf16             200 tokens, 100 adapters of rank 64       154 / 153      93.7 / 94.0
+//                    128 tokens, 500 adapters of rank 64       159 / 165       102 / 103
+//                    300 tokens, 500 adapters of rank 64       247 / 262       156 / 163
+//                    300 tokens, 500 adapters of rank 16       115 / 114      68.5 / 64.2
+// Where nearly every token has an adapter of rank 64 of its own the vector kernels stay 3 to 6 % ahead (their workgroups read
+// whole KiB of a page row); which batches those are is only known on the device.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -111,25 +126,25 @@ __device__ __forceinline__ uint64_t address_of(const uint16_t* mine, int from) {
   return (uint64_t)(uint32_t)__shfl((int)(uint32_t)ad, from) | (uint64_t)(uint32_t)__shfl((int)(ad >> 32), from) << 32;
 }
 
-// v of one group for NB tiles of 16 ranks over the chunks [c0, c1) of 64 coefficients.  The rows of x and of A travel as whole
+// v of one group of up to 8 NX tokens for NB tiles of 16 ranks over the chunks [c0, c1) of 64 coefficients.  The rows of x and of A travel as whole
 // 128-byte lines (8 rows per instruction) into a ring in LDS that belongs to this wave alone, so its own waits are all
 // the order it needs.  Piece j (16 bytes) of row r sits in slot j ^ ((r >> 1) & 7).  (Straight from global memory in operand
 // layout, 64 bytes of 16 rows per instruction, rows that are a multiple of 8 KiB apart met in one cache set.)
-template <typename L, int NB, int kLds>
+template <typename L, int NB, int NX, int kLds>
 __device__ __forceinline__ void shrink_group(uint8_t* smem, const uint16_t* xrow, const uint16_t* arow, int tok, int64_t ld_x, int r,
                                              int c0, int c1, int rotate, f32x4 (&v)[NB]) {
   typedef typename L::vec vec;
-  constexpr int NPER = 2 * (1 + NB), kStage = 1024 * NPER, ST = kLds / kStage;
+  constexpr int NPER = NX + 2 * NB, kStage = 1024 * NPER, ST = kLds / kStage < 6 ? kLds / kStage : 6;
   static_assert(ST >= 3, "two chunks in flight behind the one that is multiplied");
   const int lane = threadIdx.x, m16 = lane & 15, kg = lane >> 4;
   uint64_t addr[NPER];
 #pragma unroll
   for (int i = 0; i < NPER; ++i) {
-    const int row = 8 * (i & 1) + (lane >> 3), piece = (lane & 7) ^ ((row >> 1) & 7);
-    if (i < 2) {
+    const int row = 8 * (i < NX ? i : (i - NX) & 1) + (lane >> 3), piece = (lane & 7) ^ ((row >> 1) & 7);
+    if (i < NX) {
       addr[i] = (uint64_t)(uintptr_t)(xrow + (int64_t)__shfl(tok, row) * ld_x + 8 * piece);
     } else {
-      const int rho = 16 * (i / 2 - 1) + row;            // ranks past the adapter's read its first row, their v is zeroed
+      const int rho = 16 * ((i - NX) / 2) + row;         // ranks past the adapter's read its first row, their v is zeroed
       addr[i] = address_of(arow, rho < r ? rho : 0) + 16 * piece;
     }
   }
@@ -151,6 +166,7 @@ __device__ __forceinline__ void shrink_group(uint8_t* smem, const uint16_t* xrow
 #pragma unroll
   for (int c = 0; c < ST - 1; ++c) issue(c, c);
   const int off = m16 * 128 + ((kg ^ (m16 >> 1)) << 4);  // k step 0; step 1 is slot + 4: offset ^ 64
+  const int xm = NX == 1 ? m16 & 7 : m16, xoff = xm * 128 + ((kg ^ (xm >> 1)) << 4);     // NX == 1: columns past the eighth repeat
   int st = 0, st_load = ST - 1;
   for (int c = 0; c < n; ++c) {
     // chunk c has landed, and the reads of chunk c - 1, whose stage is filled next, are done
@@ -159,10 +175,10 @@ __device__ __forceinline__ void shrink_group(uint8_t* smem, const uint16_t* xrow
     const uint8_t* buf = smem + st * kStage;
 #pragma unroll
     for (int k2 = 0; k2 < 2; ++k2) {
-      const vec xf = *reinterpret_cast<const vec*>(buf + (off ^ (k2 << 6)));
+      const vec xf = *reinterpret_cast<const vec*>(buf + (xoff ^ (k2 << 6)));
 #pragma unroll
       for (int i = 0; i < NB; ++i)
-        acc[i][k2] = L::mfma(*reinterpret_cast<const vec*>(buf + 2048 * (1 + i) + (off ^ (k2 << 6))), xf, acc[i][k2]);
+        acc[i][k2] = L::mfma(*reinterpret_cast<const vec*>(buf + 1024 * (NX + 2 * i) + (off ^ (k2 << 6))), xf, acc[i][k2]);
     }
     st = st + 1 == ST ? 0 : st + 1;
     st_load = st_load + 1 == ST ? 0 : st_load + 1;
@@ -177,16 +193,16 @@ __device__ __forceinline__ void shrink_group(uint8_t* smem, const uint16_t* xrow
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the look-ahead loads must land before the LDS is released
 }
 
-// NT: tiles of 16 ranks the launch allows for
-template <typename L, int NT>
+// NT: tiles of 16 ranks the launch allows for; NB: those that a wave takes (NT == 4: two, by two waves, or all four)
+template <typename L, int NT, int NB>
 __global__ __launch_bounds__(64) void lora_small_shrink_kernel(FlpLoraArgs a, FlpLoraSmall c) {
-  constexpr int kLds = NT == 4 ? 30 * 1024 : 24 * 1024;
+  constexpr int kLds = NB == 4 ? 30 * 1024 : NT == 4 ? 20 * 1024 : 24 * 1024;
   __shared__ __attribute__((aligned(1024))) uint8_t smem[kLds];
   const int lane = threadIdx.x, m16 = lane & 15, kg = lane >> 4;
   const int t = blockIdx.x;
   const int ks = blockIdx.y % c.k_splits, p = blockIdx.y / c.k_splits;
   FlpLoraGroup* rec = c.groups + t;
-  const bool writes = blockIdx.y == 0;                 // one of the token's waves leaves the record for the expand step
+  const bool writes = blockIdx.y + blockIdx.z == 0;    // one of the token's waves leaves the record for the expand step
   const int ad = __builtin_amdgcn_readfirstlane(a.token_adapter[t]);
   int r = 0, tok = t, n = 0;
   if (ad >= 0 && ad < a.n_adapters) {
@@ -209,33 +225,41 @@ __global__ __launch_bounds__(64) void lora_small_shrink_kernel(FlpLoraArgs a, Fl
       rec->row[lane] = a.proj[lane].b_row_base[ad];
     }
   }
-  if (n == 0) return;
+  const int rank0 = NB < NT ? 16 * NB * (int)blockIdx.z : 0;   // the wave's first rank
+  if (n == 0 || rank0 >= r) return;
+  r -= rank0;
   const flp_lora_proj& pr = a.proj[p];
   const int rpb = (int)(a.block_elems / a.d_in);
-  const int row = pr.a_row_base[ad] + (lane < r ? lane : 0);       // lane rho looks up the page row of rank rho
+  const int row = pr.a_row_base[ad] + rank0 + (lane < r ? lane : 0);       // lane rho looks up the page row of rank rank0 + rho
   const uint16_t* const arow = reinterpret_cast<const uint16_t*>(a.pool) +
                                (int64_t)a.tables[pr.a_tab_off[ad] + row / rpb] * a.block_elems + (int64_t)(row % rpb) * a.d_in;
   const uint16_t* const x = reinterpret_cast<const uint16_t*>(a.x);
   const int chunks = a.d_in / 64, c0 = chunks * ks / c.k_splits, c1 = chunks * (ks + 1) / c.k_splits;
   // lane (token m16, ranks 4 kg .. 4 kg + 3 of a tile)
-  float* const vp = a.v + (((int64_t)ks * a.T + tok) * a.n_proj + p) * (16 * NT) + 4 * kg;
-  auto run = [&](auto tiles) {
-    constexpr int NB = decltype(tiles)::value;
-    f32x4 v[NB];
-    shrink_group<L, NB, kLds>(smem, x, arow, tok, a.ld_x, r, c0, c1, t + t / 16 + p, v);
+  float* const vp = a.v + (((int64_t)ks * a.T + tok) * a.n_proj + p) * (16 * NT) + rank0 + 4 * kg;
+  auto run = [&](auto tiles, auto x_loads) {
+    constexpr int B = decltype(tiles)::value, NX = decltype(x_loads)::value;
+    f32x4 v[B];
+    shrink_group<L, B, NX, kLds>(smem, x, arow, tok, a.ld_x, r, c0, c1, t + t / 16 + p, v);
 #pragma unroll
-    for (int nt = 0; nt < NB; ++nt) {
+    for (int nt = 0; nt < B; ++nt) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[nt][i] = 16 * nt + 4 * kg + i < r ? v[nt][i] : 0.f;
       if (m16 < n) *reinterpret_cast<f32x4*>(vp + 16 * nt) = v[nt];
     }
   };
-  if (NT == 1 || r <= 16)
-    run(std::integral_constant<int, 1>{});
-  else if (NT == 2 || r <= 32)
-    run(std::integral_constant<int, NT < 2 ? 1 : 2>{});
+  const auto by_tokens = [&](auto tiles) {
+    if (n <= 8)
+      run(tiles, std::integral_constant<int, 1>{});
+    else
+      run(tiles, std::integral_constant<int, 2>{});
+  };
+  if (NB == 1 || r <= 16)
+    by_tokens(std::integral_constant<int, 1>{});
+  else if (NB == 2 || r <= 32)
+    by_tokens(std::integral_constant<int, NB < 2 ? 1 : 2>{});
   else
-    run(std::integral_constant<int, NT>{});
+    by_tokens(std::integral_constant<int, NB>{});
 }
 
 // the slices' sums in order, B of them requested together
@@ -282,10 +306,15 @@ __global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, Fl
   typedef typename L::S S;
   __shared__ f32x4 v_lds[64 * NT / 4];                 // [token (of 4)][four ranks]
   const int lane = threadIdx.x, m16 = lane & 15, kg = lane >> 4;
-  const int t = blockIdx.y, p = blockIdx.z;            // columns vary fastest: rows are often a power of two bytes apart
+  // the projections one after the other; columns vary fastest: rows are often a power of two bytes apart
+  int p = 0;
+  unsigned unit = blockIdx.x, chunks = (unsigned)(a.proj[0].d_out + 127) / 128;
+  while (unit >= chunks * (unsigned)a.T) {
+    unit -= chunks * (unsigned)a.T;
+    chunks = (unsigned)(a.proj[++p].d_out + 127) / 128;
+  }
+  const int t = (int)(unit / chunks), col0 = (int)(unit % chunks) * 128;
   const flp_lora_proj& pr = a.proj[p];
-  const int col0 = blockIdx.x * 128;
-  if (col0 >= pr.d_out) return;
   const FlpLoraGroup* __restrict__ rec = c.groups + t;
   const int n = __builtin_amdgcn_readfirstlane(rec->n);
   if (n == 0) return;
@@ -411,11 +440,16 @@ __global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, Fl
 
 template <typename L, int NT>
 void launch(const FlpLoraArgs& a, const FlpLoraSmall& c, hipStream_t stream) {
-  int max_dout = 0;
-  for (int p = 0; p < a.n_proj; ++p) max_dout = a.proj[p].d_out > max_dout ? a.proj[p].d_out : max_dout;
-  const dim3 gs((unsigned)a.T, (unsigned)(a.n_proj * c.k_splits));
-  const dim3 ge((unsigned)((max_dout + 127) / 128), (unsigned)a.T, (unsigned)a.n_proj);
-  hipLaunchKernelGGL((lora_small_shrink_kernel<L, NT>), gs, dim3(64), 0, stream, a, c);
+  unsigned chunks = 0;
+  for (int p = 0; p < a.n_proj; ++p) chunks += (unsigned)(a.proj[p].d_out + 127) / 128;
+  const dim3 ge(chunks * (unsigned)a.T);
+  dim3 gs((unsigned)a.T, (unsigned)(a.n_proj * c.k_splits));
+  if (NT == 4 && a.T <= 512) {
+    gs.z = 2;
+    hipLaunchKernelGGL((lora_small_shrink_kernel<L, NT, NT == 4 ? 2 : NT>), gs, dim3(64), 0, stream, a, c);
+  } else {
+    hipLaunchKernelGGL((lora_small_shrink_kernel<L, NT, NT>), gs, dim3(64), 0, stream, a, c);
+  }
   hipLaunchKernelGGL((lora_small_expand_kernel<L, NT>), ge, dim3(64), 0, stream, a, c);
 }
 template <typename L>

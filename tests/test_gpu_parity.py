@@ -918,6 +918,8 @@ def test_dense_products_of_rows_far_apart(T, d_in, widths, ld_x, plan):
     ("f16", 96, 704, (128, 264, 8), (1, 4, 5, 16, 17, 33), (17, 32, 1, 31, 16, 32)),    # two tiles of ranks, 16 or fewer among them
     ("bf16", 1024, 4096, (136,), (1, 3, 64, 500, 19, 437), (33, 64, 48, 1, 16, 49)),    # four tiles, the largest batch
     ("f16", 3, 8192, (1032,), (3,), (64,)),                                             # sixteen slices of d_in
+    ("f16", 512, 1024, (264, 8, 1160), (8, 9, 7, 200, 24, 25), (64, 33, 48, 64, 17, 49)),   # 64 ranks by two waves, groups of 8 and 9
+    ("bf16", 513, 1024, (8, 1160, 264), (8, 9, 7, 200, 24, 25), (64, 33, 48, 64, 32, 49)),  # and by one
 ])
 def test_lora_of_small_batches_in_groups_of_every_size(dtype, T, d_in, widths, counts, ranks):
     """Adapters with 1 to 500 tokens, mixed over the batch (a group takes up to sixteen of one adapter, up to four go to
