@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "fllayer.h"
 #include "flp_internal.h"
@@ -41,27 +42,37 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-// One workgroup per token row, for rows of up to 256 NV vectors of 16 bytes: all loads of the row (and of the delta and the
-// gains) are in flight together and the row stays in registers between the sum of squares and the scaling, so the call is
-// one trip to memory.  With a delta the rounded residual is stored and the sum is taken over it.  A batch of a few rows is
-// bound by that trip, a large one by the bytes.  The layer's three calls, with a wave per row in two passes, with this:
+// W waves (4 or 1) per token row, four waves to a workgroup, for rows of up to 64 W NV vectors of 16 bytes: all loads of the row
+// (and of the delta and the gains) are in flight together and the row stays in registers between the sum of squares and the
+// scaling, so the call is one trip to memory.  With a delta the rounded residual is stored and the sum is taken over it.  A
+// batch of a few rows is bound by that trip, a large one by the bytes, or by the number of workgroups where the rows are short:
+// those of up to 96 vectors (128 without a delta) take one wave.  The layer's three calls, with a wave per row in two passes, with this:
 //   8 rows of 4096, bf16          6.7 10.5 5.7    4.7 3.7 4.6 us
 //   9876 rows of 5120, fp16      45.8 83.8 55.8   30.8 61.1 46.4 us (6.6 TB/s in the second)
-template <typename S, int NV>
+// Norm, norm with residual of short bf16 rows, in two passes, four waves, one:
+//   40000 rows of   64    15.7 27.9 14.6    19.8 36.5 18.6 us
+//   10000 rows of  256     9.1 11.8  8.8    11.5 15.0 11.3 us
+//   40000 rows of  256    19.8 31.8 17.9    28.4 45.6 26.2 us
+//   40000 rows of  512    25.4 35.5 24.3    43.2 50.3 42.7 us
+//   40000 rows of  768    38.2 44.3 37.0    63.5 61.6 62.8 us
+//   40000 rows of 1024    47.8 47.6 46.5    80.4 69.9 81.7 us
+template <typename S, int NV, int W>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const typename S::storage* x_in, typename S::storage* resid,
                                                       const typename S::storage* __restrict__ delta,
                                                       const typename S::storage* __restrict__ w,
-                                                      typename S::storage* y, int H, float eps) {
+                                                      typename S::storage* y, int T, int H, float eps) {
   typedef typename S::storage ST;
   constexpr int N = Vec<S>::N;
   __shared__ float part[4];
-  const int64_t row = (int64_t)blockIdx.x * H;
-  const int c0 = threadIdx.x * N;
+  const int t = W == 4 ? blockIdx.x : 4 * blockIdx.x + (threadIdx.x >> 6);
+  if (W < 4 && t >= T) return;                         // W == 1: the waves of a workgroup share nothing
+  const int64_t row = (int64_t)t * H;
+  const int c0 = (threadIdx.x & (64 * W - 1)) * N;
   const ST* xr = (delta ? resid : x_in) + row;
   Vec<S> a[NV], d[NV], g[NV];
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    const int c = c0 + i * 256 * N;
+    const int c = c0 + i * 64 * W * N;
     if (c >= H) break;
     a[i] = ldv<S>(xr + c);
     if (delta) d[i] = ldv<S>(delta + row + c);
@@ -70,7 +81,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const typename S::storage*
   float ss = 0.f;
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    const int c = c0 + i * 256 * N;
+    const int c = c0 + i * 64 * W * N;
     if (c >= H) break;
     if (delta) {
 #pragma unroll
@@ -85,12 +96,15 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const typename S::storage*
   }
   if (!y) return;
   ss = wave_sum(ss);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
-  __syncthreads();
-  const float inv = 1.0f / sqrtf(((part[0] + part[1]) + (part[2] + part[3])) / (float)H + eps);
+  if (W == 4) {
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = ss;
+    __syncthreads();
+    ss = (part[0] + part[1]) + (part[2] + part[3]);
+  }
+  const float inv = 1.0f / sqrtf(ss / (float)H + eps);
 #pragma unroll
   for (int i = 0; i < NV; ++i) {
-    const int c = c0 + i * 256 * N;
+    const int c = c0 + i * 64 * W * N;
     if (c >= H) break;
     Vec<S> o;
 #pragma unroll
@@ -228,14 +242,23 @@ flp_status norm_common(int32_t dtype, const void* x, void* resid, const void* de
   if (T == 0) return FLP_OK;
   hipStream_t st = (hipStream_t)hip_stream;
   const int64_t vecs = (int64_t)H * elem_bytes(dtype) / 16;         // 16-byte vectors per row
-  if (vecs <= 512)
-    FLL_BY_DTYPE(dtype, hipLaunchKernelGGL((rmsnorm_kernel<S_, 2>), dim3(T), dim3(256), 0, st, (const S_::storage*)x,
-                                           (S_::storage*)resid, (const S_::storage*)delta, (const S_::storage*)w,
-                                           (S_::storage*)y, H, eps));
+  const auto launch = [&](auto vectors, auto waves) {
+    constexpr int NV = decltype(vectors)::value, W = decltype(waves)::value;
+    FLL_BY_DTYPE(dtype, hipLaunchKernelGGL((rmsnorm_kernel<S_, NV, W>), dim3(W == 4 ? T : (T + 3) / 4), dim3(256), 0, st,
+                                           (const S_::storage*)x, (S_::storage*)resid, (const S_::storage*)delta,
+                                           (const S_::storage*)w, (S_::storage*)y, T, H, eps));
+  };
+  typedef std::integral_constant<int, 1> one;
+  typedef std::integral_constant<int, 2> two;
+  typedef std::integral_constant<int, 4> four;
+  if (vecs <= 64)
+    launch(one{}, one{});
+  else if (vecs <= (delta ? 96 : 128))                 // 10000 rows of 1024: norm 15.2 with one wave, 16.7 with four; with residual 25.2, 23.6 us
+    launch(two{}, one{});
+  else if (vecs <= 512)
+    launch(two{}, four{});
   else if (vecs <= 1024)
-    FLL_BY_DTYPE(dtype, hipLaunchKernelGGL((rmsnorm_kernel<S_, 4>), dim3(T), dim3(256), 0, st, (const S_::storage*)x,
-                                           (S_::storage*)resid, (const S_::storage*)delta, (const S_::storage*)w,
-                                           (S_::storage*)y, H, eps));
+    launch(four{}, four{});
   else
     FLL_BY_DTYPE(dtype, hipLaunchKernelGGL(rmsnorm_long_kernel<S_>, dim3((T + 3) / 4), dim3(256), 0, st,
                                            (const S_::storage*)x, (S_::storage*)resid, (const S_::storage*)delta,

@@ -29,7 +29,13 @@ def within_one_rounding(got, want, dtype):
     return not bad.any(), float(np.abs(got - want).max()), int(bad.sum())
 
 
-@pytest.mark.parametrize("dtype,T,H", [("f16", 37, 4096), ("bf16", 5, 5120), ("f32", 9, 256), ("f16", 1, 8), ("bf16", 130, 8192)])
+@pytest.mark.parametrize("dtype,T,H", [("f16", 37, 4096), ("bf16", 5, 5120), ("f32", 9, 256), ("f16", 1, 8), ("bf16", 130, 8192),
+                                       # both sides of the limits between the forms of the kernel: 64, 96, 128, 512 and 1024 vectors
+                                       # of 16 bytes; batches that do not fill the last workgroup of four rows
+                                       ("bf16", 4, 512), ("f16", 6, 520), ("f32", 7, 260), ("f16", 5, 768), ("bf16", 3, 776),
+                                       ("f32", 2, 388),
+                                       ("f16", 5, 1024), ("bf16", 6, 1032), ("bf16", 3, 4104), ("f32", 6, 2052), ("f32", 3, 4096), ("f16", 7, 8200),
+                                       ("f32", 5, 4100), ("f16", 6, 16384), ("bf16", 1, 24584), ("f32", 9, 8200)])
 def test_rmsnorm_and_fused_residual(dtype, T, H):
     rng = np.random.default_rng(T * 1000 + H)
     x_st, xv = lo.round_store(rng.normal(0, 1.5, (T, H)), dtype)
