@@ -206,9 +206,10 @@ extern "C" flp_status flp_pool_free(flp_pool* p, int32_t tier, int32_t n, const 
 flp_status flp_stage_acquire(flp_pool* p, size_t bytes, FlpStageSlot** out) {
   FlpStageSlot& s = p->stage[p->stage_next];
   p->stage_next = (p->stage_next + 1) % kStageSlots;
-  // what the event says is that the slot may be filled again; no data reaches the host by it, so it needs no system fence
-  // (5.5 -> 4 us between the kernels on either side of it)
-  if (!s.ev) FLP_TRY_HIP(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming | hipEventDisableSystemFence));
+  // The event is queried and waited for by the host (the slot may be filled again) and by other streams (the split contexts'
+  // workspace), so it keeps its fence; without one it is 1.5 us cheaper, but an inspection then says nothing about the work
+  // before it.
+  if (!s.ev) FLP_TRY_HIP(hipEventCreateWithFlags(&s.ev, hipEventDisableTiming));
   if (s.in_flight) {
     // normally the slot's last use finished long ago: poll first, block only if it has not
     hipError_t q = hipEventQuery(s.ev);

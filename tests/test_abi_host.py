@@ -309,3 +309,19 @@ def test_binding_fails_loudly_without_the_library(tmp_path):
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
     assert r.returncode == 7, r.stdout + r.stderr
     assert "not built" in r.stdout
+
+
+def test_staging_events_are_fenced_where_they_are_inspected(tmp_path):
+    """tests/stage_events.cpp: the staging ring and the workspaces handed from call to call, over a model of events that
+    refuses to be queried, synchronised with or waited for without the fence that makes that meaningful."""
+    import shutil
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    csrc, exe = os.path.join(ROOT, "paper_2505_03756_amd", "csrc"), str(tmp_path / "stage_events")
+    b = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(ROOT, "include"), "-I" + csrc,
+                        "-I/opt/rocm/include", os.path.join(ROOT, "tests", "stage_events.cpp"), os.path.join(csrc, "pool.cpp"),
+                        "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib", "-pthread", "-o", exe],
+                       capture_output=True, text=True, timeout=300)
+    assert b.returncode == 0, b.stderr[-3000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and "fenced" in r.stdout, (r.stdout + r.stderr)[-3000:]
