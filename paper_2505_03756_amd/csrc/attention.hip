@@ -35,8 +35,9 @@ constexpr int BT = 16;   // token positions per group: a block holds one (block 
 // A unit of one slot (a decode batch's) would read and write whole 16-slot runs to place one value in each; its V goes
 // straight from registers to its slots in element-wide stores.
 //
-// The first n_copy workgroups copy the work lists of the attention launch that follows, and the units are read from pinned
-// memory: one launch instead of two uploads and the append, and one event (about 4 us between two kernels) instead of two.
+// The first n_copy workgroups copy the work lists of the attention launch that follows, and the units of a small launch are read
+// from pinned memory: one launch instead of two uploads and the append, and one event (about 4 us between two kernels)
+// instead of two.
 // Whole steps: 119 fp32 tokens 46.2 -> 35.6 us, six long conversations 137 -> 124 us; layer of 8 decode tokens 231 -> 217 us.
 template <typename S, int D>
 __global__ __launch_bounds__(256, 2) void kv_append_kernel(FlpAttnArgs a, const FlpAppendUnit* __restrict__ units, int n_copy,
@@ -372,16 +373,20 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(FlpAttnArgs a, const in
     }                                                                                                        \
   } while (0)
 
-flp_status flp_launch_kv_append(int dtype, int head_dim, const FlpAttnArgs& a, const FlpAppendUnit* units_host,
-                                int32_t n_units, const void* copy_src, void* copy_dst, size_t copy_bytes, hipStream_t stream) {
+// the append kernel only moves storage words: fp16 and bf16 share the 16-bit instance
+int flp_kv_append_columns(int dtype, int n_kv, int head_dim) {
+  const int epv = dtype == FLP_F32 ? 4 : 8;
+  return (n_kv * head_dim + 256 * epv - 1) / (256 * epv);
+}
+
+flp_status flp_launch_kv_append(int dtype, int head_dim, const FlpAttnArgs& a, const FlpAppendUnit* units, int32_t n_units,
+                                const void* copy_src, void* copy_dst, size_t copy_bytes, hipStream_t stream) {
   const int64_t n_vec = (int64_t)((copy_bytes + 15) / 16);
   const int64_t n_copy = (n_vec + 255) / 256;
   if (n_units + n_copy <= 0) return FLP_OK;
-  // the append kernel only moves storage words: fp16 and bf16 share the 16-bit instance
-  const int epv = dtype == FLP_F32 ? 4 : 8;
-  const dim3 grid((unsigned)(n_units + n_copy), n_units ? (unsigned)((a.n_kv * head_dim + 256 * epv - 1) / (256 * epv)) : 1u);
+  const dim3 grid((unsigned)(n_units + n_copy), n_units ? (unsigned)flp_kv_append_columns(dtype, a.n_kv, head_dim) : 1u);
   const auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, a, units_host, (int)n_copy, (const u32x4*)copy_src, (u32x4*)copy_dst,
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, a, units, (int)n_copy, (const u32x4*)copy_src, (u32x4*)copy_dst,
                        n_vec);
   };
   if (dtype == FLP_F32 && head_dim == 64)

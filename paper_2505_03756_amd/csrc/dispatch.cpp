@@ -101,6 +101,15 @@ std::vector<FlpAppendUnit> append_units(const flp_attn_batch* b) {
   return units;
 }
 
+// Whether the append launch reads its units where they were staged, in pinned host memory, or from a copy that a launch of its
+// own makes first.  Up to as many workgroups as the chip holds at once (two per CU) all reads are under way together, and
+// sparing the copy is worth 3 us (400 workgroups: 16 -> 13 us).  More of them read in turns, and now and then such a launch has
+// taken a microsecond or so for every workgroup instead: 20 sequences of 2000 tokens, 5040 workgroups, 254 us or 4.1 ms, the mean of
+// sixty calls 252 to 990 us; 257 us each with the copy.
+bool append_reads_host(const flp_pool* p, size_t n_units) {
+  return n_units * (size_t)flp_kv_append_columns(p->cfg.dtype, p->cfg.n_kv_heads, p->cfg.head_dim) <= 512;
+}
+
 }  // namespace
 
 extern "C" flp_status flp_kv_append(flp_pool* p, const flp_attn_batch* b, void* hip_stream) {
@@ -109,10 +118,15 @@ extern "C" flp_status flp_kv_append(flp_pool* p, const flp_attn_batch* b, void* 
   const std::vector<FlpAppendUnit> units = append_units(b);
   if (units.empty()) return FLP_OK;
   FlpStageSlot* slot = nullptr;
-  FLP_TRY(flp_stage_acquire(p, units.size() * sizeof(FlpAppendUnit), &slot));
-  memcpy(slot->host, units.data(), units.size() * sizeof(FlpAppendUnit));
-  flp_status s1 = flp_launch_kv_append(p->cfg.dtype, p->cfg.head_dim, make_args(p, b), (const FlpAppendUnit*)slot->host,
-                                       (int32_t)units.size(), nullptr, nullptr, 0, (hipStream_t)hip_stream);
+  const size_t bytes = units.size() * sizeof(FlpAppendUnit);
+  FLP_TRY(flp_stage_acquire(p, bytes, &slot));
+  memcpy(slot->host, units.data(), bytes);
+  const bool direct = append_reads_host(p, units.size());
+  flp_status s1 = direct ? FLP_OK : flp_stage_upload(slot, bytes, (hipStream_t)hip_stream);
+  if (s1 == FLP_OK)
+    s1 = flp_launch_kv_append(p->cfg.dtype, p->cfg.head_dim, make_args(p, b),
+                              (const FlpAppendUnit*)(direct ? slot->host : slot->dev), (int32_t)units.size(), nullptr, nullptr, 0,
+                              (hipStream_t)hip_stream);
   flp_status s2 = flp_stage_release(slot, (hipStream_t)hip_stream);
   return s1 != FLP_OK ? s1 : s2;
 }
@@ -248,8 +262,8 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   if (n_merge)
     FLP_TRY(flp_attn_workspace(p, (size_t)merge_first.back() * b->n_q_heads * (p->cfg.head_dim + 2) * sizeof(float), stream,
                                &partials));
-  // one staging slot: the append step's units, read from pinned memory, then what is copied to the device beside the append
-  // step: the lists of the attention launches and, for the tiled kernel, the sequences' lengths
+  // one staging slot: the append step's units, then what is copied to the device by the append launch (or, with the units, before
+  // it): the lists of the attention launches and, for the tiled kernel, the sequences' lengths
   const std::vector<FlpAppendUnit> append = with_append ? append_units(b) : std::vector<FlpAppendUnit>{};
   const size_t S = (size_t)b->n_seqs;
   const auto up = [](size_t n) { return (n + 31) & ~(size_t)31; };
@@ -279,8 +293,16 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   const FlpAttnUnit* du = (const FlpAttnUnit*)(d + off_units);
   const FlpMfmaItem* di = (const FlpMfmaItem*)(d + off_items);
   const int32_t* dm = (const int32_t*)(d + off_merge);
-  flp_status st = flp_launch_kv_append(p->cfg.dtype, p->cfg.head_dim, a, (const FlpAppendUnit*)h, (int32_t)append.size(),
-                                       h + off_units, (uint8_t*)slot->dev + off_units, bytes - off_units, stream);
+  flp_status st = FLP_OK;
+  if (append_reads_host(p, append.size())) {
+    st = flp_launch_kv_append(p->cfg.dtype, p->cfg.head_dim, a, (const FlpAppendUnit*)h, (int32_t)append.size(), h + off_units,
+                              (uint8_t*)slot->dev + off_units, bytes - off_units, stream);
+  } else {
+    st = flp_stage_upload(slot, bytes, stream);
+    if (st == FLP_OK)
+      st = flp_launch_kv_append(p->cfg.dtype, p->cfg.head_dim, a, (const FlpAppendUnit*)d, (int32_t)append.size(), nullptr, nullptr,
+                                0, stream);
+  }
   if (st == FLP_OK) st = flp_launch_attn_mfma(p->cfg.dtype, a, di, (int32_t)n_items, stream);
   if (st == FLP_OK)
     st = decode_ok ? flp_launch_attn_decode(p->cfg.dtype, a, du, (int32_t)units.size(), stream)

@@ -154,10 +154,11 @@ struct FlpAttnArgs {
   float* partials;             // split-KV: [piece][n_h][head_dim + 2] fp32 (running max, sum, channels)
 };
 
-// The append units are read where they were staged, in pinned host memory; beside them the launch copies copy_bytes (a
-// multiple of 16) of the attention call's lists from pinned memory to their device mirror.
-flp_status flp_launch_kv_append(int dtype, int head_dim, const FlpAttnArgs& a, const FlpAppendUnit* units_host,
-                                int32_t n_units, const void* copy_src, void* copy_dst, size_t copy_bytes, hipStream_t stream);
+// Every unit is read by flp_kv_append_columns workgroups, from pinned host memory or the device; beside them the launch copies
+// copy_bytes (rounded up to 16) of the attention call's lists from pinned memory to their device mirror.
+int flp_kv_append_columns(int dtype, int n_kv, int head_dim);
+flp_status flp_launch_kv_append(int dtype, int head_dim, const FlpAttnArgs& a, const FlpAppendUnit* units, int32_t n_units,
+                                const void* copy_src, void* copy_dst, size_t copy_bytes, hipStream_t stream);
 flp_status flp_launch_attn_rows(int dtype, int head_dim, const FlpAttnArgs& a, const FlpAttnUnit* units_dev,
                                 int32_t n_units, hipStream_t stream);
 // single new tokens on the matrix cores: 16-bit pools, head_dim 128, n_h / n_kv <= kDecodeMaxGroup; every unit is ONE token

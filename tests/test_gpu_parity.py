@@ -130,6 +130,48 @@ def test_append_of_units_of_every_length(dtype, bt, kv, d):
         pool.close()
 
 
+@pytest.mark.parametrize("dtype,kv,d,units", [("bf16", 1, 128, 512), ("bf16", 1, 128, 513), ("f16", 17, 128, 256), ("f16", 17, 128, 257),
+                                              ("f32", 5, 64, 513)])
+def test_append_of_as_many_units_as_are_read_from_the_host_and_of_more(dtype, kv, d, units):
+    """512 workgroups read their units from pinned memory, more have them copied first (17 kv heads of 128: two workgroups per unit).
+    Single tokens and one longer sequence; the append call bit for bit, and in front of the attention step with its result."""
+    rng = np.random.default_rng(units)
+    st = np.float32 if dtype == "f32" else np.uint16
+    seqs = [(int(p), 1) for p in rng.integers(0, 40, units - 3)] + [(7, 40)]               # 9 + 16 + 15 slots
+    nb = [(p + n + 15) // 16 for p, n in seqs]
+    assert sum((p + n - 1) // 16 - p // 16 + 1 for p, n in seqs) == units
+    tables = np.full((len(seqs), max(nb)), -1, np.int32)
+    ids, at = rng.permutation(sum(nb)).astype(np.int32), 0
+    for i, k in enumerate(nb):
+        tables[i, :k] = ids[at:at + k]
+        at += k
+    cu = np.concatenate([[0], np.cumsum([n for _, n in seqs])]).astype(np.int32)
+    prefix = np.array([p for p, _ in seqs], np.int32)
+    T = int(cu[-1])
+    rand = lambda shape: wl.quantize(rng.standard_normal(shape).astype(np.float32), dtype)
+    pool0, k, v, q = rand((at, 2 * 16 * kv * d)), rand((T, kv * d)), rand((T, kv * d)), rand((T, kv * d))
+    want = pool0.copy()
+    oracle.kv_append(want, dtype, 16, kv, d, cu, prefix, tables, k, v)
+    out = oracle.paged_attention(want, dtype, 16, kv, d, kv, cu, prefix, tables, q)
+    up = lambda a: torch.from_numpy(a if dtype == "f32" else a.view(np.int16)).cuda()
+    for attend in (False, True):
+        dev = up(pool0.copy())
+        pool = flpool.Pool(dtype, kv, d, at, 0, block_tokens=16, dev=dev)
+        got = torch.empty_like(up(q))
+        for _ in range(2):                               # another staging slot, the same result
+            if attend:
+                pool.paged_prefix_attention(up(q), got, cu, prefix, torch.from_numpy(tables).cuda(), kv, k_new=up(k), v_new=up(v))
+            else:
+                pool.kv_append(up(k), up(v), cu, prefix, torch.from_numpy(tables).cuda())
+        torch.cuda.synchronize()
+        assert np.array_equal(dev.cpu().numpy().view(st).view(np.uint8), want.view(np.uint8)), attend
+        if attend:
+            rtol, atol = TOL[dtype]
+            ok, worst, nbad = close(wl.dequantize(got.cpu().numpy().view(st), dtype).reshape(out.shape), out, rtol, atol)
+            assert ok, "max err %g (%d bad)" % (worst, nbad)
+        pool.close()
+
+
 def test_attention_matches_oracle(case):
     step, cfg = case, case.cfg
     dev0 = resident_pool(step)       # fresh blocks hold NaN patterns until the append fills their slots
