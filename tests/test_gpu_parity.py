@@ -344,9 +344,10 @@ def test_lora_call_with_one_two_or_four_projections(names, case):
 @pytest.mark.parametrize("dtype,T", [("bf16", 1), ("bf16", 63), ("f32", 257), ("bf16", 1023), ("f16", 1024),
                                      ("f32", 1025)])
 def test_lora_small_batches_share_adapter_pages(dtype, T):
-    """The per-token kernels take the tokens of one adapter four at a time (batches of up to 1024 tokens): batches
-    around that limit and around the 64-token words of the kernels' bit mask, with adapters that own one token, a
-    few, or a third of the batch, tokens without an adapter, and widths that do not fill the column slabs."""
+    """Batches of up to 1024 tokens take the tokens of one adapter together, sixteen at a time in 16 bits and four at a time in
+    the vector kernels (fp32): batches around that limit and around the 64-token words of the kernels' bit masks, with
+    adapters that own one token, a few, or a third of the batch, tokens without an adapter, and widths that do not
+    fill the column slabs."""
     cfg = small_cfg(dtype, hidden=320, n_q_heads=5, n_kv_heads=1, head_dim=64, n_seqs=T, prefix_range=(0, 0),
                     new_range=(1, 1), decode_frac=1.0, n_adapters=40, ranks=(8, 16, 32, 64), n_dev_blocks=2600,
                     swap_in_frac=0.0, seed=300 + T)
@@ -927,6 +928,20 @@ def test_dense_products_with_adapters_on_every_tile_whole_and_in_slices(dtype, T
         assert bool(((yi.double() - wi).abs() <= bi).all())
 
 
+@pytest.mark.parametrize("T,d_in,widths,room,plan", [
+    (1100, 11008, (4096,), 60 << 20, ("256x256", 3)),      # slices added by a kernel that keeps the unrounded sum, sorted tokens
+    (1100, 4096, (1032, 72), 60 << 20, ("256x128", 4)),    # the same in front of the vector kernels, every token alone
+    (1000, 512, (16392, 8200), 0, ("256x256", 1)),         # 98 MB of sums: vector kernels, tokens of an adapter in fours
+])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_dense_products_with_adapters_outside_the_small_batch_kernels(dtype, T, d_in, widths, room, plan):
+    """16-bit batches with dense bases whose branches neither the kernels for small batches nor the fused product take."""
+    assert dense_plan(T, d_in, widths, room=room) == plan
+    ta, y, want, bound = _lora_call(dtype, T, d_in, widths, [-1, 0, 1, 2, 3], [8, 16, 64, 33], T)
+    for yi, wi, bi in zip(y, want, bound):
+        assert bool(((yi.double() - wi).abs() <= bi).all())
+
+
 @pytest.mark.parametrize("T,d_in,widths,ld_x,plan", [
     (641, 1024, (2056, 4104, 4104), (1 << 23) + 64, ("256x256", 1)),        # 256 rows span a little more than 4 GiB
     (300, 8192, (264, 72, 72), (1 << 24) + 64, ("128x128", 16)),            # 128 rows do
@@ -960,6 +975,9 @@ def test_dense_products_of_rows_far_apart(T, d_in, widths, ld_x, plan):
     ("f16", 96, 704, (128, 264, 8), (1, 4, 5, 16, 17, 33), (17, 32, 1, 31, 16, 32)),    # two tiles of ranks, 16 or fewer among them
     ("bf16", 1024, 4096, (136,), (1, 3, 64, 500, 19, 437), (33, 64, 48, 1, 16, 49)),    # four tiles, the largest batch
     ("f16", 3, 8192, (1032,), (3,), (64,)),                                             # sixteen slices of d_in
+    ("bf16", 96, 288, (8, 136), (1, 4, 5, 16, 17, 33), (16, 1, 15, 8, 64, 7)),          # d_in no multiple of 64: the vector kernels,
+    ("f16", 1000, 288, (128, 264, 1032), (1, 3, 64, 500, 19, 400), (33, 64, 48, 2, 16, 32)),    # tokens of an adapter in fours
+    ("f16", 1100, 704, (72, 264), (1, 3, 64, 500, 19, 437), (33, 64, 48, 2, 16, 32)),   # too long for that: every token alone
     ("f16", 512, 1024, (264, 8, 1160), (8, 9, 7, 200, 24, 25), (64, 33, 48, 64, 17, 49)),   # 64 ranks by two waves, groups of 8 and 9
     ("bf16", 513, 1024, (8, 1160, 264), (8, 9, 7, 200, 24, 25), (64, 33, 48, 64, 32, 49)),  # and by one
 ])

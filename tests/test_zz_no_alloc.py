@@ -59,7 +59,7 @@ def test_static_entry_point_matches_on_two_calls_in_a_row():
     assert 1024 <= mid.n_tokens < big.n_tokens
     _both(mid, ["q", "k", "v"])
     _both(mid, ["o"])
-    # 3) and a decode batch (per-token kernels, mixed ranks, bf16) on yet another pool
+    # 3) and a decode batch (the kernels for up to 1024 tokens, mixed ranks, bf16) on yet another pool
     small = wl.make_step(_cfg("bf16", n_seqs=97, new_range=(1, 1), decode_frac=1.0, n_adapters=20,
                               ranks=(8, 16, 32, 64), seed=504))
     assert small.n_tokens == 97
@@ -91,7 +91,7 @@ def test_static_entry_point_refuses_what_does_not_fit():
 SLICED = [   # tokens, d_in, widths, max_rank, and how many slices a layer's larger room would give
     (1747, 13824, (5120,), 8, 3),          # one slice in 64 MiB
     (257, 22016, (8192,), 8, 8),           # fewer than eight
-    (313, 16384, (13400, 13384), 16, 3),   # two slices fill the array to the last byte before every product is rounded up
+    (347, 16384, (12072, 12024), 16, 3),   # two slices would fill the array to the last byte, before every product is rounded up
     (33, 4096, (4096, 4096, 4096), 16, 4),
     (499, 4096, (4096, 4096, 4096), 16, 1),
 ]
@@ -126,4 +126,42 @@ def test_static_entry_point_sums_dense_products_in_the_same_order(dtype, T, d_in
         want = x.float() @ wi.float().T
         # one rounding of a result of standard deviation 1, and two fp32 sums in different orders
         assert float((b.float() - want).abs().max()) < (2.0 ** -8 if dtype == "f16" else 2.0 ** -5)
+    pool.close()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_slices_at_the_edge_of_the_fixed_array(dtype):
+    """Beside its other intermediates the fixed array has room for two slices of 347 x 24096 sums to the last byte, and each product's are
+    rounded up to 256: the call has to take one slice.  With eight columns less it takes two (the last bits show it), with eight
+    less and a segment list of 2048 adapters beside them one again."""
+    import torch
+    T, d_in, n1, n2 = 347, 16384, 12072, 12024
+    up = lambda n: (n + 255) & ~255
+    # slices of v (4, of 16 ranks), a record of 112 bytes per token, the segment list of one adapter, the permutation
+    rest = up(4 * T * 2 * 16 * 4) + up(112 * T) + up(9 * 4) + up(4 * T)
+    assert 2 * T * (n1 + n2) * 4 == flpool.static_scratch_bytes() - rest
+    assert up(2 * T * n1 * 4) + up(2 * T * n2 * 4) > flpool.static_scratch_bytes() - rest
+    tt = torch.float16 if dtype == "f16" else torch.bfloat16
+    pool = flpool.Pool(dtype, 8, 128, 2, 0, block_tokens=16)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.randn((T, d_in), generator=g, device="cuda").to(tt)
+    w = [(torch.randn((n, d_in), generator=g, device="cuda") / d_in ** 0.5).to(tt) for n in (n1, n2)]
+    none = torch.full((T,), -1, dtype=torch.int32, device="cuda")
+
+    def call(widths, n_adapters):
+        z = torch.zeros(n_adapters, dtype=torch.int32, device="cuda")
+        got = []
+        for static in (False, True):
+            y = [torch.full((T, n), float("nan"), dtype=tt, device="cuda") for n in widths]
+            projs = [dict(y=yi, d_out=n, w_base=wi, w_base_layout=1, a_tab_off=z, a_row_base=z, b_tab_off=z, b_row_base=z)
+                     for yi, n, wi in zip(y, widths, w)]
+            pool.lora_apply_paged(x, none, z, torch.ones(n_adapters, device="cuda"), z, projs, n_tokens=T, d_in=d_in,
+                                  n_adapters=n_adapters, max_rank=16, static=static)
+            got.append(torch.cat([y[0], y[1][:, :n2 - 8]], 1))
+        assert torch.equal(got[0], got[1]), "static and allocating entry points differ"
+        return got[1]
+
+    edge, two, one = call((n1, n2), 1), call((n1, n2 - 8), 1), call((n1, n2 - 8), 2048)
+    assert torch.equal(edge, one)
+    assert not torch.equal(edge, two)
     pool.close()
