@@ -645,8 +645,10 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
     return FLP_OK;
   }
   // base term first where the caller asked for it (x . W_base), then the adapters' deltas on top.
-  // 16-bit pools also keep the product unrounded in the workspace so that base + delta is rounded
-  // once; tokens without an adapter keep the rounded value that the product's kernels wrote into y.
+  // 16-bit pools also keep the product unrounded in the workspace so that base + delta is rounded once.  Where y is written
+  // already, by an unsliced product or by the kernel that adds slices, tokens without an adapter keep that rounded value; with
+  // base_slices > 1 nothing has written y yet, and the small batches' expand step writes every token's, those without a
+  // branch included.
   if (p->elem_bytes == 4) {
     for (int q = 0; q < b->n_proj; ++q)
       if (b->proj[q].w_base)

@@ -579,7 +579,7 @@ __global__ __launch_bounds__(64 * WF * WT, (WF * WT + 3) / 4)
 }
 
 // ---- sum of the slices, in slice order, four features per thread.  GATED: the slices hold [gate | up]; the result is
-//      silu(g) * u with both rounded first.  RED_KEEP: the unrounded sum goes back into slice 0.  RED_ADD: y is a residual
+//      silu(g) * u with both rounded first.  FLP_REDUCE_KEEP: the unrounded sum goes back into slice 0.  FLP_REDUCE_ADD: y is a residual
 //      stream that the rounded sum is added to.
 template <typename G, bool GATED>
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(FlpGemmArgs a, int mode) {
@@ -763,7 +763,9 @@ FlpGemmPlan flp_gemm_plan(int M, int K, int n_proj, const int* N, unsigned allow
                                                          : std::max((double)c.part, std::ceil(rest / 256) / c.per_cu);
       double us = (full + share) * ((double)nk / s * c.step_us + c.fill_us);
       us = std::max(us, n_all * K * 2 / 8.36e6 + 3.3);
-      if (s > 1) us += (double)s * M * n_all * 8 / 4.64e6 + 3.5;      // slices written and read, and the launch that adds them
+      // slices written and read, and the launch that adds them (also where the LoRA expand step of a small batch does: the
+      // constants were fitted with that launch, and its share of the expand step has not been told apart)
+      if (s > 1) us += (double)s * M * n_all * 8 / 4.64e6 + 3.5;
       if (us < best_us) {
         best_us = us;
         best = FlpGemmPlan{kind, s};
@@ -823,7 +825,7 @@ flp_status flp_launch_gemm(int dtype, const void* x, int64_t ld_x, int M, int K,
     pr.N = out[p].N;
     pr.tile0 = a.f_tiles;
     a.f_tiles += (pr.N + c.ft - 1) / c.ft;
-    if (plan.splits > 1) pr.y = nullptr;                 // gemm_reduce writes it
+    if (plan.splits > 1) pr.y = nullptr;                 // whoever adds the slices writes it: gemm_reduce, or the LoRA expand step
   }
   // with more than eight token tiles, 4 x 8 blocks: the workgroups that run together fetch 12 operand panels, not 33
   a.gm = a.m_tiles > 8 ? 8 : a.m_tiles;

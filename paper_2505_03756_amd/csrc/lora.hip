@@ -3,7 +3,7 @@
 // section 4.3: adapters are split along the rank dimension into pool blocks).
 //
 // This file holds the adapter segmentation (stable counting sort of token indices by
-// adapter id) and the vector-ALU shrink / expand kernels that serve fp32 pools.
+// adapter id) and the vector-ALU shrink / expand kernels that serve fp32 pools and what the matrix-core ones leave.
 #include <atomic>
 #include <hip/hip_runtime.h>
 
@@ -211,8 +211,8 @@ __global__ __launch_bounds__(1024) void lora_segment_kernel(int32_t T, const int
 // The per-token kernels below serve fp32 pools and widths the matrix-core tiles do not divide (and calls whose buffer only
 // fits their smaller intermediates); most 16-bit batches take lora_small.hip or lora_mfma.hip.  In a small batch a few
 // tokens share each adapter, and the adapters' pages, not the activations, are the traffic: the tokens of one adapter are
-// therefore taken four at a time by one workgroup, which reads the pages once for all four.  Who belongs together is found by every workgroup
-// itself from the batch's adapter ids (a bit mask of the tokens with the same id, built with ballots);
+// therefore taken four at a time by one workgroup, which reads the pages once for all four.  Who belongs together is found
+// by every workgroup itself from the batch's adapter ids (a bit mask of the tokens with the same id, built with ballots);
 // that scan is only done for batches of up to kShareMaxT tokens, larger ones take every token alone.
 constexpr int kShareTokens = 4;
 constexpr int kShareMaxT = 1024;

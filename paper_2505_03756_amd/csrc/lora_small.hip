@@ -23,7 +23,7 @@
 //              slice mend that for 1 to 7 % of the time)
 //
 // What keeps a batch of many adapters of high rank fast is how much of their pages is in flight: 64 ranks of one token are two
-// waves with a 20 KiB ring each (one with 30 KiB was 10 % slower, both together 15 to 20 % behind the vector kernels); groups of
+// waves with a 20 KiB ring each (one wave with 30 KiB: shrink step 207 against 198 us for 300 tokens of 64 x 8 heads); groups of
 // up to eight tokens fetch eight rows of x instead of sixteen, which leaves room for a fourth stage.  Above 512 tokens the waves
 // with nothing to do are so many that one wave takes all 64 ranks (500 + 500 tokens, rank 64: 109 against 113 us).  The expand
 // step's grid holds the column chunks that there are, projection by projection (64 x 8 heads: three times the chunks of q had
