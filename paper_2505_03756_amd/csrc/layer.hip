@@ -46,7 +46,7 @@ __device__ __forceinline__ float wave_sum(float v) {
 // (and of the delta and the gains) are in flight together and the row stays in registers between the sum of squares and the
 // scaling, so the call is one trip to memory.  With a delta the rounded residual is stored and the sum is taken over it.  A
 // batch of a few rows is bound by that trip, a large one by the bytes, or by the number of workgroups where the rows are short:
-// those of up to 96 vectors (128 without a delta) take one wave.  The layer's three calls, with a wave per row in two passes, with this:
+// those of up to 96 vectors take one wave.  The layer's three calls, with a wave per row in two passes, with this:
 //   8 rows of 4096, bf16          6.7 10.5 5.7    4.7 3.7 4.6 us
 //   9876 rows of 5120, fp16      45.8 83.8 55.8   30.8 61.1 46.4 us (6.6 TB/s in the second)
 // Norm, norm with residual of short bf16 rows, in two passes, four waves, one:
@@ -253,7 +253,8 @@ flp_status norm_common(int32_t dtype, const void* x, void* resid, const void* de
   typedef std::integral_constant<int, 4> four;
   if (vecs <= 64)
     launch(one{}, one{});
-  else if (vecs <= (delta ? 96 : 128))                 // 10000 rows of 1024: norm 15.2 with one wave, 16.7 with four; with residual 25.2, 23.6 us
+  else if (vecs <= 96)   // 10000 rows of 1024: norm 15.2 with one wave, 16.7 with four, with residual 25.2, 23.6 us; with and without
+                         // a residual the sum of squares is taken in one order
     launch(two{}, one{});
   else if (vecs <= 512)
     launch(two{}, four{});
