@@ -36,9 +36,8 @@ constexpr int BT = 16;   // token positions per group: a block holds one (block 
 // straight from registers to its slots in element-wide stores.
 //
 // The first n_copy workgroups copy the work lists of the attention launch that follows, and the units of a small launch are read
-// from pinned memory: one launch instead of two uploads and the append, and one event (about 4 us between two kernels)
-// instead of two.
-// Whole steps: 119 fp32 tokens 46.2 -> 35.6 us, six long conversations 137 -> 124 us; layer of 8 decode tokens 231 -> 217 us.
+// from pinned memory: one launch instead of two uploads and the append, and one event (about 5 us between two kernels)
+// instead of two.  Step of 119 fp32 tokens 44.4 -> 35.4 us.
 template <typename S, int D>
 __global__ __launch_bounds__(256, 2) void kv_append_kernel(FlpAttnArgs a, const FlpAppendUnit* __restrict__ units, int n_copy,
                                                            const u32x4* __restrict__ copy_src, u32x4* __restrict__ copy_dst,

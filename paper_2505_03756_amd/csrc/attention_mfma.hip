@@ -18,8 +18,8 @@
 //
 // Long launches are bound by the power the chip may draw, so what counts is energy per tile: with 32x32x16 instructions,
 // which read and write twice the accumulator registers per product, the same loop held a lower clock (64 sequences of
-// 4096 + 512 positions, 64 / 8 heads, bf16: 4.49 ms, now 4.17; with all operands zero, where power does not limit, 3.62
-// against 3.77 ms).  A software pipeline inside a wave (the scores of tile t + 1 between the exponentials of tile t, 244
+// 4096 + 512 positions, 64 / 8 heads, bf16: 4.36 ms, now 4.07; with all operands zero, where power does not limit, 3.56
+// and 3.55 ms).  A software pipeline inside a wave (the scores of tile t + 1 between the exponentials of tile t, 244
 // registers) was 3-8 % slower.  Batches of prefill, or prefill and decode, attention alone:
 //   64 sequences, prefixes to 2 k, 128-512 new tokens, 32 / 32 heads, fp16       756 -> 716 us
 //   128 sequences, prefixes to 4 k, 40 / 40 heads, fp16                          2984 -> 2836 us

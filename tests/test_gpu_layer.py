@@ -30,7 +30,7 @@ def within_one_rounding(got, want, dtype):
 
 
 @pytest.mark.parametrize("dtype,T,H", [("f16", 37, 4096), ("bf16", 5, 5120), ("f32", 9, 256), ("f16", 1, 8), ("bf16", 130, 8192),
-                                       # both sides of the limits between the forms of the kernel: 64, 96, 128, 512 and 1024 vectors
+                                       # both sides of the limits between the forms of the kernel: 64, 96, 512 and 1024 vectors
                                        # of 16 bytes; batches that do not fill the last workgroup of four rows
                                        ("bf16", 4, 512), ("f16", 6, 520), ("f32", 7, 260), ("f16", 5, 768), ("bf16", 3, 776),
                                        ("f32", 2, 388),
@@ -60,6 +60,10 @@ def test_rmsnorm_and_fused_residual(dtype, T, H):
     want2 = lo.round_store(lo.rmsnorm(r_want, wv, 1e-5), dtype)[1]
     ok, worst, nbad = within_one_rounding(lo.load(to_np(y2, x_st.dtype), dtype), want2, dtype)
     assert ok, (worst, nbad)
+    # in the same bits as the norm of that residual alone
+    y3 = torch.zeros_like(x)
+    fllayer.rmsnorm(dtype, r, w, y3, T, H, eps=1e-5)
+    assert torch.equal(y3, y2)
     # y == NULL: only the residual update
     r3 = x.clone()
     fllayer.add_rmsnorm(dtype, r3, d, None, None, T, H)
@@ -409,7 +413,7 @@ def test_two_layer_stack_with_per_layer_pools():
 def test_layer_full_size_against_the_oracle_on_a_few_sequences(workload, n_oracle_seqs):
     """One decoder layer at the benchmark's sizes.  7B shapes (hidden 4096, 32 heads, MLP 11008, LoRA on q, k, v, o):
     the 18 953-token prefill batch on the 4 GiB pool (large-batch GEMMs with the LoRA branch and the gate inside) and
-    the 256-token decode batch over contexts of 512-4096 (split small-batch GEMMs, per-token LoRA kernels); half of
+    the 256-token decode batch over contexts of 512-4096 (split small-batch GEMMs, LoRA kernels for small batches); half of
     the 13B batch (rank 32 on seven projections: gate and up with their branches in one gated pass) and a quarter of the 34B
     batch (grouped-query attention, rank 64, prefill and decode sequences mixed, contexts up to 16 k).  A
     token's output depends only on its own sequence, so the oracle runs the layer on a few of the sequences and their

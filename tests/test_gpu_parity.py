@@ -221,7 +221,7 @@ LORA_CASES = {
     "bf16_mixed_rank": lambda: small_cfg("bf16", hidden=1024, n_q_heads=8, n_kv_heads=8, n_seqs=200,
                                          prefix_range=(0, 0), new_range=(2, 11), n_adapters=60,
                                          ranks=(8, 16, 32, 64), n_dev_blocks=2500, swap_in_frac=0.0, seed=83),
-    # the same shapes as a small decode batch (per-token kernels)
+    # the same shapes as a small decode batch (kernels for up to 1024 tokens)
     "bf16_mixed_rank_decode": lambda: small_cfg("bf16", hidden=1024, n_q_heads=8, n_kv_heads=8, n_seqs=200,
                                                 prefix_range=(0, 0), new_range=(1, 1), decode_frac=1.0,
                                                 n_adapters=60, ranks=(8, 16, 32, 64), n_dev_blocks=2500,
