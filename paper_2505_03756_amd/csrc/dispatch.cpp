@@ -477,10 +477,16 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
     c.k_per_split = ((b->d_in + ks - 1) / ks + 127) / 128 * 128;
     c.v_rows = c.tiles_bound * tm;
     const int nt = (b->max_rank + 15) / 16 <= 2 ? (b->max_rank + 15) / 16 : 4;
-    // long segments: wide slabs amortise the gathered B fragments over many tokens; short ones
-    // (decode): narrow slabs, i.e. more waves, each gathering one piece
-    c.cols_per_slab = c.mt == 2 ? 256 : 256 / nt;
-    c.group_tokens = tm * (c.mt == 2 ? 8 : 1);
+    // Tokens per workgroup of the expand step: its slab of B is laid out once for all of them, so long groups are cheap, but a
+    // few hundred workgroups leave the chip idle.  Measured with 64, 128 and 256 tokens each (us for the call; workgroups at 256):
+    //   1500 tokens, 40 heads, q,k,v of rank 32   (360)    76    93    84
+    //   3000 tokens, 64 / 8 heads, rank 64        (480)   160   174   202
+    //   5000 tokens, 40 heads, gate and up        (2160)  245   241   269
+    //   20123 tokens, 32 heads, q,k,v of rank 16  (3792)  281   257   256
+    //   49712 tokens, 64 / 8 heads, rank 64       (7800)    -  1322  1272
+    int64_t wgs = 0;
+    for (int q = 0; q < b->n_proj; ++q) wgs += (int64_t)((T + 255) / 256) * ((b->proj[q].d_out + 255) / 256);
+    c.group_tokens = wgs < 1024 ? 64 : wgs < 4096 ? 128 : 256;
     c.groups_bound = (int32_t)((T + c.group_tokens - 1) / c.group_tokens) + seg_bound;
     c.groups_grid = (std::min(c.groups_bound, (int32_t)((T + c.group_tokens - 1) / c.group_tokens) + 64) + 7) / 8 * 8;
     const int rp = 16 * nt;

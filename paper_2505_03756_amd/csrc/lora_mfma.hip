@@ -2,22 +2,17 @@
 // row-vector form, y = base + s (x A^T) B; section 2.1: tokens of different adapters share
 // one batch; section 4.3: adapters live in pool blocks as rank rows).
 //
-// Tokens are first grouped by adapter (lora.hip); a tile is up to 16*MT consecutive tokens
-// of one adapter.  Both kernels read their operands straight from global memory in MFMA
-// operand layout: the rank-major page rows make 8 consecutive coefficients of one rank one
-// 16-byte run, which is exactly a lane's share of a 16x16x32 operand, so nothing is staged
-// or transposed in LDS and every page byte is fetched once per tile.
+// Tokens are first grouped by adapter (lora.hip); a tile is up to 16*MT consecutive tokens of one adapter.  The
+// rank-major page rows make 8 consecutive coefficients of one rank one 16-byte run, which is exactly a lane's share of a
+// 16x16x32 operand of the shrink step.
 //
 //   shrink  v[t, rho] = sum_c x[t,c] A[rho,c]     M = tokens, N = ranks, K = d_in.  K is
 //           split over the 4 waves of a workgroup (summed in LDS in a fixed order) and over
 //           KS workgroups (partial sums in global memory, added in order by the expand
 //           kernel), so that enough waves are in flight to stream x at HBM rate.
-//   expand  y[t, o] += s sum_rho v[t,rho] B[rho,o]   computed transposed, M = columns,
-//           N = tokens, K = ranks.  v stays fp32: it is split into a 16-bit high part and
-//           a 16-bit remainder that occupy the two halves of the K = 32 contraction (the
-//           B coefficients are fed to both halves).  Two column tiles are interleaved so
-//           that a lane ends up with 8 consecutive columns of one token: y is read and
-//           written in 16-byte pieces.
+//   expand  y[t, o] += s sum_rho v[t,rho] B[rho,o]   M = tokens, N = columns, K = ranks.  v stays fp32: it is
+//           split into a 16-bit high part and a 16-bit remainder that occupy the two halves of the K = 32
+//           contraction (the B coefficients are fed to both halves).
 #include <atomic>
 #include <hip/hip_runtime.h>
 
@@ -456,200 +451,40 @@ __global__ __launch_bounds__(256) void lora_shrink_lds16_kernel(FlpLoraArgs a, F
 }
 
 // ------------------------------------------------------------------------------- expand
-// One wave per (tile group, column slab, projection).  The slab's B coefficients are gathered
-// once into MFMA A-operand fragments that stay in registers (64 VGPRs) while the wave walks
-// the group's 16-token sub-tiles, so the 2-byte gathers are amortised over up to 256 tokens
-// and the inner loop is the y stream: 16-byte read, two MFMAs per rank tile, 16-byte write.
+// y is updated in place, so this is the y stream with two thin products beside it, and what counts is how y is
+// accessed.  A workgroup of four waves owns one (tile group, 256-column slab, projection); each wave takes every fourth
+// 16-token sub-tile.
+//
+// The product is y = v B with the tokens as rows.  Column n of the eight column tiles of a 128-column half is column 8 n + tau,
+// so a lane holds eight neighbouring columns of a token, sixteen lanes 256 contiguous bytes of its row, and one access
+// covers whole lines of four rows.  Only such accesses gain from the non-temporal hint, loads and stores both.  (Transposed, with
+// 32 bytes of one row per lane in two accesses, every access touches half of each line; hint or not, that is slower.)
+// y is requested half a slab ahead, v a sub-tile ahead; v is summed over its slices, split and scaled once per 256 columns.
+//
+// B of the slab lies in LDS as operand fragments, sixteen ranks times eight columns per thread: eight 16-byte loads along
+// the page rows, turned in registers (ranks 2 j, 2 j + 1 of a column make a word).  v takes k-slots 0 .. 15 with its high part and
+// 16 .. 31 with the remainder against the same coefficients, so lanes 32 apart read the same fragment.
+//
+// Measured, whole calls (segmentation, shrink, expand), against fragments gathered in registers (ranks up to 16) and
+// transposed through LDS two bytes at a time (above), both with the transposed product; us:
+//   21629 tokens, 32 heads, fp16, rank 16        q,k,v 370 -> 270      o 159 -> 122     (expand alone 4.05 -> 5.35 TB/s)
+//   40961 tokens, 40 heads, fp16, rank 32        q,k,v 837 -> 709      gate,up 1288 -> 1078      down 530 -> 458
+//   49712 tokens, 64 / 8 heads, bf16, rank 64    q,k,v 1411 -> 1246    o 966 -> 815
+//   1801 tokens of up to 100 adapters, 64 / 8 heads, rank 64   q,k,v 612 -> 251   o 412 -> 145
 template <typename L, int NT>
-__global__ __launch_bounds__(64) void lora_expand_mfma_kernel(FlpLoraArgs a, FlpLoraMfma c) {
+__global__ __launch_bounds__(256, 2) void lora_expand_stream_kernel(FlpLoraArgs a, FlpLoraMfma c) {
   typedef typename L::vec vec;
   typedef typename L::elem elem;
   typedef typename L::S S;
-  constexpr int CH = 8 / NT;                          // 32-column chunks per resident piece
-  // All column slabs and projections of one tile group run on one XCD (workgroups are placed on the
-  // 8 XCDs round-robin by their linear id): they re-read the same rows of v and the same B pages,
-  // which then stay in that XCD's L2.
-  const int per_group = c.slabs * a.n_proj;
-  const int n_seg = *a.n_seg;
-  const int n_groups = a.group_start[n_seg];
-  const int q_total = (n_groups + 7) / 8 * per_group;
-  const int xcd = blockIdx.x & 7;
-  const int lane = threadIdx.x, n = lane & 15, kg = lane >> 4, kq = kg & 1, lo_half = kg >> 1, m = lane & 15;
-  const uint16_t* __restrict__ pool = reinterpret_cast<const uint16_t*>(a.pool);
-  // the launch covers gridDim.x / 8 (group, slab, projection) items per XCD in one pass; with more segments
-  // than the host allowed for, a wave takes several items in turn
-  for (int q = blockIdx.x >> 3; q < q_total; q += gridDim.x >> 3) {
-  const int group = (q / per_group) * 8 + xcd, slab = (q % per_group) / a.n_proj, p = (q % per_group) % a.n_proj;
-  if (group >= n_groups) continue;
-  const flp_lora_proj& pr = a.proj[p];
-  const int slab_begin = slab * c.cols_per_slab;
-  if (slab_begin >= pr.d_out) continue;
-  const int s = find_segment(a.group_start, n_seg, group);
-  const int ad = a.seg_adapter[s];
-  const int r = a.rank[ad] < a.max_rank ? a.rank[ad] : a.max_rank;
-  if (r <= 0) continue;
-  const float sc = a.scale[ad];
-  const int RP = 16 * NT, TM = 16 * c.mt;
-  const int off0 = (group - a.group_start[s]) * c.group_tokens;       // first token of the group inside its segment
-  const int pos0 = a.seg_start[s] + off0;
-  const int pos_end = a.seg_start[s + 1];
-  const int pos_stop = pos0 + c.group_tokens < pos_end ? pos0 + c.group_tokens : pos_end;
-  const int64_t vrow0 = (int64_t)a.tile_start[s] * TM + off0;         // the segment's rows of v are contiguous
-  const int rpb = (int)(a.block_elems / pr.d_out);
-
-  // page rows of B for this lane's 8 ranks of every rank tile
-  const uint16_t* rowp[NT][8];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int rho = 16 * nt + 8 * kq + j;
-      const int i = pr.b_row_base[ad] + (rho < r ? rho : 0);
-      rowp[nt][j] = pool + (int64_t)a.tables[pr.b_tab_off[ad] + i / rpb] * a.block_elems + (int64_t)(i % rpb) * pr.d_out;
-    }
-
-  // the slab's columns in pieces of 64*C64, so that the resident fragments stay at 64 registers
-  constexpr int C64 = CH / 2;                         // 64-column chunks per piece
-  for (int col_begin = slab_begin; col_begin < slab_begin + c.cols_per_slab && col_begin < pr.d_out;
-       col_begin += 64 * C64) {
-    // ---- A operand: B[rho, col].  Four column tiles of a 64-column chunk are interleaved: row m of
-    //      tile tau is column 16*(m/4) + 4*tau + m%4, so a lane's 16 results are 16 consecutive columns
-    //      (32 bytes) and the four lanes of a token row cover one full 128-byte line of y.
-    vec bf[C64][4][NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int ch = 0; ch < C64; ++ch)
-#pragma unroll
-        for (int tau = 0; tau < 4; ++tau) {
-          const int col = col_begin + 64 * ch + 16 * (m >> 2) + 4 * tau + (m & 3);
-          const int colc = col < pr.d_out ? col : pr.d_out - 1;
-          uint16_t g8[8];
-          // unconditional loads (padding ranks point at a real row), zeroed afterwards: no
-          // divergent branch around each 2-byte gather
-#pragma unroll
-          for (int j = 0; j < 8; ++j) g8[j] = rowp[nt][j][colc];
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            if (!(16 * nt + 8 * kq + j < r && col < pr.d_out)) g8[j] = 0;
-          __builtin_memcpy(&bf[ch][tau][nt], g8, 16);
-        }
-
-    int tok = a.perm[pos0 + n < pos_stop ? pos0 + n : pos_stop - 1];
-    for (int pos_t = pos0; pos_t < pos_stop; pos_t += 16) {
-      const int pos = pos_t + n;
-      const bool tvalid = pos < pos_stop;
-      uint16_t* yrow = reinterpret_cast<uint16_t*>(pr.y) + (int64_t)tok * pr.ld_y + col_begin + 16 * kg;
-      const float* brow = a.base32[p] ? a.base32[p] + (int64_t)tok * pr.d_out + col_begin + 16 * kg : nullptr;
-      // the y pieces are requested first so that their latency overlaps the preparation of v;
-      // the next sub-tile's token index is fetched now as well
-      u32x4 yraw[C64][2];
-#pragma unroll
-      for (int ch = 0; ch < C64; ++ch)
-        if (col_begin + 64 * ch < pr.d_out && !brow) {
-          yraw[ch][0] = *reinterpret_cast<const u32x4*>(yrow + 64 * ch);
-          yraw[ch][1] = *reinterpret_cast<const u32x4*>(yrow + 64 * ch + 8);
-        }
-      const int pos_n = pos + 16;
-      const int tok_next = a.perm[pos_n < pos_stop ? pos_n : pos_stop - 1];
-      // ---- B operand: this token's scaled v, high part in k-slots 0..15, remainder in 16..31
-      vec vb[NT];
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        float v8[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v8[j] = 0.f;
-        if (16 * nt < r) {
-          for (int ks = 0; ks < c.k_splits; ++ks) {
-            const float* vp =
-                a.v + (((int64_t)ks * c.v_rows + vrow0 + (pos - pos0)) * a.n_proj + p) * RP + 16 * nt + 8 * kq;
-            const f32x4 x0 = *reinterpret_cast<const f32x4*>(vp), x1 = *reinterpret_cast<const f32x4*>(vp + 4);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              v8[j] += x0[j];
-              v8[4 + j] += x1[j];
-            }
-          }
-        }
-        vec out;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          elem hi, lo;
-          L::split(v8[j] * sc, &hi, &lo);
-          out[j] = lo_half ? lo : hi;
-        }
-        vb[nt] = out;
-      }
-#pragma unroll
-      for (int ch = 0; ch < C64; ++ch) {
-        if (col_begin + 64 * ch < pr.d_out) {
-          f32x4 acc[4];
-#pragma unroll
-          for (int tau = 0; tau < 4; ++tau) acc[tau] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            if (16 * nt < r) {
-#pragma unroll
-              for (int tau = 0; tau < 4; ++tau) acc[tau] = L::mfma(bf[ch][tau][nt], vb[nt], acc[tau]);
-            }
-          }
-          if (tvalid) {
-            uint16_t ys[16];
-            if (brow) {                          // unrounded base from the dense projection
-#pragma unroll
-              for (int tau = 0; tau < 4; ++tau) {
-                const f32x4 b4 = *reinterpret_cast<const f32x4*>(brow + 64 * ch + 4 * tau);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) ys[4 * tau + i] = S::from_float(b4[i] + acc[tau][i]);
-              }
-            } else {
-              __builtin_memcpy(ys, &yraw[ch][0], 32);
-#pragma unroll
-              for (int tau = 0; tau < 4; ++tau)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                  ys[4 * tau + i] = S::from_float(S::to_float(ys[4 * tau + i]) + acc[tau][i]);
-            }
-            u32x4 raw[2];
-            __builtin_memcpy(raw, ys, 32);
-            *reinterpret_cast<u32x4*>(yrow + 64 * ch) = raw[0];
-            *reinterpret_cast<u32x4*>(yrow + 64 * ch + 8) = raw[1];
-          }
-        }
-      }
-      tok = tok_next;
-    }
-  }
-  }
-}
-
-// ------------------------------------------------------------------------------- expand, ranks above 16
-// With 2 or 4 rank tiles the register-resident fragments of the kernel above cover only 64-128 columns
-// per gather, and every such piece re-reads the tokens' v rows (which grow with the rank as well): at rank
-// 64 it runs at a seventh of the y stream's rate.  Here a workgroup of four waves owns one (tile group,
-// 256-column slab, projection): the slab's B coefficients (up to 64 ranks x 256 columns) are read once,
-// coalesced, and laid out in LDS transposed - [column][rank], 128 bytes per column - so that a lane's
-// A-operand fragment (8 consecutive ranks of one column) is one 16-byte LDS read; each wave then takes
-// every fourth 16-token sub-tile: v is loaded and split once per sub-tile for all 256 columns, and per
-// 64-column chunk the wave reads y, 4 x NT fragments from LDS, multiplies and writes y back.
-// LDS slot s (16 bytes: rank tile s / 2, half s % 2) of column c sits at c * 128 + ((s ^ f(c)) * 16) with
-// f(c) = (c & 3) | ((c >> 4) & 1) << 2: the 8 lanes that read one slot of 8 different columns (the
-// interleaved column order of the product) hit 8 different 16-byte bank groups.
-template <typename L, int NT>
-__global__ __launch_bounds__(256) void lora_expand_lds_kernel(FlpLoraArgs a, FlpLoraMfma c) {
-  typedef typename L::vec vec;
-  typedef typename L::elem elem;
-  typedef typename L::S S;
-  __shared__ __attribute__((aligned(16))) uint8_t bt_lds[256 * 128];
+  __shared__ u32x4 frag[2][NT][8][32];
   const int per_group = c.slabs * a.n_proj;
   const int n_seg = *a.n_seg;
   const int n_groups = a.group_start[n_seg];
   const int q_total = (n_groups + 7) / 8 * per_group;
   const int xcd = blockIdx.x & 7;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int n = lane & 15, kg = lane >> 4, kq = kg & 1, lo_half = kg >> 1, m = lane & 15;
+  const int n = lane & 15, kg = lane >> 4, kq = kg & 1, lo_half = kg >> 1;
   const uint16_t* __restrict__ pool = reinterpret_cast<const uint16_t*>(a.pool);
-  auto col_hash = [](int col) { return (col & 3) | (((col >> 4) & 1) << 2); };
   for (int q = blockIdx.x >> 3; q < q_total; q += gridDim.x >> 3) {
     const int group = (q / per_group) * 8 + xcd, slab = (q % per_group) / a.n_proj, p = (q % per_group) % a.n_proj;
     if (group >= n_groups) continue;
@@ -668,112 +503,129 @@ __global__ __launch_bounds__(256) void lora_expand_lds_kernel(FlpLoraArgs a, Flp
     const int pos_stop = pos0 + c.group_tokens < pos_end ? pos0 + c.group_tokens : pos_end;
     const int64_t vrow0 = (int64_t)a.tile_start[s] * TM + off0;
     const int rpb = (int)(a.block_elems / pr.d_out);
+    const int n_half = pr.d_out - slab_begin > 128 ? 2 : 1;
 
-    // ---- stage the slab's B coefficients: thread -> (rank, 8 consecutive columns), 16-byte loads along the
-    //      page rows, 2-byte stores into the transposed tile; ranks past r and columns past d_out hold zeros
     __syncthreads();                                   // the previous item's fragments are no longer read
-    for (int it = tid; it < RP * 32; it += 256) {
-      const int rho = it >> 5, c8 = (it & 31) * 8;     // 32 column octets per rank
-      u32x4 raw = {0u, 0u, 0u, 0u};
-      if (rho < r && slab_begin + c8 < pr.d_out) {
-        const int i = pr.b_row_base[ad] + rho;
-        raw = *reinterpret_cast<const u32x4*>(pool + (int64_t)a.tables[pr.b_tab_off[ad] + i / rpb] * a.block_elems +
-                                              (int64_t)(i % rpb) * pr.d_out + slab_begin + c8);
-      }
-      uint16_t e8[8];
-      __builtin_memcpy(e8, &raw, 16);
+    if (tid < 64 * NT) {
+      const int bn = tid & 15, h = (tid >> 4) & 1, bq = (tid >> 5) & 1, nt = tid >> 6;
+      const int col = slab_begin + 128 * h + 8 * bn;
+      u32x4 g[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const int col = c8 + j;
-        *reinterpret_cast<uint16_t*>(bt_lds + col * 128 + (((rho >> 3) ^ col_hash(col)) << 4) + (rho & 7) * 2) = e8[j];
+        const int rho = 16 * nt + 8 * bq + j;
+        const int i = pr.b_row_base[ad] + (rho < r ? rho : 0);
+        g[j] = *reinterpret_cast<const u32x4*>(pool + (int64_t)a.tables[pr.b_tab_off[ad] + i / rpb] * a.block_elems +
+                                               (int64_t)(i % rpb) * pr.d_out + (col < pr.d_out ? col : 0));
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (!(16 * nt + 8 * bq + j < r && col < pr.d_out)) g[j] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        u32x4 e;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)                    // ranks 2 j, 2 j + 1 of column t: its half of the two words
+          e[j] = __builtin_amdgcn_perm(g[2 * j + 1][t / 2], g[2 * j][t / 2], t & 1 ? 0x07060302u : 0x05040100u);
+        frag[h][nt][t][16 * bq + bn] = e;
       }
     }
     __syncthreads();
 
-    for (int pos_t = pos0 + 16 * wave; pos_t < pos_stop; pos_t += 64) {
-      const int pos = pos_t + n;
-      const bool tvalid = pos < pos_stop;
-      const int tok = a.perm[tvalid ? pos : pos_stop - 1];
-      uint16_t* yrow = reinterpret_cast<uint16_t*>(pr.y) + (int64_t)tok * pr.ld_y + slab_begin + 16 * kg;
-      const float* brow = a.base32[p] ? a.base32[p] + (int64_t)tok * pr.d_out + slab_begin + 16 * kg : nullptr;
-      // the y pieces of all four chunks are requested first, so that their latency overlaps the preparation of v
-      // and four chunks per wave are in flight instead of one
-      u32x4 yall[4][2];
-      if (!brow) {
+    const bool from_y = !a.base32[p];
+    uint16_t* const ybase = reinterpret_cast<uint16_t*>(pr.y) + slab_begin + 8 * n;
+    const int h1 = slab_begin + 128 + 8 * n < pr.d_out ? 128 : 0;       // columns past the last one: the first ones again, not stored
+    const int h0 = slab_begin + 8 * n < pr.d_out ? 0 : -8 * n;
+    auto rows = [&](int32_t (&tok)[4], int pos_t) {
 #pragma unroll
-        for (int ch = 0; ch < 4; ++ch)
-          if (slab_begin + 64 * ch < pr.d_out) {
-            yall[ch][0] = *reinterpret_cast<const u32x4*>(yrow + 64 * ch);
-            yall[ch][1] = *reinterpret_cast<const u32x4*>(yrow + 64 * ch + 8);
-          }
+      for (int i = 0; i < 4; ++i) {
+        const int pos = pos_t + 4 * kg + i;
+        tok[i] = a.perm[pos < pos_stop ? pos : pos_stop - 1];
       }
-      // ---- B operand: this token's scaled v for all rank tiles, high part in k-slots 0..15, remainder in 16..31
-      vec vb[NT];
+    };
+    auto load_y = [&](u32x4 (&y)[4], const int32_t (&tok)[4], int off) {
+      if (from_y)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ybase + (int64_t)tok[i] * pr.ld_y + off));
+    };
+    auto v_row = [&](int pos_t, int ks) {
+      const int pos = pos_t + n < pos_stop ? pos_t + n : pos_stop - 1;
+      return a.v + (((int64_t)ks * c.v_rows + vrow0 + (pos - pos0)) * a.n_proj + p) * RP + 8 * kq;
+    };
+    auto load_v = [&](f32x4 (&v)[NT][2], int pos_t) {
+      const float* vp = v_row(pos_t, 0);
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
-        float v8[8];
+        v[nt][0] = *reinterpret_cast<const f32x4*>(vp + 16 * nt);
+        v[nt][1] = *reinterpret_cast<const f32x4*>(vp + 16 * nt + 4);
+      }
+    };
+    int pos_t = pos0 + 16 * wave;
+    if (pos_t >= pos_stop) continue;
+    int32_t tok[4];
+    u32x4 y[2][4];
+    f32x4 v[NT][2];
+    vec vb[NT];
+    rows(tok, pos_t);
+    load_y(y[0], tok, h0);
+    load_v(v, pos_t);
+    auto update = [&](int h, const u32x4 (&yh)[4]) __attribute__((always_inline)) {
+      f32x4 acc[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v8[j] = 0.f;
-        if (16 * nt < r) {
-          for (int ks = 0; ks < c.k_splits; ++ks) {
-            const float* vp =
-                a.v + (((int64_t)ks * c.v_rows + vrow0 + (pos - pos0)) * a.n_proj + p) * RP + 16 * nt + 8 * kq;
-            const f32x4 x0 = *reinterpret_cast<const f32x4*>(vp), x1 = *reinterpret_cast<const f32x4*>(vp + 4);
+      for (int t = 0; t < 8; ++t) {
+        acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              v8[j] += x0[j];
-              v8[4 + j] += x1[j];
-            }
-          }
+        for (int nt = 0; nt < NT; ++nt)
+          if (16 * nt < r) acc[t] = L::mfma(vb[nt], vec_from<vec>(frag[h][nt][t][16 * kq + n]), acc[t]);
+        if (t == 3) __builtin_amdgcn_sched_barrier(0);
+      }
+      const int col = slab_begin + 128 * h + 8 * n;
+      if (col >= pr.d_out) return;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (pos_t + 4 * kg + i >= pos_stop) continue;
+        uint16_t ys[8];
+        if (from_y) {
+          __builtin_memcpy(ys, &yh[i], 16);
+#pragma unroll
+          for (int t = 0; t < 8; ++t) ys[t] = S::from_float(S::to_float(ys[t]) + acc[t][i]);
+        } else {                                       // unrounded base from the dense projection
+          const float* brow = a.base32[p] + (int64_t)tok[i] * pr.d_out + col;
+#pragma unroll
+          for (int t = 0; t < 8; ++t) ys[t] = S::from_float(brow[t] + acc[t][i]);
         }
-        vec out;
+        u32x4 raw;
+        __builtin_memcpy(&raw, ys, 16);
+        __builtin_nontemporal_store(raw, reinterpret_cast<u32x4*>(ybase + (int64_t)tok[i] * pr.ld_y + 128 * h));
+      }
+    };
+    for (; pos_t < pos_stop; pos_t += 64) {
+      if (n_half > 1) load_y(y[1], tok, h1);
+      // ---- A operand: this token's scaled v, high part in k-slots 0..15, remainder in 16..31
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        for (int ks = 1; ks < c.k_splits; ++ks) {
+          const float* vp = v_row(pos_t, ks) + 16 * nt;
+          v[nt][0] += *reinterpret_cast<const f32x4*>(vp);
+          v[nt][1] += *reinterpret_cast<const f32x4*>(vp + 4);
+        }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
           elem hi, lo;
-          L::split(v8[j] * sc, &hi, &lo);
-          out[j] = lo_half ? lo : hi;
-        }
-        vb[nt] = out;
-      }
-#pragma unroll
-      for (int ch = 0; ch < 4; ++ch) {
-        if (slab_begin + 64 * ch >= pr.d_out) continue;
-        f32x4 acc[4];
-#pragma unroll
-        for (int tau = 0; tau < 4; ++tau) {
-          acc[tau] = f32x4{0.f, 0.f, 0.f, 0.f};
-          // row m of column tile tau is column 16*(m/4) + 4*tau + m%4 of the chunk: a lane's 16 results are 16
-          // consecutive columns and the four lanes of a token row cover one 128-byte line of y
-          const int col = 64 * ch + 16 * (m >> 2) + 4 * tau + (m & 3);
-          const uint8_t* frow = bt_lds + col * 128;
-          const int hsh = col_hash(col);
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt)
-            if (16 * nt < r)
-              acc[tau] = L::mfma(*reinterpret_cast<const vec*>(frow + (((2 * nt + kq) ^ hsh) << 4)), vb[nt], acc[tau]);
-        }
-        if (tvalid) {
-          uint16_t ys[16];
-          if (brow) {                            // unrounded base from the dense projection
-#pragma unroll
-            for (int tau = 0; tau < 4; ++tau) {
-              const f32x4 b4 = *reinterpret_cast<const f32x4*>(brow + 64 * ch + 4 * tau);
-#pragma unroll
-              for (int i = 0; i < 4; ++i) ys[4 * tau + i] = S::from_float(b4[i] + acc[tau][i]);
-            }
-          } else {
-            __builtin_memcpy(ys, &yall[ch][0], 32);
-#pragma unroll
-            for (int tau = 0; tau < 4; ++tau)
-#pragma unroll
-              for (int i = 0; i < 4; ++i) ys[4 * tau + i] = S::from_float(S::to_float(ys[4 * tau + i]) + acc[tau][i]);
-          }
-          u32x4 raw2[2];
-          __builtin_memcpy(raw2, ys, 32);
-          *reinterpret_cast<u32x4*>(yrow + 64 * ch) = raw2[0];
-          *reinterpret_cast<u32x4*>(yrow + 64 * ch + 8) = raw2[1];
+          L::split((16 * nt < r ? v[nt][j >> 2][j & 3] : 0.f) * sc, &hi, &lo);
+          vb[nt][j] = lo_half ? lo : hi;
         }
       }
+      int32_t tok_n[4];
+      rows(tok_n, pos_t + 64);
+      load_v(v, pos_t + 64);
+      __builtin_amdgcn_sched_barrier(0);
+      update(0, y[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      load_y(y[0], tok_n, h0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (n_half > 1) update(1, y[1]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) tok[i] = tok_n[i];
     }
   }
 }
@@ -828,16 +680,13 @@ flp_status launch_pair(const FlpLoraArgs& a, const FlpLoraMfma& c, hipStream_t s
   int max_dout = 0;
   for (int p = 0; p < a.n_proj; ++p) max_dout = a.proj[p].d_out > max_dout ? a.proj[p].d_out : max_dout;
   FlpLoraMfma ce = c;
-  ce.slabs = (max_dout + c.cols_per_slab - 1) / c.cols_per_slab;
+  ce.slabs = (max_dout + 255) / 256;
   const int64_t n_wg = (int64_t)c.groups_grid * ce.slabs * a.n_proj;
   if (n_wg > INT32_MAX) {
     flp_set_error("LoRA (matrix-core path): %lld workgroups, too many for one launch", (long long)n_wg);
     return FLP_ENOTSUP;
   }
-  if (NT >= 2 && c.cols_per_slab == 256)
-    hipLaunchKernelGGL((lora_expand_lds_kernel<L, NT>), dim3((unsigned)n_wg), dim3(256), 0, stream, a, ce);
-  else
-    hipLaunchKernelGGL((lora_expand_mfma_kernel<L, NT>), dim3((unsigned)n_wg), dim3(64), 0, stream, a, ce);
+  hipLaunchKernelGGL((lora_expand_stream_kernel<L, NT>), dim3((unsigned)n_wg), dim3(256), 0, stream, a, ce);
   FLP_TRY_HIP(hipGetLastError());
   return FLP_OK;
 }

@@ -341,6 +341,47 @@ def test_lora_call_with_one_two_or_four_projections(names, case):
         assert np.abs(want - base).max() > 10 * atol
 
 
+@pytest.mark.parametrize("dtype,ranks,heads,scale", [("f16", (16,), 3, 1), ("bf16", (8, 32), 5, 1), ("bf16", (64,), 6, 1),
+                                                     ("f16", (8, 64), 7, 1), ("f16", (16,), 67, 4)])
+def test_lora_expand_slab_and_group_edges(dtype, ranks, heads, scale):
+    """Long batches: the expand step takes slabs of 256 columns in halves of 128 and groups of 64 tokens (128 with 17 slabs in
+    each of three projections) sixteen at a time.  Widths of 192, 320, 384, 448 and 4288 columns (last slabs of 64, 128 and 192),
+    and adapters that own one token, one less, as many and one more than a sub-tile, four sub-tiles, and one and two
+    groups, each scattered over the batch; tokens without an adapter keep their bits."""
+    cfg = small_cfg(dtype, hidden=128, n_q_heads=heads, n_kv_heads=heads, head_dim=64, n_seqs=40, prefix_range=(0, 0),
+                    new_range=(28 * scale, 36 * scale), n_adapters=24, ranks=ranks, adapter_dist="distinct", n_dev_blocks=1200,
+                    swap_in_frac=0.0, seed=500 + heads)
+    step = wl.make_step(cfg)
+    T = step.n_tokens
+    present = np.unique(step.token_adapter)
+    runs = [1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 255, 257]
+    ta = np.full(T, present[-1], np.int32)
+    ta[:7] = -1
+    at = 7
+    for ad, n in zip(present, runs):
+        ta[at:at + n] = ad
+        at += n
+    assert T >= 1024 and at < T - 1 and len(present) > len(runs)
+    step.token_adapter = ta[np.random.default_rng(heads).permutation(T)]
+    dev0 = resident_pool(step)
+    g = GpuStep(step, dev0, np.zeros((1, cfg.block_elems), dev0.dtype))
+    rtol, atol = TOL[cfg.dtype]
+    got = g.lora(["q", "k", "v"])
+    for n in ("q", "k", "v"):
+        pr = step.proj[n]
+        want = oracle.lora_apply(dev0, cfg.dtype, step.acts["x"], step.token_adapter, step.rank, step.scale,
+                                 pr.a_tab_off, pr.a_row_base, pr.b_tab_off, pr.b_row_base, step.lora_tables,
+                                 pr.d_out, y_in=step.acts["base_" + n])
+        ok, worst, nbad = close(wl.dequantize(got[n], cfg.dtype), want, rtol, atol)
+        assert ok, "%s: max err %g, %d elements out of tolerance" % (n, worst, nbad)
+        base = wl.dequantize(step.acts["base_" + n], cfg.dtype)
+        ulp = 2.0 ** (-10 if cfg.dtype == "f16" else -7)
+        err = np.abs((wl.dequantize(got[n], cfg.dtype) - base) - (want - base))
+        assert err.max() <= ulp * (np.abs(want).max() + 1.0), (n, err.max())
+        none = step.token_adapter < 0
+        assert np.array_equal(got[n][none], step.acts["base_" + n][none])
+
+
 @pytest.mark.parametrize("dtype,T", [("bf16", 1), ("bf16", 63), ("f32", 257), ("bf16", 1023), ("f16", 1024),
                                      ("f32", 1025)])
 def test_lora_small_batches_share_adapter_pages(dtype, T):
