@@ -100,8 +100,9 @@ constexpr size_t kStaticScratchBytes = (size_t)64 << 20;   // what flp_lora_appl
 constexpr size_t kLayerSliceBytes = (size_t)1 << 30;       // what slices of a layer's dense products may take
 // flp_lora_apply_paged with its intermediates in `ws` (no allocation, no growth)
 flp_status flp_lora_apply_fixed(flp_pool* pool, const flp_lora_batch* batch, void* hip_stream, const FlpFixedWorkspace& ws);
-// flp_lora_apply_paged for the layer step, whose larger slice room only the pool's growing workspace has
-flp_status flp_lora_apply_layer(flp_pool* pool, const flp_lora_batch* batch, void* hip_stream);
+// flp_lora_apply_paged for the layer step, whose larger slice room only the pool's growing workspace has; the tokens are those of
+// n_seqs sequences one after the other, which as a rule have one adapter each (only the speed depends on that)
+flp_status flp_lora_apply_layer(flp_pool* pool, const flp_lora_batch* batch, int32_t n_seqs, void* hip_stream);
 // set-up of the file-scope scratch array for the current device (looks its device address up once per device);
 // called when a pool is created, and again by the entry point that uses the array if that first attempt failed
 flp_status flp_static_scratch_setup(int device, void** out);
@@ -230,6 +231,7 @@ struct FlpLoraGroup {
 };
 struct FlpLoraSmall {
   int32_t k_splits, n_tiles;   // slices of d_in; tiles of 16 ranks
+  bool long_runs;              // most tokens' neighbours have the same adapter (used with one and two rank tiles)
   FlpLoraGroup* groups;        // [T]
 };
 

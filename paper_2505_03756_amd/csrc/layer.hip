@@ -503,7 +503,7 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
     if (n_lora == 0) return FLP_OK;
     lb.n_proj = n_lora;
     if (gated_out) return flp_lora_apply_gated(p, &lb, gated_out, d_outs[0], hip_stream);
-    return flp_lora_apply_layer(p, &lb, hip_stream);
+    return flp_lora_apply_layer(p, &lb, b->n_seqs, hip_stream);
   };
 
   FLP_TRY(fll_rmsnorm(dtype, h, w->in_norm, n, T, H, eps, hip_stream));

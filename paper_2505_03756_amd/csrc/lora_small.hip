@@ -14,7 +14,10 @@
 //   expand  one wave per (sixteen tokens, projection, 128 columns): y^T += s B^T v^T with fp32 instructions, so that v
 //           keeps its 32 bits.  16x16x4: column 8 m + tau of the chunk is row m of tile tau (a lane reads 8 neighbouring
 //           columns of a page row and ends up with 32 neighbouring columns of one token), rank 4 k + i of a rank tile is slot k
-//           of step i.  Groups of up to four tokens take 4x4x1 instructions, a quarter of the time in the matrix pipe.
+//           of step i.  Groups of up to four tokens take 4x4x1 instructions, a quarter of the time in the matrix pipe.  Where the
+//           caller knows that the tokens come in few sequences a wave looks after eight neighbouring tokens: with one each, a
+//           499-token prompt launches 48 000 waves of which one in sixteen has something to do, and the launch takes longer than
+//           the work.  (For decode batches the form costs registers, and groups in turn: 300 single tokens 165 -> 200 us.)
 //
 // Both steps add in short chains: four chunks of d_in at a time, then those sums; a rank tile at a time (4x4x1: half a tile), then
 // the tiles.  Error of the branch against 64 bits (fp16, widths 4096 to 8192, 2-norm over 2-norm, 8 to 1000 tokens):
@@ -34,7 +37,7 @@
 //   32 / 32 heads    256 tokens, 92 adapters of ranks 8-64    93.6 / 73.5     43.9 / 40.2
 //   bf16             200 tokens, 100 adapters of ranks 8-64   75.7 / 71.5     41.4 / 35.9
 //                    8 tokens of rank 16                      19.7 / 17.5     18.3 / 15.2
-//                    499 tokens of one adapter of rank 16     64.1 / 37.8     33.8 / 26.5
+//                    499 tokens of one adapter of rank 16     64.1 / 37.8     33.8 / 26.5   (a wave per token)
 //                    64 tokens, 500 adapters of rank 64       84.2 / 88.2     40.0 / 40.5
 //   40 / 40 heads    1000 tokens of 2 sequences, rank 32       416 / 102       157 / 49.4
 //   64 / 8 heads     1000 tokens of 2 sequences, rank 64       652 / 142       321 / 81.5
@@ -300,25 +303,15 @@ __device__ __forceinline__ void add_to_y(uint16_t* yp, const float* bp, int64_t 
   }
 }
 
-// NT: tiles of 16 ranks the launch allows for
-template <typename L, int NT>
-__global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, FlpLoraSmall c) {
+// The group of n tokens of rank r that token t works for, 128 columns.  NT: tiles of 16 ranks the launch allows for; v_lds: [token
+// (of 4)][four ranks]
+template <typename L, int NT, bool LONG>
+__device__ __forceinline__ void expand_group(const FlpLoraArgs& a, const FlpLoraSmall& c, int p, int t, int n, int r, int col0,
+                                             f32x4* v_lds) {
   typedef typename L::S S;
-  __shared__ f32x4 v_lds[64 * NT / 4];                 // [token (of 4)][four ranks]
   const int lane = threadIdx.x, m16 = lane & 15, kg = lane >> 4;
-  // the projections one after the other; columns vary fastest: rows are often a power of two bytes apart
-  int p = 0;
-  unsigned unit = blockIdx.x, chunks = (unsigned)(a.proj[0].d_out + 127) / 128;
-  while (unit >= chunks * (unsigned)a.T) {
-    unit -= chunks * (unsigned)a.T;
-    chunks = (unsigned)(a.proj[++p].d_out + 127) / 128;
-  }
-  const int t = (int)(unit / chunks), col0 = (int)(unit % chunks) * 128;
   const flp_lora_proj& pr = a.proj[p];
   const FlpLoraGroup* __restrict__ rec = c.groups + t;
-  const int n = __builtin_amdgcn_readfirstlane(rec->n);
-  if (n == 0) return;
-  const int r = __builtin_amdgcn_readfirstlane(rec->r);
   const int64_t base_slice = (int64_t)a.T * pr.d_out;
   if (r == 0) {                                        // a token without a branch: its product has only to be added up
     const int f0 = col0 + 8 * lane;
@@ -408,7 +401,7 @@ __global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, Fl
 #pragma unroll
   for (int i = 0; i < 4; ++i) yraw[i] = !bp && f0 + 8 * i < pr.d_out ? *reinterpret_cast<const u32x4*>(yp + 8 * i) : u32x4{0u, 0u, 0u, 0u};
   f32x4 acc[8];
-  u32x4 b[NT][4];                                    // ranks 16 nt + 4 kg + i of the lane's 8 columns
+  u32x4 b[NT][4];                                      // ranks 16 nt + 4 kg + i of the lane's 8 columns
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
     if (16 * nt < r) {
@@ -416,6 +409,15 @@ __global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, Fl
       for (int i = 0; i < 4; ++i)
         b[nt][i] = load_global<u32x4>(address_of(mine, 16 * nt + 4 * kg + i) + 2 * fb);
     }
+  constexpr bool kBaseFirst = LONG;                    // an unrounded base is on its way beside the pages
+  f32x4 base[kBaseFirst ? 8 : 1];
+  if (kBaseFirst && bp) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (f0 + 4 * i < pr.d_out)
+        base[kBaseFirst ? i : 0] = a.base_slices[p] == 1 ? *reinterpret_cast<const f32x4*>(bp + 4 * i)
+                                                         : sum_slices<4>(bp + 4 * i, base_slice, a.base_slices[p]);
+  }
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     if (16 * nt >= r) break;
@@ -434,15 +436,58 @@ __global__ __launch_bounds__(64) void lora_small_expand_kernel(FlpLoraArgs a, Fl
 #pragma unroll
     for (int q = 0; q < 8; ++q) acc[q] = nt ? acc[q] + part[q] : part[q];
   }
+  if (m16 >= n) return;
   // lane (token m16, kg): element i of tile q is column 32 kg + 8 i + q of the chunk
-  if (m16 < n) add_to_y<S, 4>(yp, bp, base_slice, a.base_slices[p], yraw, pr.d_out - f0, sc, [&](int i, int q) { return acc[q][i]; });
+  if (kBaseFirst && bp) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (f0 + 8 * i >= pr.d_out) break;
+      uint16_t y8[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) y8[q] = S::from_float(fmaf(sc, acc[q][i], base[kBaseFirst ? 2 * i + (q >> 2) : 0][q & 3]));
+      u32x4 raw;
+      __builtin_memcpy(&raw, y8, 16);
+      *reinterpret_cast<u32x4*>(yp + 8 * i) = raw;
+    }
+    return;
+  }
+  add_to_y<S, 4>(yp, bp, base_slice, a.base_slices[p], yraw, pr.d_out - f0, sc, [&](int i, int q) { return acc[q][i]; });
+}
+
+// LONG: a wave looks after kLongBlock neighbouring tokens.  Waves per SIMD are asked for: left to itself the compiler spreads the
+// accumulators over both register files and loses one or two of them.
+constexpr int kLongBlock = 8;
+template <typename L, int NT, bool LONG>
+__global__ __launch_bounds__(64, LONG ? 2 : NT == 4 ? 3 : 4) void lora_small_expand_kernel(FlpLoraArgs a, FlpLoraSmall c) {
+  __shared__ f32x4 v_lds[64 * NT / 4];
+  const int lane = threadIdx.x;
+  // the projections one after the other; columns vary fastest: rows are often a power of two bytes apart
+  const unsigned blocks = LONG ? (unsigned)(a.T + kLongBlock - 1) / kLongBlock : (unsigned)a.T;
+  int p = 0;
+  unsigned unit = blockIdx.x, chunks = (unsigned)(a.proj[0].d_out + 127) / 128;
+  while (unit >= chunks * blocks) {
+    unit -= chunks * blocks;
+    chunks = (unsigned)(a.proj[++p].d_out + 127) / 128;
+  }
+  const int t0 = (int)(unit / chunks) * (LONG ? kLongBlock : 1), col0 = (int)(unit % chunks) * 128;
+  if constexpr (LONG) {
+    // lane i: how many tokens token t0 + i works for, and the rank
+    const FlpLoraGroup* rec = c.groups + (t0 + lane < a.T ? t0 + lane : t0);
+    const int n = rec->n, r = rec->r;
+    for (uint64_t todo = __ballot(lane < kLongBlock && t0 + lane < a.T && n > 0); todo; todo &= todo - 1) {
+      const int i = __ffsll((long long)todo) - 1;
+      expand_group<L, NT, LONG>(a, c, p, t0 + i, __builtin_amdgcn_readlane(n, i), __builtin_amdgcn_readlane(r, i), col0, v_lds);
+    }
+  } else {
+    const int n = __builtin_amdgcn_readfirstlane(c.groups[t0].n);
+    if (n > 0) expand_group<L, NT, LONG>(a, c, p, t0, n, __builtin_amdgcn_readfirstlane(c.groups[t0].r), col0, v_lds);
+  }
 }
 
 template <typename L, int NT>
 void launch(const FlpLoraArgs& a, const FlpLoraSmall& c, hipStream_t stream) {
   unsigned chunks = 0;
   for (int p = 0; p < a.n_proj; ++p) chunks += (unsigned)(a.proj[p].d_out + 127) / 128;
-  const dim3 ge(chunks * (unsigned)a.T);
   dim3 gs((unsigned)a.T, (unsigned)(a.n_proj * c.k_splits));
   if (NT == 4 && a.T <= 512) {
     gs.z = 2;
@@ -450,7 +495,14 @@ void launch(const FlpLoraArgs& a, const FlpLoraSmall& c, hipStream_t stream) {
   } else {
     hipLaunchKernelGGL((lora_small_shrink_kernel<L, NT, NT>), gs, dim3(64), 0, stream, a, c);
   }
-  hipLaunchKernelGGL((lora_small_expand_kernel<L, NT>), ge, dim3(64), 0, stream, a, c);
+  if constexpr (NT <= 2) {
+    if (c.long_runs) {
+      const dim3 gl(chunks * (unsigned)((a.T + kLongBlock - 1) / kLongBlock));
+      hipLaunchKernelGGL((lora_small_expand_kernel<L, NT, true>), gl, dim3(64), 0, stream, a, c);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((lora_small_expand_kernel<L, NT, false>), dim3(chunks * (unsigned)a.T), dim3(64), 0, stream, a, c);
 }
 template <typename L>
 void launch(const FlpLoraArgs& a, const FlpLoraSmall& c, hipStream_t stream) {

@@ -169,6 +169,11 @@ LAYER_CASES = {
     "f16_many_adapters_inside_gemm": lambda: layer_cfg("f16", hidden=2048, n_q_heads=16, n_kv_heads=16, n_seqs=200,
                                                        prefix_range=(0, 40), new_range=(11, 14), mlp_dim=3136,
                                                        n_dev_blocks=3500, n_adapters=40, ranks=(8, 16, 32), seed=52),
+    # few sequences: a wave of the LoRA expand step takes eight neighbouring tokens, here with other adapters' and none between
+    # (one and two rank tiles, widths that leave part of a column chunk); and just too many sequences for that
+    "f16_runs_interleaved": lambda: layer_cfg("f16", n_seqs=4, new_range=(40, 60), seed=53),
+    "bf16_runs_interleaved": lambda: layer_cfg("bf16", n_seqs=3, new_range=(60, 90), ranks=(8, 32), mlp_dim=1088, seed=54),
+    "f16_no_runs_interleaved": lambda: layer_cfg("f16", n_seqs=20, new_range=(8, 15), ranks=(8, 32), seed=55),
     "bf16_fused_gate_up": lambda: layer_cfg("bf16", projections=("q", "k", "v", "o"), n_seqs=10, prefix_range=(0, 300),
                                             new_range=(110, 160), mlp_dim=3136, n_dev_blocks=2500, seed=48),
 }
@@ -181,6 +186,10 @@ def test_layer_forward_matches_composed_oracle(name):
     step = wl.make_step(cfg)
     T = step.n_tokens
     print("\n[layer case %s] T=%d" % (name, T), flush=True)
+    if name.endswith("interleaved"):
+        present = np.unique(step.token_adapter)
+        step.token_adapter[::7] = np.resize(present, len(step.token_adapter[::7]))
+        step.token_adapter[::11] = -1
     dev0 = resident_pool(step)
     g = GpuStep(step, dev0, np.zeros((1, cfg.block_elems), dev0.dtype))
     W = make_weights(cfg, np.random.default_rng(7))
