@@ -138,7 +138,7 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   hipStream_t stream = (hipStream_t)hip_stream;
 
   // Three kinds of work.  On a 16-bit pool with head_dim 128, sequences with at least 8 query rows per kv head (prefill,
-  // or decode under grouped-query attention) go to the tiled matrix-core kernel in tiles of 256 rows, and the others
+  // or decode under grouped-query attention) go to the tiled matrix-core kernel in tiles of 256 rows (128 in small launches), and the others
   // (and all short ones of a small launch, below) token by token to the decode kernel.  fp32, head_dim 64 and more than 16
   // query heads per kv head: the row-streaming kernel in runs of up to 4 tokens.  All lists are ordered heaviest first.
   //
@@ -178,6 +178,21 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
       if (G * n >= 8) mfma_items_est += (int64_t)n_kv * ((G * n + kMfmaRowsPerItem - 1) / kMfmaRowsPerItem);
     }
   const bool small_launch = mfma_items_est < 128;
+  // Query rows per item: 256, a wave for 32 of them.  A step of a workgroup takes 1.6 us with four waves at work and 2.1 with eight,
+  // so a launch whose items fit one workgroup per CU with half the rows takes those (fp16 / bf16, us, 256 rows and 128):
+  //   700 + 499 positions, 32 heads         44.3   33.7     (128 items of 128 rows)
+  //   2 sequences of 500 + 200, 32 heads    31.4   25.3     (128)
+  //   2000 + 300 positions, 64 / 8 heads    70.0   52.0     (152)
+  //   6 sequences of 300 + 120, 32 heads    23.4   23.6     (192: nothing is cut)
+  //   3 of 2000 + 200, 64 / 8 heads         71.0   90.1     (312)
+  //   1000 + 900 positions, 40 heads        60.4   74.6     (320)
+  int64_t half_items = 0;
+  if (mfma_ok)
+    for (int32_t i = 0; i < b->n_seqs; ++i) {
+      const int64_t n = b->cu_new[i + 1] - b->cu_new[i];
+      if (G * n >= 8) half_items += (int64_t)n_kv * ((G * n + kMfmaRowsPerItem / 2 - 1) / (kMfmaRowsPerItem / 2));
+    }
+  const int32_t rows = half_items <= 256 ? kMfmaRowsPerItem / 2 : kMfmaRowsPerItem;
   // matrix-core items: the row tiles of one (sequence, kv head) are dealt to ONE of 8 queues and
   // the queues are interleaved, so that under round-robin dispatch of workgroups over the 8
   // XCDs the tiles that re-read the same K/V run on the same XCD and share its L2.
@@ -192,8 +207,7 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
     if (mfma_ok && (int64_t)G * n >= 8 && blocks_i <= kMfmaMaxBlocks && !(small_launch && n <= kTokPerUnit)) {
       const int32_t R = G * n;
       for (int g = 0; g < n_kv; ++g) {
-        for (int32_t r0 = 0; r0 < R; r0 += kMfmaRowsPerItem)
-          queue[next_q].push_back(FlpMfmaItem{i, g, r0, std::min<int32_t>(kMfmaRowsPerItem, R - r0)});
+        for (int32_t r0 = 0; r0 < R; r0 += rows) queue[next_q].push_back(FlpMfmaItem{i, g, r0, std::min<int32_t>(rows, R - r0)});
         next_q = (next_q + 1) & 7;
       }
     } else {

@@ -731,6 +731,9 @@ def test_single_token_attention_at_the_edges_of_groups_tiles_and_pieces(dtype, b
     ("bf16", 16, 16, 2, ((0, 5), (59, 5), (60, 5), (120, 9), (511, 32), (500, 33))),           # 8 rows per token
     ("bf16", 32, 3, 3, ((0, 33), (31, 95), (32, 96), (129, 130), (190, 300))),
     ("f16", 32, 10, 2, ((0, 7), (700, 26), (13, 52))),                                         # 5 rows per token
+    # items of 128 rows (144 of them) and, with more than 256 of those, of 256 (320)
+    ("bf16", 16, 16, 16, ((0, 127), (0, 128), (0, 129), (63, 256), (64, 257))),
+    ("f16", 16, 32, 32, ((63, 256), (64, 257), (0, 255), (130, 300))),
 ])
 def test_tiled_attention_at_the_edges_of_tiles(dtype, bt, heads, kv, seqs):
     """New tokens over prefixes around the edges of key tiles (64 positions), the row tiles of a wave and of a workgroup.
