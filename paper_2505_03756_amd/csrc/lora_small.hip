@@ -458,7 +458,7 @@ __device__ __forceinline__ void expand_group(const FlpLoraArgs& a, const FlpLora
 // accumulators over both register files and loses one or two of them.
 constexpr int kLongBlock = 8;
 template <typename L, int NT, bool LONG>
-__global__ __launch_bounds__(64, LONG ? 2 : NT == 4 ? 3 : 4) void lora_small_expand_kernel(FlpLoraArgs a, FlpLoraSmall c) {
+__global__ __launch_bounds__(64, LONG ? 2 : NT == 4 ? 3 : 1) void lora_small_expand_kernel(FlpLoraArgs a, FlpLoraSmall c) {
   __shared__ f32x4 v_lds[64 * NT / 4];
   const int lane = threadIdx.x;
   // the projections one after the other; columns vary fastest: rows are often a power of two bytes apart
