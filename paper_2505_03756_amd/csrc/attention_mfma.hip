@@ -38,6 +38,7 @@
 // (2.5 % of the batches above).
 #include <hip/hip_runtime.h>
 
+#include "attention_decode_wave.h"
 #include "flp_internal.h"
 #include "flp_types.h"
 
@@ -58,6 +59,7 @@ typedef __bf16 b16x2 __attribute__((ext_vector_type(2)));
 
 struct MF16 {
   typedef h16x8 vec;
+  typedef flp_decode::DF16 Single;
   static __device__ __forceinline__ f32x4 mfma(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
   }
@@ -75,6 +77,7 @@ struct MF16 {
 };
 struct MBF16 {
   typedef b16x8 vec;
+  typedef flp_decode::DBF16 Single;
   static __device__ __forceinline__ f32x4 mfma(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
@@ -123,15 +126,21 @@ __device__ __forceinline__ void load_to_lds16(const void* base, uint32_t voff, u
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
 template <typename M>
-__global__ __launch_bounds__(512, 2) void attn_mfma_kernel(FlpAttnArgs a, const FlpMfmaItem* __restrict__ items) {
+__global__ __launch_bounds__(512, 2) void attn_mfma_kernel(FlpAttnArgs a, const FlpMfmaItem* __restrict__ items,
+                                                               const FlpAttnUnit* __restrict__ units) {
   typedef typename M::vec vec;
   __shared__ __attribute__((aligned(16))) uint8_t smem[kStages * kStage];
   __shared__ int32_t tab_lds[kMfmaMaxBlocks];          // this sequence's block table
 
   const FlpMfmaItem it = items[blockIdx.x];
-  if (it.n_rows <= 0) return;
+  if (it.n_rows == 0) return;
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lh = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (it.n_rows < 0) {                                 // single tokens: (unit, kv head) pairs r0 .. r0 + 7 of `seq`
+    const int pair = it.r0 + wave;
+    if (pair < it.seq) flp_decode::decode_unit<typename M::Single>(a, units[pair / a.n_kv], pair % a.n_kv);
+    return;                                            // waves share nothing
+  }
   const int G = a.n_h / a.n_kv, g = it.g;
   const int P = a.prefix_len[it.seq];
   const int t0 = a.cu_new[it.seq];
@@ -404,12 +413,12 @@ __global__ __launch_bounds__(512, 2) void attn_mfma_kernel(FlpAttnArgs a, const 
 }  // namespace
 
 flp_status flp_launch_attn_mfma(int dtype, const FlpAttnArgs& a, const FlpMfmaItem* items_dev, int32_t n_items,
-                                hipStream_t stream) {
+                                const FlpAttnUnit* units_dev, hipStream_t stream) {
   if (n_items <= 0) return FLP_OK;
   if (dtype == FLP_F16)
-    hipLaunchKernelGGL((attn_mfma_kernel<MF16>), dim3(n_items), dim3(512), 0, stream, a, items_dev);
+    hipLaunchKernelGGL((attn_mfma_kernel<MF16>), dim3(n_items), dim3(512), 0, stream, a, items_dev, units_dev);
   else if (dtype == FLP_BF16)
-    hipLaunchKernelGGL((attn_mfma_kernel<MBF16>), dim3(n_items), dim3(512), 0, stream, a, items_dev);
+    hipLaunchKernelGGL((attn_mfma_kernel<MBF16>), dim3(n_items), dim3(512), 0, stream, a, items_dev, units_dev);
   else {
     flp_set_error("attention (matrix-core path): dtype %d not supported", dtype);
     return FLP_ENOTSUP;

@@ -232,7 +232,17 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
       const int64_t n = b->cu_new[i + 1] - b->cu_new[i];
       all_groups += n * (((int64_t)b->prefix_len[i] + n + 15) / 16);
     }
-  const int64_t piece = std::max<int64_t>(kMinGroups, all_groups * n_kv / kPieces);
+  // Tiles are bound by the matrix cores and single tokens by memory, so a batch of both runs as one launch: workgroups of the tiled
+  // kernel take eight single (token, kv head) pieces each, spread over the first half of the tiles (pieces half as long, so
+  // that none of them is the launch's tail).  Two launches, one (us; f16, a quarter of the sequences are prompts):
+  //   60 sequences of up to 500 + 128-400, 32 heads          167   145
+  //   30 of up to 1000 + 128-150, 40 heads                   107    88
+  //   150 of up to 6000 + 128-900, 32 heads                 2620  2434
+  // (spread over the first fifth: 152, 92, 2454; over nine tenths: 142, 91, 2454; twice as many pieces: 5 % more at 40 heads.)
+  // Single tokens of grouped-query batches stay tiles beside prompts as well: 512 sequences of up to 16 k, 64 / 8 heads, 12.6 ms
+  // with tiles and 12.35 with pieces, but 100 of up to 4 k 720 and 762 us.
+  const bool mixed = decode_ok && !row_seqs.empty() && !queue[0].empty();
+  const int64_t piece = std::max<int64_t>(kMinGroups, all_groups * n_kv / (mixed ? 2 * kPieces : kPieces));
   std::vector<int32_t> merge_tok, merge_first{0};
   for (int32_t i : row_seqs) {
     const int32_t n = b->cu_new[i + 1] - b->cu_new[i];
@@ -268,7 +278,9 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return cost[x] > cost[y]; });
   size_t qmax = 0;
   for (auto& q : queue) qmax = std::max(qmax, q.size());
-  const size_t n_items = qmax * 8;
+  // single tokens beside tiles: rows of eight workgroups, eight (unit, kv head) pairs each, between the rows of tiles
+  const size_t pairs = mixed ? units.size() * n_kv : 0, pair_rows = (pairs + 63) / 64;
+  const size_t n_items = (qmax + pair_rows) * 8;
   if (units.empty() && n_items == 0) return FLP_OK;
 
   void* partials = nullptr;
@@ -292,8 +304,14 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   FlpAttnUnit* hu = (FlpAttnUnit*)(h + off_units);
   for (size_t k = 0; k < order.size(); ++k) hu[k] = units[order[k]];
   FlpMfmaItem* hi = (FlpMfmaItem*)(h + off_items);
-  for (size_t s = 0; s < qmax; ++s)
-    for (int x = 0; x < 8; ++x) hi[8 * s + x] = s < queue[x].size() ? queue[x][s] : FlpMfmaItem{0, 0, 0, 0};
+  size_t at = 0, done = 0;
+  for (size_t s = 0; s < qmax; ++s) {
+    for (; done < pair_rows && done * qmax <= 2 * pair_rows * s; ++done)
+      for (int x = 0; x < 8; ++x) hi[at++] = FlpMfmaItem{(int32_t)pairs, 0, (int32_t)(64 * done + 8 * x), -1};
+    for (int x = 0; x < 8; ++x) hi[at++] = s < queue[x].size() ? queue[x][s] : FlpMfmaItem{0, 0, 0, 0};
+  }
+  for (; done < pair_rows; ++done)
+    for (int x = 0; x < 8; ++x) hi[at++] = FlpMfmaItem{(int32_t)pairs, 0, (int32_t)(64 * done + 8 * x), -1};
   if (n_merge) memcpy(h + off_merge, merge_tok.data(), n_merge * sizeof(int32_t));
   memcpy(h + off_merge + n_merge * sizeof(int32_t), merge_first.data(), (n_merge + 1) * sizeof(int32_t));
   if (n_items) {
@@ -317,8 +335,8 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
       st = flp_launch_kv_append(p->cfg.dtype, p->cfg.head_dim, a, (const FlpAppendUnit*)d, (int32_t)append.size(), nullptr, nullptr,
                                 0, stream);
   }
-  if (st == FLP_OK) st = flp_launch_attn_mfma(p->cfg.dtype, a, di, (int32_t)n_items, stream);
-  if (st == FLP_OK)
+  if (st == FLP_OK) st = flp_launch_attn_mfma(p->cfg.dtype, a, di, (int32_t)n_items, du, stream);
+  if (st == FLP_OK && !mixed)
     st = decode_ok ? flp_launch_attn_decode(p->cfg.dtype, a, du, (int32_t)units.size(), stream)
                    : flp_launch_attn_rows(p->cfg.dtype, p->cfg.head_dim, a, du, (int32_t)units.size(), stream);
   if (st == FLP_OK)

@@ -134,7 +134,9 @@ struct FlpAttnUnit {     // new tokens t .. t + n_tok - 1 of sequence `seq`; pos
   int32_t g_lo, g_hi, part, pad;
 };
 
-struct FlpMfmaItem {     // query rows [r0, r0+n_rows) of (sequence, kv head g); n_rows == 0: padding
+// query rows [r0, r0+n_rows) of (sequence, kv head g); n_rows == 0: padding; n_rows < 0: single tokens, the pairs r0 .. r0 + 7 of
+// `seq` (unit, kv head) pairs of the decode list, a wave each
+struct FlpMfmaItem {
   int32_t seq, g, r0, n_rows;
 };
 
@@ -177,7 +179,7 @@ flp_status flp_launch_attn_merge(int dtype, int head_dim, const FlpAttnArgs& a, 
 flp_status flp_attn_workspace(flp_pool* pool, size_t bytes, hipStream_t stream, void** out);
 
 flp_status flp_launch_attn_mfma(int dtype, const FlpAttnArgs& a, const FlpMfmaItem* items_dev, int32_t n_items,
-                                hipStream_t stream);
+                                const FlpAttnUnit* units_dev, hipStream_t stream);
 constexpr int kMfmaRowsPerItem = 256;
 constexpr int kMfmaMaxBlocks = 4096;       // longest context of the matrix-core kernel: 65536 positions
 

@@ -734,6 +734,11 @@ def test_single_token_attention_at_the_edges_of_groups_tiles_and_pieces(dtype, b
     # items of 128 rows (144 of them) and, with more than 256 of those, of 256 (320)
     ("bf16", 16, 16, 16, ((0, 127), (0, 128), (0, 129), (63, 256), (64, 257))),
     ("f16", 16, 32, 32, ((63, 256), (64, 257), (0, 255), (130, 300))),
+    # single tokens beside tiles in one launch: contexts of one piece and of several, pairs that do not fill a workgroup, and more
+    # workgroups of them than of tiles
+    ("bf16", 16, 5, 5, ((0, 1), (255, 1), (256, 1), (1500, 1), (33, 7), (63, 256), (2100, 2))),
+    ("f16", 32, 4, 2, ((700, 1), (0, 3), (90, 40))),
+    ("f16", 16, 3, 3, tuple((40 * i, 1) for i in range(60)) + ((9, 8),)),
 ])
 def test_tiled_attention_at_the_edges_of_tiles(dtype, bt, heads, kv, seqs):
     """New tokens over prefixes around the edges of key tiles (64 positions), the row tiles of a wave and of a workgroup.
