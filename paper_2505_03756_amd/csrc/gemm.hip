@@ -303,12 +303,21 @@ __global__ __launch_bounds__(64 * WF * WT, (WF * WT + 3) / 4)
 
   // workgroup -> (feature tile, slice, token tile): blocks of gf (feature tile, slice) units x gm token tiles run next
   // to each other on one XCD (workgroups are placed on the 8 XCDs in turn), so that an operand tile crosses from memory
-  // into one L2 once
-  const int xcd = blockIdx.x & 7, l = blockIdx.x >> 3;
-  const int grp = (l / (a.gf * a.gm)) * 8 + xcd, within = l % (a.gf * a.gm);
-  const int n_units = a.f_tiles * a.splits, ug = (n_units + a.gf - 1) / a.gf;
-  const int u = (grp % ug) * a.gf + within % a.gf, tm = (grp / ug) * a.gm + within / a.gf;
-  if (u >= n_units || tm >= a.m_tiles) return;
+  // into one L2 once.  The tiles, in the order of their blocks, are dealt out 256 at a time, 32 to an XCD and the last ones in
+  // eighths.  (Whole blocks dealt to the XCDs in turn left some with one more than the others: 240 tiles of 256 x 256, 30 for each
+  // XCD, took two rounds.  An eighth of all tiles to each XCD keeps them apart, and the operands cross from memory more often: layer of
+  // 9874 tokens, 13B shapes, 6660 -> 6917 us.)
+  const int n_units = a.f_tiles * a.splits, n_tiles = n_units * a.m_tiles, xcd = blockIdx.x & 7;
+  const int first = (int)(blockIdx.x >> 8) << 8, part = n_tiles - first < 256 ? n_tiles - first : 256;
+  int at = (part * xcd >> 3) + (int)((blockIdx.x & 255) >> 3);
+  if (at >= part * (xcd + 1) >> 3) return;
+  at += first;
+  const int mb = at / (n_units * a.gm);                 // row of blocks
+  const int rows = a.m_tiles - mb * a.gm < a.gm ? a.m_tiles - mb * a.gm : a.gm;
+  at -= mb * n_units * a.gm;
+  const int ub = at / (a.gf * rows), cols = n_units - ub * a.gf < a.gf ? n_units - ub * a.gf : a.gf;
+  at -= ub * a.gf * rows;
+  const int u = ub * a.gf + at % cols, tm = mb * a.gm + at / cols;
   const int z = u / a.f_tiles;
   int ft = u - z * a.f_tiles;
   int p = 0;
@@ -830,8 +839,7 @@ flp_status flp_launch_gemm(int dtype, const void* x, int64_t ld_x, int M, int K,
   // with more than eight token tiles, 4 x 8 blocks: the workgroups that run together fetch 12 operand panels, not 33
   a.gm = a.m_tiles > 8 ? 8 : a.m_tiles;
   a.gf = a.m_tiles > 8 ? 4 : 1;
-  const int64_t ug = ((int64_t)a.f_tiles * a.splits + a.gf - 1) / a.gf, mg = (a.m_tiles + a.gm - 1) / a.gm;
-  const int64_t grid = (ug * mg + 7) / 8 * 8 * a.gf * a.gm;
+  const int64_t n_tiles = (int64_t)a.f_tiles * a.splits * a.m_tiles, grid = (n_tiles + 7) / 8 * 8;    // 256s, then eighths rounded up
   if (grid > INT32_MAX) {
     flp_set_error("dense product: %lld workgroups, too many for one launch", (long long)grid);
     return FLP_ENOTSUP;
