@@ -270,6 +270,7 @@ enum { FLP_GEMM_64x32 = 0, FLP_GEMM_128x64, FLP_GEMM_128x128, FLP_GEMM_256x128, 
 struct FlpGemmPlan {
   int kind;                    // tile, features x tokens
   int splits;                  // slices of the contraction
+  float us;                    // what the planner reckons with, the launch that adds slices included
 };
 struct FlpGemmOut {
   const void* w;               // [N, K]

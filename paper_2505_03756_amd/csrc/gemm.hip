@@ -751,7 +751,7 @@ size_t flp_gemm_part_bytes(const FlpGemmPlan& plan, int M, int n_proj, const int
 // The plan with the least estimated time: rounds of workgroups x (k tiles of a slice x time per k tile + start-up),
 // at least the time the matrices take from memory, plus the slices' way through memory and the kernel that adds them.
 FlpGemmPlan flp_gemm_plan(int M, int K, int n_proj, const int* N, unsigned allow, size_t max_part_bytes) {
-  FlpGemmPlan best{FLP_GEMM_128x128, 1};
+  FlpGemmPlan best{FLP_GEMM_128x128, 1, 0.f};
   double best_us = 1e30, n_all = 0;
   bool split_ok = !(allow & FLP_GEMM_NO_SPLIT);
   for (int p = 0; p < n_proj; ++p) {
@@ -777,7 +777,7 @@ FlpGemmPlan flp_gemm_plan(int M, int K, int n_proj, const int* N, unsigned allow
       if (s > 1) us += (double)s * M * n_all * 8 / 4.64e6 + 3.5;
       if (us < best_us) {
         best_us = us;
-        best = FlpGemmPlan{kind, s};
+        best = FlpGemmPlan{kind, s, (float)us};
       }
     }
   }

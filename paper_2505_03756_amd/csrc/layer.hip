@@ -365,6 +365,31 @@ bool cfg_ok(const flp_pool* p, const fll_layer_config* c) {
   return p && c && c->hidden > 0 && c->n_q_heads > 0 && c->mlp_dim > 0 && c->n_q_heads % p->cfg.n_kv_heads == 0;
 }
 
+// How many of T tokens a large product takes in whole rounds of 256 x 256 tiles, one per CU; the rest, less than a round, follows
+// in a launch (with LoRA: a call) of its own, on smaller tiles and in slices.  T where the planner sees no gain in that: the last
+// round of a launch lasts two thirds of a full one however few tiles it has.  extra_us: what the second call costs beside its
+// product.  Layers, one launch and two, us:
+//   4400 tokens, 7B shapes     2059   1868      8300 tokens    3528   3201
+//   2200 tokens, 34B shapes    3230   2960      4300 tokens    5665   5263
+//   3300 tokens, 13B shapes    2326   2145      9874 tokens    6673   6454      5000 tokens    3496   3491 (one launch, mostly)
+constexpr double kRestUs = 4, kLoraRestUs = 30;        // a launch; the two launches of the branch and the base's way through memory
+int32_t whole_rounds(int T, int K, int n, const int* N, bool lora, double extra_us) {
+  int64_t f_tiles = 0;
+  bool fits = K % 64 == 0;                              // widths that the LoRA branch's tiles divide: it runs inside the large product
+  for (int i = 0; i < n; ++i) {
+    f_tiles += (N[i] + 255) / 256;
+    fits = fits && (!lora || N[i] % 64 == 0);
+  }
+  const int64_t rounds = f_tiles * ((T + 255) / 256) / 256;
+  const int64_t first = rounds < 1 ? 0 : 256 * (256 * rounds / f_tiles), rest = T - first;
+  if (!fits || first < 2048 || rest < 1 || rest > 1024) return T;
+  const unsigned allow = lora ? FLP_GEMM_NO_SPLIT | FLP_GEMM_LARGE_ONLY : 0;
+  const size_t room = kLayerSliceBytes;
+  const double whole = flp_gemm_plan(T, K, n, N, allow, room).us;
+  const double parts = flp_gemm_plan((int)first, K, n, N, allow, room).us + flp_gemm_plan((int)rest, K, n, N, 0, room).us + extra_us;
+  return parts < 0.98 * whole ? (int32_t)first : T;
+}
+
 // Dense products alone (gated: the gated-SiLU pair as one output).  Slices of a small batch's contraction live in the
 // pool's workspace (stream order keeps them apart from the LoRA intermediates of the calls before and after).  Larger
 // batches without LoRA needed no workspace before they were sliced, so calls on several streams owe each other no order:
@@ -373,16 +398,27 @@ bool cfg_ok(const flp_pool* p, const fll_layer_config* c) {
 constexpr int kSharedWorkTokens = 1024;
 // `resid`, one product: where its slices are added by a kernel, that kernel adds the rounded result to the residual stream
 // instead of writing out->y, and *added says so.
+// rest: the last tokens of a batch whose first ones went ahead
 flp_status dense_products(flp_pool* p, const void* x, int d_in, int T, int n, FlpGemmOut* out, const int* N, bool gated,
-                          hipStream_t stream, void* resid = nullptr, bool* added = nullptr) {
+                          hipStream_t stream, void* resid = nullptr, bool* added = nullptr, bool rest = false) {
   if (p->elem_bytes == 4) {
     for (int i = 0; i < n; ++i)
       FLP_TRY(flp_launch_gemm_f32((const float*)x, d_in, (const float*)out[i].w, 1, (float*)out[i].y, out[i].ld_y, T, N[i], d_in,
                                   stream));
     return FLP_OK;
   }
+  const int32_t first = whole_rounds(T, d_in, n, N, false, kRestUs);
+  if (first < T) {
+    FLP_TRY(dense_products(p, x, d_in, first, n, out, N, gated, stream));
+    for (int i = 0; i < n; ++i) {
+      out[i].y = (uint8_t*)out[i].y + (int64_t)first * out[i].ld_y * p->elem_bytes;
+      out[i].part = nullptr;
+    }
+    return dense_products(p, (const uint8_t*)x + (int64_t)first * d_in * p->elem_bytes, d_in, T - first, n, out, N, gated, stream,
+                          nullptr, nullptr, true);
+  }
   const FlpGemmPlan plan = flp_gemm_plan(T, d_in, n, N, 0, kLayerSliceBytes);
-  const bool own = plan.splits > 1 && T > kSharedWorkTokens;
+  const bool own = plan.splits > 1 && (rest || T > kSharedWorkTokens);
   std::unique_lock<std::mutex> lk(p->mu, std::defer_lock);
   if (plan.splits > 1) {
     void* part = nullptr;
@@ -412,6 +448,11 @@ flp_status dense_products(flp_pool* p, const void* x, int d_in, int T, int n, Fl
   return s;
 }
 }  // namespace
+
+// whole_rounds for tests that state where a shape is cut
+extern "C" int32_t flp_dense_first_tokens(int32_t T, int32_t K, int32_t n, const int32_t* N, int32_t lora) {
+  return whole_rounds(T, K, n, N, lora != 0, lora ? kLoraRestUs : kRestUs);
+}
 
 extern "C" int64_t fll_layer_scratch_bytes(const flp_pool* pool, const fll_layer_config* cfg, int32_t n_tokens) {
   if (!cfg_ok(pool, cfg) || n_tokens < 0) return -1;
@@ -503,7 +544,17 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
     if (n_lora == 0) return FLP_OK;
     lb.n_proj = n_lora;
     if (gated_out) return flp_lora_apply_gated(p, &lb, gated_out, d_outs[0], hip_stream);
-    return flp_lora_apply_layer(p, &lb, b->n_seqs, hip_stream);
+    int N[3];
+    for (int i = 0; i < n_lora; ++i) N[i] = lb.proj[i].d_out;
+    const int32_t first = p->elem_bytes == 2 ? whole_rounds(T, d_in, n_lora, N, true, kLoraRestUs) : T;
+    lb.n_tokens = first;
+    FLP_TRY(flp_lora_apply_layer(p, &lb, b->n_seqs, hip_stream));
+    if (first == T) return FLP_OK;
+    lb.n_tokens = T - first;
+    lb.x = (const uint8_t*)x + (int64_t)first * d_in * p->elem_bytes;
+    lb.token_adapter = b->token_adapter + first;
+    for (int i = 0; i < n_lora; ++i) lb.proj[i].y = (uint8_t*)lb.proj[i].y + (int64_t)first * lb.proj[i].ld_y * p->elem_bytes;
+    return flp_lora_apply_layer(p, &lb, (int32_t)((int64_t)b->n_seqs * (T - first) / T) + 1, hip_stream);
   };
 
   FLP_TRY(fll_rmsnorm(dtype, h, w->in_norm, n, T, H, eps, hip_stream));

@@ -1,5 +1,6 @@
 """GPU parity of the layer glue (include/fllayer.h) against oracle/layer_oracle.py: each element-wise step
 on its own, then the composed decoder layer over the paged pool."""
+import ctypes
 import math
 
 import numpy as np
@@ -7,7 +8,7 @@ import pytest
 
 import oracle
 from oracle import layer_oracle as lo
-from paper_2505_03756_amd import fllayer, workload as wl
+from paper_2505_03756_amd import fllayer, flpool, workload as wl
 from helpers import close
 from paper_2505_03756_amd.harness import GpuStep, resident_pool, to_dev, to_np
 
@@ -169,6 +170,10 @@ LAYER_CASES = {
     "f16_many_adapters_inside_gemm": lambda: layer_cfg("f16", hidden=2048, n_q_heads=16, n_kv_heads=16, n_seqs=200,
                                                        prefix_range=(0, 40), new_range=(11, 14), mlp_dim=3136,
                                                        n_dev_blocks=3500, n_adapters=40, ranks=(8, 16, 32), seed=52),
+    # 24 x 11 tiles of 256 x 256 for q, k, v and 25 x 11 for gate and up: the first 2560 tokens run in whole rounds, the rest by themselves
+    "f16_cut_at_whole_rounds": lambda: layer_cfg("f16", hidden=4096, n_q_heads=16, n_kv_heads=16, projections=("q", "k", "v", "o"),
+                                                 n_seqs=24, prefix_range=(0, 100), new_range=(113, 115), mlp_dim=3200, ranks=(8, 32),
+                                                 n_dev_blocks=1500, seed=56),
     # few sequences: a wave of the LoRA expand step takes eight neighbouring tokens, here with other adapters' and none between
     # (one and two rank tiles, widths that leave part of a column chunk); and just too many sequences for that
     "f16_runs_interleaved": lambda: layer_cfg("f16", n_seqs=4, new_range=(40, 60), seed=53),
@@ -186,6 +191,9 @@ def test_layer_forward_matches_composed_oracle(name):
     step = wl.make_step(cfg)
     T = step.n_tokens
     print("\n[layer case %s] T=%d" % (name, T), flush=True)
+    if "cut" in name:
+        first = flpool.load().flp_dense_first_tokens
+        assert first(T, 4096, 3, (ctypes.c_int32 * 3)(2048, 2048, 2048), 1) == first(T, 4096, 1, (ctypes.c_int32 * 1)(6400), 0) == 2560 < T
     if name.endswith("interleaved"):
         present = np.unique(step.token_adapter)
         step.token_adapter[::7] = np.resize(present, len(step.token_adapter[::7]))
@@ -294,14 +302,19 @@ def test_gated_pair_without_lora(dtype, T, H, M, plan):
     pool.close()
 
 
-def test_layers_without_lora_on_two_streams_of_one_pool():
+@pytest.mark.parametrize("T", [1100, 4150])
+def test_layers_without_lora_on_two_streams_of_one_pool(T):
     """Two batches of 1100 tokens through a layer without LoRA, each on a stream of its own with nothing between them: their
-    sliced products (q, k, v and down) do not meet in the pool's workspace."""
+    sliced products (q, k, v and down) do not meet in the pool's workspace; nor do those of down for the last 54 of 4150
+    tokens, which follow the whole rounds of the first 4096."""
     import torch
     from helpers import dense_plan
-    from paper_2505_03756_amd import flpool
-    T, H, M, d = 1100, 4096, 11008, 128
-    assert dense_plan(T, M, (H,))[1] > 1
+    H, M, d = 4096, 11008, 128
+    if T == 1100:
+        assert dense_plan(T, M, (H,))[1] > 1
+    else:
+        assert flpool.load().flp_dense_first_tokens(T, M, 1, (ctypes.c_int32 * 1)(H), 0) == 4096
+        assert dense_plan(T - 4096, M, (H,))[1] > 1
     tt, n_blk = torch.bfloat16, (T + 15) // 16
     g = torch.Generator(device="cuda").manual_seed(3)
     rnd = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(tt)
