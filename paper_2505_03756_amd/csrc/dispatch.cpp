@@ -384,12 +384,12 @@ flp_status flp_lora_apply_layer(flp_pool* p, const flp_lora_batch* b, int32_t n_
   return lora_apply_impl(p, b, hip_stream, kLayerSliceBytes, nullptr, 0, nullptr, n_seqs);
 }
 
-flp_status flp_lora_apply_gated(flp_pool* p, const flp_lora_batch* b, void* out, int64_t ld_out, void* hip_stream) {
+flp_status flp_lora_apply_gated(flp_pool* p, const flp_lora_batch* b, int32_t n_seqs, void* out, int64_t ld_out, void* hip_stream) {
   if (!out || ((uintptr_t)out & 15)) {
     flp_set_error("flp_lora_apply_gated: out is null or misaligned");
     return FLP_EINVAL;
   }
-  return lora_apply_impl(p, b, hip_stream, kLayerSliceBytes, out, ld_out);
+  return lora_apply_impl(p, b, hip_stream, kLayerSliceBytes, out, ld_out, nullptr, n_seqs);
 }
 
 namespace {
@@ -482,12 +482,35 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
   // Matrix-core path with tokens sorted by adapter for 16-bit pools when every width is a multiple of the tile widths (32
   // in, 64 out) and the batch is large enough for token tiles to fill (prefill); smaller batches on the matrix cores as
   // well, but without the sort (below); fp32 pools and odd widths on the vector-ALU kernels.
-  bool mfma_ok = p->cfg.dtype != FLP_F32 && b->d_in % 32 == 0 && b->n_tokens >= 1024;
+  bool mfma_ok = p->cfg.dtype != FLP_F32 && b->d_in % 32 == 0;
   int max_dout = 0;
   for (int q = 0; q < b->n_proj; ++q) {
     mfma_ok = mfma_ok && b->proj[q].d_out % 64 == 0;
     max_dout = std::max(max_dout, b->proj[q].d_out);
   }
+  const bool long_runs = n_seqs > 0 && b->n_tokens > 64 && b->n_tokens >= 16 * (int64_t)n_seqs;
+  // Dense base on every projection, and products that together have enough of the large tiles: the expand step runs as
+  // their epilogue (segment, shrink, then one launch for the projections, or one each where W is stored [d_in, d_out],
+  // that adds the LoRA branch to its accumulators before it rounds): no fp32 copy of the product, no second pass over y.
+  // The epilogue walks the adapters present among a wave's 64 or 128 tokens, which are one or two when tokens come in sequences and
+  // as many as tokens in a large pure-decode batch: batches of 2048 tokens and more, and smaller ones that are known to come in
+  // sequences of 16 tokens and more.  Below 1024 tokens only in fp16: v enters as value and remainder, 22 bits there, 16 in bf16,
+  // where the small batches' own expand step keeps 32; and below 512 only with enough tiles.  Layers, us, separate steps / epilogue:
+  //   1200 tokens, 7B shapes, rank 16     684 /  631      1200, 13B, rank 32 on all seven     1321 / 1119
+  //   1980 of 60 sequences, 34B, rank 64 2731 / 2583      1080 of 60, 7B, rank 16 on all      876 /  802
+  //   900 tokens, 7B shapes, rank 16      598 /  548      600, 13B, rank 32 on all             821 /  791
+  //   499-token prompt, 7B shapes         387 /  376      300, 13B (180 tiles of q,k,v)        515 /  478
+  //   300 tokens, 34B (120 tiles)         764 /  812
+  const bool sequences = long_runs && (b->n_tokens >= 1024 || (p->cfg.dtype == FLP_F16 && b->n_tokens >= 256));
+  bool fused = mfma_ok && (b->n_tokens >= 2048 || sequences) && b->d_in % 64 == 0 &&
+               flp_gemm_offsets_fit(FLP_GEMM_256x256, b->n_tokens, b->ld_x);
+  int64_t fused_tiles = 0;                     // enough 256 x 128 tiles to occupy the chip without slices
+  for (int q = 0; q < b->n_proj; ++q) {
+    fused = fused && b->proj[q].w_base;
+    fused_tiles += (int64_t)((b->proj[q].d_out + 255) / 256) * ((b->n_tokens + 127) / 128);
+  }
+  fused = fused && fused_tiles >= (b->n_tokens < 512 ? 160 : 96);
+  mfma_ok = mfma_ok && (b->n_tokens >= 1024 || fused);
   FlpLoraMfma c{};
   size_t v_elems = T * b->n_proj * b->max_rank;
   if (mfma_ok) {
@@ -525,18 +548,6 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
     const int rp = 16 * nt;
     v_elems = (size_t)ks * c.v_rows * b->n_proj * rp;
   }
-  // Dense base on every projection, and products that together have enough of the large tiles: the expand step runs as
-  // their epilogue (segment, shrink, then one launch for the projections, or one each where W is stored [d_in, d_out],
-  // that adds the LoRA branch to its accumulators before it rounds): no fp32 copy of the product, no second pass over y.
-  // (Batches of 2048 tokens and more only: the epilogue walks the adapters present among a wave's 64 or 128 tokens,
-  // which are one or two when tokens come in sequences and as many as tokens in a large pure-decode batch.)
-  bool fused = mfma_ok && b->n_tokens >= 2048 && b->d_in % 64 == 0 && flp_gemm_offsets_fit(FLP_GEMM_256x256, b->n_tokens, b->ld_x);
-  int64_t fused_tiles = 0;                     // enough 256 x 128 tiles to occupy the chip without slices
-  for (int q = 0; q < b->n_proj; ++q) {
-    fused = fused && b->proj[q].w_base;
-    fused_tiles += (int64_t)((b->proj[q].d_out + 255) / 256) * ((b->n_tokens + 127) / 128);
-  }
-  fused = fused && fused_tiles >= 96;
   if (gated_out) {
     const bool ok = fused && b->n_proj == 2 && b->proj[0].d_out == b->proj[1].d_out && b->proj[0].d_out % 32 == 0 &&
                     b->proj[0].w_base_layout == 1 && b->proj[1].w_base_layout == 1 && ld_gated >= b->proj[0].d_out &&
@@ -571,7 +582,7 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
     while (small.k_splits > 1 && b->d_in / 64 / small.k_splits < 4) small.k_splits /= 2;
     // sequences of 16 tokens and more on average: most tokens are not the first of a group.  Layer of a 499-token prompt
     // 414 -> 393 us; with four rank tiles no difference (1000 tokens of two sequences, rank 64: 674 and 676).
-    small.long_runs = n_seqs > 0 && b->n_tokens > 64 && b->n_tokens >= 16 * (int64_t)n_seqs;
+    small.long_runs = long_runs;
     const size_t v_small = ((size_t)small.k_splits * T * b->n_proj * 16 * small.n_tiles * 4 + 255) & ~(size_t)255;
     const size_t g_small = (T * sizeof(FlpLoraGroup) + 255) & ~(size_t)255;
     size_t total = v_small + g_small + seg_bytes + perm_bytes + wt_bytes;

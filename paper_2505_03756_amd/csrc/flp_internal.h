@@ -318,4 +318,5 @@ flp_status flp_launch_gemm_f32(const float* x, int64_t ld_x, const float* w, int
 // up of an MLP), whose results are not stored: out = silu(y0) * y1 in one pass of the large-batch GEMM, each product
 // with its LoRA branch added before it is rounded.  FLP_ENOTSUP, nothing launched, when the batch is not one that
 // this path takes; the caller then runs flp_lora_apply_layer and the element-wise step.
-flp_status flp_lora_apply_gated(flp_pool* pool, const flp_lora_batch* batch, void* out, int64_t ld_out, void* hip_stream);
+flp_status flp_lora_apply_gated(flp_pool* pool, const flp_lora_batch* batch, int32_t n_seqs, void* out, int64_t ld_out,
+                                void* hip_stream);

@@ -543,7 +543,7 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
                              added && n_proj == 1 ? h : nullptr, added));
     if (n_lora == 0) return FLP_OK;
     lb.n_proj = n_lora;
-    if (gated_out) return flp_lora_apply_gated(p, &lb, gated_out, d_outs[0], hip_stream);
+    if (gated_out) return flp_lora_apply_gated(p, &lb, b->n_seqs, gated_out, d_outs[0], hip_stream);
     int N[3];
     for (int i = 0; i < n_lora; ++i) N[i] = lb.proj[i].d_out;
     const int32_t first = p->elem_bytes == 2 ? whole_rounds(T, d_in, n_lora, N, true, kLoraRestUs) : T;

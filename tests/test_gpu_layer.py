@@ -178,6 +178,12 @@ LAYER_CASES = {
     # (one and two rank tiles, widths that leave part of a column chunk); and just too many sequences for that
     "f16_runs_interleaved": lambda: layer_cfg("f16", n_seqs=4, new_range=(40, 60), seed=53),
     "bf16_runs_interleaved": lambda: layer_cfg("bf16", n_seqs=3, new_range=(60, 90), ranks=(8, 32), mlp_dim=1088, seed=54),
+    # sequences of 16 tokens and more: the branch of q, k, v inside the large product from 1024 tokens on, and in fp16 from 256 with 160 tiles
+    # (here 180) on, with other adapters' tokens between as well
+    "f16_prompts_inside_gemm_interleaved": lambda: layer_cfg("f16", n_seqs=2, hidden=512, n_q_heads=40, n_kv_heads=40, new_range=(140, 155),
+                                                             ranks=(8, 32), n_dev_blocks=300, seed=57),
+    "bf16_sequences_inside_gemm_interleaved": lambda: layer_cfg("bf16", n_seqs=20, hidden=2048, n_q_heads=16, n_kv_heads=16,
+                                                                new_range=(54, 60), ranks=(8, 64), n_dev_blocks=1500, seed=58),
     "f16_no_runs_interleaved": lambda: layer_cfg("f16", n_seqs=20, new_range=(8, 15), ranks=(8, 32), seed=55),
     "bf16_fused_gate_up": lambda: layer_cfg("bf16", projections=("q", "k", "v", "o"), n_seqs=10, prefix_range=(0, 300),
                                             new_range=(110, 160), mlp_dim=3136, n_dev_blocks=2500, seed=48),
