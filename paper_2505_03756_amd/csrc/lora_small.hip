@@ -454,8 +454,8 @@ __device__ __forceinline__ void expand_group(const FlpLoraArgs& a, const FlpLora
   add_to_y<S, 4>(yp, bp, base_slice, a.base_slices[p], yraw, pr.d_out - f0, sc, [&](int i, int q) { return acc[q][i]; });
 }
 
-// LONG: a wave looks after kLongBlock neighbouring tokens.  Waves per SIMD are asked for: left to itself the compiler spreads the
-// accumulators over both register files and loses one or two of them.
+// LONG: a wave looks after kLongBlock neighbouring tokens.  Waves per SIMD are asked for with LONG and with four rank tiles: there
+// the compiler by itself spreads the accumulators over both register files and loses one or two waves.
 constexpr int kLongBlock = 8;
 template <typename L, int NT, bool LONG>
 __global__ __launch_bounds__(64, LONG ? 2 : NT == 4 ? 3 : 1) void lora_small_expand_kernel(FlpLoraArgs a, FlpLoraSmall c) {
