@@ -482,7 +482,7 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
   // Matrix-core path with tokens sorted by adapter for 16-bit pools when every width is a multiple of the tile widths (32
   // in, 64 out) and the batch is large enough for token tiles to fill (prefill); smaller batches on the matrix cores as
   // well, but without the sort (below); fp32 pools and odd widths on the vector-ALU kernels.
-  bool mfma_ok = p->cfg.dtype != FLP_F32 && b->d_in % 32 == 0;
+  bool mfma_ok = p->cfg.dtype != FLP_F32 && b->d_in % 32 == 0 && b->n_tokens >= 1024;
   int max_dout = 0;
   for (int q = 0; q < b->n_proj; ++q) {
     mfma_ok = mfma_ok && b->proj[q].d_out % 64 == 0;
@@ -493,24 +493,20 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
   // their epilogue (segment, shrink, then one launch for the projections, or one each where W is stored [d_in, d_out],
   // that adds the LoRA branch to its accumulators before it rounds): no fp32 copy of the product, no second pass over y.
   // The epilogue walks the adapters present among a wave's 64 or 128 tokens, which are one or two when tokens come in sequences and
-  // as many as tokens in a large pure-decode batch: batches of 2048 tokens and more, and smaller ones that are known to come in
-  // sequences of 16 tokens and more.  Below 1024 tokens only in fp16: v enters as value and remainder, 22 bits there, 16 in bf16,
-  // where the small batches' own expand step keeps 32; and below 512 only with enough tiles.  Layers, us, separate steps / epilogue:
+  // as many as tokens in a large pure-decode batch: batches of 2048 tokens and more, and from 1024 tokens on those that are known to
+  // come in sequences of 16 tokens and more.  (Smaller ones keep the small batches' expand step, which holds v in 32 bits: here, as
+  // in the expand step of the sorted tokens, it enters as value and remainder of the 16-bit type, scaled, so that it has to stay
+  // within fp16's range and has fewer bits where it is small.)  Layers, us, separate steps / epilogue:
   //   1200 tokens, 7B shapes, rank 16     684 /  631      1200, 13B, rank 32 on all seven     1321 / 1119
   //   1980 of 60 sequences, 34B, rank 64 2731 / 2583      1080 of 60, 7B, rank 16 on all      876 /  802
-  //   900 tokens, 7B shapes, rank 16      598 /  548      600, 13B, rank 32 on all             821 /  791
-  //   499-token prompt, 7B shapes         387 /  376      300, 13B (180 tiles of q,k,v)        515 /  478
-  //   300 tokens, 34B (120 tiles)         764 /  812
-  const bool sequences = long_runs && (b->n_tokens >= 1024 || (p->cfg.dtype == FLP_F16 && b->n_tokens >= 256));
-  bool fused = mfma_ok && (b->n_tokens >= 2048 || sequences) && b->d_in % 64 == 0 &&
+  bool fused = mfma_ok && (b->n_tokens >= 2048 || long_runs) && b->d_in % 64 == 0 &&
                flp_gemm_offsets_fit(FLP_GEMM_256x256, b->n_tokens, b->ld_x);
   int64_t fused_tiles = 0;                     // enough 256 x 128 tiles to occupy the chip without slices
   for (int q = 0; q < b->n_proj; ++q) {
     fused = fused && b->proj[q].w_base;
     fused_tiles += (int64_t)((b->proj[q].d_out + 255) / 256) * ((b->n_tokens + 127) / 128);
   }
-  fused = fused && fused_tiles >= (b->n_tokens < 512 ? 160 : 96);
-  mfma_ok = mfma_ok && (b->n_tokens >= 1024 || fused);
+  fused = fused && fused_tiles >= 96;
   FlpLoraMfma c{};
   size_t v_elems = T * b->n_proj * b->max_rank;
   if (mfma_ok) {

@@ -350,6 +350,63 @@ def test_layers_without_lora_on_two_streams_of_one_pool(T):
     pool.close()
 
 
+@pytest.mark.parametrize("size", [1e-3, 1.0, 1e6])
+@pytest.mark.parametrize("dtype,T,heads", [("f16", 300, 40), ("f16", 600, 16), ("f16", 1000, 16), ("bf16", 600, 16)])
+def test_lora_branch_of_prompts_keeps_32_bits(dtype, T, heads, size):
+    """The branch alone (no base) of v in layers of two prompts below 1024 tokens against 64 bits, with scaled shrink results about
+    `size`: beyond fp16's range, and where an fp16 remainder would be subnormal.  The layer's scratch holds v, after n, q and k."""
+    import torch
+    cfg = layer_cfg(dtype, n_seqs=2, hidden=512, n_q_heads=heads, n_kv_heads=heads, prefix_range=(0, 0), new_range=(T // 2, T // 2),
+                    projections=("q", "k", "v"), ranks=(16,), n_dev_blocks=300, lora_std=1.0, lora_scale=1.0, seed=60)
+    step = wl.make_step(cfg)
+    dev0 = resident_pool(step)
+    pr = step.proj["v"]
+    v_std = math.sqrt(cfg.hidden)                      # of x A^T: both have standard deviation 1
+    step.scale[:] = size / v_std
+    A, B = {}, {}
+    for ad in np.unique(step.token_adapter):
+        for name, off, base, width, to in (("a", pr.a_tab_off, pr.a_row_base, pr.d_in, A), ("b", pr.b_tab_off, pr.b_row_base, pr.d_out, B)):
+            per = cfg.block_elems // width
+            to[ad] = np.zeros((16, width))
+            for k, row in enumerate(int(base[ad]) + np.arange(16)):
+                cells = dev0[step.lora_tables[off[ad] + row // per], row % per * width:row % per * width + width]
+                if name == "b":
+                    cells[:] = wl.quantize(wl.dequantize(cells, dtype) / np.float32(size if size > 1 else 1), dtype)
+                to[ad][k] = wl.dequantize(cells, dtype)
+    g = GpuStep(step, dev0, np.zeros((1, cfg.block_elems), dev0.dtype))
+    W = make_weights(cfg, np.random.default_rng(7))
+    W["v"][:] = 0
+    Wd = {k: to_dev(w) for k, w in W.items()}
+    layer = fllayer.Layer(g.pool, cfg.hidden, heads, cfg.mlp_dim, Wd)
+    batch = fllayer.Batch(step.cu_new, step.prefix_len, to_dev(np.concatenate([np.arange(T // 2, dtype=np.int32)] * 2)), g.kv_tables,
+                          g.token_adapter, g.rank, g.scale, g.lora_tables, g.proj, n_adapters=len(step.rank), max_rank=16,
+                          max_blocks_per_seq=step.kv_tables.shape[1])
+    nbytes = layer.scratch_bytes(T)
+    scratch = torch.zeros(nbytes + 256, dtype=torch.uint8, device="cuda")
+    at = -scratch.data_ptr() % 256
+    h0_st, _ = lo.round_store(np.random.default_rng(8).normal(0, 1, (T, cfg.hidden)), dtype)
+    n = torch.empty((T, cfg.hidden), dtype=torch.int16, device="cuda")
+    fllayer.rmsnorm(dtype, to_dev(h0_st), Wd["in_norm"], n, T, cfg.hidden)
+    layer.forward(batch, to_dev(h0_st), scratch.data_ptr() + at, nbytes)
+    torch.cuda.synchronize()
+    pad = lambda b: (b + 255) // 256 * 256
+    at += pad(T * cfg.hidden * 2) + 2 * pad(T * pr.d_out * 2)
+    got_st = to_np(scratch[at:at + T * pr.d_out * 2].view(torch.int16), h0_st.dtype).reshape(T, pr.d_out)
+    x = wl.dequantize(to_np(n, h0_st.dtype), dtype).astype(np.float64)
+    want = np.empty((T, pr.d_out))
+    for ad in A:
+        at_ad = step.token_adapter == ad
+        want[at_ad] = float(step.scale[ad]) * (x[at_ad] @ A[ad].T) @ B[ad]
+    got = wl.dequantize(got_st, dtype)
+    assert np.isfinite(got).all() and np.abs(want).max() < 6e4
+    # Sums in 32 bits: an error of about 2^-22 of the terms' size (528 of them, in short chains) is 2^-10 of fp16's spacing, so about
+    # one result in a thousand rounds to a neighbour of the 64-bit result's rounding, fewer in bf16; ten times that.  With v as an fp16
+    # value and an unscaled remainder one in fourteen does at size 1e-3, and at 1e6 the results are NaN.
+    share = float((got_st != wl.quantize(want.astype(np.float32), dtype)).mean())
+    print("size %g: %.2e of %d results are not the rounded ones" % (size, share, got.size), flush=True)
+    assert share < 0.01
+
+
 def test_an_adapter_s_infinities_stay_with_its_tokens_in_the_gated_pair():
     """Infinities and NaN in one adapter's B of gate and up: the rows of sequences with other adapters come out as before, bit
     for bit (the branches of both are added inside the gated pass; sequences meet inside its tiles)."""
