@@ -67,7 +67,7 @@ struct flp_pool {
   size_t attn_work_cap = 0;
   FlpStageSlot* attn_slot = nullptr;   // its event follows the last call that used attn_work, which ran on attn_stream
   hipStream_t attn_stream = nullptr;
-  void* dense_work = nullptr;          // slices of a layer's dense products without LoRA on more than 1024 tokens
+  void* dense_work = nullptr;          // slices of a layer's dense products without LoRA, batches of more than 1024 tokens
   size_t dense_work_cap = 0;
   hipEvent_t dense_ev = nullptr;       // follows the last use of dense_work, which was on dense_stream
   hipStream_t dense_stream = nullptr;

@@ -390,35 +390,23 @@ int32_t whole_rounds(int T, int K, int n, const int* N, bool lora, double extra_
   return parts < 0.98 * whole ? (int32_t)first : T;
 }
 
-// Dense products alone (gated: the gated-SiLU pair as one output).  Slices of a small batch's contraction live in the
-// pool's workspace (stream order keeps them apart from the LoRA intermediates of the calls before and after).  Larger
-// batches without LoRA needed no workspace before they were sliced, so calls on several streams owe each other no order:
-// their slices have a workspace of their own that one call hands to the next, for an event per product (products of
-// 100 us and more; the small ones would notice it).
+// Dense products of the T tokens from token `at` on, in one launch (and one that adds the slices).  Slices of a small batch's
+// contraction live in the pool's workspace (stream order keeps them apart from the LoRA intermediates of the calls before and
+// after).  Larger batches without LoRA needed no workspace before they were sliced, so calls on several streams owe each other no
+// order: their slices, those of their last tokens among them, have a workspace of their own that one call hands to the next, for an
+// event per product (products of 100 us and more; the small ones would notice it).
 constexpr int kSharedWorkTokens = 1024;
-// `resid`, one product: where its slices are added by a kernel, that kernel adds the rounded result to the residual stream
-// instead of writing out->y, and *added says so.
-// rest: the last tokens of a batch whose first ones went ahead
-flp_status dense_products(flp_pool* p, const void* x, int d_in, int T, int n, FlpGemmOut* out, const int* N, bool gated,
-                          hipStream_t stream, void* resid = nullptr, bool* added = nullptr, bool rest = false) {
-  if (p->elem_bytes == 4) {
-    for (int i = 0; i < n; ++i)
-      FLP_TRY(flp_launch_gemm_f32((const float*)x, d_in, (const float*)out[i].w, 1, (float*)out[i].y, out[i].ld_y, T, N[i], d_in,
-                                  stream));
-    return FLP_OK;
-  }
-  const int32_t first = whole_rounds(T, d_in, n, N, false, kRestUs);
-  if (first < T) {
-    FLP_TRY(dense_products(p, x, d_in, first, n, out, N, gated, stream));
-    for (int i = 0; i < n; ++i) {
-      out[i].y = (uint8_t*)out[i].y + (int64_t)first * out[i].ld_y * p->elem_bytes;
-      out[i].part = nullptr;
-    }
-    return dense_products(p, (const uint8_t*)x + (int64_t)first * d_in * p->elem_bytes, d_in, T - first, n, out, N, gated, stream,
-                          nullptr, nullptr, true);
+// batch: the tokens of the whole call
+flp_status dense_launch(flp_pool* p, const void* x, int d_in, int at, int T, int batch, int n, const FlpGemmOut* whole, const int* N,
+                        bool gated, hipStream_t stream, void* resid, bool* added) {
+  const void* const x_at = (const uint8_t*)x + (int64_t)at * d_in * p->elem_bytes;
+  FlpGemmOut out[3];
+  for (int i = 0; i < n; ++i) {
+    out[i] = whole[i];
+    out[i].y = (uint8_t*)whole[i].y + (int64_t)at * whole[i].ld_y * p->elem_bytes;
   }
   const FlpGemmPlan plan = flp_gemm_plan(T, d_in, n, N, 0, kLayerSliceBytes);
-  const bool own = plan.splits > 1 && (rest || T > kSharedWorkTokens);
+  const bool own = plan.splits > 1 && batch > kSharedWorkTokens;
   std::unique_lock<std::mutex> lk(p->mu, std::defer_lock);
   if (plan.splits > 1) {
     void* part = nullptr;
@@ -433,7 +421,7 @@ flp_status dense_products(flp_pool* p, const void* x, int d_in, int T, int n, Fl
       f += (size_t)plan.splits * T * N[i];
     }
   }
-  flp_status s = flp_launch_gemm(p->cfg.dtype, x, d_in, T, d_in, plan, n, out, gated, nullptr, stream);
+  flp_status s = flp_launch_gemm(p->cfg.dtype, x_at, d_in, T, d_in, plan, n, out, gated, nullptr, stream);
   if (s == FLP_OK && plan.splits > 1) {
     if (resid) {
       out->y = resid;
@@ -446,6 +434,24 @@ flp_status dense_products(flp_pool* p, const void* x, int d_in, int T, int n, Fl
     return s != FLP_OK ? s : r;
   }
   return s;
+}
+
+// Dense products alone (gated: the gated-SiLU pair as one output).  `resid`, one product: where its slices are added by a kernel,
+// that kernel adds the rounded result to the residual stream instead of writing out->y, and *added says so.
+flp_status dense_products(flp_pool* p, const void* x, int d_in, int T, int n, const FlpGemmOut* out, const int* N, bool gated,
+                          hipStream_t stream, void* resid = nullptr, bool* added = nullptr) {
+  if (p->elem_bytes == 4) {
+    for (int i = 0; i < n; ++i)
+      FLP_TRY(flp_launch_gemm_f32((const float*)x, d_in, (const float*)out[i].w, 1, (float*)out[i].y, out[i].ld_y, T, N[i], d_in,
+                                  stream));
+    return FLP_OK;
+  }
+  // Cut once: the planner, asked for the first part alone, may see a gain in cutting that as well (K 28672, N 35840: 2564 tokens,
+  // 2560, 2304).
+  const int32_t first = whole_rounds(T, d_in, n, N, false, kRestUs);
+  if (first == T) return dense_launch(p, x, d_in, 0, T, T, n, out, N, gated, stream, resid, added);
+  FLP_TRY(dense_launch(p, x, d_in, 0, first, T, n, out, N, gated, stream, nullptr, nullptr));
+  return dense_launch(p, x, d_in, first, T - first, T, n, out, N, gated, stream, nullptr, nullptr);
 }
 }  // namespace
 

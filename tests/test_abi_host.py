@@ -325,3 +325,20 @@ def test_staging_events_are_fenced_where_they_are_inspected(tmp_path):
     assert b.returncode == 0, b.stderr[-3000:]
     r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "fenced" in r.stdout, (r.stdout + r.stderr)[-3000:]
+
+
+def test_launches_of_a_layer_cover_every_row_once(tmp_path):
+    """tests/layer_rows.cpp: the rows that a layer's products and LoRA branches work on where large batches are cut, among them
+    shapes whose first part the planner would cut again if it were asked."""
+    import shutil
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    flpool.load()
+    pkg, exe = os.path.join(ROOT, "paper_2505_03756_amd"), str(tmp_path / "layer_rows")
+    b = subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(ROOT, "include"),
+                        "-I" + os.path.join(pkg, "csrc"), "-I/opt/rocm/include", os.path.join(ROOT, "tests", "layer_rows.cpp"),
+                        "-rdynamic", flpool.LIB_PATH, "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib:" + pkg, "-o", exe],
+                       capture_output=True, text=True, timeout=300)
+    assert b.returncode == 0, b.stderr[-3000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and "written once" in r.stdout, (r.stdout + r.stderr)[-3000:]

@@ -308,6 +308,43 @@ def test_gated_pair_without_lora(dtype, T, H, M, plan):
     pool.close()
 
 
+def test_cut_of_a_batch_whose_first_part_the_planner_would_cut_again():
+    """gate and up of width 28672 x 35840 and 2564 tokens: the first 2560 in one launch, though the planner would cut 2560 at 2304,
+    and the last four behind them.  The down matrix selects features of the gated product, so the layer shows every row of it."""
+    import torch
+    T, H, M, d = 2564, 28672, 17920, 128
+    first = flpool.load().flp_dense_first_tokens
+    N = (ctypes.c_int32 * 1)(2 * M)
+    assert first(T, H, 1, N, 0) == 2560 and first(2560, H, 1, N, 0) == 2304
+    tt, n_blk = torch.bfloat16, (T + 15) // 16
+    g = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda shape, std: (torch.randn(shape, generator=g, device="cuda") * std).to(tt)
+    W = {p: torch.zeros((d, H), dtype=tt, device="cuda") for p in "qkv"}
+    W.update(o=torch.zeros((H, d), dtype=tt, device="cuda"), gate=rnd((M, H), H ** -0.5), up=rnd((M, H), H ** -0.5),
+             down=torch.zeros((H, M), dtype=tt, device="cuda"), in_norm=rnd((H,), 0.1) + 1, post_norm=rnd((H,), 0.1) + 1)
+    W["down"][torch.arange(M, device="cuda"), torch.arange(M, device="cuda")] = 1
+    h0 = rnd((T, H), 2.0 ** -10)
+    n2 = torch.empty_like(h0)
+    fllayer.rmsnorm("bf16", h0, W["post_norm"], n2, T, H, eps=1e-20)
+    pool = flpool.Pool("bf16", 1, d, n_blk, 0, block_tokens=16)
+    layer = fllayer.Layer(pool, H, 1, M, W, rms_eps=1e-20)
+    i32 = lambda a: torch.tensor(a, dtype=torch.int32, device="cuda")
+    batch = fllayer.Batch([0, T], [0], torch.arange(T, dtype=torch.int32, device="cuda"), i32([list(range(n_blk))]),
+                          i32([-1] * T), i32([8]), torch.ones(1, device="cuda"), i32([0]), {}, 1, 8, n_blk)
+    nbytes = layer.scratch_bytes(T)
+    scratch = torch.full((nbytes + 256,), 0x7f, dtype=torch.uint8, device="cuda")
+    h = h0.clone()
+    layer.forward(batch, h, (scratch.data_ptr() + 255) & ~255, nbytes)
+    torch.cuda.synchronize()
+    gate, up = (n2.float() @ W[p].float().T for p in ("gate", "up"))
+    want = torch.nn.functional.silu(gate) * up + h0[:, :M].float()
+    # a row's values are rounded four times (gate, up, their product, the sum), by at most 2^-9 of the value and by chance less
+    err = (h[:, :M].float() - want).norm(dim=1) / want.norm(dim=1)
+    assert bool((err < 4 * 2.0 ** -9).all()), (int(err.argmax()), float(err.max()))
+    assert torch.equal(h[:, M:], h0[:, M:])
+    pool.close()
+
+
 @pytest.mark.parametrize("T", [1100, 4150])
 def test_layers_without_lora_on_two_streams_of_one_pool(T):
     """Two batches of 1100 tokens through a layer without LoRA, each on a stream of its own with nothing between them: their
