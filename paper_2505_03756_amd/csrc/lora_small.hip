@@ -280,16 +280,17 @@ __device__ __forceinline__ f32x4 sum_slices(const float* vp, int64_t slice, int 
   return v;
 }
 
-// Adds s * delta to 8 NP columns of a token: to the unrounded base, in `slices` slices, or to y itself.
-template <typename S, int NP, typename F>
-__device__ __forceinline__ void add_to_y(uint16_t* yp, const float* bp, int64_t slice, int slices, const u32x4 (&yraw)[NP], int left,
-                                         float sc, F delta) {
+// Adds s * delta to 8 NP columns of a token: to the unrounded base (four columns of it, base(i)), or to y itself.  One function for
+// all forms of the kernel, also for the sake of the last bit: the compiler turns some of these products and their rounding to fp16
+// into one instruction that rounds once, and some into two.
+template <typename S, int NP, typename B, typename F>
+__device__ __forceinline__ void add_to_y(uint16_t* yp, bool has_base, B base, const u32x4 (&yraw)[NP], int left, float sc, F delta) {
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
     if (8 * i >= left) break;
     uint16_t y8[8];
-    if (bp) {
-      const f32x4 lo = sum_slices<4>(bp + 8 * i, slice, slices), hi = sum_slices<4>(bp + 8 * i + 4, slice, slices);
+    if (has_base) {
+      const f32x4 lo = base(2 * i), hi = base(2 * i + 1);
 #pragma unroll
       for (int q = 0; q < 8; ++q) y8[q] = S::from_float(fmaf(sc, delta(i, q), q < 4 ? lo[q & 3] : hi[q & 3]));
     } else {
@@ -313,12 +314,16 @@ __device__ __forceinline__ void expand_group(const FlpLoraArgs& a, const FlpLora
   const flp_lora_proj& pr = a.proj[p];
   const FlpLoraGroup* __restrict__ rec = c.groups + t;
   const int64_t base_slice = (int64_t)a.T * pr.d_out;
+  const int slices = a.base_slices[p];
+  const auto base_at = [&](const float* bp) {
+    return [=](int i) { return sum_slices<4>(bp + 4 * i, base_slice, slices); };
+  };
   if (r == 0) {                                        // a token without a branch: its product has only to be added up
     const int f0 = col0 + 8 * lane;
-    if (a.base_slices[p] <= 1 || lane >= 16 || f0 >= pr.d_out) return;
+    if (slices <= 1 || lane >= 16 || f0 >= pr.d_out) return;
     const u32x4 none[1] = {u32x4{0u, 0u, 0u, 0u}};
-    add_to_y<S, 1>(reinterpret_cast<uint16_t*>(pr.y) + (int64_t)t * pr.ld_y + f0, a.base32[p] + (int64_t)t * pr.d_out + f0, base_slice,
-                   a.base_slices[p], none, pr.d_out - f0, 0.f, [](int, int) { return 0.f; });
+    add_to_y<S, 1>(reinterpret_cast<uint16_t*>(pr.y) + (int64_t)t * pr.ld_y + f0, true,
+                   base_at(a.base32[p] + (int64_t)t * pr.d_out + f0), none, pr.d_out - f0, 0.f, [](int, int) { return 0.f; });
     return;
   }
   const int rpb = (int)(a.block_elems / pr.d_out);
@@ -381,7 +386,7 @@ __device__ __forceinline__ void expand_group(const FlpLoraArgs& a, const FlpLora
       acc[0] += part[0][0] + part[1][0];
       acc[1] += part[0][1] + part[1][1];
     }
-    if ((lane & 3) < n) add_to_y<S, 1>(yp, bp, base_slice, a.base_slices[p], yraw, pr.d_out - f0, sc, [&](int, int q) { return acc[q & 1][q >> 1]; });
+    if ((lane & 3) < n) add_to_y<S, 1>(yp, bp, base_at(bp), yraw, pr.d_out - f0, sc, [&](int, int q) { return acc[q & 1][q >> 1]; });
     return;
   }
 
@@ -409,15 +414,14 @@ __device__ __forceinline__ void expand_group(const FlpLoraArgs& a, const FlpLora
       for (int i = 0; i < 4; ++i)
         b[nt][i] = load_global<u32x4>(address_of(mine, 16 * nt + 4 * kg + i) + 2 * fb);
     }
-  constexpr bool kBaseFirst = LONG;                    // an unrounded base is on its way beside the pages
-  f32x4 base[kBaseFirst ? 8 : 1];
-  if (kBaseFirst && bp) {
+  f32x4 base[LONG ? 8 : 1];                            // LONG: an unrounded base is on its way beside the pages
+  if constexpr (LONG)
+    if (bp) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (f0 + 4 * i < pr.d_out)
-        base[kBaseFirst ? i : 0] = a.base_slices[p] == 1 ? *reinterpret_cast<const f32x4*>(bp + 4 * i)
-                                                         : sum_slices<4>(bp + 4 * i, base_slice, a.base_slices[p]);
-  }
+      for (int i = 0; i < 8; ++i)
+        if (f0 + 4 * i < pr.d_out)
+          base[i] = slices == 1 ? *reinterpret_cast<const f32x4*>(bp + 4 * i) : sum_slices<4>(bp + 4 * i, base_slice, slices);
+    }
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     if (16 * nt >= r) break;
@@ -438,20 +442,11 @@ __device__ __forceinline__ void expand_group(const FlpLoraArgs& a, const FlpLora
   }
   if (m16 >= n) return;
   // lane (token m16, kg): element i of tile q is column 32 kg + 8 i + q of the chunk
-  if (kBaseFirst && bp) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (f0 + 8 * i >= pr.d_out) break;
-      uint16_t y8[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) y8[q] = S::from_float(fmaf(sc, acc[q][i], base[kBaseFirst ? 2 * i + (q >> 2) : 0][q & 3]));
-      u32x4 raw;
-      __builtin_memcpy(&raw, y8, 16);
-      *reinterpret_cast<u32x4*>(yp + 8 * i) = raw;
-    }
-    return;
-  }
-  add_to_y<S, 4>(yp, bp, base_slice, a.base_slices[p], yraw, pr.d_out - f0, sc, [&](int i, int q) { return acc[q][i]; });
+  const auto delta = [&](int i, int q) { return acc[q][i]; };
+  if constexpr (LONG)
+    add_to_y<S, 4>(yp, bp, [&](int i) { return base[i]; }, yraw, pr.d_out - f0, sc, delta);
+  else
+    add_to_y<S, 4>(yp, bp, base_at(bp), yraw, pr.d_out - f0, sc, delta);
 }
 
 // LONG: a wave looks after kLongBlock neighbouring tokens.  Waves per SIMD are asked for with LONG and with four rank tiles: there

@@ -387,12 +387,36 @@ def test_layers_without_lora_on_two_streams_of_one_pool(T):
     pool.close()
 
 
+def run_layer_to_v(step, dev0, W):
+    """A layer over the step's batch: its GpuStep, the weights on the device, the first norm's output, and v as the layer's scratch
+    holds it, after n, q and k."""
+    import torch
+    cfg, T = step.cfg, step.n_tokens
+    g = GpuStep(step, dev0, np.zeros((1, cfg.block_elems), dev0.dtype))
+    Wd = {k: to_dev(w) for k, w in W.items()}
+    layer = fllayer.Layer(g.pool, cfg.hidden, cfg.n_q_heads, cfg.mlp_dim, Wd)
+    pos = np.concatenate([p + np.arange(n) for p, n in zip(step.prefix_len, step.new_len)]).astype(np.int32)
+    batch = fllayer.Batch(step.cu_new, step.prefix_len, to_dev(pos), g.kv_tables, g.token_adapter, g.rank, g.scale, g.lora_tables,
+                          g.proj, n_adapters=len(step.rank), max_rank=int(step.rank.max()), max_blocks_per_seq=step.kv_tables.shape[1])
+    nbytes = layer.scratch_bytes(T)
+    scratch = torch.zeros(nbytes + 256, dtype=torch.uint8, device="cuda")
+    at = -scratch.data_ptr() % 256
+    h0_st, _ = lo.round_store(np.random.default_rng(8).normal(0, 1, (T, cfg.hidden)), cfg.dtype)
+    n = torch.empty((T, cfg.hidden), dtype=torch.int16, device="cuda")
+    fllayer.rmsnorm(cfg.dtype, to_dev(h0_st), Wd["in_norm"], n, T, cfg.hidden)
+    layer.forward(batch, to_dev(h0_st), scratch.data_ptr() + at, nbytes)
+    torch.cuda.synchronize()
+    pad = lambda b: (b + 255) // 256 * 256
+    dq, dk = cfg.proj_dims("q")[1], cfg.proj_dims("k")[1]
+    at += pad(T * cfg.hidden * 2) + pad(T * dq * 2) + pad(T * dk * 2)
+    return g, Wd, n, to_np(scratch[at:at + T * dk * 2].view(torch.int16), h0_st.dtype).reshape(T, dk)
+
+
 @pytest.mark.parametrize("size", [1e-3, 1.0, 1e6])
 @pytest.mark.parametrize("dtype,T,heads", [("f16", 300, 40), ("f16", 600, 16), ("f16", 1000, 16), ("bf16", 600, 16)])
 def test_lora_branch_of_prompts_keeps_32_bits(dtype, T, heads, size):
     """The branch alone (no base) of v in layers of two prompts below 1024 tokens against 64 bits, with scaled shrink results about
-    `size`: beyond fp16's range, and where an fp16 remainder would be subnormal.  The layer's scratch holds v, after n, q and k."""
-    import torch
+    `size`: beyond fp16's range, and where an fp16 remainder would be subnormal."""
     cfg = layer_cfg(dtype, n_seqs=2, hidden=512, n_q_heads=heads, n_kv_heads=heads, prefix_range=(0, 0), new_range=(T // 2, T // 2),
                     projections=("q", "k", "v"), ranks=(16,), n_dev_blocks=300, lora_std=1.0, lora_scale=1.0, seed=60)
     step = wl.make_step(cfg)
@@ -410,26 +434,10 @@ def test_lora_branch_of_prompts_keeps_32_bits(dtype, T, heads, size):
                 if name == "b":
                     cells[:] = wl.quantize(wl.dequantize(cells, dtype) / np.float32(size if size > 1 else 1), dtype)
                 to[ad][k] = wl.dequantize(cells, dtype)
-    g = GpuStep(step, dev0, np.zeros((1, cfg.block_elems), dev0.dtype))
     W = make_weights(cfg, np.random.default_rng(7))
     W["v"][:] = 0
-    Wd = {k: to_dev(w) for k, w in W.items()}
-    layer = fllayer.Layer(g.pool, cfg.hidden, heads, cfg.mlp_dim, Wd)
-    batch = fllayer.Batch(step.cu_new, step.prefix_len, to_dev(np.concatenate([np.arange(T // 2, dtype=np.int32)] * 2)), g.kv_tables,
-                          g.token_adapter, g.rank, g.scale, g.lora_tables, g.proj, n_adapters=len(step.rank), max_rank=16,
-                          max_blocks_per_seq=step.kv_tables.shape[1])
-    nbytes = layer.scratch_bytes(T)
-    scratch = torch.zeros(nbytes + 256, dtype=torch.uint8, device="cuda")
-    at = -scratch.data_ptr() % 256
-    h0_st, _ = lo.round_store(np.random.default_rng(8).normal(0, 1, (T, cfg.hidden)), dtype)
-    n = torch.empty((T, cfg.hidden), dtype=torch.int16, device="cuda")
-    fllayer.rmsnorm(dtype, to_dev(h0_st), Wd["in_norm"], n, T, cfg.hidden)
-    layer.forward(batch, to_dev(h0_st), scratch.data_ptr() + at, nbytes)
-    torch.cuda.synchronize()
-    pad = lambda b: (b + 255) // 256 * 256
-    at += pad(T * cfg.hidden * 2) + 2 * pad(T * pr.d_out * 2)
-    got_st = to_np(scratch[at:at + T * pr.d_out * 2].view(torch.int16), h0_st.dtype).reshape(T, pr.d_out)
-    x = wl.dequantize(to_np(n, h0_st.dtype), dtype).astype(np.float64)
+    _, _, n, got_st = run_layer_to_v(step, dev0, W)
+    x = wl.dequantize(to_np(n, got_st.dtype), dtype).astype(np.float64)
     want = np.empty((T, pr.d_out))
     for ad in A:
         at_ad = step.token_adapter == ad
@@ -442,6 +450,30 @@ def test_lora_branch_of_prompts_keeps_32_bits(dtype, T, heads, size):
     share = float((got_st != wl.quantize(want.astype(np.float32), dtype)).mean())
     print("size %g: %.2e of %d results are not the rounded ones" % (size, share, got.size), flush=True)
     assert share < 0.01
+
+
+@pytest.mark.parametrize("dtype,n_seqs,new,ranks", [("f16", 1, (700, 700), (16, 16)), ("f16", 3, (200, 330), (8, 32)),
+                                                    ("bf16", 2, (350, 450), (8, 32))])
+def test_layer_of_prompts_gives_the_bits_of_the_lora_call(dtype, n_seqs, new, ranks):
+    """v of a layer of prompts below 1024 tokens, whose expand step goes through neighbouring tokens in one wave, and of
+    flp_lora_apply_paged on the same input, which is not told how the tokens come: the same bits.  Adapters in runs, with others'
+    tokens and tokens without one between."""
+    import torch
+    from helpers import dense_plan
+    cfg = layer_cfg(dtype, n_seqs=n_seqs, n_q_heads=16, n_kv_heads=16, prefix_range=(0, 40), new_range=new, projections=("q", "k", "v"),
+                    ranks=ranks, n_dev_blocks=400, seed=61)
+    step = wl.make_step(cfg)
+    T, widths = step.n_tokens, (2048, 2048, 2048)
+    assert 64 < T < 1024 and dense_plan(T, cfg.hidden, widths) == dense_plan(T, cfg.hidden, widths, room=48 << 20)
+    step.token_adapter[::13] = np.resize(np.unique(step.token_adapter), len(step.token_adapter[::13]))
+    step.token_adapter[::29] = -1
+    g, Wd, n, got = run_layer_to_v(step, resident_pool(step), make_weights(cfg, np.random.default_rng(7)))
+    y = [torch.zeros((T, 2048), dtype=torch.int16, device="cuda") for _ in "qkv"]
+    projs = [dict(y=y[i], d_out=2048, w_base=Wd[p], w_base_layout=1, **g.proj[p]) for i, p in enumerate("qkv")]
+    g.pool.lora_apply_paged(n, g.token_adapter, g.rank, g.scale, g.lora_tables, projs, n_tokens=T, d_in=cfg.hidden,
+                            n_adapters=len(step.rank), max_rank=int(step.rank.max()))
+    torch.cuda.synchronize()
+    assert np.array_equal(to_np(y[2], got.dtype), got)
 
 
 def test_an_adapter_s_infinities_stay_with_its_tokens_in_the_gated_pair():
