@@ -471,6 +471,7 @@ __global__ __launch_bounds__(64, LONG ? 2 : NT == 4 ? 3 : 1) void lora_small_exp
     const int n = rec->n, r = rec->r;
     for (uint64_t todo = __ballot(lane < kLongBlock && t0 + lane < a.T && n > 0); todo; todo &= todo - 1) {
       const int i = __ffsll((long long)todo) - 1;
+      __syncthreads();                                 // one wave: the last group's reads of v_lds stay before this one's writes
       expand_group<L, NT, LONG>(a, c, p, t0 + i, __builtin_amdgcn_readlane(n, i), __builtin_amdgcn_readlane(r, i), col0, v_lds);
     }
   } else {

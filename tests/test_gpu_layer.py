@@ -453,20 +453,26 @@ def test_lora_branch_of_prompts_keeps_32_bits(dtype, T, heads, size):
 
 
 @pytest.mark.parametrize("dtype,n_seqs,new,ranks", [("f16", 1, (700, 700), (16, 16)), ("f16", 3, (200, 330), (8, 32)),
-                                                    ("bf16", 2, (350, 450), (8, 32))])
+                                                    ("bf16", 2, (350, 450), (8, 32)), ("f16", 24, (28, 32), (8, 32))])
 def test_layer_of_prompts_gives_the_bits_of_the_lora_call(dtype, n_seqs, new, ranks):
     """v of a layer of prompts below 1024 tokens, whose expand step goes through neighbouring tokens in one wave, and of
     flp_lora_apply_paged on the same input, which is not told how the tokens come: the same bits.  Adapters in runs, with others'
-    tokens and tokens without one between."""
+    tokens and tokens without one between; or (24 sequences) a dozen neighbours that are the only tokens of their adapters, so that
+    a wave works for eight groups one after the other."""
     import torch
     from helpers import dense_plan
     cfg = layer_cfg(dtype, n_seqs=n_seqs, n_q_heads=16, n_kv_heads=16, prefix_range=(0, 40), new_range=new, projections=("q", "k", "v"),
-                    ranks=ranks, n_dev_blocks=400, seed=61)
+                    ranks=ranks, n_dev_blocks=400, n_adapters=max(5, n_seqs), adapter_dist="distinct", seed=61)
     step = wl.make_step(cfg)
     T, widths = step.n_tokens, (2048, 2048, 2048)
     assert 64 < T < 1024 and dense_plan(T, cfg.hidden, widths) == dense_plan(T, cfg.hidden, widths, room=48 << 20)
-    step.token_adapter[::13] = np.resize(np.unique(step.token_adapter), len(step.token_adapter[::13]))
-    step.token_adapter[::29] = -1
+    if n_seqs == 24:
+        alone = step.seq_adapter[12:]
+        step.token_adapter[np.isin(step.token_adapter, alone)] = step.seq_adapter[0]
+        step.token_adapter[16:28] = alone
+    else:
+        step.token_adapter[::13] = np.resize(np.unique(step.token_adapter), len(step.token_adapter[::13]))
+        step.token_adapter[::29] = -1
     g, Wd, n, got = run_layer_to_v(step, resident_pool(step), make_weights(cfg, np.random.default_rng(7)))
     y = [torch.zeros((T, 2048), dtype=torch.int16, device="cuda") for _ in "qkv"]
     projs = [dict(y=y[i], d_out=2048, w_base=Wd[p], w_base_layout=1, **g.proj[p]) for i, p in enumerate("qkv")]
