@@ -292,7 +292,7 @@ struct FlpGemmArgs {
   const uint16_t* x;
   int64_t ld_x;
   int32_t M, K, n_proj, f_tiles, m_tiles, splits;
-  int32_t gf, gm;              // (feature tile, slice) units x token tiles that run next to each other on one XCD
+  int32_t gf, bands;           // tiles that run next to each other on one XCD: gf (feature tile, slice) units x a band of token tiles
   FlpGemmProj proj[FLP_MAX_PROJ];
 };
 enum { FLP_GEMM_NO_SPLIT = 1, FLP_GEMM_LARGE_ONLY = 2 };   // whole contractions only; only the tiles that take a LoRA epilogue
@@ -301,6 +301,8 @@ FlpGemmPlan flp_gemm_plan(int M, int K, int n_proj, const int* N, unsigned allow
 // the same through the C ABI, for tests that state which tile and how many slices a shape gets; room < 0: a layer's
 extern "C" void flp_dense_plan(int32_t M, int32_t K, int32_t n_proj, const int32_t* N, int32_t large_only, int64_t room,
                                int32_t* kind, int32_t* splits);
+// which unit (feature tile, slice) and token tile a workgroup of a launch takes, for tests; 0: none
+extern "C" int32_t flp_dense_tile(int32_t block, int32_t n_units, int32_t m_tiles, int32_t* u, int32_t* tm);
 // rows of x this far apart can be addressed inside a tile of this kind
 bool flp_gemm_offsets_fit(int kind, int M, int64_t ld_x);
 size_t flp_gemm_part_bytes(const FlpGemmPlan& plan, int M, int n_proj, const int* N);

@@ -284,6 +284,38 @@ __device__ __forceinline__ void add_lora(const uint64_t* rows, int r, int n_nt, 
   }
 }
 
+// Workgroup -> (feature tile, slice) unit u and token tile tm.  Blocks of gf units x the token tiles of a band run next to each other
+// on one XCD (workgroups are placed on the 8 XCDs in turn), so that an operand tile crosses from memory into one L2 once.  The
+// tiles, in the order of their blocks, are dealt out 256 at a time, 32 to an XCD and the last ones in eighths.  (Whole blocks dealt to
+// the XCDs in turn left some with one more than the others: 240 tiles of 256 x 256, 30 for each XCD, took two rounds.  An eighth of
+// all tiles to each XCD keeps them apart, and the operands cross from memory more often: layer of 9874 tokens, 13B shapes, 6660 ->
+// 6917 us.)  The bands are of equal height: with eight tiles in each but the last, a last one of a single token tile put up to 32 of
+// its tiles on one XCD and none on others, and where that tile holds the batch's single tokens, with an adapter each, its tiles take
+// several times as long (2048 tokens of prompts and 200 single ones, 7B shapes, LoRA of rank 64 on all seven: layer 4690 us, with equal
+// bands 3844).
+__host__ __device__ inline bool tile_of_block(int block, int n_units, int m_tiles, int gf, int bands, int* u, int* tm) {
+  const int n_tiles = n_units * m_tiles, xcd = block & 7;
+  const int first = block >> 8 << 8, part = n_tiles - first < 256 ? n_tiles - first : 256;
+  int at = (part * xcd >> 3) + ((block & 255) >> 3);
+  if (at >= part * (xcd + 1) >> 3) return false;
+  at += first;
+  const int low = m_tiles / bands, n_high = m_tiles % bands;         // the first n_high bands have one token tile more
+  const int t = at / n_units, in_high = n_high * (low + 1);
+  const int rows = t < in_high ? low + 1 : low;
+  const int m0 = t < in_high ? t / rows * rows : in_high + (t - in_high) / rows * rows;
+  at -= m0 * n_units;
+  const int ub = at / (gf * rows), cols = n_units - ub * gf < gf ? n_units - ub * gf : gf;
+  at -= ub * gf * rows;
+  *u = ub * gf + at % cols;
+  *tm = m0 + at / cols;
+  return true;
+}
+// with more than eight token tiles, blocks of about 4 x 8: the workgroups that run together fetch 12 operand panels, not 33
+inline void tile_blocks(int m_tiles, int* gf, int* bands) {
+  *gf = m_tiles > 8 ? 4 : 1;
+  *bands = (m_tiles + 7) / 8;
+}
+
 // WF x WT waves of 64 features x 16 AT tokens each
 template <typename G, int WF, int WT, int AT, int ST, bool PP, bool GATED, bool LORA>
 __global__ __launch_bounds__(64 * WF * WT, (WF * WT + 3) / 4)
@@ -301,23 +333,8 @@ __global__ __launch_bounds__(64 * WF * WT, (WF * WT + 3) / 4)
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wf = wave % WF, wt = wave / WF;
 
-  // workgroup -> (feature tile, slice, token tile): blocks of gf (feature tile, slice) units x gm token tiles run next
-  // to each other on one XCD (workgroups are placed on the 8 XCDs in turn), so that an operand tile crosses from memory
-  // into one L2 once.  The tiles, in the order of their blocks, are dealt out 256 at a time, 32 to an XCD and the last ones in
-  // eighths.  (Whole blocks dealt to the XCDs in turn left some with one more than the others: 240 tiles of 256 x 256, 30 for each
-  // XCD, took two rounds.  An eighth of all tiles to each XCD keeps them apart, and the operands cross from memory more often: layer of
-  // 9874 tokens, 13B shapes, 6660 -> 6917 us.)
-  const int n_units = a.f_tiles * a.splits, n_tiles = n_units * a.m_tiles, xcd = blockIdx.x & 7;
-  const int first = (int)(blockIdx.x >> 8) << 8, part = n_tiles - first < 256 ? n_tiles - first : 256;
-  int at = (part * xcd >> 3) + (int)((blockIdx.x & 255) >> 3);
-  if (at >= part * (xcd + 1) >> 3) return;
-  at += first;
-  const int mb = at / (n_units * a.gm);                 // row of blocks
-  const int rows = a.m_tiles - mb * a.gm < a.gm ? a.m_tiles - mb * a.gm : a.gm;
-  at -= mb * n_units * a.gm;
-  const int ub = at / (a.gf * rows), cols = n_units - ub * a.gf < a.gf ? n_units - ub * a.gf : a.gf;
-  at -= ub * a.gf * rows;
-  const int u = ub * a.gf + at % cols, tm = mb * a.gm + at / cols;
+  int u, tm;
+  if (!tile_of_block((int)blockIdx.x, a.f_tiles * a.splits, a.m_tiles, a.gf, a.bands, &u, &tm)) return;
   const int z = u / a.f_tiles;
   int ft = u - z * a.f_tiles;
   int p = 0;
@@ -796,6 +813,12 @@ extern "C" void flp_dense_plan(int32_t M, int32_t K, int32_t n_proj, const int32
   *splits = p.splits;
 }
 
+extern "C" int32_t flp_dense_tile(int32_t block, int32_t n_units, int32_t m_tiles, int32_t* u, int32_t* tm) {
+  int gf, bands;
+  tile_blocks(m_tiles, &gf, &bands);
+  return tile_of_block(block, n_units, m_tiles, gf, bands, u, tm);
+}
+
 flp_status flp_launch_gemm(int dtype, const void* x, int64_t ld_x, int M, int K, const FlpGemmPlan& plan, int n_proj,
                            const FlpGemmOut* out, bool gated, const FlpGemmLora* lora, hipStream_t stream) {
   if (M <= 0 || K <= 0 || n_proj <= 0) return FLP_OK;
@@ -836,9 +859,7 @@ flp_status flp_launch_gemm(int dtype, const void* x, int64_t ld_x, int M, int K,
     a.f_tiles += (pr.N + c.ft - 1) / c.ft;
     if (plan.splits > 1) pr.y = nullptr;                 // whoever adds the slices writes it: gemm_reduce, or the LoRA expand step
   }
-  // with more than eight token tiles, 4 x 8 blocks: the workgroups that run together fetch 12 operand panels, not 33
-  a.gm = a.m_tiles > 8 ? 8 : a.m_tiles;
-  a.gf = a.m_tiles > 8 ? 4 : 1;
+  tile_blocks(a.m_tiles, &a.gf, &a.bands);
   const int64_t n_tiles = (int64_t)a.f_tiles * a.splits * a.m_tiles, grid = (n_tiles + 7) / 8 * 8;    // 256s, then eighths rounded up
   if (grid > INT32_MAX) {
     flp_set_error("dense product: %lld workgroups, too many for one launch", (long long)grid);

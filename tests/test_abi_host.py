@@ -342,3 +342,26 @@ def test_launches_of_a_layer_cover_every_row_once(tmp_path):
     assert b.returncode == 0, b.stderr[-3000:]
     r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "written once" in r.stdout, (r.stdout + r.stderr)[-3000:]
+
+
+@pytest.mark.parametrize("n_units,m_tiles", [(86, 9), (43, 9), (48, 10), (86, 17), (16, 9), (54, 39), (7, 3), (1, 1), (172, 8), (3, 100), (258, 25)])
+def test_tiles_of_a_dense_product_are_dealt_once_and_evenly(n_units, m_tiles):
+    """Workgroups are placed on the 8 XCDs in turn: every tile belongs to one, an XCD has at most 32 of 256 that start together, and
+    no XCD gets much more than its eighth of one token tile's (that tile may cost several times as much as the others: single
+    tokens with a LoRA adapter each).  A block has up to four units beside each other, and the runs of an XCD begin and
+    end inside one: twelve more than the eighth at most."""
+    f = flpool.load().flp_dense_tile
+    u, tm = C.c_int32(), C.c_int32()
+    n_tiles = n_units * m_tiles
+    seen, per_xcd = set(), np.zeros((m_tiles, 8), int)
+    for block in range((n_tiles + 7) // 8 * 8):
+        if not f(block, n_units, m_tiles, C.byref(u), C.byref(tm)):
+            continue
+        assert 0 <= u.value < n_units and 0 <= tm.value < m_tiles and (u.value, tm.value) not in seen
+        seen.add((u.value, tm.value))
+        per_xcd[tm.value, block & 7] += 1
+    assert len(seen) == n_tiles
+    for lo in range(0, n_tiles, 256):
+        assert max(np.bincount([b & 7 for b in range(lo, min(lo + 256, (n_tiles + 7) // 8 * 8))], minlength=8)) <= 32
+    if m_tiles > 8:
+        assert per_xcd.max() <= n_units / 8 + 12, per_xcd
