@@ -367,7 +367,7 @@ extern "C" flp_status flp_lora_segment(flp_pool* p, int32_t n_tokens, const int3
 
 namespace {
 flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_stream, size_t budget, void* gated_out,
-                           int64_t ld_gated, const FlpFixedWorkspace* fixed = nullptr, int32_t n_seqs = 0);
+                           int64_t ld_gated, const FlpFixedWorkspace* fixed = nullptr, const FlpSequences* seqs = nullptr);
 }
 
 // The call and its form in a fixed buffer plan the dense products for the same room, the fixed buffer's, so that they take
@@ -380,16 +380,17 @@ flp_status flp_lora_apply_fixed(flp_pool* p, const flp_lora_batch* b, void* hip_
   return lora_apply_impl(p, b, hip_stream, ws.cap, nullptr, 0, &ws);
 }
 
-flp_status flp_lora_apply_layer(flp_pool* p, const flp_lora_batch* b, int32_t n_seqs, void* hip_stream) {
-  return lora_apply_impl(p, b, hip_stream, kLayerSliceBytes, nullptr, 0, nullptr, n_seqs);
+flp_status flp_lora_apply_layer(flp_pool* p, const flp_lora_batch* b, const FlpSequences& seqs, void* hip_stream) {
+  return lora_apply_impl(p, b, hip_stream, kLayerSliceBytes, nullptr, 0, nullptr, &seqs);
 }
 
-flp_status flp_lora_apply_gated(flp_pool* p, const flp_lora_batch* b, int32_t n_seqs, void* out, int64_t ld_out, void* hip_stream) {
+flp_status flp_lora_apply_gated(flp_pool* p, const flp_lora_batch* b, const FlpSequences& seqs, void* out, int64_t ld_out,
+                                void* hip_stream) {
   if (!out || ((uintptr_t)out & 15)) {
     flp_set_error("flp_lora_apply_gated: out is null or misaligned");
     return FLP_EINVAL;
   }
-  return lora_apply_impl(p, b, hip_stream, kLayerSliceBytes, out, ld_out, nullptr, n_seqs);
+  return lora_apply_impl(p, b, hip_stream, kLayerSliceBytes, out, ld_out, nullptr, &seqs);
 }
 
 namespace {
@@ -424,14 +425,84 @@ size_t plan_base(const flp_lora_batch* b, bool one_launch, size_t room, std::vec
   }
 }
 
+// most sequences that any `window` tokens of the call touch, counted from the call's first token on
+int32_t most_sequences(const FlpSequences& s, int32_t n_tokens, int32_t window, int32_t* n_in_call) {
+  int32_t most = 0, here = 0, at = -1, n = 0;           // sequences in window `at`
+  for (int32_t i = 0; i < s.n; ++i) {
+    const int64_t lo = std::max<int64_t>(0, (int64_t)s.cu[i] - s.first);
+    const int64_t hi = std::min<int64_t>(n_tokens, (int64_t)s.cu[i + 1] - s.first);
+    if (hi <= lo) continue;
+    ++n;
+    const int32_t first = (int32_t)(lo / window), last = (int32_t)((hi - 1) / window);
+    here = first == at ? here + 1 : 1;
+    most = std::max(most, here);
+    if (last > first) here = 1;
+    at = last;
+  }
+  *n_in_call = n;
+  return most;
+}
+
+struct LoraRoute {
+  bool sorted;       // tokens sorted by adapter, steps on tiles of them
+  bool in_product;   // sorted, and the expand step is the dense products' epilogue
+  bool long_runs;    // not sorted: a wave of the expand step goes through neighbouring tokens
+};
+LoraRoute lora_route(int dtype, const flp_lora_batch* b, const FlpSequences* seqs) {
+  LoraRoute r{};
+  // Matrix-core path with tokens sorted by adapter for 16-bit pools when every width is a multiple of the tile widths (32
+  // in, 64 out) and the batch is large enough for token tiles to fill (prefill); smaller batches on the matrix cores as
+  // well, but without the sort; fp32 pools and odd widths on the vector-ALU kernels.
+  r.sorted = dtype != FLP_F32 && b->d_in % 32 == 0 && b->n_tokens >= 1024;
+  for (int q = 0; q < b->n_proj; ++q) r.sorted = r.sorted && b->proj[q].d_out % 64 == 0;
+  // Sequences of 16 tokens and more on average, and how many of them meet in a tile, or in a wave's neighbouring tokens: with the
+  // mean alone 110 single tokens behind four prompts counted as 17 tokens each.
+  int32_t in_tile = INT32_MAX, in_block = INT32_MAX, n = 0;
+  if (seqs && seqs->cu && b->n_tokens > 64) {
+    in_tile = most_sequences(*seqs, b->n_tokens, 128, &n);
+    in_block = most_sequences(*seqs, b->n_tokens, kLoraLongBlock, &n);
+    if (n == 0 || b->n_tokens < 16 * (int64_t)n) in_tile = in_block = INT32_MAX;
+  }
+  // Dense base on every projection, and products that together have enough of the large tiles: the expand step runs as
+  // their epilogue (segment, shrink, then one launch for the projections, or one each where W is stored [d_in, d_out],
+  // that adds the LoRA branch to its accumulators before it rounds): no fp32 copy of the product, no second pass over y.
+  // The epilogue walks the adapters present among its tile's tokens, eight at a time: one or two when tokens come in sequences and as
+  // many as tokens in a large pure-decode batch.  Batches of 2048 tokens and more, and from 1024 tokens on those with at most twenty
+  // sequences in any 128 tokens.  (Smaller ones keep the small batches' expand step, which holds v in 32 bits: here, as in the
+  // expand step of the sorted tokens, it enters as value and remainder of the 16-bit type, scaled, so that it has to stay within
+  // fp16's range and has fewer bits where it is small.)  Layers, us, separate steps / epilogue:
+  //                            7B, rank 16     7B, rank 64 on all seven     34B, rank 64
+  //   1200                     688 /  638           1013 /  837            1860 / 1758
+  //   1200 of 60 sequences     722 /  665           1205 / 1021            1938 / 1826
+  //   1800 and 16 single ones 1002 /  914           1455 / 1436            2563 / 2541
+  //   1800 and 32             1034 /  975           1513 / 1864            2621 / 2669
+  //   1200 and 64              763 /  833           1279 / 1947            2037 / 2309
+  r.in_product = r.sorted && (b->n_tokens >= 2048 || in_tile <= 20) && b->d_in % 64 == 0 &&
+                 flp_gemm_offsets_fit(FLP_GEMM_256x256, b->n_tokens, b->ld_x);
+  int64_t tiles = 0;                           // enough 256 x 128 tiles to occupy the chip without slices
+  for (int q = 0; q < b->n_proj; ++q) {
+    r.in_product = r.in_product && b->proj[q].w_base;
+    tiles += (int64_t)((b->proj[q].d_out + 255) / 256) * ((b->n_tokens + 127) / 128);
+  }
+  r.in_product = r.in_product && tiles >= 96;
+  // Most tokens are not the first of a group, and those that are do not follow each other.  Layers, us, a token per wave / eight
+  // neighbouring ones:
+  //   499-token prompt, 7B shapes, rank 16   413 / 382     500 tokens, 7B, rank 32 on all seven   539 / 489      34B   876 / 883
+  //   500 and 8 single tokens                408 / 401                                            567 / 543      34B   897 / 948
+  //   500 and 30                             445 / 447                                            604 / 609      34B  1061 / 1115
+  // With four rank tiles no difference (1000 tokens of two sequences, rank 64: 674 and 676).
+  r.long_runs = !r.sorted && dtype != FLP_F32 && b->n_tokens <= kLoraSmallTokens && b->max_rank <= 32 && in_block <= 2;
+  return r;
+}
+
 // gated_out != nullptr: two projections (gate, up) whose results are not stored; gated_out = silu(y0) * y1
 // fixed != nullptr: the intermediates go into the caller-provided buffer and nothing is allocated; a batch that
 // needs more than the buffer holds is refused before anything is enqueued
 // budget: bytes of intermediates that slices of dense products may bring the call to, whatever the buffer is (the sums'
 // order, and with it the result's last bits, depends on the number of slices)
-// n_seqs: the sequences the tokens come in, 0: not known
+// seqs: the sequences the tokens come in, null: not known
 flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_stream, size_t budget, void* gated_out,
-                           int64_t ld_gated, const FlpFixedWorkspace* fixed, int32_t n_seqs) {
+                           int64_t ld_gated, const FlpFixedWorkspace* fixed, const FlpSequences* seqs) {
   if (!p || !b) {
     flp_set_error("flp_lora_apply_paged: null pool or batch");
     return FLP_EINVAL;
@@ -479,34 +550,8 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
   hipStream_t stream = (hipStream_t)hip_stream;
   const size_t T = (size_t)b->n_tokens;
 
-  // Matrix-core path with tokens sorted by adapter for 16-bit pools when every width is a multiple of the tile widths (32
-  // in, 64 out) and the batch is large enough for token tiles to fill (prefill); smaller batches on the matrix cores as
-  // well, but without the sort (below); fp32 pools and odd widths on the vector-ALU kernels.
-  bool mfma_ok = p->cfg.dtype != FLP_F32 && b->d_in % 32 == 0 && b->n_tokens >= 1024;
-  int max_dout = 0;
-  for (int q = 0; q < b->n_proj; ++q) {
-    mfma_ok = mfma_ok && b->proj[q].d_out % 64 == 0;
-    max_dout = std::max(max_dout, b->proj[q].d_out);
-  }
-  const bool long_runs = n_seqs > 0 && b->n_tokens > 64 && b->n_tokens >= 16 * (int64_t)n_seqs;
-  // Dense base on every projection, and products that together have enough of the large tiles: the expand step runs as
-  // their epilogue (segment, shrink, then one launch for the projections, or one each where W is stored [d_in, d_out],
-  // that adds the LoRA branch to its accumulators before it rounds): no fp32 copy of the product, no second pass over y.
-  // The epilogue walks the adapters present among a wave's 64 or 128 tokens, which are one or two when tokens come in sequences and
-  // as many as tokens in a large pure-decode batch: batches of 2048 tokens and more, and from 1024 tokens on those that are known to
-  // come in sequences of 16 tokens and more.  (Smaller ones keep the small batches' expand step, which holds v in 32 bits: here, as
-  // in the expand step of the sorted tokens, it enters as value and remainder of the 16-bit type, scaled, so that it has to stay
-  // within fp16's range and has fewer bits where it is small.)  Layers, us, separate steps / epilogue:
-  //   1200 tokens, 7B shapes, rank 16     684 /  631      1200, 13B, rank 32 on all seven     1321 / 1119
-  //   1980 of 60 sequences, 34B, rank 64 2731 / 2583      1080 of 60, 7B, rank 16 on all      876 /  802
-  bool fused = mfma_ok && (b->n_tokens >= 2048 || long_runs) && b->d_in % 64 == 0 &&
-               flp_gemm_offsets_fit(FLP_GEMM_256x256, b->n_tokens, b->ld_x);
-  int64_t fused_tiles = 0;                     // enough 256 x 128 tiles to occupy the chip without slices
-  for (int q = 0; q < b->n_proj; ++q) {
-    fused = fused && b->proj[q].w_base;
-    fused_tiles += (int64_t)((b->proj[q].d_out + 255) / 256) * ((b->n_tokens + 127) / 128);
-  }
-  fused = fused && fused_tiles >= 96;
+  const LoraRoute route = lora_route(p->cfg.dtype, b, seqs);
+  const bool mfma_ok = route.sorted, fused = route.in_product;
   FlpLoraMfma c{};
   size_t v_elems = T * b->n_proj * b->max_rank;
   if (mfma_ok) {
@@ -576,9 +621,7 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
     small.k_splits = b->n_tokens <= 16 ? 16 : b->n_tokens <= 64 ? 8
                      : b->n_tokens <= 256 || b->n_tokens * b->n_proj <= 768 ? 4 : 2;
     while (small.k_splits > 1 && b->d_in / 64 / small.k_splits < 4) small.k_splits /= 2;
-    // sequences of 16 tokens and more on average: most tokens are not the first of a group.  Layer of a 499-token prompt
-    // 414 -> 393 us; with four rank tiles no difference (1000 tokens of two sequences, rank 64: 674 and 676).
-    small.long_runs = long_runs;
+    small.long_runs = route.long_runs;
     const size_t v_small = ((size_t)small.k_splits * T * b->n_proj * 16 * small.n_tiles * 4 + 255) & ~(size_t)255;
     const size_t g_small = (T * sizeof(FlpLoraGroup) + 255) & ~(size_t)255;
     size_t total = v_small + g_small + seg_bytes + perm_bytes + wt_bytes;
@@ -739,3 +782,20 @@ flp_status lora_apply_impl(flp_pool* p, const flp_lora_batch* b, void* hip_strea
   return flp_launch_lora_mfma(p->cfg.dtype, a, c, stream);
 }
 }  // namespace
+
+extern "C" int32_t flp_lora_layer_route(int32_t dtype, int32_t n_tokens, int32_t d_in, int32_t n_proj, const int32_t* d_out,
+                                        int32_t max_rank, int32_t n_seqs, const int32_t* cu, int32_t first) {
+  flp_lora_batch b{};
+  b.n_tokens = n_tokens;
+  b.d_in = d_in;
+  b.ld_x = d_in;
+  b.max_rank = max_rank;
+  b.n_proj = n_proj;
+  for (int q = 0; q < n_proj; ++q) {
+    b.proj[q].d_out = d_out[q];
+    b.proj[q].w_base = &b;                     // there is one
+  }
+  const FlpSequences seqs{cu, n_seqs, first};
+  const LoraRoute r = lora_route(dtype, &b, &seqs);
+  return r.in_product ? FLP_LORA_IN_PRODUCT : r.sorted ? FLP_LORA_SORTED : r.long_runs ? FLP_LORA_TOKENS_LONG : FLP_LORA_TOKENS;
+}

@@ -100,9 +100,19 @@ constexpr size_t kStaticScratchBytes = (size_t)64 << 20;   // what flp_lora_appl
 constexpr size_t kLayerSliceBytes = (size_t)1 << 30;       // what slices of a layer's dense products may take
 // flp_lora_apply_paged with its intermediates in `ws` (no allocation, no growth)
 flp_status flp_lora_apply_fixed(flp_pool* pool, const flp_lora_batch* batch, void* hip_stream, const FlpFixedWorkspace& ws);
-// flp_lora_apply_paged for the layer step, whose larger slice room only the pool's growing workspace has; the tokens are those of
-// n_seqs sequences one after the other, which as a rule have one adapter each (only the speed depends on that)
-flp_status flp_lora_apply_layer(flp_pool* pool, const flp_lora_batch* batch, int32_t n_seqs, void* hip_stream);
+// The sequences that a layer's tokens come in, which as a rule have one adapter each: sequence i is the tokens cu[i] .. cu[i + 1] - 1
+// of the layer's batch (host memory, as the caller passed it), and a LoRA call works on `first` and those behind it.  They decide
+// between forms of the LoRA steps that differ in speed and in the order of sums, not in the bits that v is held in.
+struct FlpSequences {
+  const int32_t* cu;
+  int32_t n, first;
+};
+// flp_lora_apply_paged for the layer step, whose larger slice room only the pool's growing workspace has
+flp_status flp_lora_apply_layer(flp_pool* pool, const flp_lora_batch* batch, const FlpSequences& seqs, void* hip_stream);
+// which steps a layer's call takes, for tests: FLP_LORA_*
+enum { FLP_LORA_TOKENS = 0, FLP_LORA_TOKENS_LONG, FLP_LORA_SORTED, FLP_LORA_IN_PRODUCT };
+extern "C" int32_t flp_lora_layer_route(int32_t dtype, int32_t n_tokens, int32_t d_in, int32_t n_proj, const int32_t* d_out,
+                                        int32_t max_rank, int32_t n_seqs, const int32_t* cu, int32_t first);
 // set-up of the file-scope scratch array for the current device (looks its device address up once per device);
 // called when a pool is created, and again by the entry point that uses the array if that first attempt failed
 flp_status flp_static_scratch_setup(int device, void** out);
@@ -231,9 +241,10 @@ struct FlpLoraGroup {
   int32_t tok[16];
   int32_t tab[FLP_MAX_PROJ], row[FLP_MAX_PROJ];      // where the projections' B lies: offset into the tables, first page row
 };
+constexpr int kLoraLongBlock = 8;      // neighbouring tokens that a wave of the expand step may take
 struct FlpLoraSmall {
   int32_t k_splits, n_tiles;   // slices of d_in; tiles of 16 ranks
-  bool long_runs;              // most tokens' neighbours have the same adapter (used with one and two rank tiles)
+  bool long_runs;              // the expand step takes kLoraLongBlock neighbouring tokens per wave (one or two rank tiles)
   FlpLoraGroup* groups;        // [T]
 };
 
@@ -320,5 +331,5 @@ flp_status flp_launch_gemm_f32(const float* x, int64_t ld_x, const float* w, int
 // up of an MLP), whose results are not stored: out = silu(y0) * y1 in one pass of the large-batch GEMM, each product
 // with its LoRA branch added before it is rounded.  FLP_ENOTSUP, nothing launched, when the batch is not one that
 // this path takes; the caller then runs flp_lora_apply_layer and the element-wise step.
-flp_status flp_lora_apply_gated(flp_pool* pool, const flp_lora_batch* batch, int32_t n_seqs, void* out, int64_t ld_out,
+flp_status flp_lora_apply_gated(flp_pool* pool, const flp_lora_batch* batch, const FlpSequences& seqs, void* out, int64_t ld_out,
                                 void* hip_stream);

@@ -549,18 +549,18 @@ extern "C" flp_status fll_layer_forward(flp_pool* p, const fll_layer_config* c, 
                              added && n_proj == 1 ? h : nullptr, added));
     if (n_lora == 0) return FLP_OK;
     lb.n_proj = n_lora;
-    if (gated_out) return flp_lora_apply_gated(p, &lb, b->n_seqs, gated_out, d_outs[0], hip_stream);
+    if (gated_out) return flp_lora_apply_gated(p, &lb, FlpSequences{b->cu_new, b->n_seqs, 0}, gated_out, d_outs[0], hip_stream);
     int N[3];
     for (int i = 0; i < n_lora; ++i) N[i] = lb.proj[i].d_out;
     const int32_t first = p->elem_bytes == 2 ? whole_rounds(T, d_in, n_lora, N, true, kLoraRestUs) : T;
     lb.n_tokens = first;
-    FLP_TRY(flp_lora_apply_layer(p, &lb, b->n_seqs, hip_stream));
+    FLP_TRY(flp_lora_apply_layer(p, &lb, FlpSequences{b->cu_new, b->n_seqs, 0}, hip_stream));
     if (first == T) return FLP_OK;
     lb.n_tokens = T - first;
     lb.x = (const uint8_t*)x + (int64_t)first * d_in * p->elem_bytes;
     lb.token_adapter = b->token_adapter + first;
     for (int i = 0; i < n_lora; ++i) lb.proj[i].y = (uint8_t*)lb.proj[i].y + (int64_t)first * lb.proj[i].ld_y * p->elem_bytes;
-    return flp_lora_apply_layer(p, &lb, (int32_t)((int64_t)b->n_seqs * (T - first) / T) + 1, hip_stream);
+    return flp_lora_apply_layer(p, &lb, FlpSequences{b->cu_new, b->n_seqs, first}, hip_stream);
   };
 
   FLP_TRY(fll_rmsnorm(dtype, h, w->in_norm, n, T, H, eps, hip_stream));

@@ -449,27 +449,26 @@ __device__ __forceinline__ void expand_group(const FlpLoraArgs& a, const FlpLora
     add_to_y<S, 4>(yp, bp, base_at(bp), yraw, pr.d_out - f0, sc, delta);
 }
 
-// LONG: a wave looks after kLongBlock neighbouring tokens.  Waves per SIMD are asked for with LONG and with four rank tiles: there
+// LONG: a wave looks after kLoraLongBlock neighbouring tokens.  Waves per SIMD are asked for with LONG and with four rank tiles: there
 // the compiler by itself spreads the accumulators over both register files and loses one or two waves.
-constexpr int kLongBlock = 8;
 template <typename L, int NT, bool LONG>
 __global__ __launch_bounds__(64, LONG ? 2 : NT == 4 ? 3 : 1) void lora_small_expand_kernel(FlpLoraArgs a, FlpLoraSmall c) {
   __shared__ f32x4 v_lds[64 * NT / 4];
   const int lane = threadIdx.x;
   // the projections one after the other; columns vary fastest: rows are often a power of two bytes apart
-  const unsigned blocks = LONG ? (unsigned)(a.T + kLongBlock - 1) / kLongBlock : (unsigned)a.T;
+  const unsigned blocks = LONG ? (unsigned)(a.T + kLoraLongBlock - 1) / kLoraLongBlock : (unsigned)a.T;
   int p = 0;
   unsigned unit = blockIdx.x, chunks = (unsigned)(a.proj[0].d_out + 127) / 128;
   while (unit >= chunks * blocks) {
     unit -= chunks * blocks;
     chunks = (unsigned)(a.proj[++p].d_out + 127) / 128;
   }
-  const int t0 = (int)(unit / chunks) * (LONG ? kLongBlock : 1), col0 = (int)(unit % chunks) * 128;
+  const int t0 = (int)(unit / chunks) * (LONG ? kLoraLongBlock : 1), col0 = (int)(unit % chunks) * 128;
   if constexpr (LONG) {
     // lane i: how many tokens token t0 + i works for, and the rank
     const FlpLoraGroup* rec = c.groups + (t0 + lane < a.T ? t0 + lane : t0);
     const int n = rec->n, r = rec->r;
-    for (uint64_t todo = __ballot(lane < kLongBlock && t0 + lane < a.T && n > 0); todo; todo &= todo - 1) {
+    for (uint64_t todo = __ballot(lane < kLoraLongBlock && t0 + lane < a.T && n > 0); todo; todo &= todo - 1) {
       const int i = __ffsll((long long)todo) - 1;
       __syncthreads();                                 // one wave: the last group's reads of v_lds stay before this one's writes
       expand_group<L, NT, LONG>(a, c, p, t0 + i, __builtin_amdgcn_readlane(n, i), __builtin_amdgcn_readlane(r, i), col0, v_lds);
@@ -493,7 +492,7 @@ void launch(const FlpLoraArgs& a, const FlpLoraSmall& c, hipStream_t stream) {
   }
   if constexpr (NT <= 2) {
     if (c.long_runs) {
-      const dim3 gl(chunks * (unsigned)((a.T + kLongBlock - 1) / kLongBlock));
+      const dim3 gl(chunks * (unsigned)((a.T + kLoraLongBlock - 1) / kLoraLongBlock));
       hipLaunchKernelGGL((lora_small_expand_kernel<L, NT, true>), gl, dim3(64), 0, stream, a, c);
       return;
     }

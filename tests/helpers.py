@@ -34,6 +34,21 @@ def dense_plan(n_tokens, d_in, widths, large_only=False, room=-1):
     return GEMM_TILES[kind.value], slices.value
 
 
+LORA_ROUTES = ("tokens", "neighbouring tokens", "sorted", "in the product")
+
+
+def lora_route(dtype, cu, d_in, widths, max_rank, first=0):
+    """Which steps a layer takes for the LoRA branches of projections over one input, for the tokens from `first` on: token by
+    token, eight neighbouring tokens per wave of the expand step, sorted by adapter, or the expand step inside the product."""
+    import ctypes as C
+
+    from paper_2505_03756_amd import flpool
+    f = flpool.load().flp_lora_layer_route
+    i32 = lambda a: (C.c_int32 * len(a))(*[int(x) for x in a])
+    return LORA_ROUTES[f({"f32": 0, "f16": 1, "bf16": 2}[dtype], int(cu[-1]) - first, d_in, len(widths), i32(widths), max_rank,
+                         len(cu) - 1, i32(cu), first)]
+
+
 # ------------------------------------------------------------------ stratified samples of a large batch
 def attention_rows_sample(step, rng, per_cell=1, cells_per_seq=None, seqs=None):
     """Token indices for the attention check, chosen over the structure the matrix-core kernel works in: a

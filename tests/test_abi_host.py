@@ -346,8 +346,8 @@ def test_launches_of_a_layer_cover_every_row_once(tmp_path):
 
 @pytest.mark.parametrize("n_units,m_tiles", [(86, 9), (43, 9), (48, 10), (86, 17), (16, 9), (54, 39), (7, 3), (1, 1), (172, 8), (3, 100), (258, 25)])
 def test_tiles_of_a_dense_product_are_dealt_once_and_evenly(n_units, m_tiles):
-    """Workgroups are placed on the 8 XCDs in turn: every tile belongs to one, an XCD has at most 32 of 256 that start together, and
-    no XCD gets much more than its eighth of one token tile's (that tile may cost several times as much as the others: single
+    """Workgroups are placed on the 8 XCDs in turn: every tile belongs to one, no XCD gets more than one tile more than another, and
+    none gets much more than its eighth of one token tile's (that tile may cost several times as much as the others: single
     tokens with a LoRA adapter each).  A block has up to four units beside each other, and the runs of an XCD begin and
     end inside one: twelve more than the eighth at most."""
     f = flpool.load().flp_dense_tile
@@ -361,7 +361,27 @@ def test_tiles_of_a_dense_product_are_dealt_once_and_evenly(n_units, m_tiles):
         seen.add((u.value, tm.value))
         per_xcd[tm.value, block & 7] += 1
     assert len(seen) == n_tiles
-    for lo in range(0, n_tiles, 256):
-        assert max(np.bincount([b & 7 for b in range(lo, min(lo + 256, (n_tiles + 7) // 8 * 8))], minlength=8)) <= 32
+    assert np.ptp(per_xcd.sum(0)) <= 1
     if m_tiles > 8:
         assert per_xcd.max() <= n_units / 8 + 12, per_xcd
+
+
+@pytest.mark.parametrize("lens,kw,want", [
+    ([1023], {}, "neighbouring tokens"), ([1024], {}, "in the product"), ([64], {}, "tokens"), ([65], {}, "neighbouring tokens"),
+    ([499], dict(rank=32), "neighbouring tokens"), ([499], dict(rank=33), "tokens"), ([499], dict(dtype="f32"), "tokens"),
+    ([16] * 63, {}, "neighbouring tokens"), ([16] * 62 + [15], {}, "tokens"),                # 16 tokens each on average
+    ([496, 1, 490], {}, "neighbouring tokens"), ([496, 1, 1, 490], {}, "tokens"), ([498] + [1] * 6, {}, "tokens"),
+    ([16] * 64, {}, "in the product"), ([15] * 69, {}, "sorted"),
+    ([1024 + 64] + [1] * 19, {}, "in the product"), ([1024 + 64] + [1] * 20, {}, "sorted"), ([1] * 20 + [1088], {}, "sorted"),
+    ([480] * 4 + [1] * 110, {}, "sorted"), ([480] * 4 + [1] * 128, {}, "in the product"),    # 2030 and 2048 tokens
+    ([0] * 500 + [1200], {}, "in the product"),                                              # empty sequences are none
+    ([1200] + [1] * 100, dict(first=1200), "tokens"), ([1] * 100 + [1200], dict(first=1100), "neighbouring tokens"),
+    ([2048, 1100], dict(first=2048), "in the product"),
+    ([1200], dict(widths=(512,)), "sorted"), ([1200], dict(widths=(2048, 2048, 2000)), "tokens"),
+])
+def test_lora_steps_of_a_layer_are_chosen_by_its_sequences(lens, kw, want):
+    """Both sides of every rule that chooses between the LoRA steps of a layer: by the tokens, the rank, and how many sequences meet
+    in 128 tokens (a tile of the product) or in eight (a wave of the expand step)."""
+    from helpers import lora_route
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    assert lora_route(kw.get("dtype", "f16"), cu, 2048, kw.get("widths", (2048, 2048, 2048)), kw.get("rank", 16), kw.get("first", 0)) == want

@@ -9,7 +9,7 @@ import pytest
 import oracle
 from oracle import layer_oracle as lo
 from paper_2505_03756_amd import fllayer, flpool, workload as wl
-from helpers import close
+from helpers import close, lora_route
 from paper_2505_03756_amd.harness import GpuStep, resident_pool, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
@@ -178,15 +178,26 @@ LAYER_CASES = {
     # (one and two rank tiles, widths that leave part of a column chunk); and just too many sequences for that
     "f16_runs_interleaved": lambda: layer_cfg("f16", n_seqs=4, new_range=(40, 60), seed=53),
     "bf16_runs_interleaved": lambda: layer_cfg("bf16", n_seqs=3, new_range=(60, 90), ranks=(8, 32), mlp_dim=1088, seed=54),
-    # sequences of 16 tokens and more: the branch of q, k, v inside the large product from 1024 tokens on, and in fp16 from 256 with 160 tiles
-    # (here 180) on, with other adapters' tokens between as well
-    "f16_prompts_inside_gemm_interleaved": lambda: layer_cfg("f16", n_seqs=2, hidden=512, n_q_heads=40, n_kv_heads=40, new_range=(140, 155),
-                                                             ranks=(8, 32), n_dev_blocks=300, seed=57),
+    "f16_no_runs_interleaved": lambda: layer_cfg("f16", n_seqs=20, new_range=(8, 15), ranks=(8, 32), seed=55),
+    # few sequences in any tile: the branch of q, k, v inside the large product from 1024 tokens on, with other adapters' tokens between
+    "f16_prompts_inside_gemm_interleaved": lambda: layer_cfg("f16", n_seqs=8, hidden=512, n_q_heads=40, n_kv_heads=40, new_range=(140, 155),
+                                                             ranks=(8, 32), n_dev_blocks=500, seed=57),
     "bf16_sequences_inside_gemm_interleaved": lambda: layer_cfg("bf16", n_seqs=20, hidden=2048, n_q_heads=16, n_kv_heads=16,
                                                                 new_range=(54, 60), ranks=(8, 64), n_dev_blocks=1500, seed=58),
-    "f16_no_runs_interleaved": lambda: layer_cfg("f16", n_seqs=20, new_range=(8, 15), ranks=(8, 32), seed=55),
+    # prompts with runs of single tokens between them, an adapter each: more of them in a tile than the product's epilogue is given
+    "bf16_prompts_and_single_tokens": lambda: layer_cfg("bf16", n_seqs=60, hidden=2048, n_q_heads=16, n_kv_heads=16, prefix_range=(0, 60),
+                                                        new_range=(360, 400), decode_frac=0.95, ranks=(8, 32), n_adapters=60,
+                                                        adapter_dist="distinct", n_dev_blocks=2500, seed=60),
     "bf16_fused_gate_up": lambda: layer_cfg("bf16", projections=("q", "k", "v", "o"), n_seqs=10, prefix_range=(0, 300),
                                             new_range=(110, 160), mlp_dim=3136, n_dev_blocks=2500, seed=48),
+}
+
+
+LAYER_ROUTES = {        # of q, k, v
+    "f16_runs_interleaved": "neighbouring tokens", "bf16_runs_interleaved": "neighbouring tokens", "f16_no_runs_interleaved": "tokens",
+    "f16_prompts_inside_gemm_interleaved": "in the product", "bf16_sequences_inside_gemm_interleaved": "in the product",
+    "bf16_prompts_and_single_tokens": "sorted", "f16_lora_inside_gemm": "in the product", "bf16_all_lora_inside_gemm": "in the product",
+    "f16_many_adapters_inside_gemm": "in the product",
 }
 
 
@@ -200,6 +211,8 @@ def test_layer_forward_matches_composed_oracle(name):
     if "cut" in name:
         first = flpool.load().flp_dense_first_tokens
         assert first(T, 4096, 3, (ctypes.c_int32 * 3)(2048, 2048, 2048), 1) == first(T, 4096, 1, (ctypes.c_int32 * 1)(6400), 0) == 2560 < T
+    if name in LAYER_ROUTES:
+        assert lora_route(cfg.dtype, step.cu_new, cfg.hidden, [cfg.proj_dims(p)[1] for p in "qkv"], int(step.rank.max())) == LAYER_ROUTES[name]
     if name.endswith("interleaved"):
         present = np.unique(step.token_adapter)
         step.token_adapter[::7] = np.resize(present, len(step.token_adapter[::7]))
@@ -466,6 +479,7 @@ def test_layer_of_prompts_gives_the_bits_of_the_lora_call(dtype, n_seqs, new, ra
     step = wl.make_step(cfg)
     T, widths = step.n_tokens, (2048, 2048, 2048)
     assert 64 < T < 1024 and dense_plan(T, cfg.hidden, widths) == dense_plan(T, cfg.hidden, widths, room=48 << 20)
+    assert lora_route(dtype, step.cu_new, cfg.hidden, widths, int(step.rank.max())) == "neighbouring tokens"
     if n_seqs == 24:
         alone = step.seq_adapter[12:]
         step.token_adapter[np.isin(step.token_adapter, alone)] = step.seq_adapter[0]
