@@ -131,6 +131,93 @@ extern "C" flp_status flp_kv_append(flp_pool* p, const flp_attn_batch* b, void* 
   return s1 != FLP_OK ? s1 : s2;
 }
 
+namespace {
+constexpr int kTokPerUnit = 4;
+enum { FLP_ATTN_APART = 0, FLP_ATTN_BEHIND, FLP_ATTN_BETWEEN };      // single tokens: a launch of their own; behind the tiles; between them
+
+// Which kernel takes which sequence of an attention call, and in how many launches
+struct AttnRoute {
+  bool mfma_ok, decode_ok;     // head size and type of the matrix-core kernels; as many query heads per kv head as the decode kernel takes
+  int G, bt;
+  bool small_launch;
+  int32_t rows;                // query rows per item of the tiled kernel
+  int mix;                     // FLP_ATTN_*
+  bool tiled(int64_t prefix, int64_t n) const {
+    return mfma_ok && G * n >= 8 && (prefix + n + bt - 1) / bt <= kMfmaMaxBlocks && !(small_launch && n <= kTokPerUnit);
+  }
+};
+AttnRoute attn_route(bool mfma_ok, int n_q, int n_kv, int bt, int32_t n_seqs, const int32_t* cu, const int32_t* prefix) {
+  AttnRoute r{};
+  r.mfma_ok = mfma_ok;
+  r.G = n_q / n_kv;
+  r.bt = bt;
+  r.decode_ok = mfma_ok && r.G <= kDecodeMaxGroup;
+  // A launch of fewer than 128 matrix-core items (a few decode sequences under grouped-query attention) goes to the
+  // decode kernel (more than 16 heads per kv head: the row kernel) instead, where long contexts are split over many waves.
+  //
+  // Query rows per item: 256, a wave for 32 of them.  A step of a workgroup takes 1.6 us with four waves at work and 2.1 with eight,
+  // so a launch whose items fit one workgroup per CU with half the rows takes those (fp16 / bf16, us, 256 rows and 128):
+  //   700 + 499 positions, 32 heads         44.3   33.7     (128 items of 128 rows)
+  //   2 sequences of 500 + 200, 32 heads    31.4   25.3     (128)
+  //   2000 + 300 positions, 64 / 8 heads    70.0   52.0     (152)
+  //   6 sequences of 300 + 120, 32 heads    23.4   23.6     (192: nothing is cut)
+  //   3 of 2000 + 200, 64 / 8 heads         71.0   90.1     (312)
+  //   1000 + 900 positions, 40 heads        60.4   74.6     (320)
+  int64_t whole = 0, half = 0;
+  const auto items_of = [&](int64_t n, int rows) { return (int64_t)n_kv * ((r.G * n + rows - 1) / rows); };
+  if (mfma_ok)
+    for (int32_t i = 0; i < n_seqs; ++i) {
+      const int64_t n = cu[i + 1] - cu[i];
+      if (r.G * n < 8) continue;
+      whole += items_of(n, kMfmaRowsPerItem);
+      half += items_of(n, kMfmaRowsPerItem / 2);
+    }
+  r.small_launch = whole < 128;
+  r.rows = half <= 256 ? kMfmaRowsPerItem / 2 : kMfmaRowsPerItem;
+  // Tiles are bound by the matrix cores and single tokens by memory, so where it pays a batch of both runs as one launch:
+  // workgroups of the tiled kernel take eight single (token, kv head) pieces each.  Behind the tiles they take the CUs that the
+  // tiles' last round leaves idle, and where that is less than a quarter of the chip there is nothing to take.  (Between the tiles of
+  // one or two rounds they push some of those into another: 256 tiles of 2 x 900 tokens over 1000 positions and 100 single tokens of
+  // short contexts, 32 heads, 104 us in two launches, 164 in one.)  From three rounds on they are spread over the first half of the
+  // tiles, so that memory is busy beside the matrix cores.  A tile of a short context ends before a piece of a long one: then
+  // only the gap between the launches is saved, and the larger workgroups cost more than that unless the single tokens are few and
+  // short as well.  Two launches, behind, between (us; f16, prompts and single tokens, items):
+  //   500 + 1000 positions, 100 of up to 64, 32 heads     (128)       71     55     70
+  //   3 x 700 + 1000, 50 of up to 2048, 40 heads          (360)      343    308    322
+  //   16 x 300 + 0, 50 of up to 2048, 32 heads           (1024)      301    301    296
+  //   16 x 300 + 1000, 100 of up to 2048, 40 heads       (1280)      678    679    670
+  //   2 x 500 + 0, 4 of up to 2048, 32 heads              (256)       50     56     46
+  //   4 x 900 + 1000, 200 of up to 64, 32 heads           (512)      193    195    276
+  //   20 + 0, 4 of up to 2048 / 64, 32 heads               (32)   39, 25 43, 23 44, 23
+  // Single tokens of grouped-query batches of 128 items and more are tiles themselves: 512 sequences of up to 16 k, 64 / 8 heads,
+  // 12.6 ms with tiles and 12.35 with pieces, but 100 of up to 4 k 720 and 762 us.
+  int64_t items = 0, row_tokens = 0, longest_tile = 0, longest_row = 0;
+  for (int32_t i = 0; i < n_seqs; ++i) {
+    const int64_t n = cu[i + 1] - cu[i], len = prefix[i] + n;
+    if (n <= 0) continue;
+    if (r.tiled(prefix[i], n)) {
+      items += items_of(n, r.rows);
+      longest_tile = std::max(longest_tile, len);
+    } else {
+      row_tokens += n;
+      longest_row = std::max(longest_row, len);
+    }
+  }
+  const int64_t idle = (256 - items % 256) % 256;
+  const bool worth = longest_tile >= 256 || (longest_row <= 256 && row_tokens * n_kv <= 4096);
+  r.mix = !r.decode_ok || !items || !row_tokens || !worth ? FLP_ATTN_APART
+          : items >= 768                                  ? FLP_ATTN_BETWEEN
+          : idle >= 64                                    ? FLP_ATTN_BEHIND
+                                                          : FLP_ATTN_APART;
+  return r;
+}
+}  // namespace
+
+extern "C" int32_t flp_attention_route(int32_t n_q_heads, int32_t n_kv_heads, int32_t block_tokens, int32_t n_seqs, const int32_t* cu,
+                                       const int32_t* prefix) {
+  return attn_route(true, n_q_heads, n_kv_heads, block_tokens, n_seqs, cu, prefix).mix;
+}
+
 extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_batch* b, void* hip_stream) {
   const bool with_append = b && (b->k_new || b->v_new);
   FLP_TRY(check_attn_batch(p, b, true, with_append, "flp_paged_prefix_attention"));
@@ -152,9 +239,11 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   // but single tokens (and with 128 prefill sequences beside 384 decoding ones: 17.5 ms for the step against 17.8); with
   // few the tiles leave the chip idle.  The line, 128 items (16 sequences here), is right for equal contexts; where they
   // differ, the longest one decides what unsplit tiles take and the decode kernel would stay ahead up to 32 sequences.
-  const bool mfma_ok = p->cfg.dtype != FLP_F32 && p->cfg.head_dim == 128;
-  const int G = b->n_q_heads / p->cfg.n_kv_heads;
+  const AttnRoute route = attn_route(p->cfg.dtype != FLP_F32 && p->cfg.head_dim == 128, b->n_q_heads, p->cfg.n_kv_heads,
+                                     p->cfg.block_tokens, b->n_seqs, b->cu_new, b->prefix_len);
+  const int G = route.G;
   const int n_kv = p->cfg.n_kv_heads;
+  const bool decode_ok = route.decode_ok;
   std::vector<int32_t> seq_order(b->n_seqs);
   std::iota(seq_order.begin(), seq_order.end(), 0);
   auto seq_cost = [&](int32_t i) {
@@ -163,36 +252,8 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   };
   std::stable_sort(seq_order.begin(), seq_order.end(), [&](int32_t x, int32_t y) { return seq_cost(x) > seq_cost(y); });
 
-  const bool decode_ok = mfma_ok && G <= kDecodeMaxGroup;
-
   std::vector<FlpAttnUnit> units;
   std::vector<int64_t> cost;
-  constexpr int kTokPerUnit = 4;
-  // A launch of fewer than 128 matrix-core items (a few decode sequences under grouped-query attention) goes to the
-  // decode kernel (more than 16 heads per kv head: the row kernel) instead, where long contexts are split over many waves
-  // (below).
-  int64_t mfma_items_est = 0;
-  if (mfma_ok)
-    for (int32_t i = 0; i < b->n_seqs; ++i) {
-      const int64_t n = b->cu_new[i + 1] - b->cu_new[i];
-      if (G * n >= 8) mfma_items_est += (int64_t)n_kv * ((G * n + kMfmaRowsPerItem - 1) / kMfmaRowsPerItem);
-    }
-  const bool small_launch = mfma_items_est < 128;
-  // Query rows per item: 256, a wave for 32 of them.  A step of a workgroup takes 1.6 us with four waves at work and 2.1 with eight,
-  // so a launch whose items fit one workgroup per CU with half the rows takes those (fp16 / bf16, us, 256 rows and 128):
-  //   700 + 499 positions, 32 heads         44.3   33.7     (128 items of 128 rows)
-  //   2 sequences of 500 + 200, 32 heads    31.4   25.3     (128)
-  //   2000 + 300 positions, 64 / 8 heads    70.0   52.0     (152)
-  //   6 sequences of 300 + 120, 32 heads    23.4   23.6     (192: nothing is cut)
-  //   3 of 2000 + 200, 64 / 8 heads         71.0   90.1     (312)
-  //   1000 + 900 positions, 40 heads        60.4   74.6     (320)
-  int64_t half_items = 0;
-  if (mfma_ok)
-    for (int32_t i = 0; i < b->n_seqs; ++i) {
-      const int64_t n = b->cu_new[i + 1] - b->cu_new[i];
-      if (G * n >= 8) half_items += (int64_t)n_kv * ((G * n + kMfmaRowsPerItem / 2 - 1) / (kMfmaRowsPerItem / 2));
-    }
-  const int32_t rows = half_items <= 256 ? kMfmaRowsPerItem / 2 : kMfmaRowsPerItem;
   // matrix-core items: the row tiles of one (sequence, kv head) are dealt to ONE of 8 queues and
   // the queues are interleaved, so that under round-robin dispatch of workgroups over the 8
   // XCDs the tiles that re-read the same K/V run on the same XCD and share its L2.
@@ -203,11 +264,11 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   for (int32_t i : seq_order) {
     const int32_t n = b->cu_new[i + 1] - b->cu_new[i];
     if (n <= 0) continue;
-    const int64_t blocks_i = ((int64_t)b->prefix_len[i] + n + p->cfg.block_tokens - 1) / p->cfg.block_tokens;
-    if (mfma_ok && (int64_t)G * n >= 8 && blocks_i <= kMfmaMaxBlocks && !(small_launch && n <= kTokPerUnit)) {
+    if (route.tiled(b->prefix_len[i], n)) {
       const int32_t R = G * n;
       for (int g = 0; g < n_kv; ++g) {
-        for (int32_t r0 = 0; r0 < R; r0 += rows) queue[next_q].push_back(FlpMfmaItem{i, g, r0, std::min<int32_t>(rows, R - r0)});
+        for (int32_t r0 = 0; r0 < R; r0 += route.rows)
+          queue[next_q].push_back(FlpMfmaItem{i, g, r0, std::min<int32_t>(route.rows, R - r0)});
         next_q = (next_q + 1) & 7;
       }
     } else {
@@ -232,16 +293,8 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
       const int64_t n = b->cu_new[i + 1] - b->cu_new[i];
       all_groups += n * (((int64_t)b->prefix_len[i] + n + 15) / 16);
     }
-  // Tiles are bound by the matrix cores and single tokens by memory, so a batch of both runs as one launch: workgroups of the tiled
-  // kernel take eight single (token, kv head) pieces each, spread over the first half of the tiles (pieces half as long, so
-  // that none of them is the launch's tail).  Two launches, one (us; f16, a quarter of the sequences are prompts):
-  //   60 sequences of up to 500 + 128-400, 32 heads          167   145
-  //   30 of up to 1000 + 128-150, 40 heads                   107    88
-  //   150 of up to 6000 + 128-900, 32 heads                 2620  2434
-  // (spread over the first fifth: 152, 92, 2454; over nine tenths: 142, 91, 2454; twice as many pieces: 5 % more at 40 heads.)
-  // Single tokens of grouped-query batches stay tiles beside prompts as well: 512 sequences of up to 16 k, 64 / 8 heads, 12.6 ms
-  // with tiles and 12.35 with pieces, but 100 of up to 4 k 720 and 762 us.
-  const bool mixed = decode_ok && !row_seqs.empty() && !queue[0].empty();
+  // beside tiles pieces are half as long, so that none of them is the launch's tail
+  const bool mixed = route.mix != FLP_ATTN_APART;
   const int64_t piece = std::max<int64_t>(kMinGroups, all_groups * n_kv / (mixed ? 2 * kPieces : kPieces));
   std::vector<int32_t> merge_tok, merge_first{0};
   for (int32_t i : row_seqs) {
@@ -278,7 +331,7 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return cost[x] > cost[y]; });
   size_t qmax = 0;
   for (auto& q : queue) qmax = std::max(qmax, q.size());
-  // single tokens beside tiles: rows of eight workgroups, eight (unit, kv head) pairs each, between the rows of tiles
+  // single tokens beside tiles: rows of eight workgroups, eight (unit, kv head) pairs each
   const size_t pairs = mixed ? units.size() * n_kv : 0, pair_rows = (pairs + 63) / 64;
   const size_t n_items = (qmax + pair_rows) * 8;
   if (units.empty() && n_items == 0) return FLP_OK;
@@ -306,7 +359,7 @@ extern "C" flp_status flp_paged_prefix_attention(flp_pool* p, const flp_attn_bat
   FlpMfmaItem* hi = (FlpMfmaItem*)(h + off_items);
   size_t at = 0, done = 0;
   for (size_t s = 0; s < qmax; ++s) {
-    for (; done < pair_rows && done * qmax <= 2 * pair_rows * s; ++done)
+    for (; route.mix == FLP_ATTN_BETWEEN && done < pair_rows && done * qmax <= 2 * pair_rows * s; ++done)
       for (int x = 0; x < 8; ++x) hi[at++] = FlpMfmaItem{(int32_t)pairs, 0, (int32_t)(64 * done + 8 * x), -1};
     for (int x = 0; x < 8; ++x) hi[at++] = s < queue[x].size() ? queue[x][s] : FlpMfmaItem{0, 0, 0, 0};
   }

@@ -190,6 +190,9 @@ flp_status flp_attn_workspace(flp_pool* pool, size_t bytes, hipStream_t stream, 
 
 flp_status flp_launch_attn_mfma(int dtype, const FlpAttnArgs& a, const FlpMfmaItem* items_dev, int32_t n_items,
                                 const FlpAttnUnit* units_dev, hipStream_t stream);
+// how single tokens run beside tiles on a 16-bit pool with head_dim 128, for tests: 0 a launch of their own, 1 behind the tiles, 2 between them
+extern "C" int32_t flp_attention_route(int32_t n_q_heads, int32_t n_kv_heads, int32_t block_tokens, int32_t n_seqs, const int32_t* cu,
+                                       const int32_t* prefix);
 constexpr int kMfmaRowsPerItem = 256;
 constexpr int kMfmaMaxBlocks = 4096;       // longest context of the matrix-core kernel: 65536 positions
 

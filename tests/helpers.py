@@ -49,6 +49,20 @@ def lora_route(dtype, cu, d_in, widths, max_rank, first=0):
                          len(cu) - 1, i32(cu), first)]
 
 
+ATTENTION_ROUTES = ("apart", "behind", "between")
+
+
+def attention_route(heads, kv, bt, seqs):
+    """How an attention call (16-bit pool, head_dim 128) of sequences of (prefix, new) tokens runs single tokens: in a launch of
+    their own, behind the tiles, or between them."""
+    import ctypes as C
+
+    from paper_2505_03756_amd import flpool
+    i32 = lambda a: (C.c_int32 * len(a))(*[int(x) for x in a])
+    cu = np.concatenate([[0], np.cumsum([n for _, n in seqs])])
+    return ATTENTION_ROUTES[flpool.load().flp_attention_route(heads, kv, bt, len(seqs), i32(cu), i32([p for p, _ in seqs]))]
+
+
 # ------------------------------------------------------------------ stratified samples of a large batch
 def attention_rows_sample(step, rng, per_cell=1, cells_per_seq=None, seqs=None):
     """Token indices for the attention check, chosen over the structure the matrix-core kernel works in: a

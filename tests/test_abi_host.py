@@ -385,3 +385,24 @@ def test_lora_steps_of_a_layer_are_chosen_by_its_sequences(lens, kw, want):
     from helpers import lora_route
     cu = np.concatenate([[0], np.cumsum(lens)])
     assert lora_route(kw.get("dtype", "f16"), cu, 2048, kw.get("widths", (2048, 2048, 2048)), kw.get("rank", 16), kw.get("first", 0)) == want
+
+
+@pytest.mark.parametrize("heads,kv,seqs,want", [
+    (32, 32, [(0, 300)] + [(40, 1)] * 100, "behind"),                       # 96 items
+    (32, 32, [(0, 256)] + [(5000, 1)], "behind"), (32, 32, [(0, 255)] + [(5000, 1)], "apart"),
+    (32, 32, [(0, 255)] + [(255, 1)], "behind"), (32, 32, [(0, 255)] + [(256, 1)], "apart"),
+    (32, 32, [(0, 20)] + [(40, 1)] * 128, "behind"), (32, 32, [(0, 20)] + [(40, 1)] * 129, "apart"),
+    (32, 32, [(0, 768)] + [(40, 1)], "behind"), (32, 32, [(0, 769)] + [(40, 1)], "apart"),           # 192 and 224 items of 128 rows
+    (32, 32, [(0, 500)] * 4 + [(40, 1)], "apart"), (32, 32, [(0, 500)] * 5 + [(40, 1)], "behind"),   # 256 and 320 of 256 rows
+    (32, 32, [(0, 500)] * 8 + [(40, 1)], "apart"), (32, 32, [(0, 500)] * 11 + [(40, 1)], "behind"),  # 512 and 704
+    (32, 32, [(0, 500)] * 12 + [(40, 1)], "between"), (32, 32, [(0, 500)] * 16 + [(40, 1)], "between"),
+    (32, 32, [(0, 500)], "apart"), (32, 32, [(0, 7)] * 50, "apart"),
+    (64, 8, [(0, 480)] + [(1000, 1)] * 3, "apart"),                         # 144 items of 256 rows: single tokens are tiles
+    (64, 8, [(200, 80)] + [(40, 1)] * 20, "apart"),
+    (64, 8, [(300, 80)] + [(40, 1)] * 5, "behind"),                         # too few items: single tokens go to the decode kernel
+    (64, 2, [(300, 80)] + [(40, 1)] * 5, "apart"),                          # more query heads than the decode kernel takes
+])
+def test_single_tokens_run_beside_tiles_where_those_leave_room(heads, kv, seqs, want):
+    """Both sides of the rule that puts single tokens into the launch of the tiles."""
+    from helpers import attention_route
+    assert attention_route(heads, kv, 16, seqs) == want

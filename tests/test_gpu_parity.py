@@ -783,6 +783,23 @@ def test_tiled_attention_at_the_edges_of_tiles(dtype, bt, heads, kv, seqs):
         assert bool((err <= bound).all()), (p, n, float((err / bound).max()))
 
 
+@pytest.mark.parametrize("route,dtype,bt,heads,kv,seqs", [
+    ("behind", "bf16", 16, 5, 5, ((0, 1), (255, 1), (256, 1), (1500, 1), (33, 7), (63, 256), (2100, 2))),
+    ("behind", "f16", 32, 4, 2, ((700, 1), (0, 3), (290, 40))),
+    ("behind", "f16", 16, 3, 3, tuple((40 * i, 1) for i in range(60)) + ((300, 8),)),
+    ("behind", "bf16", 16, 8, 8, ((30, 20), (255, 1), (0, 1))),                                # all of them short
+    ("between", "f16", 16, 16, 16, tuple((3 * i, 9) for i in range(47)) + ((600, 1), (250, 9), (0, 1), (1300, 1), (77, 3))),
+    ("apart", "bf16", 16, 16, 16, tuple((3 * i, 9) for i in range(15)) + ((600, 1), (250, 9), (0, 1), (77, 3))),       # 256 items
+    ("apart", "f16", 16, 4, 4, ((30, 20), (256, 1))),
+])
+def test_single_tokens_beside_tiles(route, dtype, bt, heads, kv, seqs):
+    """Single tokens in the tiles' launch, behind and between them, and in their own: contexts of one piece and of several, pairs that
+    do not fill a workgroup, and more workgroups of them than of tiles."""
+    from helpers import attention_route
+    assert attention_route(heads, kv, bt, seqs) == route
+    test_tiled_attention_at_the_edges_of_tiles(dtype, bt, heads, kv, seqs)
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 def test_merge_of_up_to_64_pieces(dtype):
     """8, 9, 16, 17, 32, 33 and 64 pieces of 256 positions: the edges of what the merge requests together."""
