@@ -87,7 +87,8 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __rest
 // LORA: the expand step of the projections' LoRA branches as an epilogue.  For every adapter among a wave's tokens
 // (tokens of a sequence are neighbours, so one or two) it adds B^T (64 features x ranks) times the tokens' scaled v,
 // 16 ranks per step: v enters as a 16-bit high part (k slots 0 .. 15) plus remainder (16 .. 31) against the same
-// coefficients, so it keeps its fp32 precision.  The look-ups are made before the loop and v is laid out in LDS once
+// coefficients: 16 bits of it in bf16; in fp16 22 from 0.25 on, fewer below (the remainder's spacing ends at 2^-24), and
+// it has to stay below 65504, scaled.  The look-ups are made before the loop and v is laid out in LDS once
 // per workgroup; chains of dependent loads per adapter, token tile and slice of v had cost a fifth of the launch.  The coefficients come from the adapter's pages eight bytes (four
 // features) per lane and rank and are turned into the four tiles' fragments in registers.  The sum is rounded once.
 constexpr int GK = 64;

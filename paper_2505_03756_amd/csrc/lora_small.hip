@@ -14,8 +14,8 @@
 //   expand  one wave per (sixteen tokens, projection, 128 columns): y^T += s B^T v^T with fp32 instructions, so that v
 //           keeps its 32 bits.  16x16x4: column 8 m + tau of the chunk is row m of tile tau (a lane reads 8 neighbouring
 //           columns of a page row and ends up with 32 neighbouring columns of one token), rank 4 k + i of a rank tile is slot k
-//           of step i.  Groups of up to four tokens take 4x4x1 instructions, a quarter of the time in the matrix pipe.  Where the
-//           caller knows that the tokens come in few sequences a wave looks after eight neighbouring tokens: with one each, a
+//           of step i.  Groups of up to four tokens take 4x4x1 instructions, a quarter of the time in the matrix pipe.  In a
+//           layer any eight tokens of which belong to one or two sequences a wave looks after eight neighbouring ones: with one each, a
 //           499-token prompt launches 48 000 waves of which one in sixteen has something to do, and the launch takes longer than
 //           the work.  (For decode batches the form costs registers, and groups in turn: 300 single tokens 165 -> 200 us.)
 //
