@@ -461,6 +461,13 @@ __global__ __launch_bounds__(256) void lora_shrink_lds16_kernel(FlpLoraArgs a, F
 // 32 bytes of one row per lane in two accesses, every access touches half of each line; hint or not, that is slower.)
 // y is requested half a slab ahead, v a sub-tile ahead; v is summed over its slices, split and scaled once per 256 columns.
 //
+// Where an adapter has few tokens (up to sixteen: decode batches) three of the four waves would have nothing to do, and finding a
+// group's adapter and pages takes longer than its work.  With ranks up to 16 such a group's workgroup takes four slabs, one per wave,
+// and those of the other three slabs leave; the slab that a workgroup begins with moves on from group to group and from turn to
+// turn, so that those with work are spread over the CUs.  (A workgroup per slab, and a wave per slab as before this kernel, q,k,v /
+// o call of 1500 single tokens, up to 2000 adapters of rank 16, 32 heads: 754 / 299, 586 / 278 us; now 505 / 231.  Higher ranks are
+// ahead without it, 0.6 to 0.8 of the former kernel, and their fragments would leave LDS for one workgroup less.)
+//
 // B of the slab lies in LDS as operand fragments, sixteen ranks times eight columns per thread: eight 16-byte loads along
 // the page rows, turned in registers (ranks 2 j, 2 j + 1 of a column make a word).  v takes k-slots 0 .. 15 with its high part and
 // 16 .. 31 with the remainder against the same coefficients, so lanes 32 apart read the same fragment.
@@ -476,7 +483,9 @@ __global__ __launch_bounds__(256, 2) void lora_expand_stream_kernel(FlpLoraArgs 
   typedef typename L::vec vec;
   typedef typename L::elem elem;
   typedef typename L::S S;
-  __shared__ u32x4 frag[2][NT][8][32];
+  // groups of up to sixteen tokens: a slab per wave (not with more rank tiles: they would leave too little LDS for a second workgroup)
+  constexpr int kAlone = NT == 1 ? 4 : 1;
+  __shared__ u32x4 frag[kAlone][2][NT][8][32];
   const int per_group = c.slabs * a.n_proj;
   const int n_seg = *a.n_seg;
   const int n_groups = a.group_start[n_seg];
@@ -485,12 +494,12 @@ __global__ __launch_bounds__(256, 2) void lora_expand_stream_kernel(FlpLoraArgs 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int n = lane & 15, kg = lane >> 4, kq = kg & 1, lo_half = kg >> 1;
   const uint16_t* __restrict__ pool = reinterpret_cast<const uint16_t*>(a.pool);
-  for (int q = blockIdx.x >> 3; q < q_total; q += gridDim.x >> 3) {
-    const int group = (q / per_group) * 8 + xcd, slab = (q % per_group) / a.n_proj, p = (q % per_group) % a.n_proj;
+  for (int q = blockIdx.x >> 3, turn = 0; q < q_total; q += gridDim.x >> 3, ++turn) {
+    const int group = (q / per_group) * 8 + xcd, p = (q % per_group) % a.n_proj;
+    const int gi = q / per_group, slab = ((q % per_group) / a.n_proj + gi + gi / 4 + turn) % c.slabs;
     if (group >= n_groups) continue;
     const flp_lora_proj& pr = a.proj[p];
-    const int slab_begin = slab * 256;
-    if (slab_begin >= pr.d_out) continue;
+    if (slab * 256 >= pr.d_out) continue;
     const int s = find_segment(a.group_start, n_seg, group);
     const int ad = a.seg_adapter[s];
     const int r = a.rank[ad] < a.max_rank ? a.rank[ad] : a.max_rank;
@@ -503,11 +512,15 @@ __global__ __launch_bounds__(256, 2) void lora_expand_stream_kernel(FlpLoraArgs 
     const int pos_stop = pos0 + c.group_tokens < pos_end ? pos0 + c.group_tokens : pos_end;
     const int64_t vrow0 = (int64_t)a.tile_start[s] * TM + off0;
     const int rpb = (int)(a.block_elems / pr.d_out);
+    const bool alone = kAlone > 1 && pos_stop - pos0 <= 16;
+    if (alone && slab % 4) continue;                   // with the slab before it
+    const int slab_begin = 256 * (slab + (alone ? wave : 0));
     const int n_half = pr.d_out - slab_begin > 128 ? 2 : 1;
+    u32x4(&mine)[2][NT][8][32] = frag[alone ? wave : 0];
 
     __syncthreads();                                   // the previous item's fragments are no longer read
-    if (tid < 64 * NT) {
-      const int bn = tid & 15, h = (tid >> 4) & 1, bq = (tid >> 5) & 1, nt = tid >> 6;
+    if (alone || tid < 64 * NT) {
+      const int bn = tid & 15, h = (tid >> 4) & 1, bq = (tid >> 5) & 1, nt = alone ? 0 : tid >> 6;
       const int col = slab_begin + 128 * h + 8 * bn;
       u32x4 g[8];
 #pragma unroll
@@ -526,10 +539,11 @@ __global__ __launch_bounds__(256, 2) void lora_expand_stream_kernel(FlpLoraArgs 
 #pragma unroll
         for (int j = 0; j < 4; ++j)                    // ranks 2 j, 2 j + 1 of column t: its half of the two words
           e[j] = __builtin_amdgcn_perm(g[2 * j + 1][t / 2], g[2 * j][t / 2], t & 1 ? 0x07060302u : 0x05040100u);
-        frag[h][nt][t][16 * bq + bn] = e;
+        mine[h][nt][t][16 * bq + bn] = e;
       }
     }
     __syncthreads();
+    if (slab_begin >= pr.d_out) continue;
 
     const bool from_y = !a.base32[p];
     uint16_t* const ybase = reinterpret_cast<uint16_t*>(pr.y) + slab_begin + 8 * n;
@@ -559,7 +573,7 @@ __global__ __launch_bounds__(256, 2) void lora_expand_stream_kernel(FlpLoraArgs 
         v[nt][1] = *reinterpret_cast<const f32x4*>(vp + 16 * nt + 4);
       }
     };
-    int pos_t = pos0 + 16 * wave;
+    int pos_t = pos0 + (alone ? 0 : 16 * wave);
     if (pos_t >= pos_stop) continue;
     int32_t tok[4];
     u32x4 y[2][4];
@@ -575,7 +589,7 @@ __global__ __launch_bounds__(256, 2) void lora_expand_stream_kernel(FlpLoraArgs 
         acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
-          if (16 * nt < r) acc[t] = L::mfma(vb[nt], vec_from<vec>(frag[h][nt][t][16 * kq + n]), acc[t]);
+          if (16 * nt < r) acc[t] = L::mfma(vb[nt], vec_from<vec>(mine[h][nt][t][16 * kq + n]), acc[t]);
         if (t == 3) __builtin_amdgcn_sched_barrier(0);
       }
       const int col = slab_begin + 128 * h + 8 * n;

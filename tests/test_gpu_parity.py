@@ -382,6 +382,39 @@ def test_lora_expand_slab_and_group_edges(dtype, ranks, heads, scale):
         assert np.array_equal(got[n][none], step.acts["base_" + n][none])
 
 
+@pytest.mark.parametrize("dtype,ranks,heads", [("f16", (8, 16), 17), ("bf16", (16,), 6), ("f16", (8, 32), 17)])
+def test_lora_expand_of_many_adapters_with_few_tokens(dtype, ranks, heads):
+    """1024 tokens and more of 300 adapters with 1 to 20 tokens each: more groups than the launch takes in one turn, most of up to
+    sixteen tokens, whose workgroup takes four slabs of 256 columns (ranks up to 16; widths of 1088 and 384 columns: five slabs
+    and two), some of more."""
+    cfg = small_cfg(dtype, hidden=128, n_q_heads=heads, n_kv_heads=heads, head_dim=64, n_seqs=300, prefix_range=(0, 0), new_range=(1, 8),
+                    n_adapters=300, ranks=ranks, adapter_dist="distinct", n_dev_blocks=2400, swap_in_frac=0.0, seed=520 + heads)
+    step = wl.make_step(cfg)
+    rng = np.random.default_rng(heads)
+    for ad in rng.choice(step.seq_adapter, 20, replace=False):          # up to 20 tokens, scattered
+        step.token_adapter[rng.choice(step.n_tokens, 14, replace=False)] = ad
+    step.token_adapter[::31] = -1
+    present, counts = np.unique(step.token_adapter[step.token_adapter >= 0], return_counts=True)
+    assert step.n_tokens >= 1024 and len(present) > 200 and counts.max() > 16 and (counts <= 16).sum() > 200
+    dev0 = resident_pool(step)
+    g = GpuStep(step, dev0, np.zeros((1, cfg.block_elems), dev0.dtype))
+    rtol, atol = TOL[cfg.dtype]
+    got = g.lora(["q", "k", "v"])
+    for n in ("q", "k", "v"):
+        pr = step.proj[n]
+        want = oracle.lora_apply(dev0, cfg.dtype, step.acts["x"], step.token_adapter, step.rank, step.scale,
+                                 pr.a_tab_off, pr.a_row_base, pr.b_tab_off, pr.b_row_base, step.lora_tables,
+                                 pr.d_out, y_in=step.acts["base_" + n])
+        base = wl.dequantize(step.acts["base_" + n], cfg.dtype)
+        value = wl.dequantize(got[n], cfg.dtype)
+        ok, worst, nbad = close(value, want, rtol, atol)
+        assert ok, "%s: max err %g, %d elements out of tolerance" % (n, worst, nbad)
+        ulp = 2.0 ** (-10 if cfg.dtype == "f16" else -7)
+        assert np.abs((value - base) - (want - base)).max() <= ulp * (np.abs(want).max() + 1.0)
+        none = step.token_adapter < 0
+        assert np.array_equal(got[n][none], step.acts["base_" + n][none])
+
+
 @pytest.mark.parametrize("dtype,T", [("bf16", 1), ("bf16", 63), ("f32", 257), ("bf16", 1023), ("f16", 1024),
                                      ("f32", 1025)])
 def test_lora_small_batches_share_adapter_pages(dtype, T):
